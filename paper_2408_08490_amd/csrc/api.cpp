@@ -4,13 +4,10 @@
 #include <cstring>
 #include <unistd.h>
 
-#include "common.h"
+#include "layer_host.h"
 
 namespace hgnn {
 const char *get_error();
-
-static inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
-static inline int esize(int dtype) { return dtype == HGNN_BF16 ? 2 : 4; }
 
 static void builder_main(hgnn_ctx *ctx, Builder *bd) {
   if (ctx->device >= 0) (void)hipSetDevice(ctx->device);
@@ -67,8 +64,6 @@ static void root_rows_only(Plan &pl) {
   }
   pl.tt.xroot_off[pl.tt.num_types] = o;
 }
-
-static hgnn_status layer_dev(hgnn_ctx *ctx, hgnn_graph *g, int32_t layer, LayerDev &D);
 
 static hgnn_status make_plan(hgnn_ctx *ctx, hgnn_graph *g, int32_t layer, const hgnn_layer_params *p, Plan &pl,
                              bool need_built) {
@@ -156,7 +151,7 @@ static hgnn_status make_plan(hgnn_ctx *ctx, hgnn_graph *g, int32_t layer, const 
 }
 
 // Waits for the host build and fills the device-side view of one layer's index arrays.
-static hgnn_status layer_dev(hgnn_ctx *ctx, hgnn_graph *g, int32_t layer, LayerDev &D) {
+hgnn_status layer_dev(hgnn_ctx *ctx, hgnn_graph *g, int32_t layer, LayerDev &D) {
   const LayerHost &L = g->L[layer];
   {
     hgnn_status st = wait_built(g);
@@ -179,23 +174,25 @@ static thread_local hgnn_ctx *tl_probe_ctx = nullptr;
 static thread_local int tl_probe_slot = -1;
 static thread_local bool tl_probe_first = false;
 
-struct Probe {
-  bool active = false;
-  Probe(hgnn_ctx *c, hipStream_t, int kernel, int layer, bool enabled = true) {
-    int slot = -1;
-    if (!enabled) return;
-    for (int i = 0; i < c->probe_n; ++i)
-      if (c->probe_sel[i][0] == kernel && (c->probe_sel[i][1] < 0 || c->probe_sel[i][1] == layer)) slot = i;
-    if (slot < 0) return;
-    tl_probe_ctx = c;
-    tl_probe_slot = slot;
-    tl_probe_first = true;
-    active = true;
-  }
-  ~Probe() {
-    if (active) tl_probe_ctx = nullptr;
-  }
-};
+Probe::Probe(hgnn_ctx *c, int kernel, int layer, bool enabled) {
+  int slot = -1;
+  if (!enabled) return;
+  for (int i = 0; i < c->probe_n; ++i)
+    if (c->probe_sel[i][0] == kernel && (c->probe_sel[i][1] < 0 || c->probe_sel[i][1] == layer)) slot = i;
+  if (slot < 0) return;
+  tl_probe_ctx = c;
+  tl_probe_slot = slot;
+  tl_probe_first = true;
+  active = true;
+}
+Probe::~Probe() {
+  if (active) tl_probe_ctx = nullptr;
+}
+
+AttnVariant &attn_variant() {
+  static AttnVariant v;
+  return v;
+}
 
 bool probe_take_events(hipEvent_t *start, hipEvent_t *stop) {
   hgnn_ctx *c = tl_probe_ctx;
@@ -215,362 +212,6 @@ bool probe_take_events(hipEvent_t *start, hipEvent_t *stop) {
   *start = pr.first;
   *stop = pr.second;
   return true;
-}
-
-// ---------------------------------------------------------------------------------------------
-// Attention variant: plan (tables, work-area layout) shared by forward and backward.
-// ---------------------------------------------------------------------------------------------
-struct AttnPlan {
-  TypeTab tt;
-  RelTab rt;
-  PtrTab pt;      // w_root := w_type (per-type projection), bias
-  LayerDev dev;
-  int H = 0, heads = 1, es = 4;
-  int64_t src_rows = 0, rows = 0, edges = 0, total_dst = 0;
-  // saved (forward -> backward)
-  size_t s_z = 0, s_m = 0, s_t = 0, s_mx = 0, s_ls = 0, s_beta = 0, s_wsum = 0, saved_bytes = 0;
-  // scratch (backward)
-  size_t c_gp = 0, c_small = 0, c_du = 0, c_dm = 0, c_alpha = 0, c_ds = 0, c_dsum = 0, c_dz = 0, c_partial = 0, scratch_bytes = 0;
-  // fp32 copies of what the boundary holds in bf16 (scratch; bf16 storage only)
-  bool widen = false;
-  size_t c_w32 = 0, c_h32 = 0, c_g32 = 0, c_dz16 = 0;
-};
-constexpr int kSemDimHost = 128;
-
-static hgnn_status make_attn_plan(hgnn_ctx *ctx, hgnn_graph *g, int32_t layer, const hgnn_layer_params *p, AttnPlan &pl,
-                                  bool need_built) {
-  if (!ctx || !g || !p) HGNN_FAIL(HGNN_EINVAL, "NULL context, graph or parameters");
-  if (layer < 0 || layer >= g->num_layers) HGNN_FAIL(HGNN_EINVAL, "layer %d outside [0,%d)", layer, g->num_layers);
-  if (ctx->fuse != HGNN_FUSE_SEMATTN) HGNN_FAIL(HGNN_EUNSUPPORTED, "attention aggregation is implemented with semantic-attention fusion only");
-  if (!p->in_dim || !p->w_type || !p->a_src || !p->a_dst || !p->w_sem || !p->b_sem || !p->q_sem || p->out_dim <= 0)
-    HGNN_FAIL(HGNN_EINVAL, "incomplete attention layer parameters");
-  const int T = ctx->T, R = ctx->R;
-  const LayerHost &L = g->L[layer];
-  // The attention variant computes and keeps its intermediates (projected features, aggregates, scores, every
-  // gradient between the stages) in fp32 whatever the storage type: the gradients of the attention vectors are what
-  // is left of a cancellation between the neighbours of a vertex (the softmax gradient sums to zero over them), and
-  // the ReLU decisions sit on sums without head-room, so both need more than bf16 intermediates carry.  In bf16
-  // storage the inputs, parameters and incoming gradients are widened into scratch (exact) and the layer output and
-  // the input gradient are rounded once on the way out.
-  pl.es = 4;
-  pl.widen = ctx->dtype == HGNN_BF16;
-  const int vec = 4, vec_io = 16 / esize(ctx->dtype);
-  pl.H = p->out_dim;
-  pl.heads = ctx->heads;
-  if (pl.H % pl.heads) HGNN_FAIL(HGNN_EINVAL, "out_dim %d is not a multiple of heads %d", pl.H, pl.heads);
-  const int D = pl.H / pl.heads;
-  auto pow2 = [](int n) { return n > 0 && (n & (n - 1)) == 0; };
-  if (D % vec || !pow2(D / vec) || !pow2(pl.H / vec) || pl.H / vec > 64)
-    HGNN_FAIL(HGNN_EUNSUPPORTED, "attention needs out_dim/heads = %d scalars x a power of two and out_dim/%d a power of two <= 64", vec, vec);
-  if (L.tmask != ~0u) HGNN_FAIL(HGNN_EINVAL, "the attention variant needs the transpose entries of every vertex type");
-  std::memset(&pl.tt, 0, sizeof(pl.tt));
-  std::memset(&pl.rt, 0, sizeof(pl.rt));
-  std::memset(&pl.pt, 0, sizeof(pl.pt));
-  pl.tt.num_types = T;
-  pl.rt.num_rels = R;
-  int64_t eo = 0;
-  for (int t = 0; t < T; ++t) {
-    if (p->in_dim[t] <= 0 || p->in_dim[t] % vec_io != 0)
-      HGNN_FAIL(HGNN_EUNSUPPORTED, "in_dim[%d]=%d is not a positive multiple of %d", t, p->in_dim[t], vec_io);
-    if (!p->w_type[t] || ((uintptr_t)p->w_type[t] & 15)) HGNN_FAIL(HGNN_EINVAL, "w_type[%d] is NULL or not 16-byte aligned", t);
-    pl.tt.in_dim[t] = p->in_dim[t];
-    pl.tt.n_dst[t] = (int32_t)L.n_dst[t];
-    pl.tt.elem_off[t] = eo;
-    pl.tt.xroot_off[t] = eo;
-    eo += L.n_src[t] * (int64_t)p->in_dim[t];
-    pl.tt.row_off[t + 1] = pl.tt.row_off[t] + (int32_t)L.n_src[t];
-    pl.tt.out_row_off[t + 1] = pl.tt.out_row_off[t] + (int32_t)L.n_dst[t];
-    pl.pt.w_root[t] = p->w_type[t];
-    pl.pt.bias[t] = p->bias ? p->bias[t] : nullptr;
-  }
-  pl.tt.elem_off[T] = eo;
-  for (int r = 0; r < R; ++r) {
-    if (!p->a_src[r] || !p->a_dst[r] || (((uintptr_t)p->a_src[r] | (uintptr_t)p->a_dst[r]) & 15))
-      HGNN_FAIL(HGNN_EINVAL, "a_src[%d] / a_dst[%d] is NULL or not 16-byte aligned", r, r);
-    pl.rt.src[r] = (uint8_t)ctx->rel_src[r];
-    pl.rt.dst[r] = (uint8_t)ctx->rel_dst[r];
-  }
-  if (((uintptr_t)p->w_sem | (uintptr_t)p->b_sem | (uintptr_t)p->q_sem) & 15) HGNN_FAIL(HGNN_EINVAL, "semantic attention parameters must be 16-byte aligned");
-  pl.src_rows = L.src_rows; pl.rows = L.rows; pl.edges = L.edges; pl.total_dst = pl.tt.out_row_off[T];
-  const size_t H = (size_t)pl.H, es = (size_t)pl.es, hd = (size_t)pl.heads;
-  auto take = [](size_t &o, size_t bytes) { const size_t at = o; o += align_up(std::max<size_t>(bytes, 1), 256); return at; };
-  size_t o = 0;
-  pl.s_z = take(o, (size_t)pl.src_rows * H * es);
-  pl.s_m = take(o, (size_t)pl.rows * H * es);
-  pl.s_t = take(o, (size_t)pl.rows * kSemDimHost * es);
-  pl.s_mx = take(o, (size_t)pl.rows * hd * 4);
-  pl.s_ls = take(o, (size_t)pl.rows * hd * 4);
-  pl.s_beta = take(o, (size_t)kMaxR * 4);
-  pl.s_wsum = take(o, (size_t)kMaxR * 4);
-  pl.saved_bytes = o;
-  o = 0;
-  pl.c_gp = take(o, (size_t)pl.total_dst * H * es);
-  pl.c_small = take(o, (size_t)4 * kMaxR * 4);                 // dbeta, coef
-  pl.c_du = take(o, (size_t)pl.rows * kSemDimHost * es);
-  pl.c_dm = take(o, (size_t)pl.rows * H * es);
-  pl.c_alpha = take(o, (size_t)pl.edges * hd * 4);
-  pl.c_ds = take(o, (size_t)pl.edges * hd * 4);
-  pl.c_dsum = take(o, (size_t)pl.rows * hd * 4);
-  pl.c_dz = take(o, (size_t)pl.src_rows * H * es);
-  pl.c_partial = take(o, (size_t)L.max_chunks * H * 4);
-  if (pl.widen) {
-    if (pl.H % vec_io) HGNN_FAIL(HGNN_EUNSUPPORTED, "out_dim %d is not a multiple of %d", pl.H, vec_io);
-    size_t wf = (size_t)2 * R * H + H * kSemDimHost + 2 * kSemDimHost + (size_t)T * H;
-    pl.c_w32 = take(o, wf * 4);
-    pl.c_h32 = take(o, (size_t)pl.total_dst * H * 4);
-    pl.c_g32 = take(o, (size_t)pl.total_dst * H * 4);
-    pl.c_dz16 = take(o, (size_t)pl.src_rows * H * 2);   // the projected features' gradient rounded for the projection's backward
-  }
-  pl.scratch_bytes = o;
-  if (need_built) return layer_dev(ctx, g, layer, pl.dev);
-  return HGNN_OK;
-}
-
-// fp32 stand-ins (in the scratch area) of the parameters of a bf16 layer that its fp32 kernels read: attention vectors,
-// semantic-attention parameters, biases.  `q` then takes the place of the caller's parameter block for those kernels.
-// The per-type projection weights and the input stay bf16: the projection and its backward run on the bf16 MFMA kernels
-// (a product of two bf16 numbers is exact in fp32).  Not copyable: q points into the arrays beside it.
-struct AttnWide {
-  hgnn_layer_params q;
-  const void *bias[kMaxT], *a_src[kMaxR], *a_dst[kMaxR];
-  AttnWide() = default;
-  AttnWide(const AttnWide &) = delete;
-};
-static hgnn_status attn_widen(hgnn_ctx *ctx, hipStream_t s, AttnPlan &pl, const hgnn_layer_params *p, char *sc, AttnWide &w) {
-  const int T = ctx->T, R = ctx->R;
-  const int64_t H = pl.H;
-  std::vector<const void *> src;
-  std::vector<void *> dst;
-  std::vector<int64_t> cnt;
-  float *at = (float *)(sc + pl.c_w32);
-  auto put = [&](const void *from, int64_t n) -> const void * {
-    if (!from) return nullptr;
-    float *to = at;
-    at += n;
-    src.push_back(from); dst.push_back(to); cnt.push_back(n);
-    return to;
-  };
-  w.q = *p;
-  for (int t = 0; t < T; ++t) {
-    w.bias[t] = put(p->bias ? p->bias[t] : nullptr, H);
-    pl.pt.bias[t] = w.bias[t];
-  }
-  for (int r = 0; r < R; ++r) {
-    w.a_src[r] = put(p->a_src[r], H);
-    w.a_dst[r] = put(p->a_dst[r], H);
-  }
-  w.q.bias = p->bias ? w.bias : nullptr;
-  w.q.a_src = w.a_src;
-  w.q.a_dst = w.a_dst;
-  w.q.w_sem = put(p->w_sem, H * kSemDimHost);
-  w.q.b_sem = put(p->b_sem, kSemDimHost);
-  w.q.q_sem = put(p->q_sem, kSemDimHost);
-  return launch_convert(s, true, src.data(), dst.data(), cnt.data(), (int)src.size());
-}
-
-static hgnn_status attn_fwd(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_t layer, const hgnn_layer_params *p, const void *x,
-                            void *h, void *saved, size_t saved_bytes, void *scratch, size_t scratch_bytes) {
-  AttnPlan pl;
-  hgnn_status st = make_attn_plan(ctx, g, layer, p, pl, true);
-  if (st != HGNN_OK) return st;
-  if (pl.src_rows > 0 && !x) HGNN_FAIL(HGNN_EINVAL, "x_merged is NULL");
-  if (pl.total_dst > 0 && !h) HGNN_FAIL(HGNN_EINVAL, "h_out is NULL");
-  if (!saved || !scratch) HGNN_FAIL(HGNN_EINVAL, "NULL work area");
-  if (saved_bytes < pl.saved_bytes || scratch_bytes < pl.scratch_bytes)
-    HGNN_FAIL(HGNN_EINVAL, "work areas too small: need %zu saved, %zu scratch bytes", pl.saved_bytes, pl.scratch_bytes);
-  if (((uintptr_t)saved | (uintptr_t)scratch | (uintptr_t)x | (uintptr_t)h) & 15)
-    HGNN_FAIL(HGNN_EINVAL, "device buffers must be 16-byte aligned");
-  hipStream_t s = (hipStream_t)stream;
-  HGNN_HIP(hipStreamWaitEvent(s, g->ready, 0));
-  char *sv = (char *)saved;
-  const int T = ctx->T;
-  AttnWide wide;
-  void *h_io = h;
-  if (pl.widen) {
-    if ((st = attn_widen(ctx, s, pl, p, (char *)scratch, wide)) != HGNN_OK) return st;
-    p = &wide.q;
-    h = (char *)scratch + pl.c_h32;
-  }
-  SegTab tl;   // projection tiles: every source row of every type
-  std::memset(&tl, 0, sizeof(tl));
-  tl.num_segs = T;
-  const int tn = (pl.H + 127) / 128;
-  for (int t = 0; t < T; ++t) tl.tile_off[t + 1] = tl.tile_off[t] + (int)((g->L[layer].n_src[t] + 127) / 128) * tn;
-  {
-    Probe pb(ctx, s, HGNN_K_GEMM_FWD, layer);
-    // bf16 storage: bf16 operands straight from the caller's buffers, fp32 result
-    if ((st = launch_attn_proj(s, ctx->dtype, pl.tt, pl.pt, tl, pl.H, x, sv + pl.s_z, pl.widen)) != HGNN_OK) return st;
-  }
-  {
-    Probe pb(ctx, s, HGNN_K_SPMM_FWD, layer);
-    if ((st = launch_attn_agg(s, HGNN_F32, pl.dev, pl.tt, pl.rt, p->a_src, p->a_dst, pl.H, pl.heads, sv + pl.s_z, sv + pl.s_m,
-                              (float *)(sv + pl.s_mx), (float *)(sv + pl.s_ls))) != HGNN_OK) return st;
-  }
-  float *wsum = (float *)(sv + pl.s_wsum), *beta = (float *)(sv + pl.s_beta);
-  if ((st = launch_fill_zero(s, wsum, (size_t)kMaxR * 4)) != HGNN_OK) return st;
-  if ((st = launch_attn_sem(s, HGNN_F32, pl.dev, pl.tt, pl.rt, pl.H, sv + pl.s_m, p->w_sem, p->b_sem, p->q_sem, sv + pl.s_t, wsum)) != HGNN_OK) return st;
-  if ((st = launch_attn_beta(s, pl.tt, pl.rt, wsum, beta, nullptr, nullptr, 0)) != HGNN_OK) return st;
-  if ((st = launch_attn_fuse(s, HGNN_F32, pl.dev, pl.tt, pl.rt, pl.pt, pl.H, p->relu, sv + pl.s_m, beta, h)) != HGNN_OK) return st;
-  if (pl.widen && pl.total_dst > 0) {
-    const void *src = h;
-    const int64_t n = pl.total_dst * (int64_t)pl.H;
-    return launch_convert(s, false, &src, &h_io, &n, 1);
-  }
-  return HGNN_OK;
-}
-
-static hgnn_status attn_bwd(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_t layer, const hgnn_layer_params *p, const void *x,
-                            const void *h_out, const void *saved, const void *grad_h, void *grad_x, const hgnn_layer_grads *go,
-                            void *scratch, size_t scratch_bytes) {
-  AttnPlan pl;
-  hgnn_status st = make_attn_plan(ctx, g, layer, p, pl, true);
-  if (st != HGNN_OK) return st;
-  if (!saved || !scratch || !go) HGNN_FAIL(HGNN_EINVAL, "NULL work area or gradient table");
-  if (!go->dw_type || !go->da_src || !go->da_dst || !go->dw_sem || !go->db_sem || !go->dq_sem)
-    HGNN_FAIL(HGNN_EINVAL, "the attention backward needs every gradient buffer of the attention parameters");
-  if (pl.total_dst > 0 && (!x || !grad_h || (p->relu && !h_out))) HGNN_FAIL(HGNN_EINVAL, "NULL input");
-  if (scratch_bytes < pl.scratch_bytes) HGNN_FAIL(HGNN_EINVAL, "scratch too small: need %zu bytes", pl.scratch_bytes);
-  if (((uintptr_t)saved | (uintptr_t)scratch | (uintptr_t)x | (uintptr_t)grad_h | (uintptr_t)grad_x) & 15)
-    HGNN_FAIL(HGNN_EINVAL, "device buffers must be 16-byte aligned");
-  const int R = ctx->R, T = ctx->T, H = pl.H;
-  hipStream_t s = (hipStream_t)stream;
-  HGNN_HIP(hipStreamWaitEvent(s, g->ready, 0));
-  const char *sv = (const char *)saved;
-  char *sc = (char *)scratch;
-  const LayerHost &L = g->L[layer];
-  AttnWide wide;
-  if (pl.widen) {
-    if ((st = attn_widen(ctx, s, pl, p, sc, wide)) != HGNN_OK) return st;
-    p = &wide.q;
-    // incoming gradient and (for the ReLU decisions, a sign test that the rounding of the output keeps) the output
-    const void *src[2] = {grad_h, p->relu ? h_out : nullptr};
-    void *dst[2] = {sc + pl.c_g32, sc + pl.c_h32};
-    const int64_t n[2] = {pl.total_dst * (int64_t)H, p->relu ? pl.total_dst * (int64_t)H : 0};
-    if ((st = launch_convert(s, true, src, dst, n, 2)) != HGNN_OK) return st;
-    grad_h = dst[0];
-    h_out = dst[1];
-  }
-  float *dbeta = (float *)(sc + pl.c_small), *coef = dbeta + kMaxR;
-  const float *beta = (const float *)(sv + pl.s_beta);
-  // zero everything that is accumulated into
-  GradPtrTab gt;
-  std::memset(&gt, 0, sizeof(gt));
-  bool any_db = false;
-  {
-    std::vector<float *> zp;
-    std::vector<int64_t> zn;
-    for (int t = 0; t < T; ++t) {
-      if (!go->dw_type[t]) HGNN_FAIL(HGNN_EINVAL, "dw_type[%d] is NULL", t);
-      gt.dw_root[t] = go->dw_type[t];
-      gt.dbias[t] = (go->dbias && p->bias && p->bias[t]) ? go->dbias[t] : nullptr;
-      any_db |= gt.dbias[t] != nullptr;
-      zp.push_back(go->dw_type[t]); zn.push_back((int64_t)p->in_dim[t] * H);
-      if (gt.dbias[t]) { zp.push_back(gt.dbias[t]); zn.push_back(H); }
-    }
-    for (int r = 0; r < R; ++r) {
-      if (!go->da_src[r] || !go->da_dst[r]) HGNN_FAIL(HGNN_EINVAL, "da_src[%d] / da_dst[%d] is NULL", r, r);
-      zp.push_back(go->da_src[r]); zn.push_back(H);
-      zp.push_back(go->da_dst[r]); zn.push_back(H);
-    }
-    zp.push_back(go->dw_sem); zn.push_back((int64_t)H * kSemDimHost);
-    zp.push_back(go->db_sem); zn.push_back(kSemDimHost);
-    zp.push_back(go->dq_sem); zn.push_back(kSemDimHost);
-    zp.push_back(dbeta); zn.push_back(2 * kMaxR);
-    Probe pb(ctx, s, HGNN_K_ZERO_GRADS, layer);
-    if ((st = launch_attn_zero(s, zp.data(), zn.data(), (int)zp.size())) != HGNN_OK) return st;
-  }
-  // activation / bias backward
-  const void *gp = grad_h;
-  if (pl.total_dst > 0 && (p->relu || any_db)) {
-    Probe pb(ctx, s, HGNN_K_RELU_BIAS_BWD, layer);
-    if ((st = launch_relu_bias_bwd(s, HGNN_F32, pl.tt, H, H, p->relu, grad_h, h_out, sc + pl.c_gp, gt)) != HGNN_OK) return st;
-    if (p->relu) gp = sc + pl.c_gp;   // without an activation the pass only sums the bias gradient
-  }
-  // semantic-attention fusion backward
-  if ((st = launch_attn_dbeta(s, HGNN_F32, pl.dev, pl.tt, pl.rt, H, H, gp, sv + pl.s_m, dbeta)) != HGNN_OK) return st;
-  if ((st = launch_attn_beta(s, pl.tt, pl.rt, nullptr, const_cast<float *>(beta), dbeta, coef, 1)) != HGNN_OK) return st;
-  if ((st = launch_attn_du(s, HGNN_F32, pl.dev, pl.rt, sv + pl.s_t, p->q_sem, coef, sc + pl.c_du, go->dq_sem, go->db_sem)) != HGNN_OK) return st;
-  {
-    Probe pb(ctx, s, HGNN_K_GEMM_DW, layer);
-    if ((st = launch_attn_dws(s, HGNN_F32, pl.rows, H, sv + pl.s_m, sc + pl.c_du, go->dw_sem)) != HGNN_OK) return st;
-  }
-  {
-    Probe pb(ctx, s, HGNN_K_GEMM_DA, layer);
-    if ((st = launch_attn_dm(s, HGNN_F32, pl.dev, pl.tt, pl.rt, H, H, sc + pl.c_du, p->w_sem, gp, beta, sc + pl.c_dm)) != HGNN_OK) return st;
-  }
-  // aggregation backward
-  {
-    Probe pb(ctx, s, HGNN_K_SPMM_BWD, layer);
-    if ((st = launch_attn_agg_bwd(s, HGNN_F32, pl.dev, pl.tt, pl.rt, p->a_src, p->a_dst, go->da_src, go->da_dst, H, pl.heads, sv + pl.s_z,
-                                  sv + pl.s_m, sc + pl.c_dm, (const float *)(sv + pl.s_mx), (const float *)(sv + pl.s_ls),
-                                  (float *)(sc + pl.c_alpha), (float *)(sc + pl.c_ds), (float *)(sc + pl.c_dsum), sc + pl.c_dz,
-                                  (float *)(sc + pl.c_partial))) != HGNN_OK) return st;
-  }
-  // projection backward on the layer GEMMs: every type is a "root" segment over ALL its source rows
-  TypeTab tt2 = pl.tt;
-  RelTab rt2 = pl.rt;
-  for (int t = 0; t < T; ++t) {
-    tt2.n_dst[t] = (int32_t)L.n_src[t];
-    tt2.out_row_off[t + 1] = pl.tt.row_off[t + 1];
-    rt2.zroot_off4[t] = (uint32_t)(pl.tt.elem_off[t] / 4);
-  }
-  tt2.out_row_off[0] = 0;
-  if (pl.src_rows > 0) {
-    DwTab dt;
-    std::memset(&dt, 0, sizeof(dt));
-    int ne = 0;
-    for (int t = 0; t < T; ++t) {
-      dt.first[t] = (uint16_t)ne;
-      int u = 0;
-      if (L.n_src[t] > 0) {
-        dt.seg[ne] = (uint8_t)(R + t);
-        dt.u_off[ne] = 0;
-        u = (p->in_dim[t] + 127) / 128;
-        ++ne;
-      }
-      dt.u_total[t] = (uint16_t)u;
-    }
-    dt.first[T] = (uint16_t)ne;
-    const int tiles_h = (H + 127) / 128;
-    int split_rows = 4096;
-    for (;;) {
-      int64_t tiles = 0;
-      for (int t = 0; t < T; ++t) tiles += (int64_t)dt.u_total[t] * tiles_h * ((L.n_src[t] + split_rows - 1) / split_rows);
-      if (tiles >= 320 || split_rows <= 1024) break;
-      split_rows /= 2;
-    }
-    for (int t = 0; t < T; ++t)
-      dt.tile_off[t + 1] = dt.tile_off[t] + dt.u_total[t] * tiles_h * (int)((L.n_src[t] + split_rows - 1) / split_rows);
-    // bf16 storage: both GEMMs run on the bf16 MFMA kernels, on the caller's own x and weights and on dZ rounded to
-    // bf16 (a relative 2^-9 per element of a gradient that is summed over the rows; no decision hangs on it), and the
-    // input gradient leaves in the storage type directly
-    const void *dzp = sc + pl.c_dz;
-    const int gdt = pl.widen ? HGNN_BF16 : HGNN_F32;
-    if (pl.widen) {
-      const void *src = dzp;
-      void *dst = sc + pl.c_dz16;
-      const int64_t n = pl.src_rows * (int64_t)H;
-      if ((st = launch_convert(s, false, &src, &dst, &n, 1)) != HGNN_OK) return st;
-      dzp = dst;
-    }
-    if ((st = launch_gemm_dw(s, gdt, pl.dev, tt2, rt2, gt, dt, split_rows, H, H, true, x, nullptr, dzp)) != HGNN_OK) return st;
-    if (grad_x) {
-      SegTab tl;
-      std::memset(&tl, 0, sizeof(tl));
-      tl.num_segs = R + T;
-      for (int sgi = 0; sgi < R + T; ++sgi) {
-        int cnt = 0;
-        if (sgi >= R) {
-          const int t = sgi - R;
-          const bool want = !p->input_grad || p->input_grad[t];
-          if (want && L.n_src[t] > 0) cnt = (int)((L.n_src[t] + 127) / 128) * ((p->in_dim[t] + 127) / 128);
-        }
-        tl.tile_off[sgi + 1] = tl.tile_off[sgi] + cnt;
-      }
-      if ((st = launch_gemm_da(s, gdt, pl.dev, tt2, rt2, pl.pt, tl, H, true, dzp, grad_x)) != HGNN_OK) return st;
-    }
-  }
-  return HGNN_OK;
 }
 
 // A forward launch of fewer 128x128 tiles than this leaves compute units without a block (two fit on each of
@@ -710,7 +351,7 @@ hgnn_status hgnn_merge_features(hgnn_ctx *ctx, void *stream, const void *const *
   if (ctx->device < 0) HGNN_FAIL(HGNN_EUNSUPPORTED, "host-only context cannot run device work");
   hgnn_status st;
   {
-    Probe pb(ctx, (hipStream_t)stream, HGNN_K_MERGE, -1);
+    Probe pb(ctx, HGNN_K_MERGE, -1);
     st = launch_merge((hipStream_t)stream, ctx->dtype, T, store, feat_dim, ids, n_rows, tmp_eo, x_merged);
   }
   if (st != HGNN_OK) return st;
@@ -753,7 +394,7 @@ hgnn_status hgnn_merge_features_index_first(hgnn_ctx *ctx, void *stream, const v
   for (int t = 0; t < ctx->T; ++t)
     if (n_rows[t] > 0 && (!store[t] || !ids[t])) HGNN_FAIL(HGNN_EINVAL, "type %d has rows but a NULL store or id list", t);
   if (tmp_ro[ctx->T] > 0 && !x_interleaved) HGNN_FAIL(HGNN_EINVAL, "x_interleaved is NULL");
-  Probe pb(ctx, (hipStream_t)stream, HGNN_K_MERGE, -1);
+  Probe pb(ctx, HGNN_K_MERGE, -1);
   return launch_merge((hipStream_t)stream, ctx->dtype, ctx->T, store, feat_dim, ids, n_rows, tmp_eo, x_interleaved, 1, pos, nullptr);
 }
 
@@ -767,7 +408,7 @@ hgnn_status hgnn_select_type_first(hgnn_ctx *ctx, void *stream, const void *x_in
   if (st != HGNN_OK) return st;
   if (tmp_ro[ctx->T] > 0 && (!x_interleaved || !x_merged)) HGNN_FAIL(HGNN_EINVAL, "NULL buffer");
   {
-    Probe pb(ctx, (hipStream_t)stream, HGNN_K_MERGE, -1);
+    Probe pb(ctx, HGNN_K_MERGE, -1);
     st = launch_merge((hipStream_t)stream, ctx->dtype, ctx->T, nullptr, feat_dim, nullptr, n_rows, tmp_eo, x_merged, 2, pos, x_interleaved);
   }
   if (st != HGNN_OK) return st;
@@ -1101,12 +742,7 @@ void hgnn_graph_release(hgnn_ctx *ctx, hgnn_graph *g) {
 hgnn_status hgnn_layer_workspace_bytes(hgnn_ctx *ctx, hgnn_graph *g, int32_t layer, const hgnn_layer_params *p,
                                        size_t *saved_bytes, size_t *scratch_bytes) {
   if (ctx && ctx->agg == HGNN_AGG_ATTN) {
-    AttnPlan ap;
-    hgnn_status sa = make_attn_plan(ctx, g, layer, p, ap, false);
-    if (sa != HGNN_OK) return sa;
-    if (saved_bytes) *saved_bytes = ap.saved_bytes;
-    if (scratch_bytes) *scratch_bytes = ap.scratch_bytes;
-    return HGNN_OK;
+    return attn_variant().workspace(ctx, g, layer, p, saved_bytes, scratch_bytes);
   }
   Plan pl;
   hgnn_status st = make_plan(ctx, g, layer, p, pl, false);
@@ -1189,7 +825,7 @@ static hgnn_status fwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
   make_transpose_jobs(pl.tt, pl.rt, pl.pt, pl.wt, pl.H, wtb, tj);
   const bool rides = !naive && !feature_cat && transposes_ride(pl);
   if (!rides) {
-    Probe pb(ctx, s, HGNN_K_TRANSPOSE_W, layer, !static_area);
+    Probe pb(ctx, HGNN_K_TRANSPOSE_W, layer, !static_area);
     if ((st = launch_transpose_jobs(s, ctx->dtype, tj)) != HGNN_OK) return st;
     ++n;
   }
@@ -1201,7 +837,7 @@ static hgnn_status fwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
       const size_t need = (size_t)pl.dev.edges * p->in_dim[0] * pl.es;
       if (feature_cat_bytes < need) HGNN_FAIL(HGNN_EINVAL, "feature_cat too small: need %zu bytes", need);
       if ((uintptr_t)feature_cat & 15) HGNN_FAIL(HGNN_EINVAL, "device buffers must be 16-byte aligned");
-      Probe pb(ctx, s, HGNN_K_SPMM_FWD, layer, !static_area);
+      Probe pb(ctx, HGNN_K_SPMM_FWD, layer, !static_area);
       if ((st = launch_aggregate_literal(s, ctx->dtype, pl.dev, p->in_dim[0], x, feature_cat, saved, zlo)) != HGNN_OK) return st;
       n += (pl.dev.edges > 0) + (pl.dev.rows > 0);
     } else {
@@ -1209,7 +845,7 @@ static hgnn_status fwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
         uint64_t *gaddr = (uint64_t *)(sc + pl.off_gaddr);
         if ((st = launch_gather_addresses(s, pl.dev, gs, p->in_dim[0] * pl.es, gaddr)) != HGNN_OK) return st;
         if (pl.dev.edges > 0) ++n;
-        Probe pb(ctx, s, HGNN_K_SPMM_FWD, layer);
+        Probe pb(ctx, HGNN_K_SPMM_FWD, layer);
         if (pl.dev.rows > 0) {
           if (!launch_spmm_fwd_uniform(s, ctx->dtype, pl.dev, p->in_dim[0], nullptr, saved, zlo, 0, pl.dev.rows, gaddr, rides ? &tj : nullptr))
             HGNN_FAIL(HGNN_EUNSUPPORTED, "input width %d is outside what the gather kernels cover", p->in_dim[0]);
@@ -1217,13 +853,13 @@ static hgnn_status fwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
           ++n;
         }
       } else {
-        Probe pb(ctx, s, HGNN_K_SPMM_FWD, layer, !static_area);
+        Probe pb(ctx, HGNN_K_SPMM_FWD, layer, !static_area);
         if ((st = launch_spmm_fwd(s, ctx->dtype, pl.dev, pl.tt, pl.rt, pl.max_dim, x, saved, zlo, 0, pl.dev.rows, rides ? &tj : nullptr)) != HGNN_OK) return st;
         if (pl.dev.rows > 0) ++n;
       }
     }
     {
-      Probe pb(ctx, s, HGNN_K_GEMM_FWD, layer, !static_area);
+      Probe pb(ctx, HGNN_K_GEMM_FWD, layer, !static_area);
       bool done = false;
       if (ctx->dtype == HGNN_BF16 && !ctx->legacy_gemm) {
         done = launch_gemm2_fwd(s, pl.tt, pl.rt, pl.pt, pl.wt, live, pl.H, p->relu, x, saved, zlo, wtb, h, &st);
@@ -1286,7 +922,7 @@ hgnn_status hgnn_layer_fwd(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_t l
                            const void *x_merged, void *h_out, void *saved, size_t saved_bytes, void *scratch,
                            size_t scratch_bytes) {
   if (ctx && ctx->agg == HGNN_AGG_ATTN)
-    return attn_fwd(ctx, stream, g, layer, p, x_merged, h_out, saved, saved_bytes, scratch, scratch_bytes);
+    return attn_variant().fwd(ctx, stream, g, layer, p, x_merged, h_out, saved, saved_bytes, scratch, scratch_bytes);
   return fwd_common(ctx, stream, g, layer, p, x_merged, h_out, saved, saved_bytes, scratch, scratch_bytes, false, nullptr);
 }
 
@@ -1359,7 +995,7 @@ static hgnn_status bwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
   if (launches) *launches = 0;
   if (ctx && ctx->agg == HGNN_AGG_ATTN) {
     if (naive) HGNN_FAIL(HGNN_EUNSUPPORTED, "the per-relation launch loop exists for the mean-aggregation layer only");
-    return attn_bwd(ctx, stream, g, layer, p, x_merged, h_out, saved, grad_h, grad_x_merged, go, scratch, scratch_bytes);
+    return attn_variant().bwd(ctx, stream, g, layer, p, x_merged, h_out, saved, grad_h, grad_x_merged, go, scratch, scratch_bytes);
   }
   Plan pl;
   hgnn_status st = make_plan(ctx, g, layer, p, pl, true);
@@ -1391,7 +1027,7 @@ static hgnn_status bwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
   const LayerHost &L = g->L[layer];
   const int32_t *reo = g->slab.host + L.o_rel_edge_off;
   if ((any_dw || any_db) && pl.total_dst == 0) {  // nothing flows back: the gradients are zero
-    Probe pb(ctx, s, HGNN_K_ZERO_GRADS, layer);
+    Probe pb(ctx, HGNN_K_ZERO_GRADS, layer);
     return launch_zero_grads(s, pl.tt, pl.rt, gt, pl.H);
   }
   // The GEMMs want 16-byte aligned rows.  When H is not a multiple of 16 bytes (or a weight pointer is not
@@ -1508,7 +1144,7 @@ static hgnn_status bwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
   int rpb = 0;  // rows of G per row of bpart: set by the launcher
   if (pl.total_dst > 0) {
     void *gpw = sc + pl.off_gp;
-    Probe pb(ctx, s, HGNN_K_RELU_BIAS_BWD, layer);
+    Probe pb(ctx, HGNN_K_RELU_BIAS_BWD, layer);
     if ((st = launch_bwd_prep(s, ctx->dtype, pl.tt, pl.rt, pl.pt, wo, gt, pl.H, ldg, p->relu, row_pass, any_dw, grad_h, h_out, gpw,
                               bpart, pl.bpart_rows, wpad, &rpb)) != HGNN_OK) return st;
     if (p->relu || ldg != pl.H) gp = gpw;
@@ -1557,7 +1193,7 @@ static hgnn_status bwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
     }
     for (int d = 0; d < T; ++d)
       tl.tile_off[d + 1] = tl.tile_off[d] + tl.u_total[d] * tiles_h * ((pl.tt.n_dst[d] + split_rows - 1) / split_rows);
-    Probe pb(ctx, s, HGNN_K_GEMM_DW, layer);
+    Probe pb(ctx, HGNN_K_GEMM_DW, layer);
     if (want_dx && da_tl.tile_off[da_tl.num_segs] > 0 && tl.tile_off[T] > 0) {
       // both backward GEMMs read G' and are independent of each other: one launch
       DwTab da_grouped;
@@ -1573,10 +1209,10 @@ static hgnn_status bwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
   if (bpart && (st = launch_bias_reduce(s, pl.tt, gt, pl.H, rpb, bpart)) != HGNN_OK) return st;
   if (want_dx) {
     if (!da_done) {
-      Probe pb(ctx, s, HGNN_K_GEMM_DA, layer);
+      Probe pb(ctx, HGNN_K_GEMM_DA, layer);
       if ((st = launch_gemm_da(s, ctx->dtype, pl.dev, pl.tt, pl.rt, wpt, da_tl, ldg, fast, gp, dz)) != HGNN_OK) return st;
     }
-    Probe pb(ctx, s, HGNN_K_SPMM_BWD, layer);
+    Probe pb(ctx, HGNN_K_SPMM_BWD, layer);
     uint32_t want = 0;
     for (int t = 0; t < T; ++t)
       if (!p->input_grad || p->input_grad[t]) want |= 1u << t;
@@ -1608,14 +1244,7 @@ hgnn_status hgnn_layer_bwd_naive(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int
 hgnn_status hgnn_layer_launch_count(hgnn_ctx *ctx, hgnn_graph *g, int32_t layer, const hgnn_layer_params *p,
                                     int32_t *fwd_launches, int32_t *bwd_launches) {
   if (ctx && ctx->agg == HGNN_AGG_ATTN) {
-    AttnPlan ap;
-    hgnn_status sa = make_attn_plan(ctx, g, layer, p, ap, true);
-    if (sa != HGNN_OK) return sa;
-    // forward: projection, aggregation, zero scores, semantic scores, relation softmax, fusion
-    if (fwd_launches) *fwd_launches = 6;
-    // backward: zero, (activation/bias), relation dots, relation softmax, du, dW_s, dm, row pass, transpose pass, dW_t, dX
-    if (bwd_launches) *bwd_launches = 10 + ((p->relu || p->bias) ? 1 : 0);
-    return HGNN_OK;
+    return attn_variant().launch_count(ctx, g, layer, p, fwd_launches, bwd_launches);
   }
   Plan pl;
   hgnn_status st = make_plan(ctx, g, layer, p, pl, true);
@@ -1635,7 +1264,7 @@ hgnn_status hgnn_softmax_xent(hgnn_ctx *ctx, void *stream, const void *logits, c
   if (rows < 0 || classes < 1) HGNN_FAIL(HGNN_EINVAL, "bad shape %lld x %d", (long long)rows, classes);
   if (rows > 0 && (!logits || !labels || !grad_logits)) HGNN_FAIL(HGNN_EINVAL, "NULL argument");
   if (ctx->device < 0) HGNN_FAIL(HGNN_EUNSUPPORTED, "host-only context cannot run device work");
-  Probe pb(ctx, (hipStream_t)stream, HGNN_K_XENT, -1);
+  Probe pb(ctx, HGNN_K_XENT, -1);
   return launch_xent((hipStream_t)stream, ctx->dtype, logits, labels, rows, classes, loss, grad_logits);
 }
 

@@ -347,30 +347,6 @@ hgnn_status launch_gemm_fwd(hipStream_t s, int dtype, const LayerDev &L, const T
 // bf16 forward on the LDS-DMA core; false = shape not covered (nothing was launched), else *st is the launch's status
 bool launch_gemm2_fwd(hipStream_t s, const TypeTab &tt, const RelTab &rt, const PtrTab &pt, const WtTab &wt, const uint32_t *live_mask,
                       int H, int relu, const void *x, const void *z, const void *zlo, const void *wt_buf, void *h, hgnn_status *st);
-// attention variant
-hgnn_status launch_attn_proj(hipStream_t s, int dtype, const TypeTab &tt, const PtrTab &w_type_as_root, const SegTab &tiles, int H,
-                             const void *x, void *z, bool z_f32 = false);
-hgnn_status launch_attn_agg(hipStream_t s, int dtype, const LayerDev &L, const TypeTab &tt, const RelTab &rt,
-                            const void *const *a_src, const void *const *a_dst, int H, int heads, const void *z, void *mout,
-                            float *mx, float *ls);
-hgnn_status launch_attn_sem(hipStream_t s, int dtype, const LayerDev &L, const TypeTab &tt, const RelTab &rt, int H, const void *mbuf,
-                            const void *w_sem, const void *b_sem, const void *q_sem, void *tbuf, float *wsum);
-hgnn_status launch_attn_beta(hipStream_t s, const TypeTab &tt, const RelTab &rt, const float *wsum, float *beta, const float *dbeta,
-                             float *coef, int mode);
-hgnn_status launch_attn_fuse(hipStream_t s, int dtype, const LayerDev &L, const TypeTab &tt, const RelTab &rt, const PtrTab &pt, int H,
-                             int relu, const void *mbuf, const float *beta, void *h);
-hgnn_status launch_attn_zero(hipStream_t s, float *const *ptrs, const int64_t *counts, int n);
-hgnn_status launch_attn_dbeta(hipStream_t s, int dtype, const LayerDev &L, const TypeTab &tt, const RelTab &rt, int H, int ldg,
-                              const void *gp, const void *mbuf, float *dbeta);
-hgnn_status launch_attn_du(hipStream_t s, int dtype, const LayerDev &L, const RelTab &rt, const void *tbuf, const void *q_sem,
-                           const float *coef, void *du, float *dq, float *dbs);
-hgnn_status launch_attn_dm(hipStream_t s, int dtype, const LayerDev &L, const TypeTab &tt, const RelTab &rt, int H, int ldg, const void *du,
-                           const void *w_sem, const void *gp, const float *beta, void *dm);
-hgnn_status launch_attn_dws(hipStream_t s, int dtype, int64_t rows, int H, const void *mbuf, const void *du, float *dws);
-hgnn_status launch_attn_agg_bwd(hipStream_t s, int dtype, const LayerDev &L, const TypeTab &tt, const RelTab &rt, const void *const *a_src,
-                                const void *const *a_dst, float *const *da_src, float *const *da_dst, int H, int heads, const void *z,
-                                const void *mbuf, const void *dm, const float *mx, const float *ls, float *alpha, float *dsb,
-                                float *dsum, void *dz, float *partial);
 hgnn_status launch_bias_act(hipStream_t s, int dtype, const TypeTab &tt, const PtrTab &pt, int H, int relu,
                             int type, const float *acc32, void *h);
 // gp has leading dimension ldg >= H (zero beyond H), and so have the weights in `pt`
@@ -406,8 +382,6 @@ hgnn_status launch_bias_reduce(hipStream_t s, const TypeTab &tt, const GradPtrTa
 // blocks of 256 threads that add up the partial bias sums: 32 columns of one type each
 inline int bias_reduce_blocks(int num_types, int H) { return num_types * ((H + 31) / 32); }
 hgnn_status launch_fill_zero(hipStream_t s, void *p, size_t bytes);
-constexpr int kCvtItems = 64;  // tensors per launch of the storage-type conversion
-hgnn_status launch_convert(hipStream_t s, bool widen, const void *const *src, void *const *dst, const int64_t *n, int count);
 hgnn_status launch_xent(hipStream_t s, int dtype, const void *logits, const int64_t *labels, int64_t rows,
                         int classes, float *loss, void *grad);
 }  // namespace hgnn

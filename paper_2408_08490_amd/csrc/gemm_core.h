@@ -218,11 +218,16 @@ template <typename P> __device__ __forceinline__ const P *uniform_ptr(const P *p
   return reinterpret_cast<const P *>(((uint64_t)hi << 32) | lo);
 }
 
+struct NoXform {
+  template <typename M> __device__ __forceinline__ void operator()(M &, int) const {}
+};
+
 // Runs the K-steps of sm.seg[0..nseg) (must be visible to the whole block) into `acc`.
 // KC operand: matrix [extent x K] row-major (ld); KS operand: matrix [K x extent] row-major (ld).
-template <typename T, bool FAST, bool AKC, bool BKC, int MI, int NI>
+// xa(mover, step) / xb: what happens to a K-step's operand tile in the registers, on its way to LDS.
+template <typename T, bool FAST, bool AKC, bool BKC, int MI, int NI, typename XA = NoXform, typename XB = NoXform>
 __device__ __forceinline__ void gemm_run(f32x16 (&acc)[MI][NI], GemmLds<T, MI, NI> &sm, int nseg, int a_extent, int a0,
-                                         int b_extent, int b0) {
+                                         int b_extent, int b0, XA xa = XA(), XB xb = XB()) {
   using M = Mma<T>;
   constexpr int TM = 64 * MI, TN = 64 * NI;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -274,12 +279,16 @@ __device__ __forceinline__ void gemm_run(f32x16 (&acc)[MI][NI], GemmLds<T, MI, N
   issue(ta0, tb0, s_set0);
   issue(ta1, tb1, s_set1);
   for (int step = 0; step < total; step += 2) {
+    xa(ta0, step);
+    xb(tb0, step);
     ta0.store(sm.a[0]);
     tb0.store(sm.b[0]);
     __syncthreads();
     issue(ta0, tb0, s_set0);
     mma_tile<T, AKC, BKC>(acc, sm.a[0], sm.b[0], wm, wn, lane);
     if (step + 1 < total) {
+      xa(ta1, step + 1);
+      xb(tb1, step + 1);
       ta1.store(sm.a[1]);
       tb1.store(sm.b[1]);
       __syncthreads();

@@ -5,29 +5,22 @@
 //                LeakyReLU(a_src . z_u + a_dst . z_v), evaluated in one pass with a running maximum
 //   fusion       semantic attention: tanh MLP scores per relation segment (MFMA GEMM with the row reduction
 //                in its epilogue), softmax over the relations of a destination type, weighted sum + bias + act
+// Everything between the boundary's tensors (z, m, t, dm and the small statistics) is fp32 in both storage types; the
+// kernels read parameters, the incoming gradient and the features in the storage type TS and widen them on load.
 #include <cstring>
 
+#include "attn_layer.h"
 #include "gemm_core.h"
 
 namespace hgnn {
 
 constexpr float kLeaky = 0.2f;
 constexpr int kSemDim = 128;
-constexpr int kAttnMaxH = 1024;  // widest layer output of the attention variant (64 lanes x 16 bytes)
+constexpr int kAttnMaxH = 256;  // widest layer output (64 lanes x 16 bytes of fp32)
 
-struct AttnPtrs {
-  const void *a_src[kMaxR];
-  const void *a_dst[kMaxR];
-};
-// relations grouped by destination type
-struct RelsOfType {
-  uint16_t first[kMaxT + 1];
-  uint8_t rel[kMaxR];
-};
-
-template <typename T> struct Piece;   // 16 bytes of a row as floats
-template <> struct Piece<float> {
-  static constexpr int N = 4;
+// four consecutive scalars of the storage type, as floats
+template <typename T> struct Quad;
+template <> struct Quad<float> {
   static __device__ __forceinline__ void load(float *f, const float *p) {
     const f32x4 v = *reinterpret_cast<const f32x4 *>(p);
     f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
@@ -36,20 +29,19 @@ template <> struct Piece<float> {
     *reinterpret_cast<f32x4 *>(p) = f32x4{f[0], f[1], f[2], f[3]};
   }
 };
-template <> struct Piece<bf16> {
-  static constexpr int N = 8;
+template <> struct Quad<bf16> {
   static __device__ __forceinline__ void load(float *f, const bf16 *p) {
-    const u32x4 v = *reinterpret_cast<const u32x4 *>(p);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      f[2 * i] = __uint_as_float(v[i] << 16);
-      f[2 * i + 1] = __uint_as_float(v[i] & 0xffff0000u);
-    }
+    const u32x2 v = *reinterpret_cast<const u32x2 *>(p);
+    f[0] = __uint_as_float(v.x << 16);
+    f[1] = __uint_as_float(v.x & 0xffff0000u);
+    f[2] = __uint_as_float(v.y << 16);
+    f[3] = __uint_as_float(v.y & 0xffff0000u);
   }
   static __device__ __forceinline__ void store(bf16 *p, const float *f) {
-    *reinterpret_cast<u32x4 *>(p) = u32x4{pack2(f[0], f[1]), pack2(f[2], f[3]), pack2(f[4], f[5]), pack2(f[6], f[7])};
+    *reinterpret_cast<u32x2 *>(p) = u32x2{pack2(f[0], f[1]), pack2(f[2], f[3])};
   }
 };
+typedef Quad<float> Q4;
 
 __device__ __forceinline__ int find_le(const int32_t *off, int n, int x) {  // largest i in [0, n) with off[i] <= x
   int lo = 0, hi = n;
@@ -60,14 +52,150 @@ __device__ __forceinline__ int find_le(const int32_t *off, int n, int x) {  // l
   return lo;
 }
 
+__device__ __forceinline__ float leaky(float s) { return s > 0.f ? s : kLeaky * s; }
+
 // ------------------------------------------------------------------------------------------
-// Projection: Z[row_off[t] + i, :] = X_t[i, :] W_t for every source row of every type.
-// TO = type of Z: fp32 with bf16 operands when the layer computes in fp32 on bf16 storage (the products of two bf16
-// numbers are exact in fp32, so this is the fp32 projection of the widened inputs up to the order of the adds).
-template <typename T, typename TO>
-__global__ void __launch_bounds__(kThreads, 2) attn_proj_kernel(TypeTab tt, PtrTab pt, SegTab tiles, int H, const T *__restrict__ x,
-                                                              TO *__restrict__ z) {
-  __shared__ GemmLds<T> sm;
+// Products of an fp32 operand with a bf16 one on the bf16 matrix cores.  An fp32 value is the exact sum of three bf16
+// values (8 + 8 + 8 significant bits), a product of two bf16 values is exact in fp32, so three MFMAs give what the fp32
+// MFMA would, at 3/16 of its cost.  A tile of A (fp32, K contiguous) is split into its three planes on the way from the
+// registers to LDS; B goes through the ordinary mover.  One LDS stage (74 KB, two blocks per CU: the other block's MFMAs
+// cover a block's barriers), the next K-step's loads in flight during the MFMAs.
+constexpr int kWideBK = 64;
+template <int MI, int NI> struct WideLds {
+  static constexpr int PA = kWideBK + 8, TM = 64 * MI, TN = 64 * NI;
+  static constexpr int B_ELEMS = TN * PA > kWideBK * ks_pitch<bf16>(TN) ? TN * PA : kWideBK * ks_pitch<bf16>(TN);
+  __attribute__((aligned(16))) bf16 a[3][TM * PA];
+  __attribute__((aligned(16))) bf16 b[B_ELEMS];
+};
+
+template <int TM> struct WideMover {
+  static constexpr int VPR = kWideBK / 4, NV = TM * VPR / kThreads, PA = kWideBK + 8;
+  f32x4 reg[NV];
+  // rows o0.. of A (clamped to the extent), K columns k0..k0+63
+  __device__ __forceinline__ void load(const float *A, int lda, int extent, int o0, int k0, int k_end) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int v = threadIdx.x + i * kThreads, r = v / VPR, c = (v % VPR) * 4;
+      const int o = min(o0 + r, extent - 1);
+      f32x4 x = *reinterpret_cast<const f32x4 *>(A + (int64_t)o * lda + min(k0 + c, k_end - 4));
+      if (k0 + c >= k_end) x = f32x4{0.f, 0.f, 0.f, 0.f};
+      reg[i] = x;
+    }
+  }
+  template <typename F> __device__ __forceinline__ void store(bf16 (*a)[TM * PA], F f) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int v = threadIdx.x + i * kThreads, r = v / VPR, c = (v % VPR) * 4;
+      const f32x4 x = f(reg[i]);
+      float d[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+      for (int p = 0; p < 3; ++p) {
+        const u32x2 w = {pack2(d[0], d[1]), pack2(d[2], d[3])};
+        *reinterpret_cast<u32x2 *>(a[p] + r * PA + c) = w;
+        if (p < 2) {
+          d[0] -= __uint_as_float(w.x << 16);
+          d[1] -= __uint_as_float(w.x & 0xffff0000u);
+          d[2] -= __uint_as_float(w.y << 16);
+          d[3] -= __uint_as_float(w.y & 0xffff0000u);
+        }
+      }
+    }
+  }
+};
+
+// acc += f(A)[a0.., k] * B[k, b0..] over k in [0, K).  BKC: B is [b_extent x K] (K contiguous), else [K x b_extent].
+// `f(piece, k)` maps four consecutive values of A starting at column k.
+template <bool BKC, int MI, int NI, typename F>
+__device__ __forceinline__ void wide_run(f32x16 (&acc)[MI][NI], WideLds<MI, NI> &sm, const float *A, int lda, int a_extent, int a0,
+                                         const bf16 *B, int ldb, int b_extent, int b0, int K, F f) {
+  constexpr int TM = 64 * MI, TN = 64 * NI, PA = kWideBK + 8, PB = BKC ? PA : ks_pitch<bf16>(TN);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wm = (wave >> 1) * 32 * MI, wn = (wave & 1) * 32 * NI;
+  WideMover<TM> ma;
+  TileMover<bf16, BKC ? TN : kWideBK, BKC ? kWideBK : TN, PB, BKC> mb;
+  mb.setup(ldb, b_extent, b0);
+  ma.load(A, lda, a_extent, a0, 0, K);
+  mb.load_fast(B, K);
+  for (int k0 = 0; k0 < K; k0 += kWideBK) {
+    const int kc = k0 + (threadIdx.x % WideMover<TM>::VPR) * 4;
+    ma.store(sm.a, [&](f32x4 v) { return f(v, kc); });
+    mb.store(sm.b);
+    __syncthreads();
+    if (k0 + kWideBK < K) {
+      ma.load(A, lda, a_extent, a0, k0 + kWideBK, K);
+      mb.load_fast(BKC ? B + k0 + kWideBK : B + (int64_t)(k0 + kWideBK) * ldb, K - k0 - kWideBK);
+    }
+#pragma unroll
+    for (int ks = 0; ks < kWideBK / 16; ++ks) {
+      bf16x8_t b[NI];
+#pragma unroll
+      for (int j = 0; j < NI; ++j) b[j] = frag_bf16<BKC, PB>(sm.b, wn + j * 32, ks, lane);
+#pragma unroll
+      for (int p = 2; p >= 0; --p) {   // smallest plane first
+        bf16x8_t a[MI];
+#pragma unroll
+        for (int i = 0; i < MI; ++i) a[i] = frag_bf16<true, PA>(sm.a[p], wm + i * 32, ks, lane);
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+          for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+      }
+    }
+    __syncthreads();
+  }
+}
+
+// Hands the block's tile out of LDS in pieces of four columns: f(row, col, values) for rows below `rows`.  A thread's
+// column is the same in all its pieces.
+template <int MI, int NI, typename F>
+__device__ __forceinline__ void tile_pieces(f32x16 (&acc)[MI][NI], float *stage, int rows, F f) {
+  constexpr int TM = 64 * MI, TN = 64 * NI, P = TN + kOutPitchPad, VPR = TN / 4;
+  HGNN_FOR_EACH_ACC({ stage[row * P + col] = val; })
+  __syncthreads();
+  const int c = (threadIdx.x % VPR) * 4;
+#pragma unroll
+  for (int i = 0; i < TM * VPR / kThreads; ++i) {
+    const int r = threadIdx.x / VPR + i * (kThreads / VPR);
+    if (r < rows) f(r, c, *reinterpret_cast<const f32x4 *>(stage + r * P + c));
+  }
+}
+
+// LDS of a block that multiplies an fp32 matrix with one of the storage type.
+template <typename TS, int MI> struct MixLds;
+template <int MI> struct MixLds<bf16, MI> {
+  WideLds<MI, 2> w;
+  __device__ __forceinline__ float *stage() { return reinterpret_cast<float *>(&w); }
+  static_assert(sizeof(WideLds<MI, 2>) >= sizeof(float) * 64 * MI * (128 + kOutPitchPad), "output tile must fit");
+};
+template <int MI> struct MixLds<float, MI> {
+  GemmLds<float, MI, 2> g;
+  __device__ __forceinline__ float *stage() { return reinterpret_cast<float *>(&g.a[0][0]); }
+};
+
+template <bool BKC, typename TS, int MI, typename F>
+__device__ __forceinline__ void mix_run(f32x16 (&acc)[MI][2], MixLds<TS, MI> &sm, const float *A, int lda, int a_extent, int a0,
+                                        const TS *B, int ldb, int b_extent, int b0, int K, F f) {
+  if constexpr (sizeof(TS) == 2) {
+    wide_run<BKC>(acc, sm.w, A, lda, a_extent, a0, B, ldb, b_extent, b0, K, f);
+  } else {
+    if (threadIdx.x == 0) put_seg(sm.g.seg[0], A, lda, B, ldb, 0, K);
+    __syncthreads();
+    gemm_run<float, true, true, BKC>(acc, sm.g, 1, a_extent, a0, b_extent, b0, [&](auto &mv, int step) {
+      const int kc = step * Mma<float>::BK + (threadIdx.x % (Mma<float>::BK / 4)) * 4;
+      for (auto &r : mv.reg) r = __builtin_bit_cast(u32x4, f(__builtin_bit_cast(f32x4, r), kc));
+    });
+  }
+}
+
+// ------------------------------------------------------------------------------------------
+// Projection: Z[row_off[t] + i, :] = X_t[i, :] W_t for every source row of every type, fp32 result (the products of two
+// bf16 numbers are exact in fp32).  Its first block also clears the score sums of the kernel after next.
+template <typename TS, int MI>
+__global__ void __launch_bounds__(kThreads, 2) attn_proj_kernel(TypeTab tt, PtrTab pt, SegTab tiles, int H, const TS *__restrict__ x,
+                                                              float *__restrict__ z, float *__restrict__ wsum) {
+  constexpr int BM = 64 * MI, BN = 64 * MI;
+  __shared__ GemmLds<TS, MI, MI> sm;
+  if (blockIdx.x == 0 && threadIdx.x < kMaxR) wsum[threadIdx.x] = 0.f;
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
   const int T_ = tt.num_types;
   if (tile >= tiles.tile_off[T_]) return;
@@ -77,133 +205,109 @@ __global__ void __launch_bounds__(kThreads, 2) attn_proj_kernel(TypeTab tt, PtrT
   const int local = tile - tiles.tile_off[t];
   const int m0 = (local / tiles_n) * BM, n0 = (local % tiles_n) * BN;
   const int M = tt.row_off[t + 1] - tt.row_off[t], F = tt.in_dim[t];
-  f32x16 acc[2][2];
+  f32x16 acc[MI][MI];
   zero_acc(acc);
-  if (threadIdx.x == 0) put_seg(sm.seg[0], x + tt.elem_off[t], F, reinterpret_cast<const T *>(pt.w_root[t]), H, 0, F);
+  if (threadIdx.x == 0) put_seg(sm.seg[0], x + tt.elem_off[t], F, reinterpret_cast<const TS *>(pt.w_root[t]), H, 0, F);
   __syncthreads();
-  gemm_run<T, true, true, false>(acc, sm, 1, M, m0, H, n0);
+  gemm_run<TS, true, true, false>(acc, sm, 1, M, m0, H, n0);
   write_tile(acc, sm, z + ((int64_t)tt.row_off[t] + m0) * H + n0, H, M - m0, H - n0, [](float v, int, int) { return v; });
 }
 
 // ------------------------------------------------------------------------------------------
-// Aggregation.  A group of `lpr` lanes owns one merged row; lane q holds 16 bytes of the row; `hl` lanes form a
-// head.  Softmax over the row's edges in one pass: running maximum m, running sum l and accumulator rescaled
-// whenever the maximum grows.  Saves m and l per (row, head) for the backward pass.
-template <typename T>
-__global__ void __launch_bounds__(256) attn_agg_kernel(LayerDev L, TypeTab tt, RelTab rt, AttnPtrs ap, int H, int heads, int lpr_log2,
-                                                       int hl, const T *__restrict__ z, T *__restrict__ mout,
+// Aggregation.  Blocks are cut per relation (the relation, its vectors and its rows are then the same for the whole
+// block).  A group of `lpr` lanes owns one merged row at a time; lane q holds four floats of it; `hl` lanes form a head.
+// Softmax over the row's edges in one pass: running maximum m, running sum l and accumulator rescaled whenever the
+// maximum grows; four neighbour rows in flight.  Bound: the gather of fp32 rows (1 KB at H = 256).
+template <typename TS>
+__global__ void __launch_bounds__(256) attn_agg_kernel(LayerDev L, RelRows rr, AttnPtrs ap, int H, int heads, int lpr_log2, int hl,
+                                                       int rpg, const float *__restrict__ z, float *__restrict__ mout,
                                                        float *__restrict__ mx, float *__restrict__ ls) {
-  using P = Piece<T>;
-  const int lpr = 1 << lpr_log2;
-  const int q = threadIdx.x & (lpr - 1);
-  const int64_t rho = (int64_t)blockIdx.x * (256 >> lpr_log2) + (threadIdx.x >> lpr_log2);
-  if (rho >= L.rows) return;   // whole lane groups leave together
-  const int r = find_le(L.rel_row_off, rt.num_rels, (int)rho);
-  const int v = (int)rho - L.rel_row_off[r];
-  const int d = rt.dst[r];
-  const int k = (q * P::N) / (H / heads);
-  float as[P::N], ad[P::N], zv[P::N], acc[P::N];
-  P::load(as, reinterpret_cast<const T *>(ap.a_src[r]) + q * P::N);
-  P::load(ad, reinterpret_cast<const T *>(ap.a_dst[r]) + q * P::N);
-  P::load(zv, z + ((int64_t)tt.row_off[d] + v) * H + q * P::N);
-  float sd = 0.f;
+  const int gpb = 256 >> lpr_log2;
+  const int q = threadIdx.x & ((1 << lpr_log2) - 1), grp = threadIdx.x >> lpr_log2;
+  const int r = find_le(rr.tile_off, rr.n, (int)blockIdx.x);
+  const int row0 = rr.row_off[r], M = rr.row_off[r + 1] - row0;
+  const int v0 = ((int)blockIdx.x - rr.tile_off[r]) * gpb * rpg;
+  const float *zd = z + (int64_t)rr.zdst[r] * H + q * 4;
+  const float *zq = z + q * 4;
+  const int k = (q * 4) / (H / heads);
+  float as[4], ad[4];
+  Quad<TS>::load(as, reinterpret_cast<const TS *>(ap.a_src[r]) + q * 4);
+  Quad<TS>::load(ad, reinterpret_cast<const TS *>(ap.a_dst[r]) + q * 4);
+  for (int i = 0; i < rpg; ++i) {
+    const int v = v0 + i * gpb + grp;
+    if (v >= M) return;   // whole lane groups leave together
+    const int64_t rho = row0 + v;
+    const int e0 = L.rowptr[rho], e1 = L.rowptr[rho + 1];
+    float zv[4], acc[4] = {0.f, 0.f, 0.f, 0.f};
+    float m = -INFINITY, l = 0.f;
+    if (e1 > e0) {
+      Q4::load(zv, zd + (int64_t)v * H);
+      float sd = 0.f;
 #pragma unroll
-  for (int i = 0; i < P::N; ++i) {
-    sd += ad[i] * zv[i];
-    acc[i] = 0.f;
-  }
-  for (int o = hl >> 1; o > 0; o >>= 1) sd += __shfl_xor(sd, o);
-  float m = -INFINITY, l = 0.f;
-  const int e0 = L.rowptr[rho], e1 = L.rowptr[rho + 1];
-  int e = e0;
-  for (; e + 2 <= e1; e += 2) {   // two rows in flight
-    const int u0 = L.colidx[e], u1 = L.colidx[e + 1];
-    float z0[P::N], z1[P::N];
-    P::load(z0, z + (int64_t)u0 * H + q * P::N);
-    P::load(z1, z + (int64_t)u1 * H + q * P::N);
-    float s0 = 0.f, s1 = 0.f;
+      for (int j = 0; j < 4; ++j) sd += ad[j] * zv[j];
+      for (int o = hl >> 1; o > 0; o >>= 1) sd += __shfl_xor(sd, o);
+      for (int e = e0; e < e1; e += 4) {
+        float zu[4][4], s[4];
+        int u[4];
 #pragma unroll
-    for (int i = 0; i < P::N; ++i) {
-      s0 += as[i] * z0[i];
-      s1 += as[i] * z1[i];
+        for (int j = 0; j < 4; ++j) u[j] = L.colidx[min(e + j, e1 - 1)];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) Q4::load(zu[j], zq + (int64_t)u[j] * H);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) s[j] = (as[0] * zu[j][0] + as[1] * zu[j][1]) + (as[2] * zu[j][2] + as[3] * zu[j][3]);
+        for (int o = hl >> 1; o > 0; o >>= 1) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) s[j] += __shfl_xor(s[j], o);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) s[j] = e + j < e1 ? leaky(s[j] + sd) : -INFINITY;
+        const float mn = fmaxf(m, fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])));
+        const float c = __expf(m - mn);
+        float p[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) p[j] = __expf(s[j] - mn);
+        l = l * c + ((p[0] + p[1]) + (p[2] + p[3]));
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+          acc[d] = acc[d] * c + ((p[0] * zu[0][d] + p[1] * zu[1][d]) + (p[2] * zu[2][d] + p[3] * zu[3][d]));
+        m = mn;
+      }
+      const float inv = 1.f / l;
+#pragma unroll
+      for (int d = 0; d < 4; ++d) acc[d] *= inv;
     }
-    for (int o = hl >> 1; o > 0; o >>= 1) {
-      s0 += __shfl_xor(s0, o);
-      s1 += __shfl_xor(s1, o);
+    Q4::store(mout + rho * H + q * 4, acc);
+    if ((q & (hl - 1)) == 0) {
+      mx[rho * heads + k] = e1 > e0 ? m : 0.f;
+      ls[rho * heads + k] = l;
     }
-    s0 += sd; s1 += sd;
-    s0 = s0 > 0.f ? s0 : kLeaky * s0;
-    s1 = s1 > 0.f ? s1 : kLeaky * s1;
-    const float mn = fmaxf(m, fmaxf(s0, s1));
-    const float c = __expf(m - mn), p0 = __expf(s0 - mn), p1 = __expf(s1 - mn);
-    l = l * c + p0 + p1;
-#pragma unroll
-    for (int i = 0; i < P::N; ++i) acc[i] = acc[i] * c + p0 * z0[i] + p1 * z1[i];
-    m = mn;
-  }
-  if (e < e1) {
-    const int u0 = L.colidx[e];
-    float z0[P::N];
-    P::load(z0, z + (int64_t)u0 * H + q * P::N);
-    float s0 = 0.f;
-#pragma unroll
-    for (int i = 0; i < P::N; ++i) s0 += as[i] * z0[i];
-    for (int o = hl >> 1; o > 0; o >>= 1) s0 += __shfl_xor(s0, o);
-    s0 += sd;
-    s0 = s0 > 0.f ? s0 : kLeaky * s0;
-    const float mn = fmaxf(m, s0);
-    const float c = __expf(m - mn), p0 = __expf(s0 - mn);
-    l = l * c + p0;
-#pragma unroll
-    for (int i = 0; i < P::N; ++i) acc[i] = acc[i] * c + p0 * z0[i];
-    m = mn;
-  }
-  const float inv = l > 0.f ? 1.f / l : 0.f;
-#pragma unroll
-  for (int i = 0; i < P::N; ++i) acc[i] *= inv;
-  P::store(mout + rho * H + q * P::N, acc);
-  if ((q & (hl - 1)) == 0) {
-    mx[rho * heads + k] = e1 > e0 ? m : 0.f;
-    ls[rho * heads + k] = l;
   }
 }
 
 // ------------------------------------------------------------------------------------------
 // Semantic scores: t = tanh(m W_s + b_s) stored for the backward pass; wsum[r] += sum over the segment's rows of q . t
-template <typename T>
-__global__ void __launch_bounds__(kThreads, 2) attn_sem_kernel(LayerDev L, TypeTab tt, RelTab rt, SegTab tiles, int H,
-                                                             const T *__restrict__ mbuf, const T *__restrict__ w_sem,
-                                                             const T *__restrict__ b_sem, const T *__restrict__ q_sem,
-                                                             T *__restrict__ tbuf, float *__restrict__ wsum) {
-  __shared__ GemmLds<T> sm;
+template <typename TS, int MI>
+__global__ void __launch_bounds__(kThreads, 2) attn_sem_kernel(RelRows rr, int H, const float *__restrict__ mbuf, const TS *__restrict__ w_sem,
+                                                             const TS *__restrict__ b_sem, const TS *__restrict__ q_sem,
+                                                             float *__restrict__ tbuf, float *__restrict__ wsum) {
+  constexpr int TM = 64 * MI;
+  __shared__ MixLds<TS, MI> sm;
   __shared__ float red[4];
-  const int tile = xcd_tile(blockIdx.x, gridDim.x);
-  const int R = rt.num_rels;
-  if (tile >= tiles.tile_off[R]) return;
-  const int r = find_le(tiles.tile_off, R, tile);
-  const int m0 = (tile - tiles.tile_off[r]) * BM;
-  const int M = tt.n_dst[rt.dst[r]];
-  const int64_t row0 = L.rel_row_off[r];
-  f32x16 acc[2][2];
+  const int r = find_le(rr.tile_off, rr.n, (int)blockIdx.x);
+  const int m0 = ((int)blockIdx.x - rr.tile_off[r]) * TM;
+  const int64_t row0 = rr.row_off[r];
+  const int M = rr.row_off[r + 1] - (int)row0;
+  f32x16 acc[MI][2];
   zero_acc(acc);
-  if (threadIdx.x == 0) put_seg(sm.seg[0], mbuf + row0 * H, H, w_sem, kSemDim, 0, H);
-  __syncthreads();
-  gemm_run<T, true, true, false>(acc, sm, 1, M, m0, kSemDim, 0);
-  float bq[2][2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int c = ((threadIdx.x >> 6) & 1) * 64 + j * 32 + (threadIdx.x & 31);
-    bq[j][0] = to_float(b_sem[c]);
-    bq[j][1] = to_float(q_sem[c]);
-  }
-  const int wn0 = ((threadIdx.x >> 6) & 1) * 64;
-  float part = 0.f;
-  const int valid = M - m0;
-  write_tile(acc, sm, tbuf + (row0 + m0) * kSemDim, kSemDim, valid, kSemDim, [&](float v, int row, int col) {
-    const int j = (col - wn0) >> 5;
-    const float t = tanhf(v + bq[j][0]);
-    if (row < valid) part += t * bq[j][1];
-    return t;
+  mix_run<false>(acc, sm, mbuf + row0 * H, H, M, m0, w_sem, kSemDim, kSemDim, 0, H, [](f32x4 v, int) { return v; });
+  float bs[4], qs[4], part = 0.f;
+  const int cc = (threadIdx.x % (kSemDim / 4)) * 4;
+  Quad<TS>::load(bs, b_sem + cc);
+  Quad<TS>::load(qs, q_sem + cc);
+  tile_pieces(acc, sm.stage(), M - m0, [&](int row, int col, f32x4 v) {
+    float t[4] = {tanhf(v.x + bs[0]), tanhf(v.y + bs[1]), tanhf(v.z + bs[2]), tanhf(v.w + bs[3])};
+    part += (t[0] * qs[0] + t[1] * qs[1]) + (t[2] * qs[2] + t[3] * qs[3]);
+    Q4::store(tbuf + (row0 + m0 + row) * kSemDim + col, t);
   });
   for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = part;
@@ -211,67 +315,59 @@ __global__ void __launch_bounds__(kThreads, 2) attn_sem_kernel(LayerDev L, TypeT
   if (threadIdx.x == 0) atomicAdd(wsum + r, red[0] + red[1] + red[2] + red[3]);
 }
 
-// beta[r] = softmax over the relations with the same destination type of wsum[r] / M_d.
-// mode 1 (backward): coef[r] = beta_r (dbeta_r - sum_r' beta_r' dbeta_r') / M_d, the factor of q (1 - t^2).
-__global__ void attn_beta_kernel(TypeTab tt, RelTab rt, const float *__restrict__ wsum, float *__restrict__ beta,
-                                 const float *__restrict__ dbeta, float *__restrict__ coef, int mode) {
+// beta[r] = softmax over the relations with the same destination type of wsum[r] / M_d, for all relations by the first
+// threads of a block.  `out` may be LDS or global memory.
+__device__ __forceinline__ void relation_softmax(const RelRows &rr, const float *__restrict__ wsum, float *out) {
   const int r = threadIdx.x;
-  if (r >= rt.num_rels) return;
-  const int d = rt.dst[r];
-  const int M = tt.n_dst[d];
+  if (r >= rr.n) return;
+  const int d = rr.dst[r], M = rr.row_off[r + 1] - rr.row_off[r];
   if (M == 0) {
-    if (mode == 0) beta[r] = 0.f; else coef[r] = 0.f;
+    out[r] = 0.f;
     return;
   }
-  if (mode == 0) {
-    float mxv = -INFINITY;
-    for (int o = 0; o < rt.num_rels; ++o)
-      if (rt.dst[o] == d) mxv = fmaxf(mxv, wsum[o] / (float)M);
-    float s = 0.f;
-    for (int o = 0; o < rt.num_rels; ++o)
-      if (rt.dst[o] == d) s += __expf(wsum[o] / (float)M - mxv);
-    beta[r] = __expf(wsum[r] / (float)M - mxv) / s;
-  } else {
-    float dot = 0.f;
-    for (int o = 0; o < rt.num_rels; ++o)
-      if (rt.dst[o] == d) dot += beta[o] * dbeta[o];
-    coef[r] = beta[r] * (dbeta[r] - dot) / (float)M;
-  }
+  float mxv = -INFINITY, s = 0.f;
+  for (int o = 0; o < rr.n; ++o)
+    if (rr.dst[o] == d) mxv = fmaxf(mxv, wsum[o] / (float)M);
+  for (int o = 0; o < rr.n; ++o)
+    if (rr.dst[o] == d) s += __expf(wsum[o] / (float)M - mxv);
+  out[r] = __expf(wsum[r] / (float)M - mxv) / s;
 }
 
-// h[v] = act( sum_{r -> type(v)} beta_r m[rel_row_off[r] + v] + b )
-template <typename T>
-__global__ void __launch_bounds__(256) attn_fuse_kernel(LayerDev L, TypeTab tt, RelsOfType ro, PtrTab pt, int H, int relu, int lpr_log2,
-                                                        const T *__restrict__ mbuf, const float *__restrict__ beta,
-                                                        T *__restrict__ h) {
-  using P = Piece<T>;
-  const int lpr = 1 << lpr_log2;
-  const int q = threadIdx.x & (lpr - 1);
-  const int64_t row = (int64_t)blockIdx.x * (256 >> lpr_log2) + (threadIdx.x >> lpr_log2);
-  const int T_ = tt.num_types;
-  if (row >= tt.out_row_off[T_]) return;
-  const int d = find_le(tt.out_row_off, T_, (int)row);
-  const int v = (int)row - tt.out_row_off[d];
-  float acc[P::N];
-  const T *bias = reinterpret_cast<const T *>(pt.bias[d]);
-  if (bias) P::load(acc, bias + q * P::N);
-  else {
+// h[v] = act( sum_{r -> type(v)} beta_r m[rel_row_off[r] + v] + b ).  Every block takes the softmax over the relations
+// itself (a few hundred flops; as a launch of one block it cost 5 us); the first one writes it out for the backward.
+template <typename TS>
+__global__ void __launch_bounds__(256) attn_fuse_kernel(RelRows rr, TypeTiles ty, RelsOfType ro, PtrTab pt, int H, int relu, int lpr_log2,
+                                                        int rpg, const float *__restrict__ mbuf, const float *__restrict__ wsum,
+                                                        float *__restrict__ beta, TS *__restrict__ h) {
+  __shared__ float sb[kMaxR];
+  relation_softmax(rr, wsum, sb);
+  __syncthreads();
+  if (blockIdx.x == 0 && threadIdx.x < rr.n) beta[threadIdx.x] = sb[threadIdx.x];
+  const int gpb = 256 >> lpr_log2;
+  const int q = threadIdx.x & ((1 << lpr_log2) - 1), grp = threadIdx.x >> lpr_log2;
+  const int d = find_le(ty.tile_off, ty.n, (int)blockIdx.x);
+  const int M = ty.row_off[d + 1] - ty.row_off[d];
+  const int v0 = ((int)blockIdx.x - ty.tile_off[d]) * gpb * rpg;
+  float bv[4] = {0.f, 0.f, 0.f, 0.f};
+  if (pt.bias[d]) Quad<TS>::load(bv, reinterpret_cast<const TS *>(pt.bias[d]) + q * 4);
+  for (int i = 0; i < rpg; ++i) {
+    const int v = v0 + i * gpb + grp;
+    if (v >= M) return;
+    float acc[4] = {bv[0], bv[1], bv[2], bv[3]};
+    for (int j = ro.first[d]; j < ro.first[d + 1]; ++j) {
+      const int r = ro.rel[j];
+      const float b = sb[r];
+      float mv[4];
+      Q4::load(mv, mbuf + ((int64_t)rr.row_off[r] + v) * H + q * 4);
 #pragma unroll
-    for (int i = 0; i < P::N; ++i) acc[i] = 0.f;
-  }
-  for (int j = ro.first[d]; j < ro.first[d + 1]; ++j) {
-    const int r = ro.rel[j];
-    const float b = beta[r];
-    float mv[P::N];
-    P::load(mv, mbuf + ((int64_t)L.rel_row_off[r] + v) * H + q * P::N);
+      for (int c = 0; c < 4; ++c) acc[c] += b * mv[c];
+    }
+    if (relu) {
 #pragma unroll
-    for (int i = 0; i < P::N; ++i) acc[i] += b * mv[i];
+      for (int c = 0; c < 4; ++c) acc[c] = fmaxf(acc[c], 0.f);
+    }
+    Quad<TS>::store(h + ((int64_t)ty.row_off[d] + v) * H + q * 4, acc);
   }
-  if (relu) {
-#pragma unroll
-    for (int i = 0; i < P::N; ++i) acc[i] = fmaxf(acc[i], 0.f);
-  }
-  P::store(h + row * H + q * P::N, acc);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -282,110 +378,130 @@ static int log2_exact(int n) {
   return l;
 }
 
-hgnn_status launch_attn_proj(hipStream_t s, int dtype, const TypeTab &tt, const PtrTab &w_type_as_root, const SegTab &tiles, int H,
-                             const void *x, void *z, bool z_f32) {
+// Tiles of `rows` rows, cut per relation; returns their number.
+static int tile_relations(RelRows &rr, int rows) {
+  rr.tile_off[0] = 0;
+  for (int r = 0; r < rr.n; ++r) rr.tile_off[r + 1] = rr.tile_off[r] + (rr.row_off[r + 1] - rr.row_off[r] + rows - 1) / rows;
+  return rr.tile_off[rr.n];
+}
+static int tile_types(TypeTiles &ty, int rows) {
+  ty.tile_off[0] = 0;
+  for (int t = 0; t < ty.n; ++t) ty.tile_off[t + 1] = ty.tile_off[t] + (ty.row_off[t + 1] - ty.row_off[t] + rows - 1) / rows;
+  return ty.tile_off[ty.n];
+}
+// Rows a lane group walks: one while that leaves fewer than `blocks` blocks, at most `most`.
+static int rows_per_group(int64_t rows, int gpb, int blocks, int most) {
+  int n = 1;
+  while (n < most && rows >= (int64_t)gpb * n * 2 * blocks) n *= 2;
+  return n;
+}
+
+hgnn_status launch_attn_proj(hipStream_t s, int dtype, const TypeTab &tt, const PtrTab &w_type_as_root, int H, const void *x, float *z,
+                             float *wsum) {
+  SegTab tiles;
+  std::memset(&tiles, 0, sizeof(tiles));
+  tiles.num_segs = tt.num_types;
+  int mi = 2;
+  for (;; mi = 1) {   // 64x64 tiles where 128x128 ones would leave compute units without a block
+    const int e = 64 * mi, tn = (H + e - 1) / e;
+    for (int t = 0; t < tt.num_types; ++t)
+      tiles.tile_off[t + 1] = tiles.tile_off[t] + ((tt.row_off[t + 1] - tt.row_off[t] + e - 1) / e) * tn;
+    if (mi == 1 || tiles.tile_off[tt.num_types] >= 512) break;
+  }
   const int n = tiles.tile_off[tt.num_types];
   if (n == 0) return HGNN_OK;
   dim3 grid(round_up8(n)), blk(kThreads);
-  if (dtype == HGNN_BF16 && z_f32)
-    HGNN_LAUNCH((attn_proj_kernel<bf16, float>), grid, blk, 0, s, tt, w_type_as_root, tiles, H, (const bf16 *)x, (float *)z);
-  else if (dtype == HGNN_BF16)
-    HGNN_LAUNCH((attn_proj_kernel<bf16, bf16>), grid, blk, 0, s, tt, w_type_as_root, tiles, H, (const bf16 *)x, (bf16 *)z);
-  else
-    HGNN_LAUNCH((attn_proj_kernel<float, float>), grid, blk, 0, s, tt, w_type_as_root, tiles, H, (const float *)x, (float *)z);
-  HGNN_HIP(hipGetLastError());
-  return HGNN_OK;
-}
-
-hgnn_status launch_attn_agg(hipStream_t s, int dtype, const LayerDev &L, const TypeTab &tt, const RelTab &rt,
-                            const void *const *a_src, const void *const *a_dst, int H, int heads, const void *z, void *mout,
-                            float *mx, float *ls) {
-  if (L.rows == 0) return HGNN_OK;
-  AttnPtrs ap;
-  std::memset(&ap, 0, sizeof(ap));
-  for (int r = 0; r < rt.num_rels; ++r) {
-    ap.a_src[r] = a_src[r];
-    ap.a_dst[r] = a_dst[r];
+#define HGNN_PROJ(TY, MI_) HGNN_LAUNCH((attn_proj_kernel<TY, MI_>), grid, blk, 0, s, tt, w_type_as_root, tiles, H, (const TY *)x, z, wsum)
+  if (dtype == HGNN_BF16) {
+    if (mi == 2) HGNN_PROJ(bf16, 2); else HGNN_PROJ(bf16, 1);
+  } else {
+    if (mi == 2) HGNN_PROJ(float, 2); else HGNN_PROJ(float, 1);
   }
-  const int es = dtype == HGNN_BF16 ? 2 : 4;
-  const int lpr = H * es / 16, l2 = log2_exact(lpr), hl = (H / heads) * es / 16;
-  dim3 grid((unsigned)((L.rows + (256 >> l2) - 1) / (256 >> l2)));
-  if (dtype == HGNN_BF16)
-    HGNN_LAUNCH(attn_agg_kernel<bf16>, grid, dim3(256), 0, s, L, tt, rt, ap, H, heads, l2, hl, (const bf16 *)z, (bf16 *)mout, mx, ls);
-  else
-    HGNN_LAUNCH(attn_agg_kernel<float>, grid, dim3(256), 0, s, L, tt, rt, ap, H, heads, l2, hl, (const float *)z, (float *)mout, mx, ls);
+#undef HGNN_PROJ
   HGNN_HIP(hipGetLastError());
   return HGNN_OK;
 }
 
-hgnn_status launch_attn_sem(hipStream_t s, int dtype, const LayerDev &L, const TypeTab &tt, const RelTab &rt, int H, const void *mbuf,
-                            const void *w_sem, const void *b_sem, const void *q_sem, void *tbuf, float *wsum) {
-  SegTab tiles;
-  std::memset(&tiles, 0, sizeof(tiles));
-  for (int r = 0; r < rt.num_rels; ++r) tiles.tile_off[r + 1] = tiles.tile_off[r] + (tt.n_dst[rt.dst[r]] + BM - 1) / BM;
-  tiles.num_segs = rt.num_rels;
-  const int n = tiles.tile_off[rt.num_rels];
+hgnn_status launch_attn_agg(hipStream_t s, int dtype, const LayerDev &L, RelRows rr, const AttnPtrs &ap, int H, int heads,
+                            const float *z, float *mout, float *mx, float *ls) {
+  if (L.rows == 0) return HGNN_OK;
+  const int lpr = H / 4, l2 = log2_exact(lpr), hl = (H / heads) / 4, gpb = 256 >> l2;
+  const int rpg = rows_per_group(L.rows, gpb, 4096, 4);
+  dim3 grid(tile_relations(rr, gpb * rpg));
+  if (dtype == HGNN_BF16) HGNN_LAUNCH(attn_agg_kernel<bf16>, grid, dim3(256), 0, s, L, rr, ap, H, heads, l2, hl, rpg, z, mout, mx, ls);
+  else HGNN_LAUNCH(attn_agg_kernel<float>, grid, dim3(256), 0, s, L, rr, ap, H, heads, l2, hl, rpg, z, mout, mx, ls);
+  HGNN_HIP(hipGetLastError());
+  return HGNN_OK;
+}
+
+// Rows per tile of the semantic-attention GEMMs: 64 where 128 would leave compute units without a block.
+static int sem_tile_rows(RelRows &rr) { return tile_relations(rr, 128) >= 512 ? 128 : 64; }
+
+hgnn_status launch_attn_sem(hipStream_t s, int dtype, RelRows rr, int H, const float *mbuf, const void *w_sem, const void *b_sem,
+                            const void *q_sem, float *tbuf, float *wsum) {
+  const int tm = sem_tile_rows(rr);
+  const int n = tile_relations(rr, tm);
   if (n == 0) return HGNN_OK;
-  dim3 grid(round_up8(n)), blk(kThreads);
-  if (dtype == HGNN_BF16)
-    HGNN_LAUNCH(attn_sem_kernel<bf16>, grid, blk, 0, s, L, tt, rt, tiles, H, (const bf16 *)mbuf, (const bf16 *)w_sem, (const bf16 *)b_sem,
-                (const bf16 *)q_sem, (bf16 *)tbuf, wsum);
-  else
-    HGNN_LAUNCH(attn_sem_kernel<float>, grid, blk, 0, s, L, tt, rt, tiles, H, (const float *)mbuf, (const float *)w_sem,
-                (const float *)b_sem, (const float *)q_sem, (float *)tbuf, wsum);
+#define HGNN_SEM(TY, MI_)                                                                                                       \
+  HGNN_LAUNCH((attn_sem_kernel<TY, MI_>), dim3(n), dim3(kThreads), 0, s, rr, H, mbuf, (const TY *)w_sem, (const TY *)b_sem,      \
+              (const TY *)q_sem, tbuf, wsum)
+  if (dtype == HGNN_BF16) {
+    if (tm == 128) HGNN_SEM(bf16, 2); else HGNN_SEM(bf16, 1);
+  } else {
+    if (tm == 128) HGNN_SEM(float, 2); else HGNN_SEM(float, 1);
+  }
+#undef HGNN_SEM
   HGNN_HIP(hipGetLastError());
   return HGNN_OK;
 }
 
-hgnn_status launch_attn_beta(hipStream_t s, const TypeTab &tt, const RelTab &rt, const float *wsum, float *beta, const float *dbeta,
-                             float *coef, int mode) {
-  HGNN_LAUNCH(attn_beta_kernel, dim3(1), dim3(kMaxR), 0, s, tt, rt, wsum, beta, dbeta, coef, mode);
-  HGNN_HIP(hipGetLastError());
-  return HGNN_OK;
-}
-
-static void rels_of_type(const TypeTab &tt, const RelTab &rt, RelsOfType &ro) {
+static void rels_of_type(const RelRows &rr, int num_types, RelsOfType &ro) {
   std::memset(&ro, 0, sizeof(ro));
   int n = 0;
-  for (int d = 0; d < tt.num_types; ++d) {
+  for (int d = 0; d < num_types; ++d) {
     ro.first[d] = (uint16_t)n;
-    for (int r = 0; r < rt.num_rels; ++r)
-      if (rt.dst[r] == d) ro.rel[n++] = (uint8_t)r;
+    for (int r = 0; r < rr.n; ++r)
+      if (rr.dst[r] == d) ro.rel[n++] = (uint8_t)r;
   }
-  ro.first[tt.num_types] = (uint16_t)n;
+  ro.first[num_types] = (uint16_t)n;
 }
 
-hgnn_status launch_attn_fuse(hipStream_t s, int dtype, const LayerDev &L, const TypeTab &tt, const RelTab &rt, const PtrTab &pt, int H,
-                             int relu, const void *mbuf, const float *beta, void *h) {
-  const int64_t rows = tt.out_row_off[tt.num_types];
+static void dst_types(const TypeTab &tt, TypeTiles &ty) {
+  std::memset(&ty, 0, sizeof(ty));
+  ty.n = tt.num_types;
+  for (int t = 0; t <= ty.n; ++t) ty.row_off[t] = tt.out_row_off[t];
+}
+
+hgnn_status launch_attn_fuse(hipStream_t s, int dtype, const TypeTab &tt, const RelRows &rr, const PtrTab &pt, int H, int relu,
+                             const float *mbuf, const float *wsum, float *beta, void *h) {
+  TypeTiles ty;
+  dst_types(tt, ty);
+  const int64_t rows = ty.row_off[ty.n];
   if (rows == 0) return HGNN_OK;
   RelsOfType ro;
-  rels_of_type(tt, rt, ro);
-  const int es = dtype == HGNN_BF16 ? 2 : 4;
-  const int l2 = log2_exact(H * es / 16);
-  dim3 grid((unsigned)((rows + (256 >> l2) - 1) / (256 >> l2)));
-  if (dtype == HGNN_BF16)
-    HGNN_LAUNCH(attn_fuse_kernel<bf16>, grid, dim3(256), 0, s, L, tt, ro, pt, H, relu, l2, (const bf16 *)mbuf, beta, (bf16 *)h);
-  else
-    HGNN_LAUNCH(attn_fuse_kernel<float>, grid, dim3(256), 0, s, L, tt, ro, pt, H, relu, l2, (const float *)mbuf, beta, (float *)h);
+  rels_of_type(rr, tt.num_types, ro);
+  const int l2 = log2_exact(H / 4), gpb = 256 >> l2, rpg = rows_per_group(rows, gpb, 2048, 4);
+  dim3 grid(tile_types(ty, gpb * rpg));
+  if (dtype == HGNN_BF16) HGNN_LAUNCH(attn_fuse_kernel<bf16>, grid, dim3(256), 0, s, rr, ty, ro, pt, H, relu, l2, rpg, mbuf, wsum, beta, (bf16 *)h);
+  else HGNN_LAUNCH(attn_fuse_kernel<float>, grid, dim3(256), 0, s, rr, ty, ro, pt, H, relu, l2, rpg, mbuf, wsum, beta, (float *)h);
   HGNN_HIP(hipGetLastError());
   return HGNN_OK;
 }
 
 // ==========================================================================================
 // Backward part.
-//   fusion      dbeta_r = sum_v G'_v . m_v^r ; softmax over relations backward -> coef_r (attn_beta_kernel, mode 1)
-//               du = coef_r q (1 - t^2), dq, db_s (column sums) ; dW_s += m^T du (MFMA, split over rows)
-//               dm = beta_r G'_v + du W_s^T (MFMA)
-//   aggregation per merged row: alpha recomputed from the saved maximum and sum; sum_u alpha_u dalpha_u in a first pass;
-//               per edge alpha and ds (gradient before the LeakyReLU) are stored by CSR position, da_src / da_dst
-//               accumulated in registers over a run of rows; per source row (transpose): dz = sum over its edges
-//               of alpha dm_v + ds a_src, plus, for a destination row, sum_r (sum_u ds) a_dst
+//   fusion      G' = G [h > 0] and db; dbeta_r = sum_v G'_v . m_v^r in the same pass;
+//               du = coef_r q (1 - t^2) with coef from the softmax over relations (taken in each block that needs it),
+//               never stored: dW_s += m^T du, dq, db_s (column sums) and dm = beta_r G'_v + du W_s^T build it as they load t
+//   aggregation per merged row, one pass over its edges: alpha from the saved maximum and sum, dalpha = dm . z_u,
+//               (alpha, dalpha) stored per edge and sum_u alpha_u dalpha_u per row, so that the score gradient
+//               ds = alpha (dalpha - sum) LeakyReLU' can be formed where it is used; per source row (transpose):
+//               dz = sum over its edges of alpha dm_v + ds a_src, plus, for a destination row, sum_r (sum_u ds) a_dst
 //   projection  dW_t = X_t^T dZ_t and dX_t = dZ_t W_t^T run on the layer GEMMs of the mean variant.
 // ==========================================================================================
 struct ZeroList {
-  float *p[2 * kMaxR + 8];
-  int32_t n[2 * kMaxR + 8];
+  float *p[2 * kMaxR + 2 * kMaxT + 8];
+  int32_t n[2 * kMaxR + 2 * kMaxT + 8];
   int32_t count;
 };
 __global__ void attn_zero_kernel(ZeroList zl) {
@@ -395,280 +511,309 @@ __global__ void attn_zero_kernel(ZeroList zl) {
   for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < zl.n[i]; j += gridDim.x * blockDim.x) p[j] = 0.f;
 }
 
-// dbeta[r] += sum over the rows of relation r of G'[v] . m[row]
-template <typename T>
-__global__ void __launch_bounds__(256) attn_dbeta_kernel(LayerDev L, TypeTab tt, RelTab rt, int H, int ldg, int lpr_log2, int rows_per_group,
-                                                         const T *__restrict__ gp, const T *__restrict__ mbuf,
-                                                         float *__restrict__ dbeta) {
-  using P = Piece<T>;
+// One pass over the incoming gradient: mask by the activation (gp), bias gradient, and dbeta[r] += sum of G'[v] . m[row]
+// for every relation that ends in the row's type.  A lane group takes four rows at a time: their G' stay in registers
+// while the aggregates of one relation after the other are read.  Bound: the read of m.
+template <typename TS>
+__global__ void __launch_bounds__(256) attn_mask_dbeta_kernel(RelRows rr, TypeTiles ty, RelsOfType ro, GradPtrTab gt, int H, int relu,
+                                                              int lpr_log2, int trips, const TS *__restrict__ g, const TS *__restrict__ h,
+                                                              TS *__restrict__ gp, const float *__restrict__ mbuf,
+                                                              float *__restrict__ dbeta) {
   __shared__ float part[kMaxR];
+  __shared__ float s_b[kAttnMaxH];
+  const int lpr = 1 << lpr_log2, gpb = 256 >> lpr_log2;
+  const int q = threadIdx.x & (lpr - 1), grp = threadIdx.x >> lpr_log2;
+  const int d = find_le(ty.tile_off, ty.n, (int)blockIdx.x);
+  const int M = ty.row_off[d + 1] - ty.row_off[d];
+  const int v0 = ((int)blockIdx.x - ty.tile_off[d]) * gpb * 4 * trips;
+  const int j0 = ro.first[d], j1 = ro.first[d + 1];
   for (int i = threadIdx.x; i < kMaxR; i += 256) part[i] = 0.f;
+  for (int i = threadIdx.x; i < kAttnMaxH; i += 256) s_b[i] = 0.f;
   __syncthreads();
-  const int lpr = 1 << lpr_log2;
-  const int q = threadIdx.x & (lpr - 1);
-  const int64_t g0 = ((int64_t)blockIdx.x * (256 >> lpr_log2) + (threadIdx.x >> lpr_log2)) * rows_per_group;
-  for (int64_t rho = g0; rho < g0 + rows_per_group && rho < L.rows; ++rho) {
-    const int r = find_le(L.rel_row_off, rt.num_rels, (int)rho);
-    const int v = (int)rho - L.rel_row_off[r];
-    float a[P::N], b[P::N];
-    P::load(a, gp + ((int64_t)tt.out_row_off[rt.dst[r]] + v) * ldg + q * P::N);
-    P::load(b, mbuf + rho * H + q * P::N);
-    float d = 0.f;
+  float bsum[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int it = 0; it < trips; ++it) {
+    const int vb = v0 + it * gpb * 4 + grp;
+    if (vb >= M) break;   // whole groups
+    float gv[4][4], hv[4][4];
 #pragma unroll
-    for (int i = 0; i < P::N; ++i) d += a[i] * b[i];
-    for (int o = lpr >> 1; o > 0; o >>= 1) d += __shfl_xor(d, o);
-    if (q == 0) atomicAdd(&part[r], d);
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < rt.num_rels; i += 256)
-    if (part[i] != 0.f) atomicAdd(dbeta + i, part[i]);
-}
-
-// du = coef_r q (1 - t^2); dq[c] += coef_r sum_rows t ; db_s[c] += sum_rows du.  128 columns x 2 row lanes per block.
-template <typename T>
-__global__ void __launch_bounds__(256) attn_du_kernel(LayerDev L, RelTab rt, int rows_per_block, const T *__restrict__ tbuf,
-                                                      const T *__restrict__ q_sem, const float *__restrict__ coef,
-                                                      T *__restrict__ du, float *__restrict__ dq, float *__restrict__ dbs) {
-  __shared__ float sq[256], sb[256];
-  const int c = threadIdx.x & (kSemDim - 1), half = threadIdx.x >> 7;
-  const float qc = to_float(q_sem[c]);
-  float aq = 0.f, ab = 0.f;
-  const int64_t r0 = (int64_t)blockIdx.x * rows_per_block;
-  int r = -1, r_end = -1;
-  float cf = 0.f;
-  for (int64_t rho = r0 + half; rho < r0 + rows_per_block && rho < L.rows; rho += 2) {
-    if ((int)rho >= r_end) {
-      r = find_le(L.rel_row_off, rt.num_rels, (int)rho);
-      r_end = L.rel_row_off[r + 1];
-      cf = coef[r];
+    for (int u = 0; u < 4; ++u) {
+      const int64_t at = ((int64_t)ty.row_off[d] + min(vb + u * gpb, M - 1)) * H + q * 4;
+      Quad<TS>::load(gv[u], g + at);
+      if (relu) Quad<TS>::load(hv[u], h + at);
     }
-    const float t = to_float(tbuf[rho * kSemDim + c]);
-    const float d = cf * qc * (1.f - t * t);
-    du[rho * kSemDim + c] = from_float<T>(d);
-    aq += cf * t;
-    ab += d;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const bool on = vb + u * gpb < M;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        if (!on || (relu && !(hv[u][c] > 0.f))) gv[u][c] = 0.f;
+        bsum[c] += gv[u][c];
+      }
+      if (relu && on) Quad<TS>::store(gp + ((int64_t)ty.row_off[d] + vb + u * gpb) * H + q * 4, gv[u]);
+    }
+    for (int j = j0; j < j1; ++j) {
+      const float *mr = mbuf + (int64_t)rr.row_off[ro.rel[j]] * H + q * 4;
+      float mv[4][4], dot = 0.f;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) Q4::load(mv[u], mr + (int64_t)min(vb + u * gpb, M - 1) * H);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        dot += (gv[u][0] * mv[u][0] + gv[u][1] * mv[u][1]) + (gv[u][2] * mv[u][2] + gv[u][3] * mv[u][3]);
+      for (int o = lpr >> 1; o > 0; o >>= 1) dot += __shfl_xor(dot, o);
+      if (q == 0) atomicAdd(&part[j - j0], dot);
+    }
   }
-  sq[threadIdx.x] = aq;
-  sb[threadIdx.x] = ab;
+  float *db = gt.dbias[d];
+  if (db) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) atomicAdd(&s_b[q * 4 + c], bsum[c]);
+  }
   __syncthreads();
-  if (half == 0) {
-    atomicAdd(dq + c, sq[c] + sq[c + kSemDim]);
-    atomicAdd(dbs + c, sb[c] + sb[c + kSemDim]);
-  }
+  if (db)
+    for (int i = threadIdx.x; i < H; i += 256) atomicAdd(db + i, s_b[i]);
+  for (int i = threadIdx.x; i < j1 - j0; i += 256) atomicAdd(dbeta + ro.rel[j0 + i], part[i]);
 }
 
-// dm[row] = du[row] W_s^T + beta_r G'[v]
-template <typename T>
-__global__ void __launch_bounds__(kThreads, 2) attn_dm_kernel(LayerDev L, TypeTab tt, RelTab rt, SegTab tiles, int H, int ldg,
-                                                            const T *__restrict__ du, const T *__restrict__ w_sem,
-                                                            const T *__restrict__ gp, const float *__restrict__ beta,
-                                                            T *__restrict__ dm) {
-  __shared__ GemmLds<T> sm;
-  const int tile = xcd_tile(blockIdx.x, gridDim.x);
-  const int R = rt.num_rels;
-  if (tile >= tiles.tile_off[R]) return;
-  const int r = find_le(tiles.tile_off, R, tile);
-  const int tiles_n = (H + BN - 1) / BN;
-  const int local = tile - tiles.tile_off[r];
-  const int m0 = (local / tiles_n) * BM, n0 = (local % tiles_n) * BN;
-  const int d = rt.dst[r];
-  const int M = tt.n_dst[d];
-  const int64_t row0 = L.rel_row_off[r];
+// coef_r = beta_r (dbeta_r - sum_r' beta_r' dbeta_r') / M_d, the factor of q (1 - t^2) in du.
+__device__ __forceinline__ float relation_coef(const RelRows &rr, const float *__restrict__ beta, const float *__restrict__ dbeta, int r) {
+  const int d = rr.dst[r];
+  float dot = 0.f;
+  for (int o = 0; o < rr.n; ++o)
+    if (rr.dst[o] == d) dot += beta[o] * dbeta[o];
+  return beta[r] * (dbeta[r] - dot) / (float)(rr.row_off[r + 1] - rr.row_off[r]);
+}
+
+// dW_s += m^T du, dq += coef sum t, db_s += coef q sum (1 - t^2) over `rows` rows of one relation: the block multiplies
+// m^T (1 - t^2) and scales the result (fp32 MFMA, whose rate bounds this part).
+__device__ __forceinline__ void attn_dws_part(GemmLds<float, 2, 2> &sm, const float *m, const float *t, int64_t row0, int k_begin, int k_end,
+                                              int H, int f0, float coef, const float *qs, float *__restrict__ dws,
+                                              float *__restrict__ dq, float *__restrict__ dbs) {
   f32x16 acc[2][2];
   zero_acc(acc);
-  if (threadIdx.x == 0) put_seg(sm.seg[0], du + row0 * kSemDim, kSemDim, w_sem, kSemDim, 0, kSemDim);
+  if (threadIdx.x == 0) put_seg(sm.seg[0], m + row0 * H, H, t + row0 * kSemDim, kSemDim, k_begin, k_end);
   __syncthreads();
-  gemm_run<T, true, true, true>(acc, sm, 1, M, m0, H, n0);
-  const float b = beta[r];
-  const T *g = gp + ((int64_t)tt.out_row_off[d] + m0) * ldg + n0;
-  const int vr = M - m0, vc = H - n0;
-  write_tile(acc, sm, dm + (row0 + m0) * H + n0, H, vr, vc, [&](float v, int row, int col) {
-    return (row < vr && col < vc) ? v + b * to_float(g[(int64_t)row * ldg + col]) : 0.f;
+  float st[4] = {0.f, 0.f, 0.f, 0.f}, s1[4] = {0.f, 0.f, 0.f, 0.f};
+  gemm_run<float, true, false, false>(acc, sm, 1, H, f0, kSemDim, 0, NoXform(), [&](auto &mv, int) {
+    int i = 0;
+    for (auto &rg : mv.reg) {
+      const f32x4 v = __builtin_bit_cast(f32x4, rg);
+      const f32x4 w = {1.f - v.x * v.x, 1.f - v.y * v.y, 1.f - v.z * v.z, 1.f - v.w * v.w};
+      if ((mv.okmask >> i) & 1u) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          st[c] += v[c];
+          s1[c] += w[c];
+        }
+      }
+      rg = __builtin_bit_cast(u32x4, w);
+      ++i;
+    }
+  });
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  float qc[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) qc[j] = coef * qs[(wave & 1) * 64 + j * 32 + (lane & 31)];
+  HGNN_FOR_EACH_ACC({
+    if (f0 + row < H) atomicAdd(dws + (int64_t)(f0 + row) * kSemDim + col, val * qc[j_]);
+  })
+  if (f0 != 0) return;   // one block per row slice adds the column sums
+  float *red = reinterpret_cast<float *>(&sm.a[0][0]);   // [8 row lanes][128], twice
+  const int c0 = (threadIdx.x % 32) * 4, part = threadIdx.x / 32;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    red[part * kSemDim + c0 + c] = st[c];
+    red[1024 + part * kSemDim + c0 + c] = s1[c];
+  }
+  __syncthreads();
+  const int c = threadIdx.x & (kSemDim - 1), half = threadIdx.x >> 7;
+  float s = 0.f;
+#pragma unroll
+  for (int p = 0; p < 8; ++p) s += red[half * 1024 + p * kSemDim + c];
+  if (half == 0) atomicAdd(dq + c, coef * s);
+  else atomicAdd(dbs + c, coef * qs[c] * s);
+}
+
+// dm[row] = du[row] W_s^T + beta_r G'[v], one tile of 64 MI rows x 128 columns.
+template <typename TS, int MI>
+__device__ __forceinline__ void attn_dm_part(MixLds<TS, MI> &sm, const float *t, const TS *__restrict__ w_sem, const TS *__restrict__ gp,
+                                             float *__restrict__ dm, int64_t row0, int M, int m0, int n0, int H, float coef, float beta,
+                                             const float *qs) {
+  f32x16 acc[MI][2];
+  zero_acc(acc);
+  mix_run<true>(acc, sm, t + row0 * kSemDim, kSemDim, M, m0, w_sem, kSemDim, H, n0, kSemDim, [&](f32x4 v, int k) {
+    const f32x4 q = *reinterpret_cast<const f32x4 *>(qs + k);
+    return f32x4{coef * q.x * (1.f - v.x * v.x), coef * q.y * (1.f - v.y * v.y), coef * q.z * (1.f - v.z * v.z), coef * q.w * (1.f - v.w * v.w)};
+  });
+  tile_pieces(acc, sm.stage(), M - m0, [&](int row, int col, f32x4 v) {
+    if (n0 + col >= H) return;
+    float gv[4];
+    Quad<TS>::load(gv, gp + (int64_t)(m0 + row) * H + n0 + col);
+    float o[4] = {v.x + beta * gv[0], v.y + beta * gv[1], v.z + beta * gv[2], v.w + beta * gv[3]};
+    Q4::store(dm + (row0 + m0 + row) * H + n0 + col, o);
   });
 }
 
-// dW_s += m^T du over the row slice [k_begin, k_end)
-template <typename T>
-__global__ void __launch_bounds__(kThreads, 2) attn_dws_kernel(int64_t rows, int split_rows, int H, const T *__restrict__ mbuf,
-                                                             const T *__restrict__ du, float *__restrict__ dws) {
-  __shared__ GemmLds<T> sm;
-  const int tiles_f = (H + BM - 1) / BM;
-  const int tf = blockIdx.x % tiles_f, sp = blockIdx.x / tiles_f;
-  const int64_t k_begin = (int64_t)sp * split_rows;
-  if (k_begin >= rows) return;
-  const int k_end = (int)(k_begin + split_rows < rows ? k_begin + split_rows : rows);
-  f32x16 acc[2][2];
-  zero_acc(acc);
-  if (threadIdx.x == 0) put_seg(sm.seg[0], mbuf, H, du, kSemDim, (int)k_begin, k_end);
+// Both products of the semantic attention's backward in ONE launch, their blocks interleaved: dW_s is bound by the fp32
+// matrix rate, dm by memory, and neither depends on the other.
+template <typename TS, int MI>
+__global__ void __launch_bounds__(kThreads, 2) attn_sem_bwd_kernel(RelRows dwt, RelRows dmt, SemBwd p, int H, const float *__restrict__ mbuf,
+                                                                 const float *__restrict__ tbuf, const TS *__restrict__ w_sem,
+                                                                 const TS *__restrict__ q_sem, const TS *__restrict__ gp,
+                                                                 const float *__restrict__ beta, const float *__restrict__ dbeta,
+                                                                 float *__restrict__ dm, float *__restrict__ dws, float *__restrict__ dq,
+                                                                 float *__restrict__ dbs) {
+  union Lds {
+    GemmLds<float, 2, 2> dw;
+    MixLds<TS, MI> dm;
+  };
+  __shared__ Lds sm;
+  __shared__ __attribute__((aligned(16))) float qs[kSemDim];
+  if (threadIdx.x < kSemDim) qs[threadIdx.x] = to_float(q_sem[threadIdx.x]);
   __syncthreads();
-  const int f0 = tf * BM;
-  gemm_run<T, true, false, false>(acc, sm, 1, H, f0, kSemDim, 0);
-  HGNN_FOR_EACH_ACC({
-    if (f0 + row < H) atomicAdd(dws + (int64_t)(f0 + row) * kSemDim + col, val);
-  })
+  const int64_t b = blockIdx.x, total = gridDim.x;
+  const int before = (int)(b * p.n_dw / total);
+  if ((int)((b + 1) * p.n_dw / total) > before) {
+    const int tiles_f = (H + 127) / 128, tf = before % tiles_f, sl = before / tiles_f;
+    const int r = find_le(dwt.tile_off, dwt.n, sl);
+    const int64_t row0 = dwt.row_off[r];
+    const int M = dwt.row_off[r + 1] - (int)row0, k0 = (sl - dwt.tile_off[r]) * p.dw_rows;
+    attn_dws_part(sm.dw, mbuf, tbuf, row0, k0, min(k0 + p.dw_rows, M), H, tf * 128, relation_coef(dwt, beta, dbeta, r), qs, dws, dq, dbs);
+  } else {
+    const int tl = (int)b - before, tiles_n = (H + 127) / 128, tm = tl / tiles_n;
+    const int r = find_le(dmt.tile_off, dmt.n, tm);
+    const int64_t row0 = dmt.row_off[r];
+    const int M = dmt.row_off[r + 1] - (int)row0;
+    attn_dm_part<TS, MI>(sm.dm, tbuf, w_sem, gp + (int64_t)dmt.gdst[r] * H, dm, row0, M, (tm - dmt.tile_off[r]) * 64 * MI,
+                         (tl % tiles_n) * 128, H, relation_coef(dmt, beta, dbeta, r), beta[r], qs);
+  }
 }
 
-// Aggregation backward, by merged row.  A lane group walks `rows_per_group` consecutive rows and keeps the sums for
-// da_src / da_dst of the current relation in registers; they go out with atomic adds when the relation changes.
-template <typename T>
-__global__ void __launch_bounds__(256) attn_agg_bwd_rows_kernel(LayerDev L, TypeTab tt, RelTab rt, AttnPtrs ap, AttnPtrs dap, int H, int heads,
-                                                                int lpr_log2, int hl, int rows_per_group, const T *__restrict__ z,
-                                                                const T *__restrict__ dm,
-                                                                const float *__restrict__ mx, const float *__restrict__ ls,
-                                                                float *__restrict__ alpha, float *__restrict__ dsb,
-                                                                float *__restrict__ dsum) {
-  using P = Piece<T>;
-  const int lpr = 1 << lpr_log2;
-  const int q = threadIdx.x & (lpr - 1);
-  const int k = (q * P::N) / (H / heads);
-  const bool head_lead = (q & (hl - 1)) == 0;
-  const int64_t g0 = ((int64_t)blockIdx.x * (256 >> lpr_log2) + (threadIdx.x >> lpr_log2)) * rows_per_group;
-  // The block's sums for da_src / da_dst meet in LDS first (nearly every block lies inside one relation); only a
-  // group in another relation than the block's first row adds to global memory directly.
+// Aggregation backward, by merged row; blocks are cut per relation.  A lane group walks `rpg` rows and keeps the sums
+// for da_src / da_dst in registers; the block's groups meet in LDS and leave with one atomic add per element.
+// With ds_u = alpha_u f_u (x_u - X), f = LeakyReLU' (1 or 0.2), x = dalpha relative to the row's first edge and
+// X = sum_u alpha_u x_u, one pass over the edges is enough: sum ds z = S1 - X S2 with S1 = sum alpha f x z and
+// S2 = sum alpha f z, and likewise for sum ds.  Taking dalpha relative to the row's first edge leaves ds as it is (the
+// alphas add up to 1) and keeps the difference from cancelling large equal parts.  X and, per edge, (alpha with the sign
+// of the score, x) are stored for the pass over the transpose.  (Two passes over the edges read every neighbour row twice.)
+template <typename TS>
+__global__ void __launch_bounds__(256) attn_agg_bwd_rows_kernel(LayerDev L, RelRows rr, AttnPtrs ap, AttnPtrs dap, int H, int heads,
+                                                                int lpr_log2, int hl, int rpg, const float *__restrict__ z,
+                                                                const float *__restrict__ dm, const float *__restrict__ mx,
+                                                                const float *__restrict__ ls, float2 *__restrict__ ead,
+                                                                float *__restrict__ xsum, float *__restrict__ dsum) {
   __shared__ float s_das[kAttnMaxH], s_dad[kAttnMaxH];
-  __shared__ int s_rel;
+  const int gpb = 256 >> lpr_log2;
+  const int q = threadIdx.x & ((1 << lpr_log2) - 1), grp = threadIdx.x >> lpr_log2;
+  const int k = (q * 4) / (H / heads);
+  const bool lead = (q & (hl - 1)) == 0;
+  const int r = find_le(rr.tile_off, rr.n, (int)blockIdx.x);
+  const int row0 = rr.row_off[r], M = rr.row_off[r + 1] - row0;
+  const int v0 = ((int)blockIdx.x - rr.tile_off[r]) * gpb * rpg;
   for (int i = threadIdx.x; i < H; i += 256) s_das[i] = s_dad[i] = 0.f;
-  if (threadIdx.x == 0) {
-    const int64_t first = (int64_t)blockIdx.x * (256 >> lpr_log2) * rows_per_group;
-    s_rel = first < L.rows ? find_le(L.rel_row_off, rt.num_rels, (int)first) : -1;
-  }
   __syncthreads();
-  int r = -1;
-  float as[P::N], ad[P::N], das[P::N], dad[P::N];
-  auto flush = [&]() {
-    if (r < 0) return;
-    if (r == s_rel) {
-#pragma unroll
-      for (int i = 0; i < P::N; ++i) {
-        if (das[i] != 0.f) atomicAdd(&s_das[q * P::N + i], das[i]);
-        if (dad[i] != 0.f) atomicAdd(&s_dad[q * P::N + i], dad[i]);
-      }
-      return;
-    }
-    float *ps = reinterpret_cast<float *>(const_cast<void *>(dap.a_src[r])) + q * P::N;
-    float *pd = reinterpret_cast<float *>(const_cast<void *>(dap.a_dst[r])) + q * P::N;
-#pragma unroll
-    for (int i = 0; i < P::N; ++i) {
-      if (das[i] != 0.f) atomicAdd(ps + i, das[i]);
-      if (dad[i] != 0.f) atomicAdd(pd + i, dad[i]);
-    }
-  };
-  for (int64_t rho = g0; rho < g0 + rows_per_group && rho < L.rows; ++rho) {
-    if (r < 0 || (int)rho >= L.rel_row_off[r + 1]) {
-      flush();
-      r = find_le(L.rel_row_off, rt.num_rels, (int)rho);
-      P::load(as, reinterpret_cast<const T *>(ap.a_src[r]) + q * P::N);
-      P::load(ad, reinterpret_cast<const T *>(ap.a_dst[r]) + q * P::N);
-#pragma unroll
-      for (int i = 0; i < P::N; ++i) das[i] = dad[i] = 0.f;
-    }
+  const float *zd = z + (int64_t)rr.zdst[r] * H + q * 4, *zq = z + q * 4;
+  float as[4], ad[4], das[4] = {0.f, 0.f, 0.f, 0.f}, dad[4] = {0.f, 0.f, 0.f, 0.f};
+  Quad<TS>::load(as, reinterpret_cast<const TS *>(ap.a_src[r]) + q * 4);
+  Quad<TS>::load(ad, reinterpret_cast<const TS *>(ap.a_dst[r]) + q * 4);
+  for (int i = 0; i < rpg; ++i) {
+    const int v = v0 + i * gpb + grp;
+    if (v >= M) break;
+    const int64_t rho = row0 + v;
     const int e0 = L.rowptr[rho], e1 = L.rowptr[rho + 1];
     if (e1 == e0) {
-      if (head_lead) dsum[rho * heads + k] = 0.f;
+      if (lead) {
+        xsum[rho * heads + k] = 0.f;
+        dsum[rho * heads + k] = 0.f;
+      }
       continue;
     }
-    const int v = (int)rho - L.rel_row_off[r];
-    const int d = rt.dst[r];
-    float zv[P::N], g[P::N];
-    P::load(zv, z + ((int64_t)tt.row_off[d] + v) * H + q * P::N);
-    P::load(g, dm + rho * H + q * P::N);
+    float zv[4], g[4];
+    Q4::load(zv, zd + (int64_t)v * H);
+    Q4::load(g, dm + rho * H + q * 4);
+    const float mxk = mx[rho * heads + k], inv_l = 1.f / ls[rho * heads + k];
     float sd = 0.f;
 #pragma unroll
-    for (int i = 0; i < P::N; ++i) sd += ad[i] * zv[i];
+    for (int j = 0; j < 4; ++j) sd += ad[j] * zv[j];
     for (int o = hl >> 1; o > 0; o >>= 1) sd += __shfl_xor(sd, o);
-    const float mxk = mx[rho * heads + k], inv_l = 1.f / ls[rho * heads + k];
-    // first pass: gm = sum_u alpha_u dalpha_u, summed edge by edge.  (It equals dm . m in exact arithmetic, but the
-    // stored m is rounded to the storage type and the difference would not cancel in alpha (dalpha - gm).)
-    float gm = 0.f;
-    // both passes take four edges at a time: their source rows are loaded together (independent loads in
-    // flight), the sums are then taken edge by edge in the row's order
-    constexpr int U = 4;
-    auto dots = [&](const float (&zu)[P::N], float &ss, float &da) {
-      ss = 0.f;
-      da = 0.f;
+    float S1[4] = {0.f, 0.f, 0.f, 0.f}, S2[4] = {0.f, 0.f, 0.f, 0.f};
+    float X = 0.f, w1 = 0.f, w2 = 0.f, x0 = 0.f;
+    for (int e = e0; e < e1; e += 4) {
+      float zu[4][4], ss[4], da[4];
+      int u[4];
 #pragma unroll
-      for (int i = 0; i < P::N; ++i) {
-        ss += as[i] * zu[i];
-        da += g[i] * zu[i];
+      for (int j = 0; j < 4; ++j) u[j] = L.colidx[min(e + j, e1 - 1)];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) Q4::load(zu[j], zq + (int64_t)u[j] * H);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        ss[j] = (as[0] * zu[j][0] + as[1] * zu[j][1]) + (as[2] * zu[j][2] + as[3] * zu[j][3]);
+        da[j] = (g[0] * zu[j][0] + g[1] * zu[j][1]) + (g[2] * zu[j][2] + g[3] * zu[j][3]);
       }
       for (int o = hl >> 1; o > 0; o >>= 1) {
-        ss += __shfl_xor(ss, o);
-        da += __shfl_xor(da, o);
-      }
-    };
-    for (int eb = e0; eb < e1; eb += U) {
-      float zu[U][P::N];
 #pragma unroll
-      for (int j = 0; j < U; ++j) {
-        const int u = L.colidx[min(eb + j, e1 - 1)];
-        P::load(zu[j], z + (int64_t)u * H + q * P::N);
-      }
-#pragma unroll
-      for (int j = 0; j < U; ++j) {
-        if (eb + j >= e1) break;
-        float ss, da;
-        dots(zu[j], ss, da);
-        const float sc = ss + sd;
-        const float ev = sc > 0.f ? sc : kLeaky * sc;
-        gm += __expf(ev - mxk) * inv_l * da;
-      }
-    }
-    float dsv_sum = 0.f;
-    for (int eb = e0; eb < e1; eb += U) {
-      float zu[U][P::N];
-#pragma unroll
-      for (int j = 0; j < U; ++j) {
-        const int u = L.colidx[min(eb + j, e1 - 1)];
-        P::load(zu[j], z + (int64_t)u * H + q * P::N);
-      }
-#pragma unroll
-      for (int j = 0; j < U; ++j) {
-        const int e = eb + j;
-        if (e >= e1) break;
-        float ss, da;
-        dots(zu[j], ss, da);
-        const float sc = ss + sd;
-        const float ev = sc > 0.f ? sc : kLeaky * sc;
-        const float a = __expf(ev - mxk) * inv_l;
-        const float dsv = a * (da - gm) * (sc > 0.f ? 1.f : kLeaky);
-        if (head_lead) {
-          alpha[(int64_t)e * heads + k] = a;
-          dsb[(int64_t)e * heads + k] = dsv;
+        for (int j = 0; j < 4; ++j) {
+          ss[j] += __shfl_xor(ss[j], o);
+          da[j] += __shfl_xor(da[j], o);
         }
+      }
+      if (e == e0) x0 = da[0];
 #pragma unroll
-        for (int i = 0; i < P::N; ++i) das[i] += dsv * zu[j][i];
-        dsv_sum += dsv;
+      for (int j = 0; j < 4; ++j) {
+        const float sc = ss[j] + sd;
+        const bool on = e + j < e1;
+        const float a = on ? __expf(leaky(sc) - mxk) * inv_l : 0.f;
+        const float af = sc > 0.f ? a : kLeaky * a, x = da[j] - x0;
+        X += a * x;
+        w1 += af * x;
+        w2 += af;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          S1[c] += af * x * zu[j][c];
+          S2[c] += af * zu[j][c];
+        }
+        if (lead && on) ead[(int64_t)(e + j) * heads + k] = make_float2(sc > 0.f ? a : -a, x);
       }
     }
+    const float ds = w1 - X * w2;
 #pragma unroll
-    for (int i = 0; i < P::N; ++i) dad[i] += dsv_sum * zv[i];
-    if (head_lead) dsum[rho * heads + k] = dsv_sum;
-  }
-  flush();
-  __syncthreads();
-  if (s_rel >= 0) {
-    float *ps = reinterpret_cast<float *>(const_cast<void *>(dap.a_src[s_rel]));
-    float *pd = reinterpret_cast<float *>(const_cast<void *>(dap.a_dst[s_rel]));
-    for (int i = threadIdx.x; i < H; i += 256) {
-      if (s_das[i] != 0.f) atomicAdd(ps + i, s_das[i]);
-      if (s_dad[i] != 0.f) atomicAdd(pd + i, s_dad[i]);
+    for (int c = 0; c < 4; ++c) {
+      das[c] += S1[c] - X * S2[c];
+      dad[c] += ds * zv[c];
     }
+    if (lead) {
+      xsum[rho * heads + k] = X;
+      dsum[rho * heads + k] = ds;
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    atomicAdd(&s_das[q * 4 + c], das[c]);
+    atomicAdd(&s_dad[q * 4 + c], dad[c]);
+  }
+  __syncthreads();
+  float *ps = reinterpret_cast<float *>(const_cast<void *>(dap.a_src[r])), *pd = reinterpret_cast<float *>(const_cast<void *>(dap.a_dst[r]));
+  for (int i = threadIdx.x; i < H; i += 256) {
+    atomicAdd(ps + i, s_das[i]);
+    atomicAdd(pd + i, s_dad[i]);
   }
 }
 
 // Aggregation backward, by source row (transpose): dz[c] = sum_j alpha_j dm[crow_j] + ds_j a_src[rel(crow_j)]
-// (+ for a destination row: sum over the relations ending in its type of dsum[row] a_dst[r]).
+// (+ for a destination row: sum over the relations ending in its type of dsum[row] a_dst[r]).  The entries of a row
+// ascend by merged row, so those of one relation are neighbours: their ds are summed and meet a_src once.
 // Work items: one per source row (rows longer than kLongRow entries are left to the chunk items), then one per
 // chunk of a long row, which writes an fp32 partial sum; attn_agg_bwd_long_kernel adds a long row's partials up.
-template <typename T>
-__global__ void __launch_bounds__(256) attn_agg_bwd_cols_kernel(LayerDev L, TypeTab tt, RelTab rt, RelsOfType ro, AttnPtrs ap, int H, int heads,
-                                                                int lpr_log2, const T *__restrict__ dm, const float *__restrict__ alpha,
-                                                                const float *__restrict__ dsb, const float *__restrict__ dsum,
-                                                                T *__restrict__ dz, float *__restrict__ partial) {
-  using P = Piece<T>;
-  const int lpr = 1 << lpr_log2;
-  const int q = threadIdx.x & (lpr - 1);
-  const int k = (q * P::N) / (H / heads);
+// The result leaves in the storage type (the projection's backward reads it there).
+template <typename TS>
+__global__ void __launch_bounds__(256) attn_agg_bwd_cols_kernel(LayerDev L, TypeTab tt, RelRows rr, RelsOfType ro, AttnPtrs ap, int H, int heads,
+                                                                int lpr_log2, const float *__restrict__ dm, const float2 *__restrict__ ead,
+                                                                const float *__restrict__ xsum, const float *__restrict__ dsum,
+                                                                TS *__restrict__ dz, float *__restrict__ partial) {
+  __shared__ int32_t s_off[kMaxR + 1];
+  for (int i = threadIdx.x; i <= rr.n; i += 256) s_off[i] = rr.row_off[i];
+  __syncthreads();
+  const int q = threadIdx.x & ((1 << lpr_log2) - 1);
+  const int k = (q * 4) / (H / heads);
   const int64_t item = (int64_t)blockIdx.x * (256 >> lpr_log2) + (threadIdx.x >> lpr_log2);
   if (item >= (int64_t)L.src_rows + L.n_chunks) return;
   const bool chunk = item >= L.src_rows;
@@ -680,116 +825,111 @@ __global__ void __launch_bounds__(256) attn_agg_bwd_cols_kernel(LayerDev L, Type
   } else if (j1 - j0 > kLongRow) {
     return;
   }
-  float acc[P::N];
+  float acc[4] = {0.f, 0.f, 0.f, 0.f};
+  int r = -1, r_hi = 0;
+  float sds = 0.f;
+  auto flush = [&]() {
+    if (r < 0) return;
+    float as[4];
+    Quad<TS>::load(as, reinterpret_cast<const TS *>(ap.a_src[r]) + q * 4);
 #pragma unroll
-  for (int i = 0; i < P::N; ++i) acc[i] = 0.f;
-  int r_lo = 0, r_hi = 0;
-  float as[P::N];
-  auto rel_of = [&](int rho) {
-    if (rho < r_lo || rho >= r_hi) {
-      const int r = find_le(L.rel_row_off, rt.num_rels, rho);
-      r_lo = L.rel_row_off[r];
-      r_hi = L.rel_row_off[r + 1];
-      P::load(as, reinterpret_cast<const T *>(ap.a_src[r]) + q * P::N);
-    }
+    for (int i = 0; i < 4; ++i) acc[i] += sds * as[i];
+    sds = 0.f;
   };
-  int j = j0;
-  for (; j + 2 <= j1; j += 2) {   // two rows of dm in flight
-    const int rho0 = L.crow[j], e0 = L.cperm[j], rho1 = L.crow[j + 1], e1 = L.cperm[j + 1];
-    float g0[P::N], g1[P::N];
-    P::load(g0, dm + (int64_t)rho0 * H + q * P::N);
-    P::load(g1, dm + (int64_t)rho1 * H + q * P::N);
-    const float a0 = alpha[(int64_t)e0 * heads + k], d0 = dsb[(int64_t)e0 * heads + k];
-    const float a1 = alpha[(int64_t)e1 * heads + k], d1 = dsb[(int64_t)e1 * heads + k];
-    rel_of(rho0);
+  for (int j = j0; j < j1; j += 4) {   // four rows of dm in flight
+    int rho[4], e[4];
+    float g[4][4], xs[4];
+    float2 ad[4];
 #pragma unroll
-    for (int i = 0; i < P::N; ++i) acc[i] += a0 * g0[i] + d0 * as[i];
-    rel_of(rho1);
+    for (int u = 0; u < 4; ++u) {
+      const int jj = min(j + u, j1 - 1);
+      rho[u] = L.crow[jj];
+      e[u] = L.cperm[jj];
+    }
 #pragma unroll
-    for (int i = 0; i < P::N; ++i) acc[i] += a1 * g1[i] + d1 * as[i];
+    for (int u = 0; u < 4; ++u) {
+      Q4::load(g[u], dm + (int64_t)rho[u] * H + q * 4);
+      ad[u] = ead[(int64_t)e[u] * heads + k];
+      xs[u] = xsum[(int64_t)rho[u] * heads + k];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (j + u >= j1) break;
+      if (rho[u] >= r_hi) {
+        flush();
+        r = find_le(s_off, rr.n, rho[u]);
+        r_hi = s_off[r + 1];
+      }
+      const bool pos = !(__float_as_uint(ad[u].x) >> 31);
+      const float a = fabsf(ad[u].x);
+      sds += a * (ad[u].y - xs[u]) * (pos ? 1.f : kLeaky);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[i] += a * g[u][i];
+    }
   }
-  if (j < j1) {
-    const int rho0 = L.crow[j], e0 = L.cperm[j];
-    float g0[P::N];
-    P::load(g0, dm + (int64_t)rho0 * H + q * P::N);
-    const float a0 = alpha[(int64_t)e0 * heads + k], d0 = dsb[(int64_t)e0 * heads + k];
-    rel_of(rho0);
-#pragma unroll
-    for (int i = 0; i < P::N; ++i) acc[i] += a0 * g0[i] + d0 * as[i];
-  }
+  flush();
   if (chunk) {
-    float *pp = partial + (item - L.src_rows) * H + q * P::N;
-#pragma unroll
-    for (int i = 0; i < P::N; ++i) pp[i] = acc[i];
+    Q4::store(partial + (item - L.src_rows) * H + q * 4, acc);
     return;
   }
-  const int t = find_le(tt.row_off, tt.num_types, (int)c);
+  int t = 0;
+  while (c >= tt.row_off[t + 1]) ++t;
   const int v = (int)c - tt.row_off[t];
   if (v < tt.n_dst[t]) {
     for (int jj = ro.first[t]; jj < ro.first[t + 1]; ++jj) {
-      const int rr = ro.rel[jj];
-      const float sv = dsum[((int64_t)L.rel_row_off[rr] + v) * heads + k];
-      float ad[P::N];
-      P::load(ad, reinterpret_cast<const T *>(ap.a_dst[rr]) + q * P::N);
+      const int o = ro.rel[jj];
+      const float sv = dsum[((int64_t)s_off[o] + v) * heads + k];
+      float ad[4];
+      Quad<TS>::load(ad, reinterpret_cast<const TS *>(ap.a_dst[o]) + q * 4);
 #pragma unroll
-      for (int i = 0; i < P::N; ++i) acc[i] += sv * ad[i];
+      for (int i = 0; i < 4; ++i) acc[i] += sv * ad[i];
     }
   }
-  P::store(dz + c * H + q * P::N, acc);
+  Quad<TS>::store(dz + c * H + q * 4, acc);
 }
 
 // Long rows: one block per row adds the chunk partials (threads form groups over four columns each, group g takes
 // chunks g, g + groups, ...; LDS adds the groups), then the destination-side term, and writes the row.
-template <typename T>
-__global__ void __launch_bounds__(256) attn_agg_bwd_long_kernel(LayerDev L, TypeTab tt, RelsOfType ro, AttnPtrs ap, int H, int heads,
+template <typename TS>
+__global__ void __launch_bounds__(256) attn_agg_bwd_long_kernel(LayerDev L, TypeTab tt, RelRows rr, RelsOfType ro, AttnPtrs ap, int H, int heads,
                                                                 const float *__restrict__ partial, const float *__restrict__ dsum,
-                                                                T *__restrict__ dz) {
+                                                                TS *__restrict__ dz) {
   __shared__ float red[256 * 4];
   const int i = blockIdx.x;
   const int c = L.long_row[i];
   const int j0 = L.long_chunk0[i], j1 = L.long_chunk0[i + 1];
-  const int nw = H / 4;
-  int lanes = 1;
-  while (lanes < nw && lanes < 256) lanes <<= 1;
-  const int groups = 256 / lanes, g = threadIdx.x / lanes, ln = threadIdx.x % lanes;
-  const int t = find_le(tt.row_off, tt.num_types, c);
+  const int lanes = H / 4;   // a power of two, at most 64
+  const int groups = 256 / lanes, g = threadIdx.x / lanes, q = threadIdx.x % lanes;
+  int t = 0;
+  while (c >= tt.row_off[t + 1]) ++t;
   const int v = c - tt.row_off[t];
-  for (int q0 = 0; q0 < nw; q0 += lanes) {
-    const int q = q0 + ln;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    if (q < nw) {
-      int j = j0 + g;
-      for (; j + 3 * groups < j1; j += 4 * groups) {
-        const f32x4 v0 = *reinterpret_cast<const f32x4 *>(partial + (int64_t)j * H + q * 4);
-        const f32x4 v1 = *reinterpret_cast<const f32x4 *>(partial + (int64_t)(j + groups) * H + q * 4);
-        const f32x4 v2 = *reinterpret_cast<const f32x4 *>(partial + (int64_t)(j + 2 * groups) * H + q * 4);
-        const f32x4 v3 = *reinterpret_cast<const f32x4 *>(partial + (int64_t)(j + 3 * groups) * H + q * 4);
-        acc += (v0 + v1) + (v2 + v3);
-      }
-      for (; j < j1; j += groups) acc += *reinterpret_cast<const f32x4 *>(partial + (int64_t)j * H + q * 4);
-    }
-    if (groups > 1) {
-      *reinterpret_cast<f32x4 *>(red + threadIdx.x * 4) = acc;
-      __syncthreads();
-      if (g == 0)
-        for (int o = 1; o < groups; ++o) acc += *reinterpret_cast<const f32x4 *>(red + (o * lanes + ln) * 4);
-    }
-    if (g == 0 && q < nw) {
-      const int k = (q * 4) / (H / heads);
-      if (v < tt.n_dst[t]) {
-        for (int jj = ro.first[t]; jj < ro.first[t + 1]; ++jj) {
-          const int rr = ro.rel[jj];
-          const float sv = dsum[((int64_t)L.rel_row_off[rr] + v) * heads + k];
-          const T *ad = reinterpret_cast<const T *>(ap.a_dst[rr]) + q * 4;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[e] += sv * to_float(ad[e]);
-        }
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) dz[(int64_t)c * H + q * 4 + e] = from_float<T>(acc[e]);
-    }
-    if (groups > 1) __syncthreads();
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  int j = j0 + g;
+  for (; j + 3 * groups < j1; j += 4 * groups) {
+    const f32x4 v0 = *reinterpret_cast<const f32x4 *>(partial + (int64_t)j * H + q * 4);
+    const f32x4 v1 = *reinterpret_cast<const f32x4 *>(partial + (int64_t)(j + groups) * H + q * 4);
+    const f32x4 v2 = *reinterpret_cast<const f32x4 *>(partial + (int64_t)(j + 2 * groups) * H + q * 4);
+    const f32x4 v3 = *reinterpret_cast<const f32x4 *>(partial + (int64_t)(j + 3 * groups) * H + q * 4);
+    acc += (v0 + v1) + (v2 + v3);
   }
+  for (; j < j1; j += groups) acc += *reinterpret_cast<const f32x4 *>(partial + (int64_t)j * H + q * 4);
+  *reinterpret_cast<f32x4 *>(red + threadIdx.x * 4) = acc;
+  __syncthreads();
+  if (g != 0) return;
+  for (int o = 1; o < groups; ++o) acc += *reinterpret_cast<const f32x4 *>(red + (o * lanes + q) * 4);
+  const int k = (q * 4) / (H / heads);
+  float out[4] = {acc.x, acc.y, acc.z, acc.w};
+  if (v < tt.n_dst[t]) {
+    for (int jj = ro.first[t]; jj < ro.first[t + 1]; ++jj) {
+      const int o = ro.rel[jj];
+      const float sv = dsum[((int64_t)rr.row_off[o] + v) * heads + k];
+      float ad[4];
+      Quad<TS>::load(ad, reinterpret_cast<const TS *>(ap.a_dst[o]) + q * 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) out[e] += sv * ad[e];
+    }
+  }
+  Quad<TS>::store(dz + (int64_t)c * H + q * 4, out);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -809,99 +949,82 @@ hgnn_status launch_attn_zero(hipStream_t s, float *const *ptrs, const int64_t *c
   return HGNN_OK;
 }
 
-hgnn_status launch_attn_dbeta(hipStream_t s, int dtype, const LayerDev &L, const TypeTab &tt, const RelTab &rt, int H, int ldg,
-                              const void *gp, const void *mbuf, float *dbeta) {
-  if (L.rows == 0) return HGNN_OK;
-  const int es = dtype == HGNN_BF16 ? 2 : 4;
-  const int l2 = log2_exact(H * es / 16), gpb = 256 >> l2, rpg = 16;
-  dim3 grid((unsigned)((L.rows + (int64_t)gpb * rpg - 1) / ((int64_t)gpb * rpg)));
-  if (dtype == HGNN_BF16) HGNN_LAUNCH(attn_dbeta_kernel<bf16>, grid, dim3(256), 0, s, L, tt, rt, H, ldg, l2, rpg, (const bf16 *)gp, (const bf16 *)mbuf, dbeta);
-  else HGNN_LAUNCH(attn_dbeta_kernel<float>, grid, dim3(256), 0, s, L, tt, rt, H, ldg, l2, rpg, (const float *)gp, (const float *)mbuf, dbeta);
-  HGNN_HIP(hipGetLastError());
-  return HGNN_OK;
-}
-
-hgnn_status launch_attn_du(hipStream_t s, int dtype, const LayerDev &L, const RelTab &rt, const void *tbuf, const void *q_sem,
-                           const float *coef, void *du, float *dq, float *dbs) {
-  if (L.rows == 0) return HGNN_OK;
-  const int rpb = 256;
-  dim3 grid((unsigned)((L.rows + rpb - 1) / rpb));
-  if (dtype == HGNN_BF16) HGNN_LAUNCH(attn_du_kernel<bf16>, grid, dim3(256), 0, s, L, rt, rpb, (const bf16 *)tbuf, (const bf16 *)q_sem, coef, (bf16 *)du, dq, dbs);
-  else HGNN_LAUNCH(attn_du_kernel<float>, grid, dim3(256), 0, s, L, rt, rpb, (const float *)tbuf, (const float *)q_sem, coef, (float *)du, dq, dbs);
-  HGNN_HIP(hipGetLastError());
-  return HGNN_OK;
-}
-
-hgnn_status launch_attn_dm(hipStream_t s, int dtype, const LayerDev &L, const TypeTab &tt, const RelTab &rt, int H, int ldg, const void *du,
-                           const void *w_sem, const void *gp, const float *beta, void *dm) {
-  SegTab tiles;
-  std::memset(&tiles, 0, sizeof(tiles));
-  const int tn = (H + BN - 1) / BN;
-  for (int r = 0; r < rt.num_rels; ++r) tiles.tile_off[r + 1] = tiles.tile_off[r] + ((tt.n_dst[rt.dst[r]] + BM - 1) / BM) * tn;
-  tiles.num_segs = rt.num_rels;
-  const int n = tiles.tile_off[rt.num_rels];
-  if (n == 0) return HGNN_OK;
-  dim3 grid(round_up8(n)), blk(kThreads);
-  if (dtype == HGNN_BF16)
-    HGNN_LAUNCH(attn_dm_kernel<bf16>, grid, blk, 0, s, L, tt, rt, tiles, H, ldg, (const bf16 *)du, (const bf16 *)w_sem, (const bf16 *)gp, beta, (bf16 *)dm);
-  else
-    HGNN_LAUNCH(attn_dm_kernel<float>, grid, blk, 0, s, L, tt, rt, tiles, H, ldg, (const float *)du, (const float *)w_sem, (const float *)gp, beta, (float *)dm);
-  HGNN_HIP(hipGetLastError());
-  return HGNN_OK;
-}
-
-hgnn_status launch_attn_dws(hipStream_t s, int dtype, int64_t rows, int H, const void *mbuf, const void *du, float *dws) {
+hgnn_status launch_attn_mask_dbeta(hipStream_t s, int dtype, const TypeTab &tt, const RelRows &rr, const GradPtrTab &gt, int H, int relu,
+                                   const void *g, const void *h, void *gp, const float *mbuf, float *dbeta) {
+  TypeTiles ty;
+  dst_types(tt, ty);
+  const int64_t rows = ty.row_off[ty.n];
   if (rows == 0) return HGNN_OK;
-  const int split_rows = 2048;
-  const int tiles_f = (H + BM - 1) / BM;
-  dim3 grid((unsigned)(tiles_f * ((rows + split_rows - 1) / split_rows))), blk(kThreads);
-  if (dtype == HGNN_BF16) HGNN_LAUNCH(attn_dws_kernel<bf16>, grid, blk, 0, s, rows, split_rows, H, (const bf16 *)mbuf, (const bf16 *)du, dws);
-  else HGNN_LAUNCH(attn_dws_kernel<float>, grid, blk, 0, s, rows, split_rows, H, (const float *)mbuf, (const float *)du, dws);
+  RelsOfType ro;
+  rels_of_type(rr, tt.num_types, ro);
+  // a block ends with an atomic add to every dbeta and bias element of its type; adds to one address are serialised
+  // (~11 ns each), so large batches take more rows per block
+  const int l2 = log2_exact(H / 4), gpb = 256 >> l2, trips = rows_per_group(rows, gpb * 4, 1024, 16);
+  dim3 grid(tile_types(ty, gpb * 4 * trips));
+  if (dtype == HGNN_BF16)
+    HGNN_LAUNCH(attn_mask_dbeta_kernel<bf16>, grid, dim3(256), 0, s, rr, ty, ro, gt, H, relu, l2, trips, (const bf16 *)g, (const bf16 *)h,
+                (bf16 *)gp, mbuf, dbeta);
+  else
+    HGNN_LAUNCH(attn_mask_dbeta_kernel<float>, grid, dim3(256), 0, s, rr, ty, ro, gt, H, relu, l2, trips, (const float *)g, (const float *)h,
+                (float *)gp, mbuf, dbeta);
   HGNN_HIP(hipGetLastError());
   return HGNN_OK;
 }
 
-hgnn_status launch_attn_agg_bwd(hipStream_t s, int dtype, const LayerDev &L, const TypeTab &tt, const RelTab &rt, const void *const *a_src,
-                                const void *const *a_dst, float *const *da_src, float *const *da_dst, int H, int heads, const void *z,
-                                const void *mbuf, const void *dm, const float *mx, const float *ls, float *alpha, float *dsb,
-                                float *dsum, void *dz, float *partial) {
-  AttnPtrs ap, dap;
-  std::memset(&ap, 0, sizeof(ap));
-  std::memset(&dap, 0, sizeof(dap));
-  for (int r = 0; r < rt.num_rels; ++r) {
-    ap.a_src[r] = a_src[r];
-    ap.a_dst[r] = a_dst[r];
-    dap.a_src[r] = da_src[r];
-    dap.a_dst[r] = da_dst[r];
+hgnn_status launch_attn_sem_bwd(hipStream_t s, int dtype, const RelRows &rr, int H, const float *mbuf, const float *tbuf, const void *w_sem,
+                                const void *q_sem, const void *gp, const float *beta, const float *dbeta, float *dm, float *dws, float *dq,
+                                float *dbs) {
+  if (rr.row_off[rr.n] == 0) return HGNN_OK;
+  RelRows dwt = rr, dmt = rr;
+  const int tiles = (H + 127) / 128, tm = sem_tile_rows(dmt);
+  const int n_dm = tile_relations(dmt, tm) * tiles;
+  // rows per block of the dW_s part: about three rounds of the chip's 512 block slots (a round that is nearly empty at
+  // the end then costs little), but at least four K-steps of 32 rows for one tile's worth of atomic adds
+  SemBwd p;
+  const int64_t steps = (int64_t)rr.row_off[rr.n] / 32 * tiles;
+  p.dw_rows = 32 * (int)std::max<int64_t>(4, (steps + 1499) / 1500);
+  p.n_dw = tile_relations(dwt, p.dw_rows) * tiles;
+#define HGNN_SEMB(TY, MI_)                                                                                                         \
+  HGNN_LAUNCH((attn_sem_bwd_kernel<TY, MI_>), dim3(p.n_dw + n_dm), dim3(kThreads), 0, s, dwt, dmt, p, H, mbuf, tbuf,                 \
+              (const TY *)w_sem, (const TY *)q_sem, (const TY *)gp, beta, dbeta, dm, dws, dq, dbs)
+  if (dtype == HGNN_BF16) {
+    if (tm == 128) HGNN_SEMB(bf16, 2); else HGNN_SEMB(bf16, 1);
+  } else {
+    if (tm == 128) HGNN_SEMB(float, 2); else HGNN_SEMB(float, 1);
   }
-  const int es = dtype == HGNN_BF16 ? 2 : 4;
-  const int lpr = H * es / 16, l2 = log2_exact(lpr), hl = (H / heads) * es / 16, gpb = 256 >> l2, rpg = 8;
+#undef HGNN_SEMB
+  HGNN_HIP(hipGetLastError());
+  return HGNN_OK;
+}
+
+hgnn_status launch_attn_agg_bwd(hipStream_t s, int dtype, const LayerDev &L, const TypeTab &tt, RelRows rr, const AttnPtrs &ap,
+                                const AttnPtrs &dap, int H, int heads, const float *z, const float *dm, const float *mx, const float *ls,
+                                void *edge_ad, float *xsum, float *dsum, void *dz, float *partial) {
+  const int l2 = log2_exact(H / 4), hl = (H / heads) / 4, gpb = 256 >> l2;
+  float2 *ead = (float2 *)edge_ad;
   if (L.rows > 0) {
-    dim3 grid((unsigned)((L.rows + (int64_t)gpb * rpg - 1) / ((int64_t)gpb * rpg)));
+    const int rpg = rows_per_group(L.rows, gpb, 1024, 16);
+    dim3 grid(tile_relations(rr, gpb * rpg));
     if (dtype == HGNN_BF16)
-      HGNN_LAUNCH(attn_agg_bwd_rows_kernel<bf16>, grid, dim3(256), 0, s, L, tt, rt, ap, dap, H, heads, l2, hl, rpg, (const bf16 *)z,
-                  (const bf16 *)dm, mx, ls, alpha, dsb, dsum);
+      HGNN_LAUNCH(attn_agg_bwd_rows_kernel<bf16>, grid, dim3(256), 0, s, L, rr, ap, dap, H, heads, l2, hl, rpg, z, dm, mx, ls, ead, xsum, dsum);
     else
-      HGNN_LAUNCH(attn_agg_bwd_rows_kernel<float>, grid, dim3(256), 0, s, L, tt, rt, ap, dap, H, heads, l2, hl, rpg, (const float *)z,
-                  (const float *)dm, mx, ls, alpha, dsb, dsum);
+      HGNN_LAUNCH(attn_agg_bwd_rows_kernel<float>, grid, dim3(256), 0, s, L, rr, ap, dap, H, heads, l2, hl, rpg, z, dm, mx, ls, ead, xsum, dsum);
     HGNN_HIP(hipGetLastError());
   }
   if (L.src_rows > 0) {
     RelsOfType ro;
-    rels_of_type(tt, rt, ro);
+    rels_of_type(rr, tt.num_types, ro);
     dim3 grid((unsigned)(((int64_t)L.src_rows + L.n_chunks + gpb - 1) / gpb));
     if (dtype == HGNN_BF16)
-      HGNN_LAUNCH(attn_agg_bwd_cols_kernel<bf16>, grid, dim3(256), 0, s, L, tt, rt, ro, ap, H, heads, l2, (const bf16 *)dm, alpha, dsb, dsum,
-                  (bf16 *)dz, partial);
+      HGNN_LAUNCH(attn_agg_bwd_cols_kernel<bf16>, grid, dim3(256), 0, s, L, tt, rr, ro, ap, H, heads, l2, dm, ead, xsum, dsum, (bf16 *)dz, partial);
     else
-      HGNN_LAUNCH(attn_agg_bwd_cols_kernel<float>, grid, dim3(256), 0, s, L, tt, rt, ro, ap, H, heads, l2, (const float *)dm, alpha, dsb, dsum,
-                  (float *)dz, partial);
+      HGNN_LAUNCH(attn_agg_bwd_cols_kernel<float>, grid, dim3(256), 0, s, L, tt, rr, ro, ap, H, heads, l2, dm, ead, xsum, dsum, (float *)dz, partial);
     HGNN_HIP(hipGetLastError());
     if (L.n_long > 0) {
       if (dtype == HGNN_BF16)
-        HGNN_LAUNCH(attn_agg_bwd_long_kernel<bf16>, dim3(L.n_long), dim3(256), 0, s, L, tt, ro, ap, H, heads, partial, dsum, (bf16 *)dz);
+        HGNN_LAUNCH(attn_agg_bwd_long_kernel<bf16>, dim3(L.n_long), dim3(256), 0, s, L, tt, rr, ro, ap, H, heads, partial, dsum, (bf16 *)dz);
       else
-        HGNN_LAUNCH(attn_agg_bwd_long_kernel<float>, dim3(L.n_long), dim3(256), 0, s, L, tt, ro, ap, H, heads, partial, dsum, (float *)dz);
+        HGNN_LAUNCH(attn_agg_bwd_long_kernel<float>, dim3(L.n_long), dim3(256), 0, s, L, tt, rr, ro, ap, H, heads, partial, dsum, (float *)dz);
       HGNN_HIP(hipGetLastError());
     }
   }

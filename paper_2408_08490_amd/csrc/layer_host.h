@@ -1,0 +1,42 @@
+// What the host sides of the layer variants share (api.cpp: mean aggregation and the entry points; attn_layer.cpp).
+#pragma once
+#include "common.h"
+
+namespace hgnn {
+
+static inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
+static inline int esize(int dtype) { return dtype == HGNN_BF16 ? 2 : 4; }
+
+// Waits for the host build and fills the device-side view of one layer's index arrays.
+hgnn_status layer_dev(hgnn_ctx *ctx, hgnn_graph *g, int32_t layer, LayerDev &D);
+
+// While alive, the launches made on this thread are timed if the probe selects (kernel, layer).
+struct Probe {
+  bool active = false;
+  Probe(hgnn_ctx *c, int kernel, int layer, bool enabled = true);
+  ~Probe();
+};
+
+// The attention variant's side of the layer entry points.  It registers itself when the library is loaded, so that the
+// host runtime links without any device code of the variant.
+struct AttnVariant {
+  hgnn_status (*workspace)(hgnn_ctx *, hgnn_graph *, int32_t layer, const hgnn_layer_params *, size_t *saved_bytes, size_t *scratch_bytes);
+  hgnn_status (*fwd)(hgnn_ctx *, void *stream, hgnn_graph *, int32_t layer, const hgnn_layer_params *, const void *x, void *h, void *saved,
+                     size_t saved_bytes, void *scratch, size_t scratch_bytes);
+  hgnn_status (*bwd)(hgnn_ctx *, void *stream, hgnn_graph *, int32_t layer, const hgnn_layer_params *, const void *x, const void *h_out,
+                     const void *saved, const void *grad_h, void *grad_x, const hgnn_layer_grads *, void *scratch, size_t scratch_bytes);
+  hgnn_status (*launch_count)(hgnn_ctx *, hgnn_graph *, int32_t layer, const hgnn_layer_params *, int32_t *fwd, int32_t *bwd);
+};
+AttnVariant &attn_variant();
+
+// Rows per slice of the weight-gradient reduction, for `tiles` output tiles over `rows` rows each on average and
+// `other_steps` K-steps of work in the same launch.  A block's share is 1/640 of the launch's K-steps (a bit over the
+// chip's 512 block slots: the launch is then one long round whose end is filled by the shorter blocks), but at least
+// `least` K-steps, since every slice ends with a tile's worth of atomic adds, and at most 64.
+static inline int dw_slice_rows(int dtype, int64_t dw_steps, int64_t other_steps) {
+  const int bk = dtype == HGNN_BF16 ? 64 : 32, least = dtype == HGNN_BF16 ? 8 : 4;
+  const int64_t steps = (dw_steps + other_steps + 639) / 640;
+  return bk * (int)(steps < least ? least : steps > 64 ? 64 : steps);
+}
+
+}  // namespace hgnn
