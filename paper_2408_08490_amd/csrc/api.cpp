@@ -752,14 +752,8 @@ hgnn_status hgnn_layer_workspace_bytes(hgnn_ctx *ctx, hgnn_graph *g, int32_t lay
   return HGNN_OK;
 }
 
-// Whether the layer's aggregation is one launch of the gather-mean kernel for a single input width (which can carry the
-// weight transposes): rows to aggregate, all types one width, a row of at most 256 16-byte pieces.
-static bool transposes_ride(const Plan &pl) {
-  if (pl.dev.rows <= 0) return false;
-  for (int t = 0; t < pl.tt.num_types; ++t)
-    if (pl.tt.in_dim[t] != pl.tt.in_dim[0]) return false;
-  return (int64_t)pl.tt.in_dim[0] * pl.es <= 256 * 16;
-}
+// Whether there is an aggregation launch (which carries the weight transposes as its first blocks).
+static bool transposes_ride(const Plan &pl) { return pl.dev.rows > 0; }
 
 static hgnn_status fwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_t layer, const hgnn_layer_params *p,
                               const void *x, void *h, void *saved, size_t saved_bytes, void *scratch, size_t scratch_bytes,
@@ -789,7 +783,7 @@ static hgnn_status fwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
   if (!saved || !scratch) HGNN_FAIL(HGNN_EINVAL, "NULL work area");
   if (static_area) {
     // the forward's own part of the work area, laid out back to back: transposed weights, low-order plane
-    const size_t wt_bytes = pl.off_gp - pl.off_wt, zlo_bytes = pl.scratch_bytes - pl.off_zlo;
+    const size_t wt_bytes = pl.off_gp - pl.off_wt, zlo_bytes = pl.off_gaddr - pl.off_zlo;
     if (wt_bytes + zlo_bytes > scratch_bytes)
       HGNN_FAIL(HGNN_EINVAL, "layer needs %zu bytes of work area, the static one holds %zu: use hgnn_layer_fwd with a caller-provided area",
                 wt_bytes + zlo_bytes, scratch_bytes);
@@ -819,8 +813,8 @@ static hgnn_status fwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
     for (int r = 0; r < R; ++r)
       if (reo[r + 1] > reo[r]) live[r >> 5] |= 1u << (r & 31);
   }
-  // The weight transposes ride in the aggregation launch (as its first blocks) where that launch is the gather-mean
-  // kernel for one input width; otherwise they are a launch of their own.
+  // The weight transposes ride in the aggregation launch (as its first blocks) where there is one; otherwise they are a
+  // launch of their own.
   TransposeJobs tj;
   make_transpose_jobs(pl.tt, pl.rt, pl.pt, pl.wt, pl.H, wtb, tj);
   const bool rides = !naive && !feature_cat && transposes_ride(pl);
@@ -965,11 +959,12 @@ static void seg_tiles_da(hgnn_ctx *ctx, const Plan &pl, const hgnn_layer_params 
   }
 }
 
-// The same tiles grouped for the merged backward launch: per destination type, per 128-row block, the column blocks
+// The same tiles (of any edge) grouped for the merged backward launch: per destination type, per row block, the column blocks
 // of every live segment whose input gradient is wanted.
-static void grouped_tiles_da(hgnn_ctx *ctx, const Plan &pl, const SegTab &by_seg, DwTab &tl) {
+static void grouped_tiles_da(hgnn_ctx *ctx, const Plan &pl, const SegTab &by_seg, int edge, DwTab &tl) {
   const int R = ctx->R, T = ctx->T;
   std::memset(&tl, 0, sizeof(tl));
+  tl.edge = edge;
   int ne = 0;
   for (int d = 0; d < T; ++d) {
     tl.first[d] = (uint16_t)ne;
@@ -979,11 +974,11 @@ static void grouped_tiles_da(hgnn_ctx *ctx, const Plan &pl, const SegTab &by_seg
       if ((is_rel ? ctx->rel_dst[sgi] : sgi - R) != d || by_seg.tile_off[sgi + 1] == by_seg.tile_off[sgi]) continue;
       tl.seg[ne] = (uint8_t)sgi;
       tl.u_off[ne] = (uint16_t)u;
-      u += (pl.tt.in_dim[is_rel ? ctx->rel_src[sgi] : d] + 127) / 128;
+      u += (pl.tt.in_dim[is_rel ? ctx->rel_src[sgi] : d] + edge - 1) / edge;
       ++ne;
     }
     tl.u_total[d] = (uint16_t)u;
-    tl.tile_off[d + 1] = tl.tile_off[d] + u * ((pl.tt.n_dst[d] + 127) / 128);
+    tl.tile_off[d + 1] = tl.tile_off[d] + u * ((pl.tt.n_dst[d] + edge - 1) / edge);
   }
   tl.first[T] = (uint16_t)ne;
 }
@@ -1160,44 +1155,47 @@ static hgnn_status bwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
   void *dz = sc + pl.off_dz;
   bool da_done = false;
   if (any_dw && pl.total_dst > 0) {
-    // Work list: per destination type its live segments (relations with edges, then the root) and the 128-row
-    // blocks of their weight gradients.  The reduction is split over destination rows so that the launch has
-    // about two blocks per CU, but not into slices under 2048 rows: every extra split costs a tile's worth of
-    // atomic adds, which outweigh the shorter reduction below that (in the merged launch, whose input-gradient
-    // tiles fill the chip anyway: 2048 beat 1024, 1536, 3072 and 4096 by 5 to 20 us per step on the headline).
-    DwTab tl;
-    std::memset(&tl, 0, sizeof(tl));
-    int ne = 0;
-    for (int d = 0; d < T; ++d) {
-      tl.first[d] = (uint16_t)ne;
-      int u = 0;
-      if (pl.tt.n_dst[d] > 0)
-        for (int sgi = 0; sgi < R + T; ++sgi) {
-          const bool is_rel = sgi < R;
-          if (is_rel ? (ctx->rel_dst[sgi] != d || reo[sgi + 1] == reo[sgi] || !gt.dw_rel[sgi]) : (sgi - R != d || !gt.dw_root[d])) continue;
-          tl.seg[ne] = (uint8_t)sgi;
-          tl.u_off[ne] = (uint16_t)u;
-          u += (pl.tt.in_dim[is_rel ? ctx->rel_src[sgi] : d] + 127) / 128;
-          ++ne;
-        }
-      tl.u_total[d] = (uint16_t)u;
+    // Work list: per destination type its live segments (relations with edges, then the root) and the row blocks of
+    // their weight gradients, with the input-gradient tiles of the same launch beside it.  Tiles have 128 rows and
+    // columns, or 64 where the launch would not have a block of 128 for every compute unit.
+    DwTab tl, da_grouped;
+    const bool both = want_dx && da_tl.tile_off[da_tl.num_segs] > 0;
+    const int bk = pl.es == 2 ? 64 : 32;
+    int split_rows = 0;
+    for (int edge = 128;; edge = 64) {
+      std::memset(&tl, 0, sizeof(tl));
+      tl.edge = edge;
+      int ne = 0;
+      int64_t dw_steps = 0, da_steps = 0;
+      const int tiles_h = (pl.H + edge - 1) / edge;
+      for (int d = 0; d < T; ++d) {
+        tl.first[d] = (uint16_t)ne;
+        int u = 0;
+        if (pl.tt.n_dst[d] > 0)
+          for (int sgi = 0; sgi < R + T; ++sgi) {
+            const bool is_rel = sgi < R;
+            if (is_rel ? (ctx->rel_dst[sgi] != d || reo[sgi + 1] == reo[sgi] || !gt.dw_rel[sgi]) : (sgi - R != d || !gt.dw_root[d])) continue;
+            tl.seg[ne] = (uint8_t)sgi;
+            tl.u_off[ne] = (uint16_t)u;
+            u += (pl.tt.in_dim[is_rel ? ctx->rel_src[sgi] : d] + edge - 1) / edge;
+            ++ne;
+          }
+        tl.u_total[d] = (uint16_t)u;
+        dw_steps += (int64_t)u * tiles_h * ((pl.tt.n_dst[d] + bk - 1) / bk);
+      }
+      tl.first[T] = (uint16_t)ne;
+      if (both) {
+        grouped_tiles_da(ctx, pl, da_tl, edge, da_grouped);
+        da_steps = (int64_t)da_grouped.tile_off[T] * ((ldg + bk - 1) / bk);
+      }
+      split_rows = dw_slice_rows(ctx->dtype, edge, dw_steps, da_steps);
+      for (int d = 0; d < T; ++d)
+        tl.tile_off[d + 1] = tl.tile_off[d] + tl.u_total[d] * tiles_h * ((pl.tt.n_dst[d] + split_rows - 1) / split_rows);
+      if (edge == 64 || tl.tile_off[T] + (both ? da_grouped.tile_off[T] : 0) >= 256) break;
     }
-    tl.first[T] = (uint16_t)ne;
-    const int tiles_h = (pl.H + 127) / 128;
-    int split_rows = 4096;
-    for (;;) {
-      int64_t tiles = 0;
-      for (int d = 0; d < T; ++d) tiles += (int64_t)tl.u_total[d] * tiles_h * ((pl.tt.n_dst[d] + split_rows - 1) / split_rows);
-      if (tiles >= 320 || split_rows <= 2048) break;
-      split_rows /= 2;
-    }
-    for (int d = 0; d < T; ++d)
-      tl.tile_off[d + 1] = tl.tile_off[d] + tl.u_total[d] * tiles_h * ((pl.tt.n_dst[d] + split_rows - 1) / split_rows);
     Probe pb(ctx, HGNN_K_GEMM_DW, layer);
-    if (want_dx && da_tl.tile_off[da_tl.num_segs] > 0 && tl.tile_off[T] > 0) {
+    if (both && tl.tile_off[T] > 0) {
       // both backward GEMMs read G' and are independent of each other: one launch
-      DwTab da_grouped;
-      grouped_tiles_da(ctx, pl, da_tl, da_grouped);
       if ((st = launch_gemm_bwd(s, ctx->dtype, pl.dev, pl.tt, pl.rt, wpt, da_grouped, gt, tl, split_rows, pl.H, ldg, fast, x_merged,
                                 saved, gp, dz, bpart, rpb)) != HGNN_OK) return st;
       da_done = true;

@@ -227,31 +227,39 @@ hgnn_status attn_bwd(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_t layer, 
   TypeTab tt2 = pl.tt;
   RelTab rt2 = pl.rt;
   DwTab dt, da;
-  std::memset(&dt, 0, sizeof(dt));
-  std::memset(&da, 0, sizeof(da));
-  const int bk = dtype == HGNN_BF16 ? 64 : 32, tiles_h = (H + 127) / 128;
-  int64_t dw_steps = 0;
-  int ne = 0, na = 0;
   for (int i = 0; i < T; ++i) {
     tt2.n_dst[i] = (int32_t)L.n_src[i];
     tt2.out_row_off[i + 1] = pl.tt.row_off[i + 1];
     rt2.zroot_off4[i] = (uint32_t)(pl.tt.elem_off[i] / 4);
-    dt.first[i] = (uint16_t)ne;
-    da.first[i] = (uint16_t)na;
-    const int u = L.n_src[i] > 0 ? (p->in_dim[i] + 127) / 128 : 0;
-    const bool want = grad_x && u && (!p->input_grad || p->input_grad[i]);
-    if (u) dt.seg[ne++] = (uint8_t)(R + i);
-    if (want) da.seg[na++] = (uint8_t)(R + i);
-    dt.u_total[i] = (uint16_t)u;
-    da.u_total[i] = (uint16_t)(want ? u : 0);
-    da.tile_off[i + 1] = da.tile_off[i] + (want ? u * (int)((L.n_src[i] + 127) / 128) : 0);
-    dw_steps += (int64_t)u * tiles_h * ((L.n_src[i] + bk - 1) / bk);
   }
-  dt.first[T] = (uint16_t)ne;
-  da.first[T] = (uint16_t)na;
-  const int split_rows = dw_slice_rows(dtype, dw_steps, (int64_t)da.tile_off[T] * ((H + bk - 1) / bk));
-  for (int i = 0; i < T; ++i)
-    dt.tile_off[i + 1] = dt.tile_off[i] + dt.u_total[i] * tiles_h * (int)((L.n_src[i] + split_rows - 1) / split_rows);
+  // tiles of 128 rows and columns, or of 64 where the launch would not have a block of 128 for every compute unit
+  int split_rows = 0;
+  for (int edge = 128;; edge = 64) {
+    std::memset(&dt, 0, sizeof(dt));
+    std::memset(&da, 0, sizeof(da));
+    dt.edge = da.edge = edge;
+    const int bk = dtype == HGNN_BF16 ? 64 : 32, tiles_h = (H + edge - 1) / edge;
+    int64_t dw_steps = 0;
+    int ne = 0, na = 0;
+    for (int i = 0; i < T; ++i) {
+      dt.first[i] = (uint16_t)ne;
+      da.first[i] = (uint16_t)na;
+      const int u = L.n_src[i] > 0 ? (p->in_dim[i] + edge - 1) / edge : 0;
+      const bool want = grad_x && u && (!p->input_grad || p->input_grad[i]);
+      if (u) dt.seg[ne++] = (uint8_t)(R + i);
+      if (want) da.seg[na++] = (uint8_t)(R + i);
+      dt.u_total[i] = (uint16_t)u;
+      da.u_total[i] = (uint16_t)(want ? u : 0);
+      da.tile_off[i + 1] = da.tile_off[i] + (want ? u * (int)((L.n_src[i] + edge - 1) / edge) : 0);
+      dw_steps += (int64_t)u * tiles_h * ((L.n_src[i] + bk - 1) / bk);
+    }
+    dt.first[T] = (uint16_t)ne;
+    da.first[T] = (uint16_t)na;
+    split_rows = dw_slice_rows(dtype, edge, dw_steps, (int64_t)da.tile_off[T] * ((H + bk - 1) / bk));
+    for (int i = 0; i < T; ++i)
+      dt.tile_off[i + 1] = dt.tile_off[i] + dt.u_total[i] * tiles_h * (int)((L.n_src[i] + split_rows - 1) / split_rows);
+    if (edge == 64 || dt.tile_off[T] + da.tile_off[T] >= 256) break;
+  }
   Probe pb(ctx, HGNN_K_GEMM_DW, layer);
   const void *dzp = sc + pl.c_dz;
   if (da.tile_off[T] > 0)

@@ -89,9 +89,10 @@ struct SegTab {
 struct DwTab {
   int32_t tile_off[kMaxT + 1];   // tiles before destination type d
   uint16_t first[kMaxT + 1];     // entries [first[d], first[d+1]) of seg / u_off belong to type d
-  uint16_t u_total[kMaxT];       // 128-row blocks of dW over all segments of type d
+  uint16_t u_total[kMaxT];       // row blocks of dW (of `edge` rows) over all segments of type d
   uint16_t u_off[kMaxSeg];       // first block of entry i inside its type
   uint8_t seg[kMaxSeg];          // segment of entry i (relation r -> r, root of type t -> R + t)
+  int32_t edge;                  // edge of the tiles: 128 or 64
 };
 struct WtTab {                      // where each transposed weight lives in the scratch area
   uint32_t rel4[kMaxR];

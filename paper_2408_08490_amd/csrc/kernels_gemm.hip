@@ -281,7 +281,7 @@ __device__ __forceinline__ void dw_tile(GemmLds<T, MI, MI> &sm, int bid, const T
 }
 
 template <typename T, bool FAST, int MI>
-__global__ void __launch_bounds__(kThreads, MI == 1 ? 4 : 2) gemm_dw_kernel(TypeTab tt, RelTab rt, GradPtrTab gt, DwTab tiles, XcdMap xmap, int split_rows, int H,
+__global__ void __launch_bounds__(kThreads, MI == 1 ? 3 : 2) gemm_dw_kernel(TypeTab tt, RelTab rt, GradPtrTab gt, DwTab tiles, XcdMap xmap, int split_rows, int H,
                                                            int ldg, const T *__restrict__ x, const T *__restrict__ z,
                                                            const T *__restrict__ gp) {
   __shared__ GemmLds<T, MI, MI> sm;
@@ -293,20 +293,20 @@ __global__ void __launch_bounds__(kThreads, MI == 1 ? 4 : 2) gemm_dw_kernel(Type
 // end -- the weight gradient has fewer tiles than the chip has block slots -- and the other one's tiles fill them.
 // The last n_bias blocks (when bpart is given) add up the partial bias-gradient sums that the row pass over G'
 // left: a few microseconds of work that would otherwise be a launch of its own.
-template <typename T, bool FAST>
-__global__ void __launch_bounds__(kThreads, 2) gemm_bwd_kernel(LayerDev L, TypeTab tt, RelTab rt, PtrTab pt, DwTab da_tiles,
+template <typename T, bool FAST, int MI>
+__global__ void __launch_bounds__(kThreads, MI == 1 ? 3 : 2) gemm_bwd_kernel(LayerDev L, TypeTab tt, RelTab rt, PtrTab pt, DwTab da_tiles,
                                                             GradPtrTab gt, DwTab dw_tiles, XcdMap xmap, int n_dw, int split_rows,
                                                             int H, int ldg, const T *__restrict__ x, const T *__restrict__ z,
                                                             const T *__restrict__ gp, T *__restrict__ dz,
                                                             const float *__restrict__ bpart, int rpb, int n_bias) {
-  __shared__ GemmLds<T, 2, 2> sm;
+  __shared__ GemmLds<T, MI, MI> sm;
   const int n_gemm = (int)gridDim.x - n_bias;
   if ((int)blockIdx.x >= n_gemm) {
     bias_reduce_part(tt, gt, H, rpb, bpart, (int)blockIdx.x - n_gemm);
     return;
   }
-  if ((int)blockIdx.x < n_dw) dw_tile<T, FAST, 2>(sm, blockIdx.x, tt, rt, gt, dw_tiles, xmap, split_rows, H, ldg, x, z, gp);
-  else da_tile_grouped<T, FAST, 2>(sm, blockIdx.x - n_dw, n_gemm - n_dw, L, tt, rt, pt, da_tiles, ldg, gp, dz);
+  if ((int)blockIdx.x < n_dw) dw_tile<T, FAST, MI>(sm, blockIdx.x, tt, rt, gt, dw_tiles, xmap, split_rows, H, ldg, x, z, gp);
+  else da_tile_grouped<T, FAST, MI>(sm, blockIdx.x - n_dw, n_gemm - n_dw, L, tt, rt, pt, da_tiles, ldg, gp, dz);
 }
 
 static int dw_blocks(int dtype, const TypeTab &tt, const DwTab &tiles, int split_rows, XcdMap &xmap) {
@@ -329,15 +329,17 @@ hgnn_status launch_gemm_bwd(hipStream_t s, int dtype, const LayerDev &L, const T
   const int n_da = round_up8(da_tiles.tile_off[tt.num_types]);
   const int n_bias = bpart ? bias_reduce_blocks(tt.num_types, H) : 0;
   dim3 grid(n_dw + n_da + n_bias), blk(kThreads);
-#define HGNN_BWD(TY, FA)                                                                                             \
-  HGNN_LAUNCH((gemm_bwd_kernel<TY, FA>), grid, blk, 0, s, L, tt, rt, pt, da_tiles, gt, dw_tiles, xmap, n_dw, split_rows, H, \
+#define HGNN_BWD2(TY, FA, MI_)                                                                                       \
+  HGNN_LAUNCH((gemm_bwd_kernel<TY, FA, MI_>), grid, blk, 0, s, L, tt, rt, pt, da_tiles, gt, dw_tiles, xmap, n_dw, split_rows, H, \
               ldg, (const TY *)x, (const TY *)z, (const TY *)gp, (TY *)dz, bpart, rpb, n_bias)
+#define HGNN_BWD(TY, FA) { if (dw_tiles.edge == 64) HGNN_BWD2(TY, FA, 1); else HGNN_BWD2(TY, FA, 2); }
   if (dtype == HGNN_BF16) {
-    if (fast) HGNN_BWD(bf16, true); else HGNN_BWD(bf16, false);
+    if (fast) HGNN_BWD(bf16, true) else HGNN_BWD(bf16, false)
   } else {
-    if (fast) HGNN_BWD(float, true); else HGNN_BWD(float, false);
+    if (fast) HGNN_BWD(float, true) else HGNN_BWD(float, false)
   }
 #undef HGNN_BWD
+#undef HGNN_BWD2
   HGNN_HIP(hipGetLastError());
   return HGNN_OK;
 }
@@ -353,7 +355,7 @@ hgnn_status launch_gemm_dw(hipStream_t s, int dtype, const LayerDev &L, const Ty
 #define HGNN_DW(TY, FA, MI_)                                                                                  \
   HGNN_LAUNCH((gemm_dw_kernel<TY, FA, MI_>), grid, blk, 0, s, tt, rt, gt, tiles, xmap, split_rows, H, ldg, (const TY *)x, \
               (const TY *)z, (const TY *)gp)
-#define HGNN_DW2(TY, FA) { HGNN_DW(TY, FA, 2); }
+#define HGNN_DW2(TY, FA) { if (tiles.edge == 64) HGNN_DW(TY, FA, 1); else HGNN_DW(TY, FA, 2); }
   if (dtype == HGNN_BF16) {
     if (fast) HGNN_DW2(bf16, true) else HGNN_DW2(bf16, false)
   } else {

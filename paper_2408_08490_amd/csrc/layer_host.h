@@ -29,13 +29,17 @@ struct AttnVariant {
 };
 AttnVariant &attn_variant();
 
-// Rows per slice of the weight-gradient reduction, for `tiles` output tiles over `rows` rows each on average and
-// `other_steps` K-steps of work in the same launch.  A block's share is 1/640 of the launch's K-steps (a bit over the
-// chip's 512 block slots: the launch is then one long round whose end is filled by the shorter blocks), but at least
-// `least` K-steps, since every slice ends with a tile's worth of atomic adds, and at most 64.
-static inline int dw_slice_rows(int dtype, int64_t dw_steps, int64_t other_steps) {
-  const int bk = dtype == HGNN_BF16 ? 64 : 32, least = dtype == HGNN_BF16 ? 8 : 4;
-  const int64_t steps = (dw_steps + other_steps + 639) / 640;
+// Rows per slice of the weight-gradient reduction in a launch of `dw_steps` K-steps (over all its tiles) beside
+// `other_steps` K-steps of other tiles.  A block's share is 1/640 of the launch's K-steps (1/1280 with 64x64 tiles, of
+// which twice as many are resident): a bit over the chip's block slots, so that the launch is one long round whose end
+// the shorter blocks fill.  Every slice ends with a tile's worth of atomic adds (the chip does about 0.4e12 a second, 40 ns
+// of all of it per 128x128 tile), hence the least number of K-steps: 32 of bf16 (8 measured 9 us worse on 4096 rows of
+// 512 x 349); an fp32 K-step is several times as long (1.7 us of a compute unit's matrix cores per 128x128 tile), which
+// both keeps the adds cheap beside it and makes long slices a serial chain (64 K-steps in one block were 183 us of a
+// 500 us step).
+static inline int dw_slice_rows(int dtype, int edge, int64_t dw_steps, int64_t other_steps) {
+  const int bk = dtype == HGNN_BF16 ? 64 : 32, least = dtype == HGNN_BF16 ? (edge == 64 ? 8 : 32) : 4;
+  const int64_t share = edge == 64 ? 1280 : 640, steps = (dw_steps + other_steps + share - 1) / share;
   return bk * (int)(steps < least ? least : steps > 64 ? 64 : steps);
 }
 
