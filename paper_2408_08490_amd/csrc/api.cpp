@@ -52,7 +52,7 @@ struct Plan {
   int64_t total_dst = 0;
   size_t z_elems = 0, zroot_elems = 0, wt_elems = 0;
   size_t saved_bytes = 0, scratch_bytes = 0;
-  size_t off_wt = 0, off_gp = 0, off_dz = 0, off_partial = 0, off_acc32 = 0, off_bpart = 0, bpart_rows = 0, off_zlo = 0, off_gaddr = 0;
+  size_t off_wt = 0, off_gp = 0, off_dz = 0, off_partial = 0, off_acc32 = 0, off_bpart = 0, bpart_rows = 0, off_zlo = 0, off_gaddr = 0, off_part = 0;
 };
 
 // The buffer the root term reads holds the destination rows only (n_dst[t] rows per type, back to back).
@@ -142,6 +142,9 @@ static hgnn_status make_plan(hgnn_ctx *ctx, hgnn_graph *g, int32_t layer, const 
   pl.off_bpart = o;   o += align_up(pl.bpart_rows * pl.H * 4, 256);
   pl.off_zlo = o;     o += (pl.es == 2 && p->relu) ? align_up(std::max<size_t>(z, 1) * pl.es, 256) : 0;
   pl.off_gaddr = o;   o += align_up(std::max<size_t>((size_t)L.edges, 1) * 8, 256);  // per-edge row addresses (gather from the stores)
+  int64_t tiles64 = 0;  // partial tiles of the forward's split reduction
+  for (int t = 0; t < T; ++t) tiles64 += (L.n_dst[t] + 63) / 64 * ((pl.H + 63) / 64);
+  pl.off_part = o;    o += tiles64 < (pl.es == 2 ? kDirectTiles / 4 : kDirectTiles) ? kDirectPartBytes : 0;
   pl.scratch_bytes = o;
   if (need_built) {
     hgnn_status st = layer_dev(ctx, g, layer, pl.dev);
@@ -189,6 +192,10 @@ Probe::~Probe() {
   if (active) tl_probe_ctx = nullptr;
 }
 
+OptionalLaunchers &optional_launchers() {
+  static OptionalLaunchers l;
+  return l;
+}
 AttnVariant &attn_variant() {
   static AttnVariant v;
   return v;
@@ -790,6 +797,7 @@ static hgnn_status fwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
     pl.off_wt = 0;
     pl.off_zlo = wt_bytes;
     pl.scratch_bytes = wt_bytes + zlo_bytes;
+    pl.off_part = scratch_bytes;   // behind the area (noalloc.hip)
   }
   if (saved_bytes < pl.saved_bytes || scratch_bytes < pl.scratch_bytes)
     HGNN_FAIL(HGNN_EINVAL, "work areas too small: need %zu saved, %zu scratch bytes", pl.saved_bytes, pl.scratch_bytes);
@@ -858,6 +866,11 @@ static hgnn_status fwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
       if (ctx->dtype == HGNN_BF16 && !ctx->legacy_gemm) {
         done = launch_gemm2_fwd(s, pl.tt, pl.rt, pl.pt, pl.wt, live, pl.H, p->relu, x, saved, zlo, wtb, h, &st);
         if (done && st != HGNN_OK) return st;
+      }
+      if (!done && optional_launchers().gemm_fwd_direct) {
+        done = optional_launchers().gemm_fwd_direct(s, ctx->dtype, pl.tt, pl.rt, pl.pt, pl.wt, live, pl.H, p->relu, x, saved, zlo, wtb, h,
+                                                    (float *)(sc + pl.off_part));
+        if (done) HGNN_HIP(hipGetLastError());
       }
       if (!done && (st = launch_gemm_fwd(s, ctx->dtype, pl.dev, pl.tt, pl.rt, pl.pt, pl.wt, tl, live, pl.H, p->relu, x, saved, zlo, wtb, h, -1, nullptr, tile_mn)) != HGNN_OK) return st;
     }

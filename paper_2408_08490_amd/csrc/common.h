@@ -348,6 +348,17 @@ hgnn_status launch_gemm_fwd(hipStream_t s, int dtype, const LayerDev &L, const T
 // bf16 forward on the LDS-DMA core; false = shape not covered (nothing was launched), else *st is the launch's status
 bool launch_gemm2_fwd(hipStream_t s, const TypeTab &tt, const RelTab &rt, const PtrTab &pt, const WtTab &wt, const uint32_t *live_mask,
                       int H, int relu, const void *x, const void *z, const void *zlo, const void *wt_buf, void *h, hgnn_status *st);
+// Launchers that register themselves when the library is loaded, so that the host runtime links without them.
+constexpr int kDirectTiles = 512;                        // forward launches of fewer 64x64 tiles than this may take the kernel below
+constexpr int kDirectUnits = 512 + kDirectTiles;         // its most (tile, split) pairs: two blocks per compute unit, rounded up per tile
+constexpr size_t kDirectPartBytes = (size_t)kDirectUnits * 64 * 64 * 4;   // their partial tiles
+struct OptionalLaunchers {
+  // forward GEMM with the reduction split over blocks and wavefronts; false: not for this launch (nothing was launched)
+  bool (*gemm_fwd_direct)(hipStream_t s, int dtype, const TypeTab &tt, const RelTab &rt, const PtrTab &pt, const WtTab &wt,
+                          const uint32_t *live_mask, int H, int relu, const void *x, const void *z, const void *zlo,
+                          const void *wt_buf, void *h, float *part) = nullptr;
+};
+OptionalLaunchers &optional_launchers();  // api.cpp
 hgnn_status launch_bias_act(hipStream_t s, int dtype, const TypeTab &tt, const PtrTab &pt, int H, int relu,
                             int type, const float *acc32, void *h);
 // gp has leading dimension ldg >= H (zero beyond H), and so have the weights in `pt`

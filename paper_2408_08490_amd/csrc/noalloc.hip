@@ -8,7 +8,8 @@
 
 namespace hgnn {
 
-static __device__ __align__(256) unsigned char scratch[HGNN_STATIC_SCRATCH_BYTES];
+// the area, and behind it the partial tiles of the forward GEMM's split reduction
+static __device__ __align__(256) unsigned char scratch[HGNN_STATIC_SCRATCH_BYTES + kDirectPartBytes];
 
 constexpr int kMaxDevices = 64;
 static std::mutex g_scratch_m;
