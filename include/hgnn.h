@@ -70,10 +70,12 @@ typedef struct {
 } hgnn_schema;
 
 /* Create a context bound to HIP device `device` (< 0: host-only, for the graph build alone)
- * with `host_threads` builder threads (<= 0: one per online core, at most 16), split evenly
- * over `concurrent_builds` builders that each work on one queued graph at a time (<= 0: a
- * quarter of the threads, at most 4 builders: lowest latency for one build; == host_threads:
- * single-threaded builds, the highest rate when many mini-batches are queued ahead).
+ * with `host_threads` threads for its graph builds (<= 0: one per online core, at most 16; the
+ * contexts of a process share one crew, as large as the largest of them asks for), of which
+ * `concurrent_builds` work on one queued graph each at a time (<= 0: a quarter of the threads, at
+ * most 4) while the others take part in the phases of whatever builds are under way: lowest latency
+ * for one build; == host_threads: single-threaded builds, the highest rate when many mini-batches
+ * are queued ahead.
  * The schema is copied. */
 hgnn_status hgnn_create(hgnn_ctx **out, const hgnn_schema *schema, int device, int host_threads,
                         int concurrent_builds);

@@ -208,6 +208,14 @@ class Graph:
                 np.zeros(0, np.int64) for t in range(T)]
         return (list(n), host, [dp[t] or 0 for t in range(T)]) if device else (list(n), host)
 
+    def device_ids(self):
+        """(n_rows per type, device pointers per type) of the first layer's source rows; blocks until the build has
+        finished."""
+        T = self.ctx.num_types
+        n, dp = (C.c_int64 * T)(), (C.c_void_p * T)()
+        _check(lib.hgnn_graph_ids(self.ctx.handle, self.handle, n, None, dp))
+        return list(n), [p or 0 for p in dp]
+
     def minibatch_view(self, layer, arrays=True):
         v = MinibatchView()
         _check(lib.hgnn_graph_minibatch_view(self.ctx.handle, self.handle, layer, C.byref(v)))

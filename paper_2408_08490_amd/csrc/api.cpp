@@ -1,5 +1,6 @@
 // C ABI entry points: argument checks, per-call planning (offset tables), launch sequences.
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstring>
 #include <unistd.h>
@@ -9,14 +10,33 @@
 namespace hgnn {
 const char *get_error();
 
-static void builder_main(hgnn_ctx *ctx, Builder *bd) {
+// Works off the context's queue with one of its builders (on a thread of the crew).
+static void build_queued(hgnn_ctx *ctx) {
   if (ctx->device >= 0) (void)hipSetDevice(ctx->device);
+  Builder *bd = nullptr;
   for (;;) {
     hgnn_graph *g = nullptr;
     {
-      std::unique_lock<std::mutex> lk(ctx->qm);
-      ctx->qcv.wait(lk, [&] { return ctx->stop || !ctx->queue.empty(); });
-      if (ctx->queue.empty()) return;  // stop requested and nothing left
+      std::lock_guard<std::mutex> lk(ctx->qm);
+      if (!bd) {
+        // there is one for each task (enqueue_graph); best one whose scratch this thread used before or nobody did
+        // (it then lies in memory near the thread), else the one used last
+        auto &idle = ctx->idle_builders;
+        size_t at = idle.size() - 1;
+        const int me = Crew::index();
+        for (size_t i = 0; i < idle.size(); ++i)
+          if (idle[i]->user == me) { at = i; break; }
+          else if (idle[i]->user < 0) at = i;
+        bd = idle[at];
+        idle.erase(idle.begin() + at);
+        bd->user = me;
+      }
+      if (ctx->queue.empty()) {
+        ctx->idle_builders.push_back(bd);
+        --ctx->building;
+        ctx->qcv.notify_all();   // under the lock: hgnn_destroy frees the context once it holds it
+        return;
+      }
       g = ctx->queue.front();
       ctx->queue.pop_front();
     }
@@ -34,8 +54,19 @@ static void free_slab(hgnn_ctx *ctx, Slab &s) {
   s = Slab();
 }
 
+// Looks at the state for a while: a build that is under way often ends before a sleeping thread would be awake again.
+static void look_built(hgnn_graph *g) {
+  if (!Crew::get().look()) return;
+  const auto t0 = std::chrono::steady_clock::now();
+  for (int i = 1; g->state.load(std::memory_order_acquire) == 0; ++i) {
+    cpu_relax();
+    if (i % 64 == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(2 * Crew::kSpinUs)) break;
+  }
+}
+
 static hgnn_status wait_built(hgnn_graph *g) {
-  std::unique_lock<std::mutex> lk(g->m);
+  look_built(g);
+  std::unique_lock<std::mutex> lk(g->m);   // also when the state is known: the builder's last touch of g is under it
   g->cv.wait(lk, [&] { return g->state != 0; });
   if (g->state == 2) HGNN_FAIL((hgnn_status)g->status, "graph build failed: %s", g->err.c_str());
   return HGNN_OK;
@@ -290,17 +321,18 @@ hgnn_status hgnn_create(hgnn_ctx **out, const hgnn_schema *s, int device, int ho
     long on = sysconf(_SC_NPROCESSORS_ONLN);
     n = (int)std::min<long>(16, std::max<long>(1, on));
   }
-  // Graphs are independent, so several are built at once, each by a builder with its own share
-  // of the host threads.  Few builders with several threads each finish one build soonest; one
-  // single-threaded builder per host thread gives the most builds per second (no barriers between
-  // the phases of a build), which is what a caller that queues many mini-batches ahead wants.
-  int nb = concurrent_builds > 0 ? std::min(n, concurrent_builds) : std::max(1, std::min(4, n / 4));
+  // Graphs are independent, so several are built at once.  Few at a time finish one build soonest (the other threads take
+  // part in its phases); one per host thread gives the most builds per second (no barriers between the phases of a
+  // build), which is what a caller that queues many mini-batches ahead wants.  One of the n threads is the caller's own.
+  const int nb = concurrent_builds > 0 ? std::min(n, concurrent_builds) : std::max(1, std::min(4, n / 4));
+  c->pool.reset(new ThreadPool(n - nb + 1));
   for (int i = 0; i < nb; ++i) {
-    Builder *b = new Builder();
-    b->pool = new ThreadPool(n / nb + (i < n % nb ? 1 : 0));
-    c->builders.push_back(b);
+    c->builders.emplace_back(new Builder());
+    c->builders.back()->pool = c->pool.get();
+    c->idle_builders.push_back(c->builders.back().get());
   }
-  for (Builder *b : c->builders) b->th = std::thread(builder_main, c, b);
+  c->crew_threads = std::max(nb, n - 1);
+  Crew::get().join(c->crew_threads, c->pool->size() > 1);
   *out = c;
   return HGNN_OK;
 }
@@ -308,15 +340,10 @@ hgnn_status hgnn_create(hgnn_ctx **out, const hgnn_schema *s, int device, int ho
 void hgnn_destroy(hgnn_ctx *c) {
   if (!c) return;
   {
-    std::lock_guard<std::mutex> lk(c->qm);
-    c->stop = true;
+    std::unique_lock<std::mutex> lk(c->qm);
+    c->qcv.wait(lk, [&] { return c->building == 0; });   // queued builds are finished
   }
-  c->qcv.notify_all();
-  for (Builder *b : c->builders) {
-    if (b->th.joinable()) b->th.join();
-    delete b->pool;
-    delete b;
-  }
+  Crew::get().leave(c->crew_threads, c->pool->size() > 1);
   if (c->device >= 0) {
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->side);
@@ -562,11 +589,16 @@ hgnn_status plan_graph(hgnn_ctx *ctx, hgnn_graph *g, std::string &msg) {
 
 // Hands a planned (or to-be-sampled) graph to the builders.
 static void enqueue_graph(hgnn_ctx *ctx, hgnn_graph *g) {
+  bool start = false;
   {
     std::lock_guard<std::mutex> lk(ctx->qm);
     ctx->queue.push_back(g);
+    if (ctx->building < (int)ctx->builders.size()) {
+      ++ctx->building;
+      start = true;
+    }
   }
-  ctx->qcv.notify_one();
+  if (start) Crew::get().submit([ctx] { build_queued(ctx); });
 }
 
 // Gives back whatever plan_graph took and deletes the graph (error paths before the graph reaches a builder).
@@ -639,6 +671,7 @@ hgnn_status hgnn_sample_and_build(hgnn_ctx *ctx, const hgnn_sampler *sm, int32_t
 hgnn_status hgnn_graph_ids(hgnn_ctx *ctx, hgnn_graph *g, int64_t *n_rows, const int64_t **host_ids, const int64_t **device_ids) {
   if (!ctx || !g) HGNN_FAIL(HGNN_EINVAL, "NULL argument");
   if (!g->job) HGNN_FAIL(HGNN_EINVAL, "the graph was not made by hgnn_sample_and_build");
+  if (device_ids) look_built(g);
   {
     std::unique_lock<std::mutex> lk(g->m);
     g->cv.wait(lk, [&] { return g->sampled || g->state != 0; });
@@ -662,7 +695,7 @@ hgnn_status hgnn_graph_minibatch_view(hgnn_ctx *ctx, hgnn_graph *g, int32_t laye
   if (!ctx || !g || !view) HGNN_FAIL(HGNN_EINVAL, "NULL argument");
   if (!g->job) HGNN_FAIL(HGNN_EINVAL, "the graph was not made by hgnn_sample_and_build");
   if (layer < 0 || layer >= g->num_layers) HGNN_FAIL(HGNN_EINVAL, "layer %d outside [0,%d)", layer, g->num_layers);
-  const hgnn_status st = hgnn_graph_wait(ctx, g);
+  const hgnn_status st = wait_built(g);   // host arrays: nothing to wait for on the device
   if (st != HGNN_OK) return st;
   std::memset(view, 0, sizeof(*view));
   for (int t = 0; t < ctx->T; ++t) {
@@ -683,7 +716,7 @@ hgnn_status hgnn_graph_wait_stream(hgnn_ctx *ctx, hgnn_graph *g, void *stream) {
     g->cv.wait(lk, [&] { return g->state != 0; });
     if (g->state != 1) HGNN_FAIL((hgnn_status)g->status, "%s", g->err.c_str());
   }
-  HGNN_HIP(hipStreamWaitEvent((hipStream_t)stream, g->ready, 0));
+  HGNN_HIP(wait_upload(g, (hipStream_t)stream));
   return HGNN_OK;
 }
 
@@ -804,7 +837,7 @@ static hgnn_status fwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
   if (((uintptr_t)saved | (uintptr_t)scratch | (uintptr_t)x | (uintptr_t)h) & 15)
     HGNN_FAIL(HGNN_EINVAL, "device buffers must be 16-byte aligned");
   hipStream_t s = (hipStream_t)stream;
-  HGNN_HIP(hipStreamWaitEvent(s, g->ready, 0));
+  HGNN_HIP(wait_upload(g, s));
   char *sc = (char *)scratch;
   void *wtb = sc + pl.off_wt;
   // bf16 storage, layer with an activation: the aggregate is kept as a pair (rounded value, remainder), so that the
@@ -1030,7 +1063,7 @@ static hgnn_status bwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
     any_db |= gt.dbias[t] != nullptr;
   }
   hipStream_t s = (hipStream_t)stream;
-  HGNN_HIP(hipStreamWaitEvent(s, g->ready, 0));
+  HGNN_HIP(wait_upload(g, s));
   char *sc = (char *)scratch;
   const LayerHost &L = g->L[layer];
   const int32_t *reo = g->slab.host + L.o_rel_edge_off;

@@ -136,7 +136,7 @@ hgnn_status attn_fwd(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_t layer, 
   if (((uintptr_t)saved | (uintptr_t)scratch | (uintptr_t)x | (uintptr_t)h) & 15)
     HGNN_FAIL(HGNN_EINVAL, "device buffers must be 16-byte aligned");
   hipStream_t s = (hipStream_t)stream;
-  HGNN_HIP(hipStreamWaitEvent(s, g->ready, 0));
+  HGNN_HIP(wait_upload(g, s));
   char *sv = (char *)saved;
   float *z = (float *)(sv + pl.s_z), *m = (float *)(sv + pl.s_m), *t = (float *)(sv + pl.s_t);
   float *wsum = (float *)(sv + pl.s_wsum), *beta = (float *)(sv + pl.s_beta);
@@ -167,7 +167,7 @@ hgnn_status attn_bwd(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_t layer, 
     HGNN_FAIL(HGNN_EINVAL, "device buffers must be 16-byte aligned");
   const int R = ctx->R, T = ctx->T, H = pl.H, dtype = ctx->dtype;
   hipStream_t s = (hipStream_t)stream;
-  HGNN_HIP(hipStreamWaitEvent(s, g->ready, 0));
+  HGNN_HIP(wait_upload(g, s));
   const char *sv = (const char *)saved;
   char *sc = (char *)scratch;
   const LayerHost &L = g->L[layer];

@@ -4,9 +4,11 @@
 #include <hip/hip_ext.h>
 
 #include <atomic>
+#include <chrono>
 #include <condition_variable>
 #include <cstdint>
 #include <cstdio>
+#include <cstdlib>
 #include <deque>
 #include <functional>
 #include <memory>
@@ -140,30 +142,78 @@ struct Slab {  // pinned host block + device block of equal capacity
   size_t cap = 0;  // in int32 units
 };
 
-class ThreadPool {
+// The host threads of the runtime: one crew for the process, shared by its contexts (with threads of their own, several
+// contexts keep more of them looking for work than the machine has cores, and every one's are asleep when its turn comes).
+// The crew has as many threads as the live context that asked for most; the last context to go takes them with it.
+// A thread builds a whole graph or takes chunks of the parallel phases of others' builds.  A phase lasts some 20 us, so
+// the threads look for work in a loop for a while before they sleep: waking one costs more than a phase.
+class Crew {
  public:
-  explicit ThreadPool(int n);
-  ~ThreadPool();
-  int size() const { return nthreads_; }
-  // Runs fn(chunk) for chunk in [0, nchunks) on the workers plus the caller; returns when all are done.
-  void parallel_for(int nchunks, const std::function<void(int)> &fn);
+  static Crew &get();
+  static int index();        // the calling thread's number in the crew
+  // A context that may use this many threads comes / goes; `eager`: its builds are shared between threads, so that the crew
+  // looks for work before it sleeps (a crew of one-thread builders has none to pass on at once, and leaves its idle time
+  // to the rest of the process).
+  void join(int threads, bool eager);
+  void leave(int threads, bool eager);
+  void submit(std::function<void()> task);
+  // Runs fn(chunk) for chunk in [0, nchunks) on the caller and at most `width` - 1 others; returns when all are done.
+  // Up to 64 chunks, a thread first looks at those that bear its number: phases that deal the same slices then meet the
+  // data they wrote a phase earlier in their own caches.
+  void parallel_for(int nchunks, int width, const std::function<void(int)> &fn);
+  // whether it pays to look for a build's end rather than sleep: not while every thread is at work, which would leave the
+  // core to one of them
+  bool look() const { return eager_.load(std::memory_order_relaxed) > 0 && at_work_.load(std::memory_order_relaxed) < target_.load(std::memory_order_relaxed); }
+  static constexpr int kSpinUs = 500;   // how long a thread looks for work before it sleeps
 
  private:
-  void worker();
-  void drain();
-  int nthreads_;
-  std::vector<std::thread> th_;
-  std::mutex m_;
-  std::condition_variable cv_, done_cv_;
-  const std::function<void(int)> *fn_ = nullptr;
-  int nchunks_ = 0;
-  std::atomic<int> next_{0};
-  int active_ = 0;
-  uint64_t epoch_ = 0;
-  bool stop_ = false;
+  static constexpr int kSlots = 32;
+  struct Job {
+    const std::function<void(int)> *fn;
+    int n, width;
+    std::atomic<int> next{0}, done{0}, joined{0};
+    std::atomic<uint64_t> taken{0};   // chunks taken, for n <= 64 (`next` counts them)
+  };
+  struct alignas(64) Slot {
+    std::atomic<Job *> job{nullptr};
+    std::atomic<int> users{0};   // threads that may be looking at *job
+  };
+  void run(int index);
+  bool try_work();
+  void wake_all();
+  void drain(Job &j);
+  Slot slots_[kSlots];
+  std::atomic<int> active_{0}, target_{0}, sleepers_{0}, waiting_tasks_{0}, at_work_{0}, eager_{0};   // at_work_: threads in a task
+  std::mutex m_, size_m_;
+  std::condition_variable cv_;
+  std::deque<std::function<void()>> tasks_;   // m_
+  std::vector<int> sizes_;                    // threads asked for by each live context (size_m_)
+  std::vector<std::thread> threads_;          // size_m_
 };
 
-// One builder: a host thread that takes whole graphs off the context's queue, its worker pool and its scratch.
+static inline void cpu_relax() {
+#if defined(__x86_64__)
+  __builtin_ia32_pause();
+#endif
+}
+
+// A context's share of the crew: how many threads one of its phases may use.
+class ThreadPool {
+ public:
+  explicit ThreadPool(int width) : width_(width < 1 ? 1 : width) {}
+  int size() const { return width_; }
+  template <typename F> void parallel_for(int nchunks, const F &fn) {
+    if (nchunks <= 1 || width_ == 1) {
+      for (int i = 0; i < nchunks; ++i) fn(i);
+      return;
+    }
+    Crew::get().parallel_for(nchunks, width_, fn);
+  }
+
+ private:
+  int width_;
+};
+
 // Growable int64 array whose new space stays uninitialised (a std::vector would zero it, and its push_back
 // checks the capacity on every element).
 struct I64Buf {
@@ -186,14 +236,20 @@ struct I64Buf {
   size_t size() const { return n; }
 };
 
-struct Builder {
-  ThreadPool *pool = nullptr;
-  std::thread th;
+// Scratch of one layer's index build.
+struct LayerScratch {
   std::vector<int32_t> key, col, hist, tkey;
   std::vector<std::vector<int32_t>> long_lists;
-  std::vector<int32_t> local_of[kMaxT];  // sampler: local row of a global vertex id (-1 = not in the hop), per type
+};
+// One builder: the scratch of a crew thread that works off the context's queue of graphs.
+struct Builder {
+  ThreadPool *pool = nullptr;
+  int user = -1;                           // crew thread that used it last
+  LayerScratch layer[kMaxLayers];          // the layers of a mini-batch are built side by side
+  std::vector<int32_t> local_of[kMaxT];    // sampler: local row of a global vertex id (-1 = not in the hop), per type
   std::vector<int64_t> hop_ids[2][kMaxT];  // sampler: destination / source lists of the current hop
-  I64Buf edge_dst;                         // sampler: local destinations of the hop's edges
+  I64Buf edge_pos;                         // sampler: global edge positions of the hop, fanout places per destination
+  std::vector<int32_t> edge_src, edge_cnt; // sampler: their source vertices; edges kept per merged row
 };
 
 // A mini-batch to be sampled on a builder's thread before its index arrays are built, and what the sampling
@@ -207,7 +263,7 @@ struct SampleJob {
   std::vector<int32_t> transpose[kMaxLayers];   // per layer: empty (= all types) or [T]
   I64Buf edge_index[kMaxLayers];                // [2 x E]: local source, local destination
   I64Buf edge_id[kMaxLayers];
-  int64_t rel_edge_off[kMaxLayers][kMaxR + 1];  // edges of relation r in a layer's lists: [rel_edge_off[r], rel_edge_off[r+1])
+  std::vector<int32_t> row_ptr[kMaxLayers];     // the merged CSR's row pointer: the lists come out in its order
   int64_t n_src[kMaxLayers][kMaxT], n_dst[kMaxLayers][kMaxT];
   std::vector<int64_t> ids[kMaxT];              // global ids of the first layer's source rows
 };
@@ -227,10 +283,12 @@ struct hgnn_graph {
   size_t used = 0;
   std::mutex m;
   std::condition_variable cv;
-  int state = 0;  // 0 building, 1 uploaded (event recorded), 2 failed
+  std::atomic<int> state{0};  // 0 building, 1 uploaded (event recorded), 2 failed; written under m
   int status = HGNN_OK;
   std::string err;
   hipEvent_t ready = nullptr;
+  std::atomic<void *> waited{nullptr};      // the stream that was last made to wait for `ready` (any_waited: there is one)
+  std::atomic<bool> any_waited{false};
   std::unique_ptr<hgnn::SampleJob> job;  // set for hgnn_sample_and_build
   bool sampled = false;                  // the job's results are complete (guarded by m)
   bool with_perm = true;                 // the build writes perm / cperm (fixed when the build is planned)
@@ -244,12 +302,15 @@ struct hgnn_ctx {
   int32_t heads = 1, agg = 0, fuse = 0, dtype = 0;
   bool legacy_gemm = true;  // false with HGNN_DMA_GEMM set in the environment when the context is created: the bf16 forward
                             // GEMM runs on the LDS-DMA core (gemm_dma.h), which measures slower than the register-staged one
-  std::vector<hgnn::Builder *> builders;  // each takes whole graphs off the queue and owns a slice of the host threads
+  std::vector<std::unique_ptr<hgnn::Builder>> builders;   // as many graphs are built at once
+  std::vector<hgnn::Builder *> idle_builders;             // qm; the one used last is taken first (its tables are in the caches)
+  std::unique_ptr<hgnn::ThreadPool> pool;                 // threads a phase of a build may use
+  int crew_threads = 0;                                   // what this context asked of the crew
   hipStream_t side = nullptr;
   std::mutex qm;
   std::condition_variable qcv;
   std::deque<hgnn_graph *> queue;
-  bool stop = false;
+  int building = 0;                  // qm; crew threads working off the queue
   std::mutex pm;  // slab / event pool
   std::vector<hgnn::Slab> free_slabs;
   std::vector<hipEvent_t> free_events;
@@ -279,6 +340,19 @@ struct hgnn_ctx {
 };
 
 namespace hgnn {
+struct PhaseTimer {
+  bool on;
+  std::chrono::steady_clock::time_point t0;
+  PhaseTimer() : on(getenv("HGNN_BUILD_TIMING") != nullptr), t0(std::chrono::steady_clock::now()) {}
+  void lap(const char *what) {
+    if (!on) return;
+    auto t1 = std::chrono::steady_clock::now();
+    fprintf(stderr, "  [build] %-28s %8.3f ms\n", what, std::chrono::duration<double, std::milli>(t1 - t0).count());
+    t0 = t1;
+  }
+};
+
+
 // log2 of the lanes that share one feature row of `max_dim` scalars: 16 bytes per lane, at most a wavefront
 static inline int lanes_log2_for(int max_dim, int esize) {
   int nvec = (max_dim * esize + 15) / 16;

@@ -23,59 +23,153 @@ void set_error(const char *fmt, ...) {
 const char *get_error() { return g_err; }
 
 // ------------------------------------------------------------------------------------------
-ThreadPool::ThreadPool(int n) : nthreads_(n < 1 ? 1 : n) {
-  for (int i = 0; i < nthreads_ - 1; ++i) th_.emplace_back([this] { worker(); });
+Crew &Crew::get() {
+  static Crew *c = new Crew();   // never destroyed: contexts may be released while the process's statics go
+  return *c;
 }
-ThreadPool::~ThreadPool() {
+void Crew::join(int threads, bool eager) {
+  eager_.fetch_add(eager ? 1 : 0);
+  std::lock_guard<std::mutex> lk(size_m_);
+  sizes_.push_back(threads);
+  const int most = *std::max_element(sizes_.begin(), sizes_.end());
+  target_.store(most);
+  while ((int)threads_.size() < most) threads_.emplace_back([this, i = (int)threads_.size()] { run(i); });
+}
+void Crew::leave(int threads, bool eager) {
+  eager_.fetch_sub(eager ? 1 : 0);
+  std::lock_guard<std::mutex> lk(size_m_);
+  sizes_.erase(std::find(sizes_.begin(), sizes_.end(), threads));
+  const int most = sizes_.empty() ? 0 : *std::max_element(sizes_.begin(), sizes_.end());
   {
-    std::lock_guard<std::mutex> lk(m_);
-    stop_ = true;
+    std::lock_guard<std::mutex> lk2(m_);
+    target_.store(most);
   }
   cv_.notify_all();
-  for (auto &t : th_) t.join();
-}
-void ThreadPool::drain() {
-  for (;;) {
-    int i = next_.fetch_add(1, std::memory_order_relaxed);
-    if (i >= nchunks_) break;
-    (*fn_)(i);
+  while ((int)threads_.size() > most) {
+    threads_.back().join();
+    threads_.pop_back();
   }
 }
-void ThreadPool::worker() {
-  uint64_t seen = 0;
-  for (;;) {
-    {
-      std::unique_lock<std::mutex> lk(m_);
-      cv_.wait(lk, [&] { return stop_ || epoch_ != seen; });
-      if (stop_) return;
-      seen = epoch_;
+static thread_local int tl_crew_index = 0;
+int Crew::index() { return tl_crew_index; }
+void Crew::drain(Job &j) {
+  if (j.n > 64) {
+    for (int i; (i = j.next.fetch_add(1, std::memory_order_relaxed)) < j.n;) {
+      (*j.fn)(i);
+      j.done.fetch_add(1, std::memory_order_release);
     }
-    drain();
-    {
-      std::lock_guard<std::mutex> lk(m_);
-      if (--active_ == 0) done_cv_.notify_all();
-    }
-  }
-}
-void ThreadPool::parallel_for(int nchunks, const std::function<void(int)> &fn) {
-  if (nchunks <= 0) return;
-  if (th_.empty() || nchunks == 1) {
-    for (int i = 0; i < nchunks; ++i) fn(i);
     return;
   }
+  const int step = std::max(1, target_.load(std::memory_order_relaxed));
+  auto take = [&](int i) {
+    const uint64_t bit = (uint64_t)1 << i;
+    if ((j.taken.load(std::memory_order_relaxed) & bit) || (j.taken.fetch_or(bit, std::memory_order_relaxed) & bit)) return;
+    j.next.fetch_add(1, std::memory_order_relaxed);
+    (*j.fn)(i);
+    j.done.fetch_add(1, std::memory_order_release);
+  };
+  for (int i = tl_crew_index; i < j.n; i += step) take(i);
+  for (int k = 1; k <= j.n && j.next.load(std::memory_order_relaxed) < j.n; ++k) take((tl_crew_index + k) % j.n);
+}
+bool Crew::try_work() {
+  if (active_.load(std::memory_order_relaxed) == 0) return false;
+  bool did = false;
+  for (Slot &s : slots_) {
+    if (!s.job.load(std::memory_order_relaxed)) continue;
+    s.users.fetch_add(1);            // before the job is read: its owner waits for users to drop once it is withdrawn
+    if (Job *j = s.job.load()) {
+      if (j->next.load(std::memory_order_relaxed) < j->n && j->joined.fetch_add(1) + 1 < j->width) {
+        drain(*j);
+        did = true;
+      }
+    }
+    s.users.fetch_sub(1);
+  }
+  return did;
+}
+void Crew::run(int index) {
+  tl_crew_index = index;
+  auto idle = std::chrono::steady_clock::now();
+  for (int spins = 0; index < target_.load(std::memory_order_relaxed);) {
+    bool did = try_work();
+    if (!did && waiting_tasks_.load(std::memory_order_relaxed) > 0) {
+      std::function<void()> task;
+      {
+        std::lock_guard<std::mutex> lk(m_);
+        if (!tasks_.empty()) {
+          task = std::move(tasks_.front());
+          tasks_.pop_front();
+          waiting_tasks_.fetch_sub(1);
+        }
+      }
+      if (task) {
+        at_work_.fetch_add(1);
+        task();
+        at_work_.fetch_sub(1);
+        did = true;
+      }
+    }
+    if (did) {
+      idle = std::chrono::steady_clock::now();
+      spins = 0;
+      continue;
+    }
+    if (eager_.load(std::memory_order_relaxed) > 0) {
+      cpu_relax();
+      if (++spins % 64) continue;
+      if (std::chrono::steady_clock::now() - idle < std::chrono::microseconds(kSpinUs)) continue;
+    }
+    {
+      std::unique_lock<std::mutex> lk(m_);
+      sleepers_.fetch_add(1);        // work posted from here on notifies; work posted before shows in the counters
+      cv_.wait(lk, [&] { return index >= target_.load() || active_.load() > 0 || waiting_tasks_.load() > 0; });
+      sleepers_.fetch_sub(1);
+    }
+    idle = std::chrono::steady_clock::now();
+  }
+}
+void Crew::wake_all() {
+  if (sleepers_.load() == 0) return;
+  { std::lock_guard<std::mutex> lk(m_); }
+  cv_.notify_all();
+}
+void Crew::submit(std::function<void()> task) {
   {
     std::lock_guard<std::mutex> lk(m_);
-    fn_ = &fn;
-    nchunks_ = nchunks;
-    next_.store(0);
-    active_ = (int)th_.size();
-    ++epoch_;
+    tasks_.push_back(std::move(task));
+    waiting_tasks_.fetch_add(1);
   }
-  cv_.notify_all();
-  drain();
-  std::unique_lock<std::mutex> lk(m_);
-  done_cv_.wait(lk, [&] { return active_ == 0; });
-  fn_ = nullptr;
+  if (eager_.load() > 0) wake_all();   // the task's phases follow at once
+  else cv_.notify_one();
+}
+void Crew::parallel_for(int nchunks, int width, const std::function<void(int)> &fn) {
+  Job j;
+  j.fn = &fn;
+  j.n = nchunks;
+  j.width = width;
+  Slot *mine = nullptr;
+  for (Slot &s : slots_) {
+    Job *none = nullptr;
+    if (!s.job.load(std::memory_order_relaxed) && s.job.compare_exchange_strong(none, &j)) {
+      mine = &s;
+      break;
+    }
+  }
+  if (mine) {
+    active_.fetch_add(1);
+    wake_all();
+  }
+  drain(j);
+  auto wait = [](auto done) {   // the chunks still running are short, unless their thread lost its core
+    for (int i = 0; !done(); ++i) {
+      if (i < 20000) cpu_relax(); else std::this_thread::yield();
+    }
+  };
+  wait([&] { return j.done.load(std::memory_order_acquire) >= nchunks; });
+  if (!mine) return;
+  active_.fetch_sub(1);
+  mine->job.store(nullptr);
+  wait([&] { return mine->users.load() == 0; });
 }
 
 // ------------------------------------------------------------------------------------------
@@ -96,7 +190,14 @@ struct BuildError {
   }
 };
 
-constexpr int kBucketShift = 12;  // 4096 consecutive keys form one bucket (its counters stay in L1)
+// At most 4096 consecutive keys form one bucket (its counters stay in L1); fewer where that makes too few buckets for
+// the threads.
+constexpr int kBucketShift = 12;
+inline int bucket_shift(int64_t keys, int threads) {
+  int s = kBucketShift;
+  while (s > 7 && threads > 1 && (keys >> s) < 3 * threads) --s;
+  return s;
+}
 
 }  // namespace
 
@@ -110,7 +211,8 @@ constexpr int kBucketShift = 12;  // 4096 consecutive keys form one bucket (its 
 struct WideRec {
   static constexpr int W = 3;
   static void put(int32_t *r, int32_t key, int32_t item, int32_t payload) { r[0] = key; r[1] = item; r[2] = payload; }
-  static int32_t key_low(const int32_t *r, int32_t k0) { return r[0] - k0; }
+  static int32_t key_low(const int32_t *r) { return r[0]; }
+  static int32_t base(int32_t k0) { return k0; }   // key_low of the bucket's first key
   static int32_t item(const int32_t *r) { return r[1]; }
   static int32_t payload(const int32_t *r) { return r[2]; }
 };
@@ -120,7 +222,8 @@ struct PackedRec {
     r[0] = item;
     r[1] = (int32_t)(((uint32_t)key << kPayloadBits) | (uint32_t)payload);  // the shift drops the bucket's bits
   }
-  static int32_t key_low(const int32_t *r, int32_t) { return (int32_t)((uint32_t)r[1] >> kPayloadBits); }
+  static int32_t key_low(const int32_t *r) { return (int32_t)((uint32_t)r[1] >> kPayloadBits); }
+  static int32_t base(int32_t k0) { return k0 & ((1 << kBucketShift) - 1); }
   static int32_t item(const int32_t *r) { return r[0]; }
   static int32_t payload(const int32_t *r) { return (int32_t)((uint32_t)r[1] & ((1u << kPayloadBits) - 1u)); }
 };
@@ -131,24 +234,13 @@ struct SlimRec {
   static void put(int32_t *r, int32_t key, int32_t, int32_t payload) {
     r[0] = (int32_t)(((uint32_t)key << kPayloadBits) | (uint32_t)payload);
   }
-  static int32_t key_low(const int32_t *r, int32_t) { return (int32_t)((uint32_t)r[0] >> kPayloadBits); }
+  static int32_t key_low(const int32_t *r) { return (int32_t)((uint32_t)r[0] >> kPayloadBits); }
+  static int32_t base(int32_t k0) { return k0 & ((1 << kBucketShift) - 1); }
   static int32_t item(const int32_t *) { return 0; }
   static int32_t payload(const int32_t *r) { return (int32_t)((uint32_t)r[0] & ((1u << kPayloadBits) - 1u)); }
 };
 
-struct PhaseTimer {
-  bool on;
-  std::chrono::steady_clock::time_point t0;
-  PhaseTimer() : on(getenv("HGNN_BUILD_TIMING") != nullptr), t0(std::chrono::steady_clock::now()) {}
-  void lap(const char *what) {
-    if (!on) return;
-    auto t1 = std::chrono::steady_clock::now();
-    fprintf(stderr, "  [build] %-28s %8.3f ms\n", what, std::chrono::duration<double, std::milli>(t1 - t0).count());
-    t0 = t1;
-  }
-};
-
-static bool build_layer(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g, int l, BuildError &err) {
+static bool build_layer(hgnn_ctx *ctx, ThreadPool &pool, LayerScratch &bd, hgnn_graph *g, int l, BuildError &err) {
   PhaseTimer tm;
   LayerHost &L = g->L[l];
   const hgnn_coo_layer &in = L.in;
@@ -163,10 +255,10 @@ static bool build_layer(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g, int l, BuildE
   rel_row_off[0] = 0;
   for (int r = 0; r < R; ++r) rel_row_off[r + 1] = rel_row_off[r] + (int32_t)L.n_dst[ctx->rel_dst[r]];
   const int64_t E = L.edges, rows = L.rows, src_rows = L.src_rows;
-  ThreadPool &pool = *bd.pool;
-  const int P = (int)std::max<int64_t>(1, std::min<int64_t>(pool.size(), (E + 16383) / 16384));
-  const int B1 = (int)((rows + (1 << kBucketShift) - 1) >> kBucketShift);
-  const int B2 = (int)((src_rows + (1 << kBucketShift) - 1) >> kBucketShift);
+  const int P = (int)std::max<int64_t>(1, std::min<int64_t>(pool.size(), (E + 4095) / 4096));
+  const int sh1 = bucket_shift(rows, P), sh2 = bucket_shift(src_rows, P);
+  const int B1 = (int)((rows + (1 << sh1) - 1) >> sh1);
+  const int B2 = (int)((src_rows + (1 << sh2) - 1) >> sh2);
   auto grow = [](std::vector<int32_t> &v, size_t n) {
     if (v.size() < n) v.resize(n + n / 4);
   };
@@ -196,42 +288,38 @@ static bool build_layer(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g, int l, BuildE
   const bool with_perm = g->with_perm;
   if (presorted) {
     const SampleJob &job = *g->job;
-    const int64_t *es = job.edge_index[l].data(), *ed = es + E;
-    const int64_t *reo = job.rel_edge_off[l];
-    for (int r = 0; r < R; ++r) {
-      const int32_t row0 = rel_row_off[r], col0 = row_off[ctx->rel_src[r]];
-      const int32_t nd = rel_row_off[r + 1] - row0;
-      const bool want = (L.tmask >> ctx->rel_src[r]) & 1u;
-      int64_t e = reo[r];
-      const int64_t e_end = reo[r + 1];
-      for (int32_t i = 0; i < nd; ++i) {
-        rowptr[row0 + i] = (int32_t)e;
-        int32_t *c2 = cnt2 + (size_t)((row0 + i) >> kBucketShift) * S2;
-        for (; e < e_end && ed[e] == i; ++e) {
-          const int32_t c = col0 + (int32_t)es[e];
-          colidx[e] = c;
-          if (with_perm) perm[e] = (int32_t)e;
-          if (want) ++c2[c >> kBucketShift];
+    const int64_t *es = job.edge_index[l].data();
+    const int32_t *rp = job.row_ptr[l].data();
+    // slices of merged rows (relations differ in size), cut at relation boundaries inside a slice
+    pool.parallel_for(P, [&](int p) {
+      const int64_t ra = rows * p / P, rb = rows * (p + 1) / P;
+      std::memcpy(rowptr + ra, rp + ra, sizeof(int32_t) * (size_t)(rb - ra));
+      for (int r = 0; r < R; ++r) {
+        const int64_t a = std::max<int64_t>(ra, rel_row_off[r]), b = std::min<int64_t>(rb, rel_row_off[r + 1]);
+        if (a >= b) continue;
+        const int32_t col0 = row_off[ctx->rel_src[r]];
+        for (int32_t e = rp[a]; e < rp[b]; ++e) {
+          colidx[e] = col0 + (int32_t)es[e];
+          if (with_perm) perm[e] = e;
         }
       }
-    }
-    for (int b = 0; b <= B1; ++b) base1[b] = b < B1 ? rowptr[(size_t)b << kBucketShift] : (int32_t)E;
+    });
+    for (int b = 0; b <= B1; ++b) base1[b] = b < B1 ? rp[(size_t)b << sh1] : (int32_t)E;
     tm.lap("csr from sampler order");
   } else {
   // Algorithm 2: the layer's edge types are looked up through the edge ids (or taken as given) and matched
   // against the relations -- for all relations in one pass: each edge gets its merged row and source row.
   const int64_t slice = (E + P - 1) / P;
-  pool.parallel_for(P, [&](int p) {
-    const int64_t a = std::min<int64_t>(E, p * slice), b = std::min<int64_t>(E, a + slice);
-    const int64_t *ei64 = in.index_is_i64 ? (const int64_t *)in.edge_index : nullptr;
-    const int32_t *ei32 = in.index_is_i64 ? nullptr : (const int32_t *)in.edge_index;
-    int32_t *cnt = cnt1 + (size_t)p * S1;
-    const uint8_t *types8 = ctx->edge_types8.data();
-    const int64_t n_types8 = (int64_t)ctx->edge_types8.size();
-    const int nruns = (int)ctx->run_end.size();
-    const int64_t *run_end = ctx->run_end.data();
-    const uint8_t *run_rel = ctx->run_rel.data(), *run_lut = ctx->run_lut.data();
-    const int run_shift = ctx->run_shift;
+  const int64_t *ei64 = in.index_is_i64 ? (const int64_t *)in.edge_index : nullptr;
+  const int32_t *ei32 = in.index_is_i64 ? nullptr : (const int32_t *)in.edge_index;
+  const uint8_t *types8 = ctx->edge_types8.data();
+  const int64_t n_types8 = (int64_t)ctx->edge_types8.size();
+  const int nruns = (int)ctx->run_end.size();
+  const int64_t *run_end = ctx->run_end.data();
+  const uint8_t *run_rel = ctx->run_rel.data(), *run_lut = ctx->run_lut.data();
+  const int run_shift = ctx->run_shift;
+  // Reports the first bad edge of [a, b).
+  auto report = [&](int64_t a, int64_t b) {
     for (int64_t e = a; e < b; ++e) {
       int64_t r;
       if (in.edge_type) {
@@ -247,10 +335,6 @@ static bool build_layer(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g, int l, BuildE
         while (id >= run_end[j]) ++j;  // ends: id < n_types8 = the last run's end
         r = run_rel[j];
       } else if (!in.global_edge_type) {   // the registered compact table
-        if (e + 48 < b) {
-          const int64_t nid = in.edge_id[e + 48];
-          if (nid >= 0 && nid < n_types8) __builtin_prefetch(types8 + nid);
-        }
         const int64_t id = in.edge_id[e];
         if (id < 0 || id >= n_types8) {
           err.set(HGNN_EINVAL, "layer " + std::to_string(l) + ": edge_id[" + std::to_string(e) + "]=" +
@@ -259,10 +343,6 @@ static bool build_layer(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g, int l, BuildE
         }
         r = types8[id];
       } else {
-        if (e + 48 < b) {
-          const int64_t nid = in.edge_id[e + 48];
-          if (nid >= 0 && nid < in.num_global_edges) __builtin_prefetch(in.global_edge_type + nid);
-        }
         const int64_t id = in.edge_id[e];
         if (id < 0 || id >= in.num_global_edges) {
           err.set(HGNN_EINVAL, "layer " + std::to_string(l) + ": edge_id[" + std::to_string(e) + "]=" +
@@ -285,12 +365,72 @@ static bool build_layer(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g, int l, BuildE
                                  std::to_string(r) + ") outside its source/destination row range");
         return;
       }
-      const int32_t k = rel_row_off[r] + (int32_t)d;
-      key[e] = k;
-      col[e] = row_off[ts] + (int32_t)s;
-      ++cnt[k >> kBucketShift];
     }
-  });
+  };
+  // What an edge of relation r becomes; one record per relation, so that an edge costs one look-up.
+  struct RelRec {
+    int32_t row, col;
+    uint32_t n_src, n_dst;
+  } rec[kMaxR];
+  for (int r = 0; r < R; ++r) {
+    const int ts = ctx->rel_src[r];
+    rec[r] = RelRec{rel_row_off[r], row_off[ts], (uint32_t)L.n_src[ts], (uint32_t)L.n_dst[ctx->rel_dst[r]]};
+  }
+  // The loop does not leave early: a bad edge is noted, takes row 0, and is looked for afterwards.
+  auto select = [&](int p, auto type_of, auto index) {
+    const int64_t a = std::min<int64_t>(E, p * slice), b = std::min<int64_t>(E, a + slice);
+    int32_t *cnt = cnt1 + (size_t)p * S1;
+    const auto *src = index, *dst = index + E;
+    bool bad = false;
+    for (int64_t e = a; e < b; ++e) {
+      const uint64_t r = type_of(e, b);
+      const bool known = r < (uint64_t)R;
+      const RelRec q = rec[known ? r : 0];
+      const uint64_t s = (uint64_t)src[e], d = (uint64_t)dst[e];
+      const bool ok = known & (s < q.n_src) & (d < q.n_dst);
+      bad |= !ok;
+      const int32_t k = ok ? q.row + (int32_t)d : 0;
+      key[e] = k;
+      col[e] = q.col + (int32_t)s;
+      ++cnt[k >> sh1];
+    }
+    if (bad) report(a, b);
+  };
+  auto select_by = [&](auto type_of) {
+    pool.parallel_for(P, [&](int p) {
+      if (ei64) select(p, type_of, ei64); else select(p, type_of, ei32);
+    });
+  };
+  constexpr uint64_t kNone = ~(uint64_t)0;   // no relation: an id outside its table
+  if (in.edge_type) {
+    select_by([&](int64_t e, int64_t) { return (uint64_t)(int64_t)in.edge_type[e]; });
+  } else if (!in.global_edge_type && nruns > 0) {   // the registered table, as runs of equal type
+    select_by([&](int64_t e, int64_t) {
+      const int64_t id = in.edge_id[e];
+      if ((uint64_t)id >= (uint64_t)n_types8) return kNone;
+      int j = run_lut[id >> run_shift];
+      while (id >= run_end[j]) ++j;  // ends: id < n_types8 = the last run's end
+      return (uint64_t)run_rel[j];
+    });
+  } else if (!in.global_edge_type) {   // the registered compact table
+    select_by([&](int64_t e, int64_t b) {
+      if (e + 48 < b) {
+        const int64_t nid = in.edge_id[e + 48];
+        if (nid >= 0 && nid < n_types8) __builtin_prefetch(types8 + nid);
+      }
+      const int64_t id = in.edge_id[e];
+      return (uint64_t)id < (uint64_t)n_types8 ? (uint64_t)types8[id] : kNone;
+    });
+  } else {
+    select_by([&](int64_t e, int64_t b) {
+      if (e + 48 < b) {
+        const int64_t nid = in.edge_id[e + 48];
+        if (nid >= 0 && nid < in.num_global_edges) __builtin_prefetch(in.global_edge_type + nid);
+      }
+      const int64_t id = in.edge_id[e];
+      return (uint64_t)id < (uint64_t)in.num_global_edges ? (uint64_t)(int64_t)in.global_edge_type[id] : kNone;
+    });
+  }
   if (err.failed.load()) return false;
   tm.lap("select (Alg.2) + count");
 
@@ -314,18 +454,19 @@ static bool build_layer(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g, int l, BuildE
       const int64_t a = std::min<int64_t>(E, p * slice), b = std::min<int64_t>(E, a + slice);
       int32_t *off = cnt1 + (size_t)p * S1;
       for (int64_t e = a; e < b; ++e) {
-        const int32_t q = off[key[e] >> kBucketShift]++;
+        const int32_t q = off[key[e] >> sh1]++;
         Rec::put(trec + (size_t)q * Rec::W, key[e], (int32_t)e, col[e]);
       }
     });
     tm.lap("csr level-1 scatter");
     pool.parallel_for(B1, [&](int b) {
       int32_t h[(1 << kBucketShift) + 1];
-      const int32_t k0 = b << kBucketShift;
-      const int32_t nk = (int32_t)std::min<int64_t>(1 << kBucketShift, rows - k0);
+      const int32_t k0 = b << sh1;
+      const int32_t nk = (int32_t)std::min<int64_t>(1 << sh1, rows - k0);
       std::memset(h, 0, sizeof(int32_t) * (nk + 1));
+      int32_t *const hk = h - Rec::base(k0);
       const int32_t ja = base1[b], jb = base1[b + 1];
-      for (int32_t j = ja; j < jb; ++j) ++h[Rec::key_low(trec + (size_t)j * Rec::W, k0)];
+      for (int32_t j = ja; j < jb; ++j) ++hk[Rec::key_low(trec + (size_t)j * Rec::W)];
       int32_t run = ja;
       for (int32_t i = 0; i < nk; ++i) {
         const int32_t t = h[i];
@@ -335,7 +476,7 @@ static bool build_layer(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g, int l, BuildE
       }
       for (int32_t j = ja; j < jb; ++j) {
         const int32_t *rec = trec + (size_t)j * Rec::W;
-        const int32_t pos = h[Rec::key_low(rec, k0)]++;
+        const int32_t pos = hk[Rec::key_low(rec)]++;
         colidx[pos] = Rec::payload(rec);
         if constexpr (kPerm) perm[pos] = Rec::item(rec);
       }
@@ -366,14 +507,13 @@ static bool build_layer(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g, int l, BuildE
   // level-1 counts of the transpose: per CSR bucket, how many of its wanted positions fall into each bucket of
   // source rows (a sweep of its own over the wanted ranges: inside the scatter loop above the test "is this
   // source row wanted" is a coin flip for the branch predictor and cost more than the whole sweep)
-  if (!presorted)
-    pool.parallel_for(B1, [&](int b1) {
-      int32_t *c2 = cnt2 + (size_t)b1 * S2;
-      for (int i = 0; i < n_pr; ++i) {
-        const int32_t ka = std::max(base1[b1], pr_lo[i]), kb = std::min(base1[b1 + 1], pr_hi[i]);
-        for (int32_t k = ka; k < kb; ++k) ++c2[colidx[k] >> kBucketShift];
-      }
-    });
+  pool.parallel_for(B1, [&](int b1) {
+    int32_t *c2 = cnt2 + (size_t)b1 * S2;
+    for (int i = 0; i < n_pr; ++i) {
+      const int32_t ka = std::max(base1[b1], pr_lo[i]), kb = std::min(base1[b1 + 1], pr_hi[i]);
+      for (int32_t k = ka; k < kb; ++k) ++c2[colidx[k] >> sh2];
+    }
+  });
   // ---- transpose: CSR positions grouped by source row, ascending position inside a group ----
   // the level-1 slices are the CSR position ranges of the buckets above (already in CSR order)
   {
@@ -394,9 +534,9 @@ static bool build_layer(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g, int l, BuildE
       const int32_t ka = std::max(base1[b1], pr_lo[i]), kb = std::min(base1[b1 + 1], pr_hi[i]);
       if (ka >= kb) continue;
       // the merged row of CSR position k: positions are walked in order, so the row pointer is walked along
-      int32_t row = b1 << kBucketShift;
+      int32_t row = b1 << sh1;
       {  // first row of the bucket that ends after ka
-        int32_t hi = (int32_t)std::min<int64_t>(rows, (int64_t)(b1 + 1) << kBucketShift);
+        int32_t hi = (int32_t)std::min<int64_t>(rows, (int64_t)(b1 + 1) << sh1);
         while (row + 1 < hi) {
           const int32_t mid = row + (hi - row) / 2;
           if (rowptr[mid] <= ka) row = mid; else hi = mid;
@@ -405,7 +545,7 @@ static bool build_layer(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g, int l, BuildE
       for (int32_t k = ka; k < kb; ++k) {
         while (rowptr[row + 1] <= k) ++row;
         const int32_t c = colidx[k];
-        const int32_t q = off[c >> kBucketShift]++;
+        const int32_t q = off[c >> sh2]++;
         if (!csc_packed) WideRec::put(trec + (size_t)q * WideRec::W, c, k, row);
         else if (with_perm) PackedRec::put(trec + (size_t)q * PackedRec::W, c, k, row);
         else SlimRec::put(trec + q, c, k, row);
@@ -420,11 +560,12 @@ static bool build_layer(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g, int l, BuildE
     constexpr bool kPerm = decltype(perm_flag)::value;
     pool.parallel_for(B2, [&](int b) {
       int32_t h[(1 << kBucketShift) + 1];
-      const int32_t k0 = b << kBucketShift;
-      const int32_t nk = (int32_t)std::min<int64_t>(1 << kBucketShift, src_rows - k0);
+      const int32_t k0 = b << sh2;
+      const int32_t nk = (int32_t)std::min<int64_t>(1 << sh2, src_rows - k0);
       std::memset(h, 0, sizeof(int32_t) * (nk + 1));
+      int32_t *const hk = h - Rec::base(k0);
       const int32_t ja = base2[b], jb = base2[b + 1];
-      for (int32_t j = ja; j < jb; ++j) ++h[Rec::key_low(trec + (size_t)j * Rec::W, k0)];
+      for (int32_t j = ja; j < jb; ++j) ++hk[Rec::key_low(trec + (size_t)j * Rec::W)];
       int32_t run = ja;
       longs[b].clear();
       for (int32_t i = 0; i < nk; ++i) {
@@ -436,7 +577,7 @@ static bool build_layer(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g, int l, BuildE
       }
       for (int32_t j = ja; j < jb; ++j) {
         const int32_t *rec = trec + (size_t)j * Rec::W;
-        const int32_t pos = h[Rec::key_low(rec, k0)]++;
+        const int32_t pos = hk[Rec::key_low(rec)]++;
         crow[pos] = Rec::payload(rec);
         if constexpr (kPerm) cperm[pos] = Rec::item(rec);
       }
@@ -478,6 +619,7 @@ static bool build_layer(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g, int l, BuildE
 void build_graph_job(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g) {
   BuildError err;
   bool ok = true;
+  PhaseTimer tm;
   if (g->job) {  // sample first; only then are the sizes known that the block is laid out for
     std::string m;
     hgnn_status st = run_sample_job(ctx, bd, g, m);
@@ -489,16 +631,26 @@ void build_graph_job(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g) {
       g->cv.notify_all();
       st = plan_graph(ctx, g, m);
     }
+    tm.lap("sample and plan");
     if (st != HGNN_OK) {
       err.set(st, m);
       ok = false;
     } else {
-      for (int t = 0; t < ctx->T; ++t)
-        if (!g->job->ids[t].empty())
-          std::memcpy(g->slab.host + g->o_ids[t], g->job->ids[t].data(), g->job->ids[t].size() * sizeof(int64_t));
+      for (int t = 0; t < ctx->T; ++t) {
+        const std::vector<int64_t> &ids = g->job->ids[t];
+        const int n = (int)std::min<size_t>((size_t)bd.pool->size(), (ids.size() + 8191) / 8192);
+        bd.pool->parallel_for(n, [&](int i) {
+          const size_t a = ids.size() * i / n, b = ids.size() * (i + 1) / n;
+          std::memcpy(g->slab.host + g->o_ids[t] + 2 * a, ids.data() + a, (b - a) * sizeof(int64_t));
+        });
+      }
     }
   }
-  for (int l = 0; l < g->num_layers && ok; ++l) ok = build_layer(ctx, bd, g, l, err);
+  if (ok) {  // the layers side by side: a small layer's phases are shorter than what it takes to start them
+    bd.pool->parallel_for(g->num_layers, [&](int l) { (void)build_layer(ctx, *bd.pool, bd.layer[l], g, l, err); });
+    ok = !err.failed.load();
+  }
+  tm.lap("all layers");
   int status = ok ? HGNN_OK : err.status;
   std::string msg = err.msg;
   if (ok && ctx->device >= 0) {
@@ -509,6 +661,7 @@ void build_graph_job(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g) {
       msg = std::string("graph upload: ") + hipGetErrorString(e);
     }
   }
+  tm.lap("start of the upload");
   {
     // notified under the lock: a waiter may release (delete) the graph as soon as it sees the new state, so the
     // unlock must be this thread's last touch of it

@@ -10,6 +10,18 @@ static inline int esize(int dtype) { return dtype == HGNN_BF16 ? 2 : 4; }
 // Waits for the host build and fills the device-side view of one layer's index arrays.
 hgnn_status layer_dev(hgnn_ctx *ctx, hgnn_graph *g, int32_t layer, LayerDev &D);
 
+// Makes `s` wait for the graph's upload, once per stream in a row: work that a stream takes after its wait is behind the
+// upload anyway (an unfinished event costs some 10 us per wait, and a step takes four or more).
+static inline hipError_t wait_upload(hgnn_graph *g, hipStream_t s) {
+  if (g->any_waited.load(std::memory_order_acquire) && g->waited.load(std::memory_order_relaxed) == (void *)s) return hipSuccess;
+  const hipError_t e = hipStreamWaitEvent(s, g->ready, 0);
+  if (e == hipSuccess) {
+    g->waited.store((void *)s, std::memory_order_relaxed);
+    g->any_waited.store(true, std::memory_order_release);
+  }
+  return e;
+}
+
 // While alive, the launches made on this thread are timed if the probe selects (kernel, layer).
 struct Probe {
   bool active = false;

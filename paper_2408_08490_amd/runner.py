@@ -23,8 +23,36 @@ def to_device(a: np.ndarray, dtype: str, dev) -> torch.Tensor:
     return torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).to(dev).to(_tdtype(dtype)).contiguous()
 
 
+class _Uploads:
+    """Integer lists to the device through a few pinned buffers, one asynchronous copy per mini-batch."""
+
+    def __init__(self, dev, slots=4):
+        self.dev, self.slots, self.next = dev, [[None, None] for _ in range(slots)], 0
+
+    def put(self, arrays):
+        """Device int64 tensors with the values of the host arrays (views of one tensor)."""
+        sizes = [len(a) for a in arrays]
+        n = sum(sizes)
+        slot = self.slots[self.next]
+        self.next = (self.next + 1) % len(self.slots)
+        if slot[1] is not None:
+            slot[1].synchronize()          # the copy that reads the buffer has long ended
+        if slot[0] is None or slot[0].numel() < n:
+            slot[0] = torch.empty(max(1024, n + n // 4), dtype=torch.int64, pin_memory=True)
+        host, at = slot[0].numpy(), 0
+        for a, k in zip(arrays, sizes):
+            host[at: at + k] = a
+            at += k
+        out = torch.empty(n, dtype=torch.int64, device=self.dev)
+        out.copy_(slot[0][:n], non_blocking=True)
+        slot[1] = torch.cuda.Event()
+        slot[1].record()
+        return list(out.split(sizes)), slot[1]
+
+
 class Batch:
     def __init__(self):
+        self.uploaded = None     # (event, stream) of the copies of ids and labels
         self.ids_dev = None
         self.graph = None
         self.labels_dev = None
@@ -106,6 +134,7 @@ class Model:
                                        input_grad=first_layer_input_grad if not self.layers else None))
         self.loss_dev = torch.zeros(1, device=self.dev, dtype=torch.float32)
         self._buf = {}
+        self._uploads = _Uploads(self.dev)
         # default of run(gather=...): the first layer's aggregation reads the feature stores directly
         self.gather = False
 
@@ -178,13 +207,16 @@ class Model:
     # ---- host side of a step: upload ids / labels, start the semantic graph build ----
     def prepare(self, mb, global_edge_type=None, use_edge_id=False, device_build=False) -> Batch:
         b = Batch()
-        b.ids_dev = [torch.from_numpy(np.ascontiguousarray(i, dtype=np.int64)).to(self.dev) for i in mb.ids]
         b.n_rows = [len(i) for i in mb.ids]
         b.blocks = mb.blocks
+        # the build runs on its own threads while the ids are copied
         b.graph = self.ctx.hgnn_build_semantic_csr(mb.blocks, global_edge_type, use_edge_id, self.transpose_types(len(mb.blocks)),
                                                    on_device=device_build)
+        lists = list(mb.ids) + ([mb.labels] if mb.labels is not None else [])
+        b.ids_dev, event = self._uploads.put(lists)
+        b.uploaded = (event, torch.cuda.current_stream(self.dev.index).cuda_stream)
         if mb.labels is not None:
-            b.labels_dev = torch.from_numpy(mb.labels.astype(np.int64)).to(self.dev)
+            b.labels_dev = b.ids_dev.pop()
         if mb.grad_out is not None:
             b.grad_out_dev = to_device(np.concatenate([g.reshape(-1) for g in mb.grad_out]), self.dtype, self.dev)
         return b
@@ -204,7 +236,7 @@ class Model:
     def _resolve_sampled(self, b: Batch):
         """Sizes and device id lists of a sampled mini-batch (waits for its host task) and the stream dependency
         of the merge on the upload."""
-        n_rows, _, dptr = b.graph.ids(device=True)
+        n_rows, dptr = b.graph.device_ids()
         b.n_rows = n_rows
         b.ids_dev = [_DevIds(p, n) for p, n in zip(dptr, n_rows)]
         b.blocks = [_Sizes(**b.graph.minibatch_view(l, arrays=False)) for l in range(len(self.layers))]
@@ -224,6 +256,8 @@ class Model:
         gather = bool(gather) and not naive and not two_step and not self.attention
         if b.sampled and b.ids_dev is None:
             self._resolve_sampled(b)
+        if b.uploaded is not None and b.uploaded[1] != torch.cuda.current_stream(self.dev.index).cuda_stream:
+            torch.cuda.current_stream(self.dev.index).wait_event(b.uploaded[0])
         if gather:
             nd0 = list(b.blocks[0].n_dst)
             x = self._typed("x0dst", sum(n * f for n, f in zip(nd0, self.feat_dim)))
