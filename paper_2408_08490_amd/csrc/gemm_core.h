@@ -1,6 +1,8 @@
 // MFMA GEMM core shared by the layer GEMMs: tile movers (global -> registers -> LDS), MFMA fragment reads,
 // the software-pipelined K loop over a segment table, and the LDS-staged epilogue.
 #pragma once
+#include <type_traits>
+
 #include "common.h"
 #include "device_types.h"
 
@@ -201,6 +203,93 @@ __device__ __forceinline__ void mma_tile(f32x16 (&acc)[MI][NI], const T *As, con
   }
 }
 
+// fp32 products on the bf16 matrix cores.  An fp32 value is the exact sum of three bf16 values x0 + x1 + x2 (8 + 8 + 8
+// significant bits; rounding to nearest makes |x1| <= 2^-9 |x|, |x2| <= 2^-18 |x|), and a product of two bf16 values is
+// exact in fp32.  Of the nine products six are taken; x1 y2 + x2 y1 + x2 y2, at most 2^-26 |x y| and of either sign, lie
+// below the rounding of the fp32 sum.  Six bf16 MFMAs take 6/16 of the time of the fp32 MFMA's.  The MFMA's own sum over 16
+// terms is not rounded to nearest, and over a whole reduction that shows (bias gradients 2x further off); so a K-step's sum
+// starts from zero and the vector unit adds it to the accumulator: against 64 bits, outputs and weight gradients are then
+// 0.1 to 0.5 of the distance that the fp32 MFMA leaves (1024 targets, fan-out 25 and 20: outputs 9e-7 -> 4e-7, weight
+// gradients 1e-6 -> 2e-7 of their norm).
+// Measured with 1024 targets in fp32 (us, fp32 MFMA -> this): forward of 1400 tiles of 64 50 -> 39, backward of the first
+// layer 96 -> 66, of ragged widths 84 -> 69; the weight gradient of the semantic attention (560k rows, with dm) 739 -> 600.
+// An operand's three planes lie one behind the other in the LDS of its two fp32 stages; with one stage a K-step costs two
+// barriers, which the other block of the compute unit covers.
+constexpr int kSplitPKC = Mma<float>::BK + 8;   // elements of a bf16 row with K contiguous (rows on disjoint banks)
+template <bool KC> constexpr int split_pitch(int extent) { return KC ? kSplitPKC : ks_pitch<bf16>(extent); }
+template <bool KC> constexpr int split_plane(int extent) { return KC ? extent * kSplitPKC : Mma<float>::BK * ks_pitch<bf16>(extent); }
+
+// Four fp32 values as the three planes' four bf16 values.
+__device__ __forceinline__ void split3(const f32x4 v, u32x2 (&w)[3]) {
+  float d[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    w[p] = u32x2{pack2(d[0], d[1]), pack2(d[2], d[3])};
+    if (p < 2) {
+      d[0] -= __uint_as_float(w[p].x << 16);
+      d[1] -= __uint_as_float(w[p].x & 0xffff0000u);
+      d[2] -= __uint_as_float(w[p].y << 16);
+      d[3] -= __uint_as_float(w[p].y & 0xffff0000u);
+    }
+  }
+}
+
+// Stores the operand tile of a mover of fp32 values as three planes.
+template <bool KC, int EXTENT, typename Mover>
+__device__ __forceinline__ void split_store(Mover &mv, bf16 *lds) {
+  constexpr int COLS = KC ? Mma<float>::BK : EXTENT, VPR = COLS / 4, NV = sizeof(mv.reg) / sizeof(mv.reg[0]);
+  constexpr int PITCH = split_pitch<KC>(EXTENT), PLANE = split_plane<KC>(EXTENT);
+  if (mv.okmask != ~0u) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+      if (!((mv.okmask >> i) & 1u)) mv.reg[i] = u32x4{0u, 0u, 0u, 0u};
+  }
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int v = threadIdx.x + i * kThreads, row = v / VPR;
+    int col = (v % VPR) * 4;
+    if constexpr (!KC && ks_swizzled<bf16>(EXTENT)) col = ks_swizzle_col(col, row);
+    u32x2 w[3];
+    split3(__builtin_bit_cast(f32x4, mv.reg[i]), w);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x2 *>(lds + p * PLANE + row * PITCH + col) = w[p];
+  }
+}
+
+template <bool AKC, bool BKC, int MI, int NI>
+__device__ __forceinline__ void mma_tile_split(f32x16 (&acc)[MI][NI], const bf16 *As, const bf16 *Bs, int wm, int wn, int lane) {
+  constexpr int PA = split_pitch<AKC>(64 * MI), PB = split_pitch<BKC>(64 * NI);
+  constexpr int QA = split_plane<AKC>(64 * MI), QB = split_plane<BKC>(64 * NI);
+  constexpr int NK = Mma<float>::BK / 16;
+  bf16x8_t b[3][NK][NI];
+#pragma unroll
+  for (int q = 0; q < 3; ++q)
+#pragma unroll
+    for (int ks = 0; ks < NK; ++ks)
+#pragma unroll
+      for (int j = 0; j < NI; ++j) b[q][ks][j] = frag_bf16<BKC, PB>(Bs + q * QB, wn + j * 32, ks, lane);
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+    f32x16 part[NI];
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) part[j][v] = 0.f;
+#pragma unroll
+    for (int p = 2; p >= 0; --p)   // smallest products first
+#pragma unroll
+      for (int ks = 0; ks < NK; ++ks) {
+        const bf16x8_t a = frag_bf16<AKC, PA>(As + p * QA, wm + i * 32, ks, lane);
+#pragma unroll
+        for (int q = 2 - p; q >= 0; --q)
+#pragma unroll
+          for (int j = 0; j < NI; ++j) part[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b[q][ks][j], part[j], 0, 0, 0);
+      }
+#pragma unroll
+    for (int j = 0; j < NI; ++j) acc[i][j] += part[j];
+  }
+}
+
 // LDS of one block: two stages of (A tile, B tile) -- reused as the output staging tile by the epilogues --
 // and the K-segment table.
 template <typename T, int MI = 2, int NI = 2> struct GemmLds {
@@ -225,7 +314,9 @@ struct NoXform {
 // Runs the K-steps of sm.seg[0..nseg) (must be visible to the whole block) into `acc`.
 // KC operand: matrix [extent x K] row-major (ld); KS operand: matrix [K x extent] row-major (ld).
 // xa(mover, step) / xb: what happens to a K-step's operand tile in the registers, on its way to LDS.
-template <typename T, bool FAST, bool AKC, bool BKC, int MI, int NI, typename XA = NoXform, typename XB = NoXform>
+// FAST fp32 tiles run on the bf16 matrix cores (see mma_tile_split) unless SPLIT is false; call them through
+// gemm_finite, which sees to infinities.
+template <typename T, bool FAST, bool AKC, bool BKC, bool SPLIT = FAST && sizeof(T) == 4, int MI, int NI, typename XA = NoXform, typename XB = NoXform>
 __device__ __forceinline__ void gemm_run(f32x16 (&acc)[MI][NI], GemmLds<T, MI, NI> &sm, int nseg, int a_extent, int a0,
                                          int b_extent, int b0, XA xa = XA(), XB xb = XB()) {
   using M = Mma<T>;
@@ -278,6 +369,26 @@ __device__ __forceinline__ void gemm_run(f32x16 (&acc)[MI][NI], GemmLds<T, MI, N
   };
   issue(ta0, tb0, s_set0);
   issue(ta1, tb1, s_set1);
+  if constexpr (SPLIT) {
+    static_assert(3 * split_plane<AKC>(TM) * sizeof(bf16) <= sizeof(sm.a) && 3 * split_plane<BKC>(TN) * sizeof(bf16) <= sizeof(sm.b), "planes must fit the stages");
+    bf16 *pa = reinterpret_cast<bf16 *>(&sm.a[0][0]), *pb = reinterpret_cast<bf16 *>(&sm.b[0][0]);
+    auto one = [&](MoverA &ta, MoverB &tb, int &s_set, int step) {
+      xa(ta, step);
+      xb(tb, step);
+      split_store<AKC, TM>(ta, pa);
+      split_store<BKC, TN>(tb, pb);
+      __syncthreads();
+      issue(ta, tb, s_set);
+      mma_tile_split<AKC, BKC>(acc, pa, pb, wm, wn, lane);
+      __syncthreads();
+    };
+    for (int step = 0; step < total; step += 2) {
+      one(ta0, tb0, s_set0, step);
+      if (step + 1 < total) one(ta1, tb1, s_set1, step + 1);
+    }
+    __syncthreads();   // a caller without K-steps may rewrite the segment table too
+    return;
+  }
   for (int step = 0; step < total; step += 2) {
     xa(ta0, step);
     xb(tb0, step);
@@ -306,6 +417,28 @@ template <int MI, int NI> __device__ __forceinline__ void zero_acc(f32x16 (&acc)
     for (int j = 0; j < NI; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+}
+
+// A tile's products through run(split): an infinity, or a value that rounds to one in bf16, leaves NaN where the fp32
+// product would be infinite or large (inf - inf in the planes, 0 * inf between them), so a tile that did not come out
+// finite is multiplied again on the fp32 MFMA (acc starts from zero both times).
+template <typename T, bool FAST, int MI, int NI, typename F>
+__device__ __forceinline__ void gemm_finite(f32x16 (&acc)[MI][NI], F run) {
+  zero_acc(acc);
+  run(std::integral_constant<bool, FAST && sizeof(T) == 4>());
+  if constexpr (FAST && sizeof(T) == 4) {
+    float s = 0.f;   // 0 * v is 0 for finite v only
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s += acc[i][j][v] * 0.f;
+    if (__syncthreads_or(!(s == 0.f))) {
+      zero_acc(acc);
+      run(std::false_type());
+    }
+  }
 }
 
 // Element (row, col) of the block tile held in acc[i][j][v] by this lane (32x32 MFMA output layout:

@@ -86,19 +86,10 @@ template <int TM> struct WideMover {
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       const int v = threadIdx.x + i * kThreads, r = v / VPR, c = (v % VPR) * 4;
-      const f32x4 x = f(reg[i]);
-      float d[4] = {x.x, x.y, x.z, x.w};
+      u32x2 w[3];
+      split3(f(reg[i]), w);
 #pragma unroll
-      for (int p = 0; p < 3; ++p) {
-        const u32x2 w = {pack2(d[0], d[1]), pack2(d[2], d[3])};
-        *reinterpret_cast<u32x2 *>(a[p] + r * PA + c) = w;
-        if (p < 2) {
-          d[0] -= __uint_as_float(w.x << 16);
-          d[1] -= __uint_as_float(w.x & 0xffff0000u);
-          d[2] -= __uint_as_float(w.y << 16);
-          d[3] -= __uint_as_float(w.y & 0xffff0000u);
-        }
-      }
+      for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x2 *>(a[p] + r * PA + c) = w[p];
     }
   }
 };
@@ -125,21 +116,29 @@ __device__ __forceinline__ void wide_run(f32x16 (&acc)[MI][NI], WideLds<MI, NI> 
       ma.load(A, lda, a_extent, a0, k0 + kWideBK, K);
       mb.load_fast(BKC ? B + k0 + kWideBK : B + (int64_t)(k0 + kWideBK) * ldb, K - k0 - kWideBK);
     }
+    constexpr int NK = kWideBK / 16;
+    bf16x8_t b[NK][NI];
 #pragma unroll
-    for (int ks = 0; ks < kWideBK / 16; ++ks) {
-      bf16x8_t b[NI];
+    for (int ks = 0; ks < NK; ++ks)
 #pragma unroll
-      for (int j = 0; j < NI; ++j) b[j] = frag_bf16<BKC, PB>(sm.b, wn + j * 32, ks, lane);
+      for (int j = 0; j < NI; ++j) b[ks][j] = frag_bf16<BKC, PB>(sm.b, wn + j * 32, ks, lane);
 #pragma unroll
-      for (int p = 2; p >= 0; --p) {   // smallest plane first
-        bf16x8_t a[MI];
+    for (int i = 0; i < MI; ++i) {
+      f32x16 part[NI];   // a K-step's sum, added by the vector unit: see mma_tile_split
 #pragma unroll
-        for (int i = 0; i < MI; ++i) a[i] = frag_bf16<true, PA>(sm.a[p], wm + i * 32, ks, lane);
+      for (int j = 0; j < NI; ++j)
 #pragma unroll
-        for (int i = 0; i < MI; ++i)
+        for (int v = 0; v < 16; ++v) part[j][v] = 0.f;
 #pragma unroll
-          for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-      }
+      for (int p = 2; p >= 0; --p)   // smallest plane first
+#pragma unroll
+        for (int ks = 0; ks < NK; ++ks) {
+          const bf16x8_t a = frag_bf16<true, PA>(sm.a[p], wm + i * 32, ks, lane);
+#pragma unroll
+          for (int j = 0; j < NI; ++j) part[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b[ks][j], part[j], 0, 0, 0);
+        }
+#pragma unroll
+      for (int j = 0; j < NI; ++j) acc[i][j] += part[j];
     }
     __syncthreads();
   }
@@ -180,9 +179,11 @@ __device__ __forceinline__ void mix_run(f32x16 (&acc)[MI][2], MixLds<TS, MI> &sm
   } else {
     if (threadIdx.x == 0) put_seg(sm.g.seg[0], A, lda, B, ldb, 0, K);
     __syncthreads();
-    gemm_run<float, true, true, BKC>(acc, sm.g, 1, a_extent, a0, b_extent, b0, [&](auto &mv, int step) {
-      const int kc = step * Mma<float>::BK + (threadIdx.x % (Mma<float>::BK / 4)) * 4;
-      for (auto &r : mv.reg) r = __builtin_bit_cast(u32x4, f(__builtin_bit_cast(f32x4, r), kc));
+    gemm_finite<float, true>(acc, [&](auto split) {
+      gemm_run<float, true, true, BKC, split.value>(acc, sm.g, 1, a_extent, a0, b_extent, b0, [&](auto &mv, int step) {
+        const int kc = step * Mma<float>::BK + (threadIdx.x % (Mma<float>::BK / 4)) * 4;
+        for (auto &r : mv.reg) r = __builtin_bit_cast(u32x4, f(__builtin_bit_cast(f32x4, r), kc));
+      });
     });
   }
 }
@@ -206,10 +207,9 @@ __global__ void __launch_bounds__(kThreads, 2) attn_proj_kernel(TypeTab tt, PtrT
   const int m0 = (local / tiles_n) * BM, n0 = (local % tiles_n) * BN;
   const int M = tt.row_off[t + 1] - tt.row_off[t], F = tt.in_dim[t];
   f32x16 acc[MI][MI];
-  zero_acc(acc);
   if (threadIdx.x == 0) put_seg(sm.seg[0], x + tt.elem_off[t], F, reinterpret_cast<const TS *>(pt.w_root[t]), H, 0, F);
   __syncthreads();
-  gemm_run<TS, true, true, false>(acc, sm, 1, M, m0, H, n0);
+  gemm_finite<TS, true>(acc, [&](auto split) { gemm_run<TS, true, true, false, split.value>(acc, sm, 1, M, m0, H, n0); });
   write_tile(acc, sm, z + ((int64_t)tt.row_off[t] + m0) * H + n0, H, M - m0, H - n0, [](float v, int, int) { return v; });
 }
 
@@ -299,7 +299,15 @@ __global__ void __launch_bounds__(kThreads, 2) attn_sem_kernel(RelRows rr, int H
   const int M = rr.row_off[r + 1] - (int)row0;
   f32x16 acc[MI][2];
   zero_acc(acc);
-  mix_run<false>(acc, sm, mbuf + row0 * H, H, M, m0, w_sem, kSemDim, kSemDim, 0, H, [](f32x4 v, int) { return v; });
+  mix_run<false>(acc, sm, mbuf + row0 * H, H, M, m0, w_sem, kSemDim, kSemDim, 0, H, [](f32x4 v, int) {
+    // beyond the largest bf16 value the first plane would be infinite and the others NaN; tanh is +-1 there either way
+    constexpr float kMax = 0x1.fep127f;
+    if constexpr (sizeof(TS) == 2) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) v[c] = fabsf(v[c]) > kMax ? copysignf(kMax, v[c]) : v[c];
+    }
+    return v;
+  });
   float bs[4], qs[4], part = 0.f;
   const int cc = (threadIdx.x % (kSemDim / 4)) * 4;
   Quad<TS>::load(bs, b_sem + cc);
@@ -589,25 +597,28 @@ __device__ __forceinline__ void attn_dws_part(GemmLds<float, 2, 2> &sm, const fl
                                               int H, int f0, float coef, const float *qs, float *__restrict__ dws,
                                               float *__restrict__ dq, float *__restrict__ dbs) {
   f32x16 acc[2][2];
-  zero_acc(acc);
   if (threadIdx.x == 0) put_seg(sm.seg[0], m + row0 * H, H, t + row0 * kSemDim, kSemDim, k_begin, k_end);
   __syncthreads();
-  float st[4] = {0.f, 0.f, 0.f, 0.f}, s1[4] = {0.f, 0.f, 0.f, 0.f};
-  gemm_run<float, true, false, false>(acc, sm, 1, H, f0, kSemDim, 0, NoXform(), [&](auto &mv, int) {
-    int i = 0;
-    for (auto &rg : mv.reg) {
-      const f32x4 v = __builtin_bit_cast(f32x4, rg);
-      const f32x4 w = {1.f - v.x * v.x, 1.f - v.y * v.y, 1.f - v.z * v.z, 1.f - v.w * v.w};
-      if ((mv.okmask >> i) & 1u) {
+  float st[4], s1[4];
+  gemm_finite<float, true>(acc, [&](auto split) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          st[c] += v[c];
-          s1[c] += w[c];
+    for (int c = 0; c < 4; ++c) st[c] = s1[c] = 0.f;
+    gemm_run<float, true, false, false, split.value>(acc, sm, 1, H, f0, kSemDim, 0, NoXform(), [&](auto &mv, int) {
+      int i = 0;
+      for (auto &rg : mv.reg) {
+        const f32x4 v = __builtin_bit_cast(f32x4, rg);
+        const f32x4 w = {1.f - v.x * v.x, 1.f - v.y * v.y, 1.f - v.z * v.z, 1.f - v.w * v.w};
+        if ((mv.okmask >> i) & 1u) {
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            st[c] += v[c];
+            s1[c] += w[c];
+          }
         }
+        rg = __builtin_bit_cast(u32x4, w);
+        ++i;
       }
-      rg = __builtin_bit_cast(u32x4, w);
-      ++i;
-    }
+    });
   });
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   float qc[2];

@@ -43,10 +43,10 @@ __global__ void __launch_bounds__(kThreads, MI == 1 ? 3 : 2) gemm_fwd_kernel(Typ
   const int m0 = (local / tiles_n) * BM, n0 = (local % tiles_n) * BN;
   const int M = tt.n_dst[d];
   f32x16 acc[MI][MI];
-  zero_acc(acc);
   // K-segments of this destination type: the aggregate of every relation ending in d (and, when the layer keeps
   // it, the aggregate's low-order remainder against the same weights), then the root term.  The first wavefront
   // looks at a window of relations at once, one per lane, and packs the ones that take part with a ballot.
+  gemm_finite<T, FAST>(acc, [&](auto split) {
   for (int cursor = 0; cursor < R; cursor += kRelWindow) {
     if (threadIdx.x < 64) {
       const int lane = threadIdx.x, r = cursor + lane;
@@ -71,8 +71,9 @@ __global__ void __launch_bounds__(kThreads, MI == 1 ? 3 : 2) gemm_fwd_kernel(Typ
       }
     }
     __syncthreads();
-    gemm_run<T, FAST, true, true>(acc, sm, s_nseg, M, m0, H, n0);
+    gemm_run<T, FAST, true, true, split.value>(acc, sm, s_nseg, M, m0, H, n0);
   }
+  });
   const int64_t orow = tt.out_row_off[d];
   if (acc32) {
     HGNN_FOR_EACH_ACC({
@@ -158,7 +159,6 @@ __device__ __forceinline__ void da_tile_at(GemmLds<T, MI, MI> &sm, int seg, int 
   const T *W = reinterpret_cast<const T *>(is_rel ? pt.w_rel[seg] : pt.w_root[d]);
   const int M = tt.n_dst[d];
   f32x16 acc[MI][MI];
-  zero_acc(acc);
   if (threadIdx.x == 0) put_seg(sm.seg[0], gp + (int64_t)tt.out_row_off[d] * ldg, ldg, W, ldg, 0, ldg);
   if (threadIdx.x < BM) {  // 1/|N_r(v)| of the tile's rows (1 for the root term)
     float sc = 1.f;
@@ -171,7 +171,7 @@ __device__ __forceinline__ void da_tile_at(GemmLds<T, MI, MI> &sm, int seg, int 
     sm.rowscale[threadIdx.x] = sc;
   }
   __syncthreads();
-  gemm_run<T, FAST, true, true>(acc, sm, 1, M, m0, F, n0);
+  gemm_finite<T, FAST>(acc, [&](auto split) { gemm_run<T, FAST, true, true, split.value>(acc, sm, 1, M, m0, F, n0); });
   T *out = dz + (int64_t)(is_rel ? rt.z_off4[seg] : rt.zroot_off4[d]) * 4;
   write_tile(acc, sm, out + (int64_t)m0 * F + n0, F, M - m0, F - n0,
              [&](float v, int row, int) { return v * sm.rowscale[row]; });
@@ -269,12 +269,11 @@ __device__ __forceinline__ void dw_tile(GemmLds<T, MI, MI> &sm, int bid, const T
   const int f0 = tf * BM, h0 = th * BN;
   const int k_begin = sp * split_rows, k_end = min(M, k_begin + split_rows);
   f32x16 acc[MI][MI];
-  zero_acc(acc);
   if (threadIdx.x == 0)
     put_seg(sm.seg[0], is_rel ? z + (int64_t)rt.z_off4[seg] * 4 : x + tt.xroot_off[d], F,
             gp + (int64_t)tt.out_row_off[d] * ldg, ldg, k_begin, k_end);
   __syncthreads();
-  gemm_run<T, FAST, false, false>(acc, sm, 1, F, f0, ldg, h0);
+  gemm_finite<T, FAST>(acc, [&](auto split) { gemm_run<T, FAST, false, false, split.value>(acc, sm, 1, F, f0, ldg, h0); });
   HGNN_FOR_EACH_ACC({
     if (f0 + row < F && h0 + col < H) atomicAdd(dW + (int64_t)(f0 + row) * H + h0 + col, val);
   })

@@ -216,6 +216,52 @@ def test_config7_widest_schema():
     _assert_ok(run_case(7, verbose=True, sampled=dict(seed=5)))
 
 
+@pytest.mark.parametrize("index", [0, 1])
+def test_fp32_products_of_values_beyond_bf16(index):
+    """fp32 GEMMs multiply on the bf16 matrix cores, three planes per operand.  A finite value that rounds to infinity in
+    bf16 (3.4e38) has no such planes: its tile is multiplied again on the fp32 units.  One such value each in the
+    features of a destination row (forward) and in the incoming gradient (backward); everything else small enough that no
+    product overflows.  Config 0: 64x64 tiles; config 1 at full size: forward tiles and both backward tile sizes."""
+    big = np.float32(3.4e38)
+
+    def features(cfg, g, mb, ws):
+        t = mb.target_type
+        g.stores[t][mb.ids[t][0], 3] = big
+
+    def gradient(cfg, g, mb, ws):
+        g.stores = [s * np.float32(0.01) for s in g.stores]
+        mb.grad_out[mb.target_type][0, 1] = big
+    _assert_ok(run_case(index, verbose=True, backward=False, cfg_edit=features))
+    if index == 0:
+        _assert_ok(run_case(index, verbose=True, cfg_edit=gradient))
+
+
+def test_fp32_products_with_infinity():
+    """An infinite feature stays infinite (not NaN) in the outputs it reaches, and reaches no others."""
+    import torch
+    from paper_2408_08490_amd.runner import Model
+    from tests.parity import prepare_inputs
+    cfg, g, mb, ws = prepare_inputs(1)
+    row = mb.ids[0][5]
+    for lw in ws:
+        lw.w_rel = [np.abs(w) + np.float32(0.01) for w in lw.w_rel]
+        lw.w_root = [None if w is None else np.abs(w) + np.float32(0.01) for w in lw.w_root]
+
+    def outputs():
+        m = Model(g.schema, g.feat_dim, g.stores, ws, dtype="f32", loss=cfg.loss, target_type=mb.target_type)
+        h = [x.cpu().numpy() for x in m.run(m.prepare(mb, g.edge_type, use_edge_id=True), backward=False)["h"]]
+        torch.cuda.synchronize()
+        m.close()
+        return h
+    before = outputs()
+    g.stores[0][row, 0] = np.inf
+    after = outputs()
+    for a, b in zip(before, after):
+        assert not np.isnan(b).any() and np.isinf(b).any()
+        same = np.isfinite(b)
+        assert same.any() and np.allclose(a[same], b[same], rtol=1e-5, atol=1e-5)
+
+
 def test_empty_minibatch():
     """No target at all: every launch is skipped or empty, the outputs are empty, and the weight gradients -- sums
     over nothing -- are exactly zero."""
