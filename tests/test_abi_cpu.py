@@ -236,6 +236,39 @@ def test_overlapping_builds_from_one_context(B, threads, builders):
     ctx.close()
 
 
+@pytest.mark.parametrize("threads", [(1, 1), (1, 6), (3, 8)])
+def test_contexts_that_share_the_crew(B, threads):
+    """The builder threads are the process's: contexts with different thread counts build at once from two caller threads,
+    and each is closed and opened again while the other's builds are under way."""
+    import threading
+    cfg = make_config(2, scale=0.02, batch=33)
+    g = build_graph(cfg)
+    mb = sample_minibatch(cfg, g)
+    refs = [O.semantic_csr(O.edge_index_select(b.edge_index, g.schema.num_rels, edge_type=b.edge_type), g.schema.rel_src,
+                           g.schema.rel_dst, b.n_src, b.n_dst) for b in mb.blocks]
+    wrong = []
+
+    def caller(n):
+        try:
+            for _ in range(3):
+                ctx = _host_ctx(B, g.schema, threads=n)
+                graphs = [ctx.hgnn_build_semantic_csr(mb.blocks) for _ in range(4)]
+                for gr in graphs:
+                    for l, ref in enumerate(refs):
+                        v = gr.host_view(l)
+                        wrong.extend((n, l, k) for k in ("rowptr", "colidx", "cptr", "crow") if not np.array_equal(v[k], ref[k]))
+                    gr.release()
+                ctx.close()
+        except Exception as e:
+            wrong.append((n, repr(e)))
+    callers = [threading.Thread(target=caller, args=(n,)) for n in threads]
+    for t in callers:
+        t.start()
+    for t in callers:
+        t.join()
+    assert not wrong, wrong
+
+
 def test_transpose_restricted_to_wanted_types(B):
     cfg = make_config(2, scale=0.02, batch=96)
     g = build_graph(cfg)
