@@ -175,7 +175,7 @@ static hgnn_status make_plan(hgnn_ctx *ctx, hgnn_graph *g, int32_t layer, const 
   pl.off_gaddr = o;   o += align_up(std::max<size_t>((size_t)L.edges, 1) * 8, 256);  // per-edge row addresses (gather from the stores)
   int64_t tiles64 = 0;  // partial tiles of the forward's split reduction
   for (int t = 0; t < T; ++t) tiles64 += (L.n_dst[t] + 63) / 64 * ((pl.H + 63) / 64);
-  pl.off_part = o;    o += tiles64 < (pl.es == 2 ? kDirectTiles / 4 : kDirectTiles) ? kDirectPartBytes : 0;
+  pl.off_part = o;    o += tiles64 < (pl.es == 2 ? kDirectTiles / 4 : p->relu ? kDirectReluTiles : kDirectTiles) ? kDirectPartBytes : 0;
   pl.scratch_bytes = o;
   if (need_built) {
     hgnn_status st = layer_dev(ctx, g, layer, pl.dev);

@@ -424,6 +424,7 @@ bool launch_gemm2_fwd(hipStream_t s, const TypeTab &tt, const RelTab &rt, const 
                       int H, int relu, const void *x, const void *z, const void *zlo, const void *wt_buf, void *h, hgnn_status *st);
 // Launchers that register themselves when the library is loaded, so that the host runtime links without them.
 constexpr int kDirectTiles = 512;                        // forward launches of fewer 64x64 tiles than this may take the kernel below
+constexpr int kDirectReluTiles = 64;                     // the same in fp32 with a ReLU
 constexpr int kDirectUnits = 512 + kDirectTiles;         // its most (tile, split) pairs: two blocks per compute unit, rounded up per tile
 constexpr size_t kDirectPartBytes = (size_t)kDirectUnits * 64 * 64 * 4;   // their partial tiles
 struct OptionalLaunchers {

@@ -421,10 +421,17 @@ template <int MI, int NI> __device__ __forceinline__ void zero_acc(f32x16 (&acc)
 
 // A tile's products through run(split): an infinity, or a value that rounds to one in bf16, leaves NaN where the fp32
 // product would be infinite or large (inf - inf in the planes, 0 * inf between them), so a tile that did not come out
-// finite is multiplied again on the fp32 MFMA (acc starts from zero both times).
+// finite is multiplied again on the fp32 MFMA (acc starts from zero both times).  decides: the sums go through a ReLU and
+// stay on the fp32 MFMA altogether (see gemm_fwd_kernel).
 template <typename T, bool FAST, int MI, int NI, typename F>
-__device__ __forceinline__ void gemm_finite(f32x16 (&acc)[MI][NI], F run) {
+__device__ __forceinline__ void gemm_finite(f32x16 (&acc)[MI][NI], F run, bool decides = false) {
   zero_acc(acc);
+  if constexpr (FAST && sizeof(T) == 4) {
+    if (decides) {
+      run(std::false_type());
+      return;
+    }
+  }
   run(std::integral_constant<bool, FAST && sizeof(T) == 4>());
   if constexpr (FAST && sizeof(T) == 4) {
     float s = 0.f;   // 0 * v is 0 for finite v only

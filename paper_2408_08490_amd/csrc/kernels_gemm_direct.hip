@@ -234,6 +234,8 @@ __global__ void __launch_bounds__(256) gemm_fwd_direct_sum_kernel(DirectArgs arg
 // the line lies further out.  Both kernels of this file together against the staged one, in us (tiles: before -> now):
 //   fp32  16: 43 -> 16, 27 -> 16 (104 relations)   96: 41 -> 23   312: 54 -> 48      700: 47 -> 52 (not taken)
 //   bf16  72: 43 -> 22 (108 relations)   16: 24 -> 16   24: 15 -> 14   96: 24 -> 21   230: 15 -> 27 (not taken)
+// In fp32 with a ReLU the line is at 64 tiles: a sum formed in another order gives units within a rounding of zero the other
+// decision (three of ten million), which moves a whole term of the gradients; up to 64 tiles there is next to never one.
 static bool launch_gemm_fwd_direct(hipStream_t s, int dtype, const TypeTab &tt, const RelTab &rt, const PtrTab &pt, const WtTab &wt,
                                    const uint32_t *live_mask, int H, int relu, const void *x, const void *z, const void *zlo,
                                    const void *wt_buf, void *h, float *part) {
@@ -246,7 +248,7 @@ static bool launch_gemm_fwd_direct(hipStream_t s, int dtype, const TypeTab &tt, 
   da.tile_off[0] = 0;
   for (int d = 0; d < T; ++d) da.tile_off[d + 1] = da.tile_off[d] + ((tt.n_dst[d] + 63) / 64) * ((H + 63) / 64);
   const int tiles = da.tile_off[T];
-  if (tiles == 0 || tiles >= (dtype == HGNN_BF16 ? kDirectTiles / 4 : kDirectTiles)) return false;
+  if (tiles == 0 || tiles >= (dtype == HGNN_BF16 ? kDirectTiles / 4 : relu ? kDirectReluTiles : kDirectTiles)) return false;
   int n = 0;
   int64_t work = 0;   // K-steps over all tiles
   for (int d = 0; d < T; ++d) {
