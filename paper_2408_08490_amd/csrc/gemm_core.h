@@ -211,7 +211,7 @@ __device__ __forceinline__ void mma_tile(f32x16 (&acc)[MI][NI], const T *As, con
 // starts from zero and the vector unit adds it to the accumulator: against 64 bits, outputs and weight gradients are then
 // 0.1 to 0.5 of the distance that the fp32 MFMA leaves (1024 targets, fan-out 25 and 20: outputs 9e-7 -> 4e-7, weight
 // gradients 1e-6 -> 2e-7 of their norm).
-// Measured with 1024 targets in fp32 (us, fp32 MFMA -> this): forward of 1400 tiles of 64 50 -> 39, backward of the first
+// Measured with 1024 targets in fp32 (us, fp32 MFMA -> this): forward of 1400 tiles of 64, no ReLU, 50 -> 39, backward of the first
 // layer 96 -> 66, of ragged widths 84 -> 69; the weight gradient of the semantic attention (560k rows, with dm) 739 -> 600.
 // An operand's three planes lie one behind the other in the LDS of its two fp32 stages; with one stage a K-step costs two
 // barriers, which the other block of the compute unit covers.

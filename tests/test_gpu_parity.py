@@ -262,6 +262,19 @@ def test_fp32_products_with_infinity():
         assert same.any() and np.allclose(a[same], b[same], rtol=1e-5, atol=1e-5)
 
 
+@pytest.mark.parametrize("index,dtype,batch", [(1, "f32", 1), (1, "f32", 63), (1, "f32", 129), (2, "bf16", 1), (2, "bf16", 65),
+                                               (4, "f32", 65), (4, "bf16", 63)])
+def test_small_batches_around_a_tile(index, dtype, batch):
+    """Mini-batches of a row, a tile less one, a tile plus one: the forward GEMM whose reduction is split over blocks and
+    wavefronts (rows and the 349 columns end inside a tile), the 64x64 backward tiles with few K-steps to share out, and
+    the attention kernels whose blocks are cut per relation.  Tolerances are the storage type's; for attention in bf16 the
+    layers are compared one by one, as in the tests of its other sizes.  (No attention batch of one target: the softmax
+    over a row's neighbours is invariant to the destination's score term unless the scores straddle zero, so that target's
+    gradients through it -- da_dst, dw_type of its type -- are exactly zero and have no scale to be compared on.)"""
+    edit = _as_f32 if index == 4 and dtype == "f32" else None
+    _assert_ok(run_case(index, scale=0.02, batch=batch, verbose=True, cfg_edit=edit, layerwise=index == 4))
+
+
 def test_empty_minibatch():
     """No target at all: every launch is skipped or empty, the outputs are empty, and the weight gradients -- sums
     over nothing -- are exactly zero."""
