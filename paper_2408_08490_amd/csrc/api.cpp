@@ -744,7 +744,10 @@ hgnn_status hgnn_graph_wait(hgnn_ctx *ctx, hgnn_graph *g) {
   if (!ctx || !g) HGNN_FAIL(HGNN_EINVAL, "NULL argument");
   hgnn_status st = wait_built(g);
   if (st != HGNN_OK) return st;
-  if (ctx->device >= 0) HGNN_HIP(hipEventSynchronize(g->ready));
+  if (ctx->device >= 0 && !g->uploaded.load(std::memory_order_acquire)) {
+    HGNN_HIP(hipEventSynchronize(g->ready));
+    g->uploaded.store(true, std::memory_order_release);
+  }
   return HGNN_OK;
 }
 

@@ -287,8 +287,7 @@ struct hgnn_graph {
   int status = HGNN_OK;
   std::string err;
   hipEvent_t ready = nullptr;
-  std::atomic<void *> waited{nullptr};      // the stream that was last made to wait for `ready` (any_waited: there is one)
-  std::atomic<bool> any_waited{false};
+  std::atomic<bool> uploaded{false};     // `ready` is known to have been reached
   std::unique_ptr<hgnn::SampleJob> job;  // set for hgnn_sample_and_build
   bool sampled = false;                  // the job's results are complete (guarded by m)
   bool with_perm = true;                 // the build writes perm / cperm (fixed when the build is planned)

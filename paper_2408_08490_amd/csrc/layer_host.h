@@ -10,16 +10,24 @@ static inline int esize(int dtype) { return dtype == HGNN_BF16 ? 2 : 4; }
 // Waits for the host build and fills the device-side view of one layer's index arrays.
 hgnn_status layer_dev(hgnn_ctx *ctx, hgnn_graph *g, int32_t layer, LayerDev &D);
 
-// Makes `s` wait for the graph's upload, once per stream in a row: work that a stream takes after its wait is behind the
-// upload anyway (an unfinished event costs some 10 us per wait, and a step takes four or more).
+// Makes `s` wait for the graph's upload.  Once the upload is known to have finished no stream has to wait any more (an
+// unfinished event costs some 10 us per wait, and a step takes four or more).  Which stream waited before says nothing: a
+// handle does not identify a stream (hipStreamPerThread names another one in every thread; a destroyed stream's may come
+// again), and a wait that went into a captured graph orders nothing outside it.
 static inline hipError_t wait_upload(hgnn_graph *g, hipStream_t s) {
-  if (g->any_waited.load(std::memory_order_acquire) && g->waited.load(std::memory_order_relaxed) == (void *)s) return hipSuccess;
-  const hipError_t e = hipStreamWaitEvent(s, g->ready, 0);
-  if (e == hipSuccess) {
-    g->waited.store((void *)s, std::memory_order_relaxed);
-    g->any_waited.store(true, std::memory_order_release);
+  if (g->uploaded.load(std::memory_order_acquire)) return hipSuccess;
+  if (hipPeekAtLastError() == hipSuccess) {   // "not ready" is left as the thread's last error, which is then taken back
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;   // the query may run while a stream is being captured
+    const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    const hipError_t e = hipEventQuery(g->ready);
+    if (e != hipSuccess) (void)hipGetLastError();
+    if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e == hipSuccess) {
+      g->uploaded.store(true, std::memory_order_release);
+      return hipSuccess;
+    }
   }
-  return e;
+  return hipStreamWaitEvent(s, g->ready, 0);
 }
 
 // While alive, the launches made on this thread are timed if the probe selects (kernel, layer).
