@@ -332,18 +332,21 @@ hgnn_status hgnn_create(hgnn_ctx **out, const hgnn_schema *s, int device, int ho
     c->idle_builders.push_back(c->builders.back().get());
   }
   c->crew_threads = std::max(nb, n - 1);
-  Crew::get().join(c->crew_threads, c->pool->size() > 1);
+  c->crew = &Crew::get();
+  c->crew->join(c->crew_threads, c->pool->size() > 1);
   *out = c;
   return HGNN_OK;
 }
 
 void hgnn_destroy(hgnn_ctx *c) {
   if (!c) return;
-  {
-    std::unique_lock<std::mutex> lk(c->qm);
-    c->qcv.wait(lk, [&] { return c->building == 0; });   // queued builds are finished
+  if (c->crew == &Crew::get()) {   // else: inherited through a fork, whose child has none of its threads
+    {
+      std::unique_lock<std::mutex> lk(c->qm);
+      c->qcv.wait(lk, [&] { return c->building == 0; });   // queued builds are finished
+    }
+    c->crew->leave(c->crew_threads, c->pool->size() > 1);
   }
-  Crew::get().leave(c->crew_threads, c->pool->size() > 1);
   if (c->device >= 0) {
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->side);

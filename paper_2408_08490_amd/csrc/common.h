@@ -149,7 +149,7 @@ struct Slab {  // pinned host block + device block of equal capacity
 // the threads look for work in a loop for a while before they sleep: waking one costs more than a phase.
 class Crew {
  public:
-  static Crew &get();
+  static Crew &get();        // the process's; a forked child has its own, without threads until a context joins it
   static int index();        // the calling thread's number in the crew
   // A context that may use this many threads comes / goes; `eager`: its builds are shared between threads, so that the crew
   // looks for work before it sleeps (a crew of one-thread builders has none to pass on at once, and leaves its idle time
@@ -304,7 +304,8 @@ struct hgnn_ctx {
   std::vector<std::unique_ptr<hgnn::Builder>> builders;   // as many graphs are built at once
   std::vector<hgnn::Builder *> idle_builders;             // qm; the one used last is taken first (its tables are in the caches)
   std::unique_ptr<hgnn::ThreadPool> pool;                 // threads a phase of a build may use
-  int crew_threads = 0;                                   // what this context asked of the crew
+  hgnn::Crew *crew = nullptr;                             // the crew it joined (a forked child has another one)
+  int crew_threads = 0;                                   // what it asked of the crew
   hipStream_t side = nullptr;
   std::mutex qm;
   std::condition_variable qcv;

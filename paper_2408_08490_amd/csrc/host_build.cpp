@@ -3,6 +3,8 @@
 // CSR per layer, plus its transpose for the backward pass.  Integer work only.  The paper runs
 // the selection with one OpenMP thread per relation; here the threads split the edge list
 // instead (relations are very uneven in size), which yields the same arrays.
+#include <pthread.h>
+
 #include <algorithm>
 #include <chrono>
 #include <cstdlib>
@@ -23,8 +25,23 @@ void set_error(const char *fmt, ...) {
 const char *get_error() { return g_err; }
 
 // ------------------------------------------------------------------------------------------
+static std::atomic<Crew *> g_crew{nullptr};   // never destroyed: contexts may be released while the process's statics go
+
 Crew &Crew::get() {
-  static Crew *c = new Crew();   // never destroyed: contexts may be released while the process's statics go
+  Crew *c = g_crew.load(std::memory_order_acquire);
+  if (!c) {
+    static std::mutex making;
+    // A forked child has none of its parent's threads, and the locks of the parent's crew as they stood: it starts afresh.
+    // (Held across the fork, so that the child finds `making` free.)
+    static const int hooked = pthread_atfork([] { making.lock(); }, [] { making.unlock(); }, [] {
+      g_crew.store(nullptr, std::memory_order_relaxed);
+      making.unlock();
+    });
+    (void)hooked;
+    std::lock_guard<std::mutex> lk(making);
+    c = g_crew.load(std::memory_order_relaxed);
+    if (!c) g_crew.store(c = new Crew(), std::memory_order_release);
+  }
   return *c;
 }
 void Crew::join(int threads, bool eager) {

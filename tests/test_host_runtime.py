@@ -1,7 +1,9 @@
 """The runtime's host side where several streams, processes, contexts or threads meet.  CPU only."""
 import os
 import shutil
+import signal
 import subprocess
+import sys
 
 import pytest
 
@@ -30,3 +32,46 @@ def test_every_call_waits_for_an_upload_that_is_not_known_to_have_finished(tmp_p
     none waits, whatever the handle."""
     run = subprocess.run([_compile(tmp_path, "upload_wait")], capture_output=True, text=True, timeout=60)
     assert run.returncode == 0 and "upload wait ok" in run.stdout, run.stdout + run.stderr
+
+
+FORK = '''
+import os, sys
+import numpy as np
+sys.path.insert(0, %r)
+from paper_2408_08490_amd import binding as B
+from workloads import make_config, build_graph, sample_minibatch
+cfg = make_config(0, scale=0.2, batch=8)
+g = build_graph(cfg)
+mb = sample_minibatch(cfg, g)
+
+def build():
+    ctx = B.Context(g.schema.rel_src, g.schema.rel_dst, g.schema.num_types, device=-1, host_threads=4)
+    gr = ctx.hgnn_build_semantic_csr(mb.blocks)
+    v = gr.host_view(0)
+    gr.release()
+    return ctx, v
+
+parent, want = build()
+pid = os.fork()
+if pid == 0:
+    ctx, got = build()
+    ctx.close()
+    parent.close()     # inherited: its threads are the parent's
+    os._exit(0 if all(np.array_equal(got[k], want[k]) for k in ("rowptr", "colidx", "cptr", "crow")) else 3)
+status = os.waitpid(pid, 0)[1]
+again = build()        # the parent's own threads are as they were
+print("fork ok" if status == 0 else "child: %%d" %% status)
+'''
+
+
+def test_a_forked_child_builds_with_threads_of_its_own():
+    """A loader worker forked while the parent holds a context: its own host-only context builds, and the inherited one can
+    be closed."""
+    run = subprocess.Popen([sys.executable, "-c", FORK % ROOT], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True,
+                           start_new_session=True)
+    try:
+        out = run.communicate(timeout=60)[0]
+    except subprocess.TimeoutExpired:
+        os.killpg(run.pid, signal.SIGKILL)      # the child too
+        pytest.fail("the child's build does not end")
+    assert run.returncode == 0 and "fork ok" in out, out
