@@ -5,6 +5,7 @@ libhgnn.so; PyTorch provides device memory and the stream.
 """
 from __future__ import annotations
 
+import threading
 from typing import List, Optional
 
 import numpy as np
@@ -24,35 +25,36 @@ def to_device(a: np.ndarray, dtype: str, dev) -> torch.Tensor:
 
 
 class _Uploads:
-    """Integer lists to the device through a few pinned buffers, one asynchronous copy per mini-batch."""
+    """Integer lists to the device in one copy per mini-batch, through a pinned buffer and on a stream of its own, so that the
+    caller waits for the copy alone and not for what its own stream still has to do.  The lists are complete when put()
+    returns, for every stream; several threads may call it."""
 
-    def __init__(self, dev, slots=4):
-        self.dev, self.slots, self.next = dev, [[None, None] for _ in range(slots)], 0
+    def __init__(self, dev):
+        self.dev, self.stream, self.host, self.lock = dev, torch.cuda.Stream(dev), None, threading.Lock()
 
     def put(self, arrays):
-        """Device int64 tensors with the values of the host arrays (views of one tensor)."""
-        sizes = [len(a) for a in arrays]
+        """Device int64 tensors with the values and shapes of the host arrays (views of one tensor)."""
+        arrays = [np.asarray(a) for a in arrays]
+        sizes = [a.size for a in arrays]
         n = sum(sizes)
-        slot = self.slots[self.next]
-        self.next = (self.next + 1) % len(self.slots)
-        if slot[1] is not None:
-            slot[1].synchronize()          # the copy that reads the buffer has long ended
-        if slot[0] is None or slot[0].numel() < n:
-            slot[0] = torch.empty(max(1024, n + n // 4), dtype=torch.int64, pin_memory=True)
-        host, at = slot[0].numpy(), 0
-        for a, k in zip(arrays, sizes):
-            host[at: at + k] = a
-            at += k
-        out = torch.empty(n, dtype=torch.int64, device=self.dev)
-        out.copy_(slot[0][:n], non_blocking=True)
-        slot[1] = torch.cuda.Event()
-        slot[1].record()
-        return list(out.split(sizes)), slot[1]
+        with self.lock:
+            if self.host is None or self.host.numel() < n:
+                self.host = torch.empty(max(1024, n + n // 4), dtype=torch.int64, pin_memory=True)
+            host, at = self.host.numpy(), 0
+            for a, k in zip(arrays, sizes):
+                host[at: at + k] = a.reshape(-1)
+                at += k
+            with torch.cuda.stream(self.stream):
+                out = torch.empty(n, dtype=torch.int64, device=self.dev)
+                out.copy_(self.host[:n], non_blocking=True)
+            self.stream.synchronize()
+        # its memory goes back to the pool for later copies only behind what the caller's stream does with it
+        out.record_stream(torch.cuda.current_stream(self.dev))
+        return [x.view(a.shape) for x, a in zip(out.split(sizes), arrays)]
 
 
 class Batch:
     def __init__(self):
-        self.uploaded = None     # (event, stream) of the copies of ids and labels
         self.ids_dev = None
         self.graph = None
         self.labels_dev = None
@@ -213,8 +215,7 @@ class Model:
         b.graph = self.ctx.hgnn_build_semantic_csr(mb.blocks, global_edge_type, use_edge_id, self.transpose_types(len(mb.blocks)),
                                                    on_device=device_build)
         lists = list(mb.ids) + ([mb.labels] if mb.labels is not None else [])
-        b.ids_dev, event = self._uploads.put(lists)
-        b.uploaded = (event, torch.cuda.current_stream(self.dev.index).cuda_stream)
+        b.ids_dev = self._uploads.put(lists)
         if mb.labels is not None:
             b.labels_dev = b.ids_dev.pop()
         if mb.grad_out is not None:
@@ -256,8 +257,6 @@ class Model:
         gather = bool(gather) and not naive and not two_step and not self.attention
         if b.sampled and b.ids_dev is None:
             self._resolve_sampled(b)
-        if b.uploaded is not None and b.uploaded[1] != torch.cuda.current_stream(self.dev.index).cuda_stream:
-            torch.cuda.current_stream(self.dev.index).wait_event(b.uploaded[0])
         if gather:
             nd0 = list(b.blocks[0].n_dst)
             x = self._typed("x0dst", sum(n * f for n, f in zip(nd0, self.feat_dim)))
