@@ -175,6 +175,7 @@ class Crew {
     std::atomic<uint64_t> taken{0};   // chunks taken, for n <= 64 (`next` counts them)
   };
   struct alignas(64) Slot {
+    std::atomic<bool> taken{false};   // by a phase, until nobody looks at its job any more
     std::atomic<Job *> job{nullptr};
     std::atomic<int> users{0};   // threads that may be looking at *job
   };

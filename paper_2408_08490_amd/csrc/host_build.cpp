@@ -166,9 +166,9 @@ void Crew::parallel_for(int nchunks, int width, const std::function<void(int)> &
   j.width = width;
   Slot *mine = nullptr;
   for (Slot &s : slots_) {
-    Job *none = nullptr;
-    if (!s.job.load(std::memory_order_relaxed) && s.job.compare_exchange_strong(none, &j)) {
+    if (!s.taken.load(std::memory_order_relaxed) && !s.taken.exchange(true)) {
       mine = &s;
+      mine->job.store(&j);
       break;
     }
   }
@@ -186,7 +186,8 @@ void Crew::parallel_for(int nchunks, int width, const std::function<void(int)> &
   if (!mine) return;
   active_.fetch_sub(1);
   mine->job.store(nullptr);
-  wait([&] { return mine->users.load() == 0; });
+  wait([&] { return mine->users.load() == 0; });   // those still on their way out of this job: the slot takes no other before
+  mine->taken.store(false);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -75,3 +75,9 @@ def test_a_forked_child_builds_with_threads_of_its_own():
         os.killpg(run.pid, signal.SIGKILL)      # the child too
         pytest.fail("the child's build does not end")
     assert run.returncode == 0 and "fork ok" in out, out
+
+
+def test_short_phases_do_not_wait_for_another_callers_long_ones(tmp_path):
+    """A caller whose phase is over leaves at once, also when another caller's phase of 60 ms follows in the same place."""
+    run = subprocess.run([_compile(tmp_path, "crew_phases")], capture_output=True, text=True, timeout=60)
+    assert run.returncode == 0 and "crew phases ok" in run.stdout, run.stdout + run.stderr
