@@ -10,7 +10,8 @@
 namespace hgnn {
 const char *get_error();
 
-// Works off the context's queue with one of its builders (on a thread of the crew).
+// Works off the context's queue with one of its builders (on a thread of the crew), as long as no other context's task
+// waits for a thread: between two graphs the task then goes to the end of the crew's list.
 static void build_queued(hgnn_ctx *ctx) {
   if (ctx->device >= 0) (void)hipSetDevice(ctx->device);
   Builder *bd = nullptr;
@@ -30,6 +31,10 @@ static void build_queued(hgnn_ctx *ctx) {
         bd = idle[at];
         idle.erase(idle.begin() + at);
         bd->user = me;
+      } else if (!ctx->queue.empty() && Crew::get().wanted()) {
+        ctx->idle_builders.push_back(bd);
+        Crew::get().submit([ctx] { build_queued(ctx); });
+        return;
       }
       if (ctx->queue.empty()) {
         ctx->idle_builders.push_back(bd);

@@ -157,6 +157,8 @@ class Crew {
   void join(int threads, bool eager);
   void leave(int threads, bool eager);
   void submit(std::function<void()> task);
+  // whether the calling thread's task should go to the end of the list: another one waits, or the thread is to end
+  bool wanted() const { return waiting_tasks_.load(std::memory_order_relaxed) > 0 || index() >= target_.load(std::memory_order_relaxed); }
   // Runs fn(chunk) for chunk in [0, nchunks) on the caller and at most `width` - 1 others; returns when all are done.
   // Up to 64 chunks, a thread first looks at those that bear its number: phases that deal the same slices then meet the
   // data they wrote a phase earlier in their own caches.

@@ -4,6 +4,7 @@ import shutil
 import signal
 import subprocess
 import sys
+import time
 
 import pytest
 
@@ -81,3 +82,53 @@ def test_short_phases_do_not_wait_for_another_callers_long_ones(tmp_path):
     """A caller whose phase is over leaves at once, also when another caller's phase of 60 ms follows in the same place."""
     run = subprocess.run([_compile(tmp_path, "crew_phases")], capture_output=True, text=True, timeout=60)
     assert run.returncode == 0 and "crew phases ok" in run.stdout, run.stdout + run.stderr
+
+
+def _contexts():
+    """(context(threads, builders) of a small graph family, queue(context, n) = n builds of one mini-batch)"""
+    from paper_2408_08490_amd import binding as B
+    from workloads import build_graph, make_config, sample_minibatch
+    cfg = make_config(2, scale=0.02, batch=64)
+    g = build_graph(cfg)
+    mb = sample_minibatch(cfg, g)
+
+    def context(threads, builders):
+        return B.Context(g.schema.rel_src, g.schema.rel_dst, g.schema.num_types, device=-1, host_threads=threads, concurrent_builds=builders)
+    return context, lambda ctx, n: [ctx.hgnn_build_semantic_csr(mb.blocks) for _ in range(n)]
+
+
+def test_a_context_does_not_wait_for_another_ones_queue():
+    """Two builders' threads, 400 graphs queued by one context, one by another: that one is built between them."""
+    context, queue = _contexts()
+    a, b = context(2, 2), context(2, 2)
+    graphs = queue(a, 400)
+    t0 = time.perf_counter()
+    one = queue(b, 1)
+    one[0].wait()
+    t_one = time.perf_counter() - t0
+    graphs[-1].wait()
+    t_all = time.perf_counter() - t0
+    for g in graphs + one:
+        g.release()
+    a.close()
+    b.close()
+    assert t_one < t_all / 3, (t_one, t_all)
+
+
+def test_closing_a_context_does_not_wait_for_another_ones_queue():
+    """The crew gives back the threads that only the closed context asked for between two graphs of the other one's."""
+    context, queue = _contexts()
+    wide, b = context(8, 8), context(2, 2)
+    own = queue(wide, 40)          # all eight threads have work, so that any of them may be the next to take some
+    graphs = queue(b, 400)
+    for g in own:
+        g.release()
+    t0 = time.perf_counter()
+    wide.close()
+    t_close = time.perf_counter() - t0
+    graphs[-1].wait()
+    t_all = time.perf_counter() - t0
+    for g in graphs:
+        g.release()
+    b.close()
+    assert t_close < t_all / 3, (t_close, t_all)
