@@ -664,13 +664,19 @@ void build_graph_job(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g) {
       }
     }
   }
+  BuildError layer_err[kMaxLayers];
+  const BuildError *first = &err;
   if (ok) {  // the layers side by side: a small layer's phases are shorter than what it takes to start them
-    bd.pool->parallel_for(g->num_layers, [&](int l) { (void)build_layer(ctx, *bd.pool, bd.layer[l], g, l, err); });
-    ok = !err.failed.load();
+    bd.pool->parallel_for(g->num_layers, [&](int l) { (void)build_layer(ctx, *bd.pool, bd.layer[l], g, l, layer_err[l]); });
+    for (int l = g->num_layers - 1; l >= 0; --l)
+      if (layer_err[l].failed.load()) {   // of several bad layers the first is reported, whichever was done first
+        first = &layer_err[l];
+        ok = false;
+      }
   }
   tm.lap("all layers");
-  int status = ok ? HGNN_OK : err.status;
-  std::string msg = err.msg;
+  int status = ok ? HGNN_OK : first->status;
+  std::string msg = first->msg;
   if (ok && ctx->device >= 0) {
     hipError_t e = hipMemcpyAsync(g->slab.dev, g->slab.host, g->used * sizeof(int32_t), hipMemcpyHostToDevice, ctx->side);
     if (e == hipSuccess) e = hipEventRecord(g->ready, ctx->side);

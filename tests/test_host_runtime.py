@@ -132,3 +132,22 @@ def test_closing_a_context_does_not_wait_for_another_ones_queue():
         g.release()
     b.close()
     assert t_close < t_all / 3, (t_close, t_all)
+
+
+def test_of_several_bad_layers_the_first_is_reported():
+    import numpy as np
+    from paper_2408_08490_amd import binding as B
+    from workloads import build_graph, make_config, sample_minibatch
+    cfg = make_config(2, scale=0.02, batch=64)
+    g = build_graph(cfg)
+    mb = sample_minibatch(cfg, g)
+    for b in mb.blocks:
+        b.edge_type = np.array(b.edge_type)
+    mb.blocks[0].edge_type[-1] = mb.blocks[1].edge_type[0] = 99     # the larger first layer's is found last
+    ctx = B.Context(g.schema.rel_src, g.schema.rel_dst, g.schema.num_types, device=-1, host_threads=6)
+    for _ in range(50):
+        gr = ctx.hgnn_build_semantic_csr(mb.blocks, use_edge_id=False)
+        with pytest.raises(B.HgnnError, match="layer 0: edge %d has type 99" % (len(mb.blocks[0].edge_type) - 1)):
+            gr.wait()
+        gr.release()
+    ctx.close()
