@@ -217,33 +217,40 @@ class ThreadPool {
   int width_;
 };
 
-// Growable int64 array whose new space stays uninitialised (a std::vector would zero it, and its push_back
-// checks the capacity on every element).
-struct I64Buf {
-  int64_t *p = nullptr;
+// Growable array whose new space stays uninitialised (a std::vector would zero it, and its push_back checks the capacity
+// on every element) and whose failure to grow is a return value.
+template <typename T> struct Buf {
+  T *p = nullptr;
   size_t n = 0, cap = 0;
-  I64Buf() = default;
-  I64Buf(const I64Buf &) = delete;
-  I64Buf &operator=(const I64Buf &) = delete;
-  ~I64Buf() { free(p); }
+  Buf() = default;
+  Buf(const Buf &) = delete;
+  Buf &operator=(const Buf &) = delete;
+  ~Buf() { free(p); }
   bool reserve(size_t c) {
     if (c <= cap) return true;
     c = std::max(c, cap + cap / 2);  // grow in few, large steps: each one is a system call that remaps pages
-    void *q = realloc(p, c * sizeof(int64_t));
+    void *q = realloc(p, c * sizeof(T));
     if (!q) return false;
-    p = (int64_t *)q;
+    p = (T *)q;
     cap = c;
     return true;
   }
-  const int64_t *data() const { return p; }
+  const T *data() const { return p; }
   size_t size() const { return n; }
 };
+typedef Buf<int64_t> I64Buf;
 
 // Scratch of one layer's index build.
 struct LayerScratch {
   std::vector<int32_t> key, col, hist, tkey;
   std::vector<std::vector<int32_t>> long_lists;
 };
+// The edges that a slice of a hop's merged rows keeps, row by row.
+struct SampleSlice {
+  Buf<int32_t> src;                        // source vertices
+  I64Buf pos;                              // global edge positions
+};
+constexpr int kSampleSlices = 64;
 // One builder: the scratch of a crew thread that works off the context's queue of graphs.
 struct Builder {
   ThreadPool *pool = nullptr;
@@ -251,8 +258,9 @@ struct Builder {
   LayerScratch layer[kMaxLayers];          // the layers of a mini-batch are built side by side
   std::vector<int32_t> local_of[kMaxT];    // sampler: local row of a global vertex id (-1 = not in the hop), per type
   std::vector<int64_t> hop_ids[2][kMaxT];  // sampler: destination / source lists of the current hop
-  I64Buf edge_pos;                         // sampler: global edge positions of the hop, fanout places per destination
-  std::vector<int32_t> edge_src, edge_cnt; // sampler: their source vertices; edges kept per merged row
+  I64Buf dst_pos;                          // sampler on one thread: the hop's local destinations
+  SampleSlice slice[kSampleSlices];        // sampler on several: what each slice of the hop's rows keeps
+  Buf<int32_t> edge_cnt;                   // sampler on several: edges kept per merged row
 };
 
 // A mini-batch to be sampled on a builder's thread before its index arrays are built, and what the sampling

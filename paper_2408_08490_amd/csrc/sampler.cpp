@@ -64,7 +64,9 @@ struct SampleTask {
   int32_t r;
   int32_t i0, i1;     // destinations of the relation
   int64_t row;        // merged row of destination i0
-  int64_t edges, fresh;
+  int64_t at;         // its first edge inside the slice
+  int64_t edges, fresh;              // edges kept; those that are the first to reach their vertex
+  int64_t first_edge, first_fresh;   // where these start in the hop's lists and in the source type's
 };
 
 hgnn_status run_sample_job(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g, std::string &msg) {
@@ -83,11 +85,11 @@ hgnn_status run_sample_job(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g, std::strin
   const uint64_t k0 = mix64(job.seed);
   hgnn_status st = HGNN_OK;
   std::vector<SampleTask> tasks;
-  // runs fn(task) for all tasks, each pass dealing the same slices of them
+  // runs fn(task, slice) for all tasks, each pass dealing the same slices of them, each slice's in order
   auto for_tasks = [&](auto fn) {
-    const int n = (int)tasks.size(), slices = std::min({n, 64, 2 * pool.size()});
+    const int n = (int)tasks.size(), slices = std::min({n, kSampleSlices, 2 * pool.size()});
     pool.parallel_for(slices, [&](int i) {
-      for (int t = (int)((int64_t)n * i / slices); t < (int)((int64_t)n * (i + 1) / slices); ++t) fn(t);
+      for (int t = (int)((int64_t)n * i / slices); t < (int)((int64_t)n * (i + 1) / slices); ++t) fn(tasks[t], bd.slice[i]);
     });
   };
   // runs fn(first, last) over [0, n) in pieces of at least `least`
@@ -125,7 +127,7 @@ hgnn_status run_sample_job(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g, std::strin
     for (int r = 0; r < R; ++r) {
       const int64_t nd = (int64_t)dst[ctx->rel_dst[r]].size();
       for (int64_t i = 0; i < nd; i += kTaskRows)
-        tasks.push_back({r, (int32_t)i, (int32_t)std::min<int64_t>(nd, i + kTaskRows), rows + i, 0, 0});
+        tasks.push_back({r, (int32_t)i, (int32_t)std::min<int64_t>(nd, i + kTaskRows), rows + i, 0, 0, 0, 0, 0});
       rows += nd;
     }
     if (st == HGNN_OK && rows > (int64_t)INT32_MAX - 2) {
@@ -134,7 +136,7 @@ hgnn_status run_sample_job(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g, std::strin
     }
     if (pool.size() == 1) {
       // a single thread: one pass that numbers the vertices as it reaches them
-      I64Buf &es = job.edge_index[l], &ed = bd.edge_pos;  // local sources; the destinations are appended below
+      I64Buf &es = job.edge_index[l], &ed = bd.dst_pos;  // local sources; the destinations are appended below
       I64Buf &eid = job.edge_id[l];
       std::vector<int32_t> &rp = job.row_ptr[l];
       {
@@ -199,24 +201,16 @@ hgnn_status run_sample_job(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g, std::strin
       es.n = 2 * ne;
       eid.n = ne;
     } else {
-    if (st == HGNN_OK && !bd.edge_pos.reserve((size_t)(rows * fanout) + 1)) {
+    if (st == HGNN_OK && !bd.edge_cnt.reserve((size_t)rows + 1)) {
       msg = "out of host memory";
       st = HGNN_ENOMEM;
     }
-    if (st == HGNN_OK) {
-      auto grow = [](std::vector<int32_t> &v, size_t n) {
-        if (v.size() < n) v.resize(n + n / 4);
-      };
-      grow(bd.edge_src, (size_t)(rows * fanout));
-      grow(bd.edge_cnt, (size_t)rows);
-    }
-    int64_t *epos = bd.edge_pos.p;      // fanout places per merged row
-    int32_t *esrc = bd.edge_src.data(), *ecnt = bd.edge_cnt.data();
+    int32_t *ecnt = bd.edge_cnt.p;
     if (st != HGNN_OK) tasks.clear();
-    const int nt = (int)tasks.size();
+    for (SampleSlice &sl : bd.slice) sl.src.n = 0;
+    std::atomic<bool> no_memory{false};
     tm.lap("hop set-up");
-    for_tasks([&](int ti) {
-      SampleTask &tk = tasks[ti];
+    for_tasks([&](SampleTask &tk, SampleSlice &sl) {
       const int r = tk.r, s = ctx->rel_src[r], d = ctx->rel_dst[r];
       const int64_t *ptr = sm.in_indptr[r], *dv = dst[d].data();
       const int32_t *nbr = sm.in_nbr[r];
@@ -224,26 +218,35 @@ hgnn_status run_sample_job(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g, std::strin
       int32_t *lut = bd.local_of[s].data();
       const uint64_t kr = mix64(kh ^ (uint64_t)r);
       int64_t pos[kBlock][kMaxFan];
+      tk.at = (int64_t)sl.src.n;
       for (int32_t i0 = tk.i0; i0 < tk.i1; i0 += kBlock) {
         const int nb = std::min(kBlock, tk.i1 - i0);
         const int64_t row0 = tk.row + (i0 - tk.i0);
         for (int b = 0; b < nb; ++b) __builtin_prefetch(ptr + dv[i0 + b]);
         choose_block(ptr, nbr, dv + i0, nb, fanout, kr, pos, ecnt + row0);
-        for (int b = 0; b < nb; ++b) tk.edges += ecnt[row0 + b];
-        for (int b = 0; b < nb; ++b) {
-          const int64_t at = (row0 + b) * fanout;
-          for (int c = 0; c < ecnt[row0 + b]; ++c) {
-            const int32_t u = nbr[pos[b][c]];
-            esrc[at + c] = u;
-            epos[at + c] = e0 + pos[b][c];
-            __builtin_prefetch(lut + u, 1);   // to be written
-          }
+        size_t kept = 0, at = sl.src.n;
+        for (int b = 0; b < nb; ++b) kept += (size_t)ecnt[row0 + b];
+        // room for what is kept, not for `fanout` per row: most rows of a graph of many relations keep next to nothing
+        if (no_memory.load(std::memory_order_relaxed) || !sl.src.reserve(at + kept) || !sl.pos.reserve(at + kept)) {
+          no_memory.store(true, std::memory_order_relaxed);
+          return;
         }
+        sl.src.n = at + kept;
+        tk.edges += (int64_t)kept;
+        int32_t *u = sl.src.p + at;
+        int64_t *p = sl.pos.p + at;
+        for (int b = 0; b < nb; ++b)
+          for (int c = 0; c < ecnt[row0 + b]; ++c) {
+            const int32_t v = nbr[pos[b][c]];
+            *u++ = v;
+            *p++ = e0 + pos[b][c];
+            __builtin_prefetch(lut + v, 1);   // to be written
+          }
+        u = sl.src.p + at;
         for (int b = 0; b < nb; ++b) {
-          const int64_t at = (row0 + b) * fanout;
           const int32_t mine = (int32_t)(-2 - (row0 + b));   // claims: -2 - row, so that an earlier row is the larger value
           for (int c = 0; c < ecnt[row0 + b]; ++c) {
-            std::atomic_ref<int32_t> slot(lut[esrc[at + c]]);
+            std::atomic_ref<int32_t> slot(lut[*u++]);
             int32_t cur = slot.load(std::memory_order_relaxed);
             while ((cur == -1 || cur < mine) && !slot.compare_exchange_weak(cur, mine, std::memory_order_relaxed)) {}
           }
@@ -251,41 +254,43 @@ hgnn_status run_sample_job(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g, std::strin
       }
     });
     tm.lap("choose and claim");
-    // the table's entries of a row a few rows ahead
-    constexpr int kAhead = 3;
-    auto ahead = [&](const SampleTask &tk, const int32_t *lut, int64_t row) {
-      if (row + kAhead >= tk.row + (tk.i1 - tk.i0)) return;
-      const int32_t *u = esrc + (row + kAhead) * fanout;
-      for (int c = 0; c < ecnt[row + kAhead]; ++c) __builtin_prefetch(lut + (u[c] < 0 ? ~u[c] : u[c]));
+    if (no_memory.load()) {
+      msg = "out of host memory";
+      st = HGNN_ENOMEM;
+    }
+    // prefetches the table's entries of the edges some way ahead of edge `e` of a task that ends at `end`
+    constexpr int64_t kAhead = 32;
+    auto ahead = [&](const int32_t *lut, const int32_t *u, int64_t end, int64_t e, int cnt) {
+      for (int64_t q = e + kAhead; q < std::min(end, e + kAhead + cnt); ++q) __builtin_prefetch(lut + (u[q] < 0 ? ~u[q] : u[q]));
     };
-    for_tasks([&](int ti) {
-      SampleTask &tk = tasks[ti];
-      const int32_t *lut = bd.local_of[ctx->rel_src[tk.r]].data();
-      for (int64_t row = tk.row; row < tk.row + (tk.i1 - tk.i0); ++row) {
-        ahead(tk, lut, row);
-        int32_t *u = esrc + row * fanout;
-        for (int c = 0; c < ecnt[row]; ++c)
-          if (lut[u[c]] == (int32_t)(-2 - row)) {
-            bool again = false;   // a vertex may be a row's neighbour twice
-            for (int q = 0; q < c; ++q) again |= u[q] == ~u[c];
-            if (again) continue;
-            u[c] = ~u[c];         // marked (vertex ids are not negative)
-            ++tk.fresh;
-          }
-      }
-    });
+    if (st == HGNN_OK)
+      for_tasks([&](SampleTask &tk, SampleSlice &sl) {
+        const int32_t *lut = bd.local_of[ctx->rel_src[tk.r]].data();
+        int32_t *u = sl.src.p + tk.at;
+        int64_t e = 0;
+        for (int64_t row = tk.row; row < tk.row + (tk.i1 - tk.i0); e += ecnt[row++]) {
+          ahead(lut, u, tk.edges, e, ecnt[row]);
+          int32_t *w = u + e;
+          for (int c = 0; c < ecnt[row]; ++c)
+            if (lut[w[c]] == (int32_t)(-2 - row)) {
+              bool again = false;   // a vertex may be a row's neighbour twice
+              for (int q = 0; q < c; ++q) again |= w[q] == ~w[c];
+              if (again) continue;
+              w[c] = ~w[c];         // marked (vertex ids are not negative)
+              ++tk.fresh;
+            }
+        }
+      });
     tm.lap("count");
     int64_t size[kMaxT], ne = 0;
     for (int t = 0; t < T; ++t) size[t] = (int64_t)src[t].size();
-    for (int ti = 0; ti < nt; ++ti) {   // from counts to starts
-      SampleTask &tk = tasks[ti];
-      const int64_t e = tk.edges, f = tk.fresh;
-      tk.edges = ne;
-      tk.fresh = size[ctx->rel_src[tk.r]];
-      ne += e;
-      size[ctx->rel_src[tk.r]] += f;
+    for (SampleTask &tk : tasks) {
+      tk.first_edge = ne;
+      tk.first_fresh = size[ctx->rel_src[tk.r]];
+      ne += tk.edges;
+      size[ctx->rel_src[tk.r]] += tk.fresh;
     }
-    for (int t = 0; t < T; ++t)
+    for (int t = 0; t < T && st == HGNN_OK; ++t)
       if (size[t] > (int64_t)INT32_MAX - 1) {
         msg = "more than 2^31-2 source rows of one type";
         st = HGNN_EOVERFLOW;
@@ -297,48 +302,38 @@ hgnn_status run_sample_job(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g, std::strin
       st = HGNN_ENOMEM;
     }
     if (st != HGNN_OK) {   // the claims go; the destinations' entries are reset below
-      for (int ti = 0; ti < nt; ++ti) {
-        const SampleTask &tk = tasks[ti];
-        int32_t *lut = bd.local_of[ctx->rel_src[tk.r]].data();
-        for (int64_t row = tk.row; row < tk.row + (tk.i1 - tk.i0); ++row)
-          for (int c = 0; c < ecnt[row]; ++c) {
-            const int32_t u = esrc[row * fanout + c], v = u < 0 ? ~u : u;
-            if (lut[v] < 0) lut[v] = -1;
-          }
-      }
+      for (int t = 0; t < T; ++t)
+        for (int32_t &v : bd.local_of[t]) v = std::max(v, -1);
     } else {
       for (int t = 0; t < T; ++t) src[t].resize((size_t)size[t]);
       std::vector<int32_t> &rp = job.row_ptr[l];
       rp.resize((size_t)rows + 1);
       rp[rows] = (int32_t)ne;
-      for_tasks([&](int ti) {
-        const SampleTask &tk = tasks[ti];
+      for_tasks([&](SampleTask &tk, SampleSlice &sl) {
         const int s = ctx->rel_src[tk.r];
         int32_t *lut = bd.local_of[s].data();
-        int64_t *sl = src[s].data(), next = tk.fresh;
-        for (int64_t row = tk.row; row < tk.row + (tk.i1 - tk.i0); ++row) {
-          const int32_t *u = esrc + row * fanout;
-          for (int c = 0; c < ecnt[row]; ++c) {
-            if (u[c] >= 0) continue;
-            sl[next] = ~u[c];
-            lut[~u[c]] = (int32_t)next++;   // this row's alone: no other task reads or writes the entry in this pass
-          }
+        const int32_t *u = sl.src.p + tk.at;
+        int64_t *ids = src[s].data(), next = tk.first_fresh;
+        for (int64_t e = 0; e < tk.edges; ++e) {
+          if (u[e] >= 0) continue;
+          ids[next] = ~u[e];
+          lut[~u[e]] = (int32_t)next++;   // this task's alone: no other reads or writes the entry in this pass
         }
       });
       tm.lap("number");
       int64_t *pes = es.p, *ped = es.p + ne, *peid = eid.p;
-      for_tasks([&](int ti) {
-        const SampleTask &tk = tasks[ti];
-        const int32_t *lut = bd.local_of[ctx->rel_src[tk.r]].data();
-        int64_t e = tk.edges, next = tk.fresh;
+      for_tasks([&](SampleTask &tk, SampleSlice &sl) {
+        const int32_t *lut = bd.local_of[ctx->rel_src[tk.r]].data(), *u = sl.src.p + tk.at;
+        const int64_t *p = sl.pos.p + tk.at;
+        int64_t e = 0, to = tk.first_edge, next = tk.first_fresh;
         for (int32_t i = tk.i0; i < tk.i1; ++i) {
-          const int64_t row = tk.row + (i - tk.i0), at = row * fanout;
-          ahead(tk, lut, row);
-          rp[row] = (int32_t)e;
-          for (int c = 0; c < ecnt[row]; ++c, ++e) {
-            pes[e] = esrc[at + c] < 0 ? next++ : lut[esrc[at + c]];
-            ped[e] = i;
-            peid[e] = epos[at + c];
+          const int64_t row = tk.row + (i - tk.i0);
+          ahead(lut, u, tk.edges, e, ecnt[row]);
+          rp[row] = (int32_t)to;
+          for (int c = 0; c < ecnt[row]; ++c, ++e, ++to) {
+            pes[to] = u[e] < 0 ? next++ : lut[u[e]];
+            ped[to] = i;
+            peid[to] = p[e];
           }
         }
       });

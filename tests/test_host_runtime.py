@@ -151,3 +151,45 @@ def test_of_several_bad_layers_the_first_is_reported():
             gr.wait()
         gr.release()
     ctx.close()
+
+
+SPARSE = '''
+import re, resource, sys
+import numpy as np
+sys.path.insert(0, %r)
+from paper_2408_08490_amd import binding as B
+R, N, E = 32, 65536, 3000
+rng = np.random.default_rng(5)
+indptr, nbr = [], []
+for r in range(R):
+    dst = np.sort(rng.integers(0, N, E))
+    indptr.append(np.concatenate([[0], np.cumsum(np.bincount(dst, minlength=N))]).astype(np.int64))
+    nbr.append(rng.integers(0, N, E).astype(np.int32))
+off = np.arange(R + 1, dtype=np.int64) * E
+
+def sample(threads, targets):
+    ctx = B.Context([0] * R, [0] * R, 1, device=-1, host_threads=threads)
+    s = ctx.hgnn_sampler_create([N], indptr, nbr, off)
+    gr = ctx.hgnn_sample_and_build(s, 0, targets, [64], 9, None)
+    gr.wait()
+    res = [gr.ids()[1][0], gr.host_view(0)["rowptr"], gr.host_view(0)["colidx"], gr.minibatch_view(0)["edge_id"]]
+    gr.release()
+    s.close()
+    ctx.close()
+    return res
+
+sample(6, np.arange(64))
+targets = np.arange(N)
+want = sample(1, targets)
+data = int(re.search(r"VmData:\\s+(\\d+) kB", open("/proc/self/status").read()).group(1)) << 10
+resource.setrlimit(resource.RLIMIT_DATA, (data + (600 << 20),) * 2)     # 2.1 million merged rows of at most 64 edges, 96,000 edges
+got = sample(6, targets)
+print("sparse ok" if all(np.array_equal(a, b) for a, b in zip(got, want)) else "different")
+'''
+
+
+def test_sampling_on_several_threads_takes_room_for_the_edges_that_are_kept():
+    """Many relations with an edge for few of their destinations, at the largest fan-out: as the one-thread path, the
+    sampler's scratch goes with the edges and not with destinations times fan-out (1.6 GB here)."""
+    run = subprocess.run([sys.executable, "-c", SPARSE % ROOT], capture_output=True, text=True, timeout=120)
+    assert run.returncode == 0 and "sparse ok" in run.stdout, run.stdout + run.stderr
