@@ -159,7 +159,8 @@ class Crew {
   void submit(std::function<void()> task);
   // whether the calling thread's task should go to the end of the list: another one waits, or the thread is to end
   bool wanted() const { return waiting_tasks_.load(std::memory_order_relaxed) > 0 || index() >= target_.load(std::memory_order_relaxed); }
-  // Runs fn(chunk) for chunk in [0, nchunks) on the caller and at most `width` - 1 others; returns when all are done.
+  // Runs fn(chunk) for chunk in [0, nchunks) on the caller and at most `width` - 1 others; returns when all are done, and
+  // throws std::bad_alloc if one of them threw.
   // Up to 64 chunks, a thread first looks at those that bear its number: phases that deal the same slices then meet the
   // data they wrote a phase earlier in their own caches.
   void parallel_for(int nchunks, int width, const std::function<void(int)> &fn);
@@ -174,6 +175,7 @@ class Crew {
     const std::function<void(int)> *fn;
     int n, width;
     std::atomic<int> next{0}, done{0}, joined{0};
+    std::atomic<bool> failed{false};
     std::atomic<uint64_t> taken{0};   // chunks taken, for n <= 64 (`next` counts them)
   };
   struct alignas(64) Slot {

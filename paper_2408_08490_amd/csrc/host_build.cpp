@@ -70,11 +70,16 @@ void Crew::leave(int threads, bool eager) {
 static thread_local int tl_crew_index = 0;
 int Crew::index() { return tl_crew_index; }
 void Crew::drain(Job &j) {
-  if (j.n > 64) {
-    for (int i; (i = j.next.fetch_add(1, std::memory_order_relaxed)) < j.n;) {
+  auto run_chunk = [&](int i) {
+    try {
       (*j.fn)(i);
-      j.done.fetch_add(1, std::memory_order_release);
+    } catch (...) {   // out of memory: the owner throws it on
+      j.failed.store(true, std::memory_order_relaxed);
     }
+    j.done.fetch_add(1, std::memory_order_release);
+  };
+  if (j.n > 64) {
+    for (int i; (i = j.next.fetch_add(1, std::memory_order_relaxed)) < j.n;) run_chunk(i);
     return;
   }
   const int step = std::max(1, target_.load(std::memory_order_relaxed));
@@ -82,8 +87,7 @@ void Crew::drain(Job &j) {
     const uint64_t bit = (uint64_t)1 << i;
     if ((j.taken.load(std::memory_order_relaxed) & bit) || (j.taken.fetch_or(bit, std::memory_order_relaxed) & bit)) return;
     j.next.fetch_add(1, std::memory_order_relaxed);
-    (*j.fn)(i);
-    j.done.fetch_add(1, std::memory_order_release);
+    run_chunk(i);
   };
   for (int i = tl_crew_index; i < j.n; i += step) take(i);
   for (int k = 1; k <= j.n && j.next.load(std::memory_order_relaxed) < j.n; ++k) take((tl_crew_index + k) % j.n);
@@ -183,11 +187,13 @@ void Crew::parallel_for(int nchunks, int width, const std::function<void(int)> &
     }
   };
   wait([&] { return j.done.load(std::memory_order_acquire) >= nchunks; });
-  if (!mine) return;
-  active_.fetch_sub(1);
-  mine->job.store(nullptr);
-  wait([&] { return mine->users.load() == 0; });   // those still on their way out of this job: the slot takes no other before
-  mine->taken.store(false);
+  if (mine) {
+    active_.fetch_sub(1);
+    mine->job.store(nullptr);
+    wait([&] { return mine->users.load() == 0; });   // those still on their way out of this job: the slot takes no other before
+    mine->taken.store(false);
+  }
+  if (j.failed.load(std::memory_order_relaxed)) throw std::bad_alloc();
 }
 
 // ------------------------------------------------------------------------------------------
@@ -634,10 +640,8 @@ static bool build_layer(hgnn_ctx *ctx, ThreadPool &pool, LayerScratch &bd, hgnn_
   return true;
 }
 
-void build_graph_job(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g) {
-  BuildError err;
-  bool ok = true;
-  PhaseTimer tm;
+// Samples (where asked for), plans and builds; false: `err` or the first failed layer's error says why.
+static bool sample_and_build(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g, BuildError &err, BuildError *layer_err, PhaseTimer &tm) {
   if (g->job) {  // sample first; only then are the sizes known that the block is laid out for
     std::string m;
     hgnn_status st = run_sample_job(ctx, bd, g, m);
@@ -652,29 +656,37 @@ void build_graph_job(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g) {
     tm.lap("sample and plan");
     if (st != HGNN_OK) {
       err.set(st, m);
-      ok = false;
-    } else {
-      for (int t = 0; t < ctx->T; ++t) {
-        const std::vector<int64_t> &ids = g->job->ids[t];
-        const int n = (int)std::min<size_t>((size_t)bd.pool->size(), (ids.size() + 8191) / 8192);
-        bd.pool->parallel_for(n, [&](int i) {
-          const size_t a = ids.size() * i / n, b = ids.size() * (i + 1) / n;
-          std::memcpy(g->slab.host + g->o_ids[t] + 2 * a, ids.data() + a, (b - a) * sizeof(int64_t));
-        });
-      }
+      return false;
+    }
+    for (int t = 0; t < ctx->T; ++t) {
+      const std::vector<int64_t> &ids = g->job->ids[t];
+      const int n = (int)std::min<size_t>((size_t)bd.pool->size(), (ids.size() + 8191) / 8192);
+      bd.pool->parallel_for(n, [&](int i) {
+        const size_t a = ids.size() * i / n, b = ids.size() * (i + 1) / n;
+        std::memcpy(g->slab.host + g->o_ids[t] + 2 * a, ids.data() + a, (b - a) * sizeof(int64_t));
+      });
     }
   }
-  BuildError layer_err[kMaxLayers];
-  const BuildError *first = &err;
-  if (ok) {  // the layers side by side: a small layer's phases are shorter than what it takes to start them
-    bd.pool->parallel_for(g->num_layers, [&](int l) { (void)build_layer(ctx, *bd.pool, bd.layer[l], g, l, layer_err[l]); });
-    for (int l = g->num_layers - 1; l >= 0; --l)
-      if (layer_err[l].failed.load()) {   // of several bad layers the first is reported, whichever was done first
-        first = &layer_err[l];
-        ok = false;
-      }
-  }
+  // the layers side by side: a small layer's phases are shorter than what it takes to start them
+  bd.pool->parallel_for(g->num_layers, [&](int l) { (void)build_layer(ctx, *bd.pool, bd.layer[l], g, l, layer_err[l]); });
+  bool ok = true;
+  for (int l = 0; l < g->num_layers; ++l) ok = ok && !layer_err[l].failed.load();
   tm.lap("all layers");
+  return ok;
+}
+
+void build_graph_job(hgnn_ctx *ctx, Builder &bd, hgnn_graph *g) {
+  BuildError err, layer_err[kMaxLayers];
+  bool ok = false;
+  PhaseTimer tm;
+  try {
+    ok = sample_and_build(ctx, bd, g, err, layer_err, tm);
+  } catch (const std::exception &) {   // a scratch array that could not grow
+    err.set(HGNN_ENOMEM, "out of host memory");
+    for (std::vector<int32_t> &t : bd.local_of) t.clear();   // the sampler may have left marks: it makes them anew
+  }
+  const BuildError *first = &err;   // of several bad layers the first is reported, whichever was done first
+  for (int l = 0; l < g->num_layers && !first->failed.load(); ++l) first = &layer_err[l];
   int status = ok ? HGNN_OK : first->status;
   std::string msg = first->msg;
   if (ok && ctx->device >= 0) {

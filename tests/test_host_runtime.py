@@ -193,3 +193,9 @@ def test_sampling_on_several_threads_takes_room_for_the_edges_that_are_kept():
     sampler's scratch goes with the edges and not with destinations times fan-out (1.6 GB here)."""
     run = subprocess.run([sys.executable, "-c", SPARSE % ROOT], capture_output=True, text=True, timeout=120)
     assert run.returncode == 0 and "sparse ok" in run.stdout, run.stdout + run.stderr
+
+
+def test_a_failed_allocation_on_a_host_thread_is_an_error_of_that_graph(tmp_path):
+    """Scratch that cannot grow, on one thread and on several, sampled or from lists: HGNN_ENOMEM, and the context goes on."""
+    run = subprocess.run([_compile(tmp_path, "out_of_memory")], capture_output=True, text=True, timeout=60)
+    assert run.returncode == 0 and "out of memory ok" in run.stdout, run.stdout + run.stderr
