@@ -145,8 +145,9 @@ struct Slab {  // pinned host block + device block of equal capacity
 // The host threads of the runtime: one crew for the process, shared by its contexts (with threads of their own, several
 // contexts keep more of them looking for work than the machine has cores, and every one's are asleep when its turn comes).
 // The crew has as many threads as the live context that asked for most; the last context to go takes them with it.
-// A thread builds a whole graph or takes chunks of the parallel phases of others' builds.  A phase lasts some 20 us, so
-// the threads look for work in a loop for a while before they sleep: waking one costs more than a phase.
+// A thread builds a whole graph or takes chunks of the parallel phases of others' builds.  A phase lasts some 20 us, and
+// waking a thread costs more than that: while a graph is being built the threads look for work in a loop.  Between builds
+// they sleep (a loop of one build and one step of 0.6 ms: 10 cores busy instead of 16, 0.60 against 0.58 ms per pass).
 class Crew {
  public:
   static Crew &get();        // the process's; a forked child has its own, without threads until a context joins it
@@ -167,7 +168,8 @@ class Crew {
   // whether it pays to look for a build's end rather than sleep: not while every thread is at work, which would leave the
   // core to one of them
   bool look() const { return eager_.load(std::memory_order_relaxed) > 0 && at_work_.load(std::memory_order_relaxed) < target_.load(std::memory_order_relaxed); }
-  static constexpr int kSpinUs = 500;   // how long a thread looks for work before it sleeps
+  static constexpr int kSpinUs = 500;   // how long a thread looks for work before it sleeps while a graph is being built
+  static constexpr int kTailUs = 50;    // and when none is
 
  private:
   static constexpr int kSlots = 32;
@@ -190,7 +192,7 @@ class Crew {
   Slot slots_[kSlots];
   std::atomic<int> active_{0}, target_{0}, sleepers_{0}, waiting_tasks_{0}, at_work_{0}, eager_{0};   // at_work_: threads in a task
   std::mutex m_, size_m_;
-  std::condition_variable cv_;
+  std::atomic<uint32_t> calls_{0};            // what sleeping threads wait to see changed
   std::deque<std::function<void()>> tasks_;   // m_
   std::vector<int> sizes_;                    // threads asked for by each live context (size_m_)
   std::vector<std::thread> threads_;          // size_m_

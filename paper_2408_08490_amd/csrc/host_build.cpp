@@ -57,11 +57,9 @@ void Crew::leave(int threads, bool eager) {
   std::lock_guard<std::mutex> lk(size_m_);
   sizes_.erase(std::find(sizes_.begin(), sizes_.end(), threads));
   const int most = sizes_.empty() ? 0 : *std::max_element(sizes_.begin(), sizes_.end());
-  {
-    std::lock_guard<std::mutex> lk2(m_);
-    target_.store(most);
-  }
-  cv_.notify_all();
+  target_.store(most);
+  calls_.fetch_add(1);
+  calls_.notify_all();
   while ((int)threads_.size() > most) {
     threads_.back().join();
     threads_.pop_back();
@@ -138,21 +136,22 @@ void Crew::run(int index) {
     if (eager_.load(std::memory_order_relaxed) > 0) {
       cpu_relax();
       if (++spins % 64) continue;
-      if (std::chrono::steady_clock::now() - idle < std::chrono::microseconds(kSpinUs)) continue;
+      const auto idle_for = std::chrono::steady_clock::now() - idle;
+      if (idle_for < std::chrono::microseconds(at_work_.load(std::memory_order_relaxed) > 0 ? kSpinUs : kTailUs)) continue;
     }
-    {
-      std::unique_lock<std::mutex> lk(m_);
-      sleepers_.fetch_add(1);        // work posted from here on notifies; work posted before shows in the counters
-      cv_.wait(lk, [&] { return index >= target_.load() || active_.load() > 0 || waiting_tasks_.load() > 0; });
-      sleepers_.fetch_sub(1);
-    }
+    // A sleeper looks once more after it has said so; work posted from there on changes the call it sleeps on.  No lock is
+    // taken on the way out of the sleep: fifteen threads woken at once would pass it on one by one.
+    const uint32_t call = calls_.load();
+    sleepers_.fetch_add(1);
+    if (index < target_.load() && active_.load() == 0 && waiting_tasks_.load() == 0) calls_.wait(call);
+    sleepers_.fetch_sub(1);
     idle = std::chrono::steady_clock::now();
   }
 }
 void Crew::wake_all() {
   if (sleepers_.load() == 0) return;
-  { std::lock_guard<std::mutex> lk(m_); }
-  cv_.notify_all();
+  calls_.fetch_add(1);
+  calls_.notify_all();
 }
 void Crew::submit(std::function<void()> task) {
   {
@@ -160,8 +159,12 @@ void Crew::submit(std::function<void()> task) {
     tasks_.push_back(std::move(task));
     waiting_tasks_.fetch_add(1);
   }
-  if (eager_.load() > 0) wake_all();   // the task's phases follow at once
-  else cv_.notify_one();
+  if (eager_.load() > 0) {
+    wake_all();   // the task's phases follow at once
+  } else if (sleepers_.load() > 0) {
+    calls_.fetch_add(1);
+    calls_.notify_one();
+  }
 }
 void Crew::parallel_for(int nchunks, int width, const std::function<void(int)> &fn) {
   Job j;

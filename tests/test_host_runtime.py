@@ -199,3 +199,24 @@ def test_a_failed_allocation_on_a_host_thread_is_an_error_of_that_graph(tmp_path
     """Scratch that cannot grow, on one thread and on several, sampled or from lists: HGNN_ENOMEM, and the context goes on."""
     run = subprocess.run([_compile(tmp_path, "out_of_memory")], capture_output=True, text=True, timeout=60)
     assert run.returncode == 0 and "out of memory ok" in run.stdout, run.stdout + run.stderr
+
+
+def test_the_crew_sleeps_between_builds():
+    """A loop of a small build and 0.4 ms of something else keeps the crew's seven threads busy while it builds, not for
+    good."""
+    context, queue = _contexts()
+    ctx = context(8, 1)
+
+    def step():
+        g = queue(ctx, 1)[0]
+        g.wait()
+        g.release()
+        time.sleep(4e-4)
+    for _ in range(20):
+        step()
+    t, c = time.perf_counter(), time.process_time()
+    for _ in range(500):
+        step()
+    busy = (time.process_time() - c) / (time.perf_counter() - t)
+    ctx.close()
+    assert busy < 4.5, busy
