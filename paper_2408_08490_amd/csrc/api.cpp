@@ -806,6 +806,14 @@ hgnn_status hgnn_layer_workspace_bytes(hgnn_ctx *ctx, hgnn_graph *g, int32_t lay
 // Whether there is an aggregation launch (which carries the weight transposes as its first blocks).
 static bool transposes_ride(const Plan &pl) { return pl.dev.rows > 0; }
 
+// Bit r: relation r has an edge in the layer.
+static void live_relations(const hgnn_ctx *ctx, const hgnn_graph *g, int32_t layer, uint32_t (&live)[kMaxR / 32]) {
+  std::memset(live, 0, sizeof(live));
+  const int32_t *reo = g->slab.host + g->L[layer].o_rel_edge_off;
+  for (int r = 0; r < ctx->R; ++r)
+    if (reo[r + 1] > reo[r]) live[r >> 5] |= 1u << (r & 31);
+}
+
 static hgnn_status fwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_t layer, const hgnn_layer_params *p,
                               const void *x, void *h, void *saved, size_t saved_bytes, void *scratch, size_t scratch_bytes,
                               bool naive, int32_t *launches, void *feature_cat = nullptr, size_t feature_cat_bytes = 0,
@@ -859,12 +867,8 @@ static hgnn_status fwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
   SegTab tl;
   const int tile_mn = fwd_tiles(pl, tl, !naive);
   const int R = ctx->R, T = ctx->T;
-  uint32_t live[kMaxR / 32] = {0};
-  {
-    const int32_t *reo = g->slab.host + g->L[layer].o_rel_edge_off;
-    for (int r = 0; r < R; ++r)
-      if (reo[r + 1] > reo[r]) live[r >> 5] |= 1u << (r & 31);
-  }
+  uint32_t live[kMaxR / 32];
+  live_relations(ctx, g, layer, live);
   // The weight transposes ride in the aggregation launch (as its first blocks) where there is one; otherwise they are a
   // launch of their own.
   TransposeJobs tj;
@@ -906,19 +910,22 @@ static hgnn_status fwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
     }
     {
       Probe pb(ctx, HGNN_K_GEMM_FWD, layer, !static_area);
-      bool done = false;
+      int kernels = 0;
       if (ctx->dtype == HGNN_BF16 && !ctx->legacy_gemm) {
-        done = launch_gemm2_fwd(s, pl.tt, pl.rt, pl.pt, pl.wt, live, pl.H, p->relu, x, saved, zlo, wtb, h, &st);
-        if (done && st != HGNN_OK) return st;
+        kernels = launch_gemm2_fwd(s, pl.tt, pl.rt, pl.pt, pl.wt, live, pl.H, p->relu, x, saved, zlo, wtb, h, &st);
+        if (kernels && st != HGNN_OK) return st;
       }
-      if (!done && optional_launchers().gemm_fwd_direct) {
-        done = optional_launchers().gemm_fwd_direct(s, ctx->dtype, pl.tt, pl.rt, pl.pt, pl.wt, live, pl.H, p->relu, x, saved, zlo, wtb, h,
-                                                    (float *)(sc + pl.off_part));
-        if (done) HGNN_HIP(hipGetLastError());
+      if (!kernels && optional_launchers().gemm_fwd_direct) {
+        kernels = optional_launchers().gemm_fwd_direct(s, ctx->dtype, pl.tt, pl.rt, pl.pt, pl.wt, live, pl.H, p->relu, x, saved, zlo, wtb, h,
+                                                       (float *)(sc + pl.off_part), false);
+        if (kernels) HGNN_HIP(hipGetLastError());
       }
-      if (!done && (st = launch_gemm_fwd(s, ctx->dtype, pl.dev, pl.tt, pl.rt, pl.pt, pl.wt, tl, live, pl.H, p->relu, x, saved, zlo, wtb, h, -1, nullptr, tile_mn)) != HGNN_OK) return st;
+      if (!kernels) {
+        if ((st = launch_gemm_fwd(s, ctx->dtype, pl.dev, pl.tt, pl.rt, pl.pt, pl.wt, tl, live, pl.H, p->relu, x, saved, zlo, wtb, h, -1, nullptr, tile_mn)) != HGNN_OK) return st;
+        kernels = tl.tile_off[T] > 0;
+      }
+      n += kernels;
     }
-    if (tl.tile_off[T] > 0) ++n;
   } else {
     // the un-merged launch structure: one aggregation and one projection launch per relation, one root
     // projection and one bias/activation launch per vertex type
@@ -1304,7 +1311,17 @@ hgnn_status hgnn_layer_launch_count(hgnn_ctx *ctx, hgnn_graph *g, int32_t layer,
   Plan pl;
   hgnn_status st = make_plan(ctx, g, layer, p, pl, true);
   if (st != HGNN_OK) return st;
-  if (fwd_launches) *fwd_launches = (transposes_ride(pl) ? 0 : 1) + (pl.dev.rows > 0) + (pl.total_dst > 0);
+  if (fwd_launches) {
+    int gemm = 0;
+    if (optional_launchers().gemm_fwd_direct && (ctx->dtype != HGNN_BF16 || ctx->legacy_gemm)) {
+      uint32_t live[kMaxR / 32];
+      live_relations(ctx, g, layer, live);
+      const void *zlo = ctx->dtype == HGNN_BF16 && p->relu ? &pl : nullptr;   // whether there is one is all that counts
+      gemm = optional_launchers().gemm_fwd_direct(nullptr, ctx->dtype, pl.tt, pl.rt, pl.pt, pl.wt, live, pl.H, p->relu, nullptr, nullptr,
+                                                  zlo, nullptr, nullptr, nullptr, true);
+    }
+    *fwd_launches = (transposes_ride(pl) ? 0 : 1) + (pl.dev.rows > 0) + (gemm ? gemm : pl.total_dst > 0);
+  }
   if (bwd_launches) {
     // zero grads + ReLU mask + bias partial sums (one launch), dW and dA GEMMs + bias sums (one launch), transposed
     // aggregation (+ long-row pass); without destination rows only the zeroing

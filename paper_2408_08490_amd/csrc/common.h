@@ -443,10 +443,11 @@ constexpr int kDirectReluTiles = 64;                     // the same in fp32 wit
 constexpr int kDirectUnits = 512 + kDirectTiles;         // its most (tile, split) pairs: two blocks per compute unit, rounded up per tile
 constexpr size_t kDirectPartBytes = (size_t)kDirectUnits * 64 * 64 * 4;   // their partial tiles
 struct OptionalLaunchers {
-  // forward GEMM with the reduction split over blocks and wavefronts; false: not for this launch (nothing was launched)
-  bool (*gemm_fwd_direct)(hipStream_t s, int dtype, const TypeTab &tt, const RelTab &rt, const PtrTab &pt, const WtTab &wt,
+  // forward GEMM with the reduction split over blocks and wavefronts: the kernels launched (with count_only: that would be),
+  // 0 if it is not for this launch
+  int (*gemm_fwd_direct)(hipStream_t s, int dtype, const TypeTab &tt, const RelTab &rt, const PtrTab &pt, const WtTab &wt,
                           const uint32_t *live_mask, int H, int relu, const void *x, const void *z, const void *zlo,
-                          const void *wt_buf, void *h, float *part) = nullptr;
+                          const void *wt_buf, void *h, float *part, bool count_only) = nullptr;
 };
 OptionalLaunchers &optional_launchers();  // api.cpp
 hgnn_status launch_bias_act(hipStream_t s, int dtype, const TypeTab &tt, const PtrTab &pt, int H, int relu,

@@ -229,16 +229,16 @@ __global__ void __launch_bounds__(256) gemm_fwd_direct_sum_kernel(DirectArgs arg
 }
 
 // For launches of fewer than kDirectTiles tiles of 64x64 (a quarter of that in bf16); `part` holds kDirectPartBytes.
-// false: not for this launch.  Beyond the line a tile per block keeps the compute units busy and the staged kernel, whose
+// Returns the kernels that it launches (with count_only: that it would launch), 0: not for this launch.  Beyond the line a tile per block keeps the compute units busy and the staged kernel, whose
 // four wavefronts share a tile's operands, needs half the operand traffic; the fp32 products are 16 times as long, so that
 // the line lies further out.  Both kernels of this file together against the staged one, in us (tiles: before -> now):
 //   fp32  16: 43 -> 16, 27 -> 16 (104 relations)   96: 41 -> 23   312: 54 -> 48      700: 47 -> 52 (not taken)
 //   bf16  72: 43 -> 22 (108 relations)   16: 24 -> 16   24: 15 -> 14   96: 24 -> 21   230: 15 -> 27 (not taken)
 // In fp32 with a ReLU the line is at 64 tiles: a sum formed in another order gives units within a rounding of zero the other
 // decision (three of ten million), which moves a whole term of the gradients; up to 64 tiles there is next to never one.
-static bool launch_gemm_fwd_direct(hipStream_t s, int dtype, const TypeTab &tt, const RelTab &rt, const PtrTab &pt, const WtTab &wt,
+static int launch_gemm_fwd_direct(hipStream_t s, int dtype, const TypeTab &tt, const RelTab &rt, const PtrTab &pt, const WtTab &wt,
                                    const uint32_t *live_mask, int H, int relu, const void *x, const void *z, const void *zlo,
-                                   const void *wt_buf, void *h, float *part) {
+                                   const void *wt_buf, void *h, float *part, bool count_only) {
   const int T = tt.num_types, R = rt.num_rels, ks = 2 * (dtype == HGNN_BF16 ? Direct<bf16>::KG : Direct<float>::KG);
   const int es = dtype == HGNN_BF16 ? 2 : 4;
   DirectArgs da;
@@ -248,7 +248,7 @@ static bool launch_gemm_fwd_direct(hipStream_t s, int dtype, const TypeTab &tt, 
   da.tile_off[0] = 0;
   for (int d = 0; d < T; ++d) da.tile_off[d + 1] = da.tile_off[d] + ((tt.n_dst[d] + 63) / 64) * ((H + 63) / 64);
   const int tiles = da.tile_off[T];
-  if (tiles == 0 || tiles >= (dtype == HGNN_BF16 ? kDirectTiles / 4 : relu ? kDirectReluTiles : kDirectTiles)) return false;
+  if (tiles == 0 || tiles >= (dtype == HGNN_BF16 ? kDirectTiles / 4 : relu ? kDirectReluTiles : kDirectTiles)) return 0;
   int n = 0;
   int64_t work = 0;   // K-steps over all tiles
   for (int d = 0; d < T; ++d) {
@@ -262,8 +262,8 @@ static bool launch_gemm_fwd_direct(hipStream_t s, int dtype, const TypeTab &tt, 
     };
     if (tt.n_dst[d] > 0) {
       for (int r = 0; r < R; ++r)
-        if (rt.dst[r] == d && ((live_mask[r >> 5] >> (r & 31)) & 1u) && !put(rt.z_off4[r], wt.rel4[r], tt.in_dim[rt.src[r]], false)) return false;
-      if (pt.w_root[d] && !put((uint32_t)(tt.xroot_off[d] / 4), wt.root4[d], tt.in_dim[d], true)) return false;
+        if (rt.dst[r] == d && ((live_mask[r >> 5] >> (r & 31)) & 1u) && !put(rt.z_off4[r], wt.rel4[r], tt.in_dim[rt.src[r]], false)) return 0;
+      if (pt.w_root[d] && !put((uint32_t)(tt.xroot_off[d] / 4), wt.root4[d], tt.in_dim[d], true)) return 0;
     }
     da.n_dst[d] = tt.n_dst[d];
     da.out_row[d] = tt.out_row_off[d];
@@ -286,16 +286,18 @@ static bool launch_gemm_fwd_direct(hipStream_t s, int dtype, const TypeTab &tt, 
     if (td > 0) max_splits = std::max(max_splits, (int)da.splits[d]);
   }
   da.unit_off[T] = units;
-  if (units > kDirectUnits) return false;
+  if (units > kDirectUnits) return 0;
+  const int launches = max_splits > 1 ? 2 : 1;
+  if (count_only) return launches;
 #define HGNN_DIRECT(TY)                                                                                                           \
   {                                                                                                                               \
     HGNN_LAUNCH(gemm_fwd_direct_kernel<TY>, dim3(units), dim3(64 * kDirW), 0, s, da, (const TY *)x, (const TY *)z, (const TY *)zlo, \
                 (const TY *)wt_buf, (TY *)h, part);                                                                                \
-    if (max_splits > 1) HGNN_LAUNCH(gemm_fwd_direct_sum_kernel<TY>, dim3(tiles * 4), dim3(256), 0, s, da, part, (TY *)h);           \
+    if (launches > 1) HGNN_LAUNCH(gemm_fwd_direct_sum_kernel<TY>, dim3(tiles * 4), dim3(256), 0, s, da, part, (TY *)h);             \
   }
   if (dtype == HGNN_BF16) HGNN_DIRECT(bf16) else HGNN_DIRECT(float)
 #undef HGNN_DIRECT
-  return true;
+  return launches;
 }
 
 static const bool registered = [] {
