@@ -928,7 +928,8 @@ static hgnn_status fwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
     }
   } else {
     // the un-merged launch structure: one aggregation and one projection launch per relation, one root
-    // projection and one bias/activation launch per vertex type
+    // projection and one bias/activation launch per vertex type (the projections are told of the activation that follows:
+    // see gemm_fwd_kernel on sums that go through a ReLU)
     float *acc32 = (float *)(sc + pl.off_acc32);
     if ((st = launch_fill_zero(s, acc32, (size_t)pl.total_dst * pl.H * 4)) != HGNN_OK) return st;
     ++n;
@@ -944,7 +945,7 @@ static hgnn_status fwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
       const int d = ctx->rel_dst[r];
       for (int t = 0; t < T; ++t)
         one.tile_off[t + 1] = one.tile_off[t] + (t == d ? tl.tile_off[t + 1] - tl.tile_off[t] : 0);
-      if ((st = launch_gemm_fwd(s, ctx->dtype, pl.dev, pl.tt, pl.rt, pl.pt, pl.wt, one, live, pl.H, 0, x, saved, zlo, wtb, h, r, acc32)) != HGNN_OK) return st;
+      if ((st = launch_gemm_fwd(s, ctx->dtype, pl.dev, pl.tt, pl.rt, pl.pt, pl.wt, one, live, pl.H, p->relu, x, saved, zlo, wtb, h, r, acc32)) != HGNN_OK) return st;
       ++n;
     }
     for (int t = 0; t < T; ++t) {
@@ -955,7 +956,7 @@ static hgnn_status fwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
         one.num_segs = T;
         for (int u = 0; u < T; ++u)
           one.tile_off[u + 1] = one.tile_off[u] + (u == t ? tl.tile_off[u + 1] - tl.tile_off[u] : 0);
-        if ((st = launch_gemm_fwd(s, ctx->dtype, pl.dev, pl.tt, pl.rt, pl.pt, pl.wt, one, live, pl.H, 0, x, saved, zlo, wtb, h, R + t, acc32)) != HGNN_OK) return st;
+        if ((st = launch_gemm_fwd(s, ctx->dtype, pl.dev, pl.tt, pl.rt, pl.pt, pl.wt, one, live, pl.H, p->relu, x, saved, zlo, wtb, h, R + t, acc32)) != HGNN_OK) return st;
         ++n;
       }
       if ((st = launch_bias_act(s, ctx->dtype, pl.tt, pl.pt, pl.H, p->relu, t, acc32, h)) != HGNN_OK) return st;

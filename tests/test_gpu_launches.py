@@ -1,4 +1,6 @@
-"""What the layer calls enqueue: their kernels counted in a captured graph, against hgnn_layer_launch_count."""
+"""What the layer calls enqueue: their kernels counted in a captured graph, against hgnn_layer_launch_count; and the
+per-relation launch structure against the merged one where both form the same sums."""
+import ctypes
 
 import numpy as np
 import pytest
@@ -56,5 +58,31 @@ def test_forward_launches_counted_in_a_captured_graph(index, scale, batch):
             model.run(bt, backward=False)
             torch.cuda.synchronize()
     assert [c for *_x, c, s in graphs] == [s for *_x, c, s in graphs]
+    bt.graph.release()
+    model.close()
+
+
+def test_per_relation_launches_form_the_merged_sums_before_a_relu():
+    """One relation, no root term: both launch structures take one product over the same terms in the same order, so an fp32
+    layer with a ReLU gives the same bits (a sum formed on other units decides units near zero differently).  1024 rows of
+    256: the merged launch is beyond the split reduction."""
+    import torch
+    from types import SimpleNamespace as NS
+    from paper_2408_08490_amd.runner import Model
+    n, F, H = 1024, 192, 256
+    rng = np.random.default_rng(8)
+    sch = NS(num_types=1, num_rels=1, rel_src=[0], rel_dst=[0])
+    lw = NS(in_dim=[F], out_dim=H, relu=True, w_rel=[rng.standard_normal((F, H)).astype(np.float32)], w_root=[None],
+            bias=[rng.standard_normal(H).astype(np.float32)], w_type=[])
+    model = Model(sch, [F], [rng.standard_normal((2000, F)).astype(np.float32)], [lw], dtype="f32", loss="dot", target_type=0)
+    E = 8 * n
+    block = NS(n_src=[1500], n_dst=[n], edge_index=np.stack([rng.integers(0, 1500, E), rng.integers(0, n, E)]),
+               edge_type=np.zeros(E, np.int32))
+    mb = NS(ids=[rng.permutation(2000)[:1500]], blocks=[block], labels=None, grad_out=None)
+    bt = model.prepare(mb)
+    merged = model.run(bt, backward=False)["h"][0].clone()
+    naive = model.run(bt, backward=False, naive=True)["h"][0].clone()
+    torch.cuda.synchronize()
+    assert torch.equal(merged, naive)
     bt.graph.release()
     model.close()
