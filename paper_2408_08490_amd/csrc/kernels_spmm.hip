@@ -43,6 +43,7 @@ __global__ void __launch_bounds__(256, (C <= 2 && !ADDR) ? 8 : 1) spmm_fwd_unifo
   using V = Vec16<T>;
   using Idx = std::conditional_t<ADDR, unsigned long long, int>;
   constexpr int LPR = 1 << LPRL, RPW = 64 / LPR;
+  static_assert(RPW < 64, "a lane for each of the RPW + 1 row pointers");
   // The first tj.blocks blocks transpose the layer's weights for the GEMM that follows this launch: a few
   // microseconds of work that would otherwise be a launch of its own in front of this one.
   __shared__ T tile[32][33];
@@ -139,10 +140,10 @@ static void launch_fwd_uniform(hipStream_t s, const LayerDev &L, const void *x, 
 // Lanes per row and 16-byte pieces per lane, measured per width on the headline's two layers: the forward's rows
 // are up to `fanout` long and run best with more rows per wavefront (256-byte rows: 8 lanes x 2 pieces, 48 -> 41 us),
 // the transpose's rows are mostly one or two entries long and run best with 16 lanes x 1 piece (32 vs 37 us);
-// 1 KB rows take a whole wavefront each in both directions.
+// 1 KB rows take a whole wavefront each in both directions.  Rows of one piece take two lanes all the same: a wavefront
+// reads the pointers of its rows and of the one behind them, one per lane, so it can own 32 rows but not 64.
 template <typename T, bool FWD, typename FN> static bool dispatch_width(int nvec, FN fn) {
-  if (nvec <= 1) fn.template operator()<0, 1>();
-  else if (nvec <= 2) fn.template operator()<1, 1>();
+  if (nvec <= 2) fn.template operator()<1, 1>();
   else if (nvec <= 4) fn.template operator()<2, 1>();
   else if (nvec <= 8) fn.template operator()<3, 1>();
   else if (nvec <= 16) {
@@ -282,6 +283,7 @@ __global__ void __launch_bounds__(256) spmm_bwd_uniform_kernel(const int32_t *__
                                                                 float *__restrict__ partial) {
   using V = Vec16<T>;
   constexpr int LPR = 1 << LPRL, RPW = 64 / LPR;
+  static_assert(RPW < 64, "a lane for each of the RPW + 1 row pointers");
   const int lane = threadIdx.x & 63;
   const int wave = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (wave >= rr.total_waves) {
