@@ -219,9 +219,13 @@ constexpr int kSplitPKC = Mma<float>::BK + 8;   // elements of a bf16 row with K
 template <bool KC> constexpr int split_pitch(int extent) { return KC ? kSplitPKC : ks_pitch<bf16>(extent); }
 template <bool KC> constexpr int split_plane(int extent) { return KC ? extent * kSplitPKC : Mma<float>::BK * ks_pitch<bf16>(extent); }
 
-// Four fp32 values as the three planes' four bf16 values.
+// Four fp32 values, times kSplitScale, as the three planes' four bf16 values.  bf16 has fp32's exponents, so without the
+// scale the low planes of values below 1e-33 would fall off its lower end (gradients of 1e-35 lost 2.7e-6 of their norm, of
+// 1e-37 2.7e-4); scaled, every normal fp32 value has normal planes.  Values and sums beyond what the scale leaves room for
+// (2e31 and 1e24) do not come out finite and take the fp32 MFMA (gemm_finite).
+constexpr float kSplitScale = 0x1p24f;
 __device__ __forceinline__ void split3(const f32x4 v, u32x2 (&w)[3]) {
-  float d[4] = {v.x, v.y, v.z, v.w};
+  float d[4] = {v.x * kSplitScale, v.y * kSplitScale, v.z * kSplitScale, v.w * kSplitScale};
 #pragma unroll
   for (int p = 0; p < 3; ++p) {
     w[p] = u32x2{pack2(d[0], d[1]), pack2(d[2], d[3])};
@@ -232,6 +236,13 @@ __device__ __forceinline__ void split3(const f32x4 v, u32x2 (&w)[3]) {
       d[3] -= __uint_as_float(w[p].y & 0xffff0000u);
     }
   }
+}
+// acc += part / scale, exact but for the sum's own rounding (scale: a power of two)
+template <int NI> __device__ __forceinline__ void add_unscaled(f32x16 (&acc)[NI], const f32x16 (&part)[NI], float scale) {
+#pragma unroll
+  for (int j = 0; j < NI; ++j)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[j][v] = fmaf(part[j][v], 1.f / scale, acc[j][v]);
 }
 
 // Stores the operand tile of a mover of fp32 values as three planes.
@@ -285,8 +296,7 @@ __device__ __forceinline__ void mma_tile_split(f32x16 (&acc)[MI][NI], const bf16
 #pragma unroll
           for (int j = 0; j < NI; ++j) part[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b[q][ks][j], part[j], 0, 0, 0);
       }
-#pragma unroll
-    for (int j = 0; j < NI; ++j) acc[i][j] += part[j];
+    add_unscaled(acc[i], part, kSplitScale * kSplitScale);
   }
 }
 
@@ -419,7 +429,7 @@ template <int MI, int NI> __device__ __forceinline__ void zero_acc(f32x16 (&acc)
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 }
 
-// A tile's products through run(split): an infinity, or a value that rounds to one in bf16, leaves NaN where the fp32
+// A tile's products through run(split): an infinity, or a value beyond the planes' range, leaves NaN where the fp32
 // product would be infinite or large (inf - inf in the planes, 0 * inf between them), so a tile that did not come out
 // finite is multiplied again on the fp32 MFMA (acc starts from zero both times).  decides: the sums go through a ReLU and
 // stay on the fp32 MFMA altogether (see gemm_fwd_kernel).

@@ -137,8 +137,7 @@ __device__ __forceinline__ void wide_run(f32x16 (&acc)[MI][NI], WideLds<MI, NI> 
 #pragma unroll
           for (int j = 0; j < NI; ++j) part[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b[ks][j], part[j], 0, 0, 0);
         }
-#pragma unroll
-      for (int j = 0; j < NI; ++j) acc[i][j] += part[j];
+      add_unscaled(acc[i], part, kSplitScale);
     }
     __syncthreads();
   }
@@ -300,8 +299,8 @@ __global__ void __launch_bounds__(kThreads, 2) attn_sem_kernel(RelRows rr, int H
   f32x16 acc[MI][2];
   zero_acc(acc);
   mix_run<false>(acc, sm, mbuf + row0 * H, H, M, m0, w_sem, kSemDim, kSemDim, 0, H, [](f32x4 v, int) {
-    // beyond the largest bf16 value the first plane would be infinite and the others NaN; tanh is +-1 there either way
-    constexpr float kMax = 0x1.fep127f;
+    // beyond this the first plane would be infinite and the others NaN; tanh is +-1 there either way
+    constexpr float kMax = 0x1.fep127f / kSplitScale;
     if constexpr (sizeof(TS) == 2) {
 #pragma unroll
       for (int c = 0; c < 4; ++c) v[c] = fabsf(v[c]) > kMax ? copysignf(kMax, v[c]) : v[c];
