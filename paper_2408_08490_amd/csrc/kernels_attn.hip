@@ -59,8 +59,9 @@ __device__ __forceinline__ float leaky(float s) { return s > 0.f ? s : kLeaky * 
 // values (8 + 8 + 8 significant bits), a product of two bf16 values is exact in fp32, so three MFMAs give what the fp32
 // MFMA would, at 3/16 of its cost.  A tile of A (fp32, K contiguous) is split into its three planes on the way from the
 // registers to LDS; B goes through the ordinary mover.  One LDS stage (74 KB, two blocks per CU: the other block's MFMAs
-// cover a block's barriers), the next K-step's loads in flight during the MFMAs.
-constexpr int kWideBK = 64;
+// cover a block's barriers), the next K-step's loads in flight during the MFMAs.  Where that does not come out finite
+// (gemm_finite) the tile of A stays as it is, B is widened as it is read, and the fp32 MFMA multiplies them.
+constexpr int kWideBK = 64, kWidePF = kWideBK + 4;   // pitch of a tile of A that is kept in fp32
 template <int MI, int NI> struct WideLds {
   static constexpr int PA = kWideBK + 8, TM = 64 * MI, TN = 64 * NI;
   static constexpr int B_ELEMS = TN * PA > kWideBK * ks_pitch<bf16>(TN) ? TN * PA : kWideBK * ks_pitch<bf16>(TN);
@@ -80,6 +81,13 @@ template <int TM> struct WideMover {
       f32x4 x = *reinterpret_cast<const f32x4 *>(A + (int64_t)o * lda + min(k0 + c, k_end - 4));
       if (k0 + c >= k_end) x = f32x4{0.f, 0.f, 0.f, 0.f};
       reg[i] = x;
+    }
+  }
+  template <typename F> __device__ __forceinline__ void store_f32(float *a, F f) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int v = threadIdx.x + i * kThreads, r = v / VPR, c = (v % VPR) * 4;
+      *reinterpret_cast<f32x4 *>(a + r * kWidePF + c) = f(reg[i]);
     }
   }
   template <typename F> __device__ __forceinline__ void store(bf16 (*a)[TM * PA], F f) {
@@ -143,6 +151,52 @@ __device__ __forceinline__ void wide_run(f32x16 (&acc)[MI][NI], WideLds<MI, NI> 
   }
 }
 
+// The same on the fp32 MFMA, for tiles that did not come out finite; nothing is prefetched, so that it needs no registers
+// beside the other one's.
+template <bool BKC, int MI, int NI, typename F>
+__device__ __forceinline__ void wide_run_f32(f32x16 (&acc)[MI][NI], WideLds<MI, NI> &sm, const float *A, int lda, int a_extent, int a0,
+                                             const bf16 *B, int ldb, int b_extent, int b0, int K, F f) {
+  constexpr int TM = 64 * MI, TN = 64 * NI, PB = BKC ? kWideBK + 8 : ks_pitch<bf16>(TN);
+  static_assert(TM * kWidePF * sizeof(float) <= sizeof(sm.a), "a tile of A in fp32 must fit the planes");
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));   // nothing of this is worth keeping in registers during wide_run
+  const int lane = tid & 63, wave = tid >> 6;
+  const int wm = (wave >> 1) * 32 * MI, wn = (wave & 1) * 32 * NI;
+  float *af = reinterpret_cast<float *>(&sm.a[0][0]);
+#pragma unroll 1
+  for (int k0 = 0; k0 < K; k0 += kWideBK) {
+    {
+      WideMover<TM> ma;
+      TileMover<bf16, BKC ? TN : kWideBK, BKC ? kWideBK : TN, PB, BKC> mb;
+      mb.setup(ldb, b_extent, b0);
+      ma.load(A, lda, a_extent, a0, k0, K);
+      mb.load_fast(BKC ? B + k0 : B + (int64_t)k0 * ldb, K - k0);
+      const int kc = k0 + (threadIdx.x % WideMover<TM>::VPR) * 4;
+      ma.store_f32(af, [&](f32x4 v) { return f(v, kc); });
+      mb.store(sm.b);
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int ks = 0; ks < kWideBK / 2; ++ks) {
+      const int k = ks * 2 + (lane >> 5);
+      float a[MI], b[NI];
+#pragma unroll
+      for (int i = 0; i < MI; ++i) a[i] = af[(wm + i * 32 + (lane & 31)) * kWidePF + k];
+#pragma unroll
+      for (int j = 0; j < NI; ++j) {
+        const int col = wn + j * 32 + (lane & 31);
+        if constexpr (BKC) b[j] = to_float(sm.b[col * PB + k]);
+        else b[j] = to_float(sm.b[k * PB + (ks_swizzled<bf16>(TN) ? ks_swizzle_col(col, k) : col)]);
+      }
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+    }
+    __syncthreads();
+  }
+}
+
 // Hands the block's tile out of LDS in pieces of four columns: f(row, col, values) for rows below `rows`.  A thread's
 // column is the same in all its pieces.
 template <int MI, int NI, typename F>
@@ -174,7 +228,10 @@ template <bool BKC, typename TS, int MI, typename F>
 __device__ __forceinline__ void mix_run(f32x16 (&acc)[MI][2], MixLds<TS, MI> &sm, const float *A, int lda, int a_extent, int a0,
                                         const TS *B, int ldb, int b_extent, int b0, int K, F f) {
   if constexpr (sizeof(TS) == 2) {
-    wide_run<BKC>(acc, sm.w, A, lda, a_extent, a0, B, ldb, b_extent, b0, K, f);
+    gemm_finite<float, true>(acc, [&](auto split) {
+      if constexpr (split.value) wide_run<BKC>(acc, sm.w, A, lda, a_extent, a0, B, ldb, b_extent, b0, K, f);
+      else wide_run_f32<BKC>(acc, sm.w, A, lda, a_extent, a0, B, ldb, b_extent, b0, K, f);
+    });
   } else {
     if (threadIdx.x == 0) put_seg(sm.g.seg[0], A, lda, B, ldb, 0, K);
     __syncthreads();
@@ -297,16 +354,7 @@ __global__ void __launch_bounds__(kThreads, 2) attn_sem_kernel(RelRows rr, int H
   const int64_t row0 = rr.row_off[r];
   const int M = rr.row_off[r + 1] - (int)row0;
   f32x16 acc[MI][2];
-  zero_acc(acc);
-  mix_run<false>(acc, sm, mbuf + row0 * H, H, M, m0, w_sem, kSemDim, kSemDim, 0, H, [](f32x4 v, int) {
-    // beyond this the first plane would be infinite and the others NaN; tanh is +-1 there either way
-    constexpr float kMax = 0x1.fep127f / kSplitScale;
-    if constexpr (sizeof(TS) == 2) {
-#pragma unroll
-      for (int c = 0; c < 4; ++c) v[c] = fabsf(v[c]) > kMax ? copysignf(kMax, v[c]) : v[c];
-    }
-    return v;
-  });
+  mix_run<false>(acc, sm, mbuf + row0 * H, H, M, m0, w_sem, kSemDim, kSemDim, 0, H, [](f32x4 v, int) { return v; });
   float bs[4], qs[4], part = 0.f;
   const int cc = (threadIdx.x % (kSemDim / 4)) * 4;
   Quad<TS>::load(bs, b_sem + cc);
@@ -649,7 +697,6 @@ __device__ __forceinline__ void attn_dm_part(MixLds<TS, MI> &sm, const float *t,
                                              float *__restrict__ dm, int64_t row0, int M, int m0, int n0, int H, float coef, float beta,
                                              const float *qs) {
   f32x16 acc[MI][2];
-  zero_acc(acc);
   mix_run<true>(acc, sm, t + row0 * kSemDim, kSemDim, M, m0, w_sem, kSemDim, H, n0, kSemDim, [&](f32x4 v, int k) {
     const f32x4 q = *reinterpret_cast<const f32x4 *>(qs + k);
     return f32x4{coef * q.x * (1.f - v.x * v.x), coef * q.y * (1.f - v.y * v.y), coef * q.z * (1.f - v.z * v.z), coef * q.w * (1.f - v.w * v.w)};
