@@ -666,7 +666,7 @@ __device__ __forceinline__ void attn_dws_part(GemmLds<float, 2, 2> &sm, const fl
         ++i;
       }
     });
-  });
+  }, k_end - k_begin <= kFewTerms);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   float qc[2];
 #pragma unroll

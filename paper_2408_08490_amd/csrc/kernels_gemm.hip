@@ -276,7 +276,8 @@ __device__ __forceinline__ void dw_tile(GemmLds<T, MI, MI> &sm, int bid, const T
     put_seg(sm.seg[0], is_rel ? z + (int64_t)rt.z_off4[seg] * 4 : x + tt.xroot_off[d], F,
             gp + (int64_t)tt.out_row_off[d] * ldg, ldg, k_begin, k_end);
   __syncthreads();
-  gemm_finite<T, FAST>(acc, [&](auto split) { gemm_run<T, FAST, false, false, split.value>(acc, sm, 1, F, f0, ldg, h0); });
+  gemm_finite<T, FAST>(acc, [&](auto split) { gemm_run<T, FAST, false, false, split.value>(acc, sm, 1, F, f0, ldg, h0); },
+                       k_end - k_begin <= kFewTerms);
   HGNN_FOR_EACH_ACC({
     if (f0 + row < F && h0 + col < H) atomicAdd(dW + (int64_t)(f0 + row) * H + h0 + col, val);
   })

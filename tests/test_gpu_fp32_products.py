@@ -1,5 +1,5 @@
 """fp32 products on the bf16 matrix cores (three planes per operand) where they could lose: values and sums beyond the planes'
-range (those tiles are multiplied again on the fp32 MFMA) and values near the lower end of fp32.
+range (those tiles are multiplied again on the fp32 MFMA), values near the lower end of fp32, and sums of very few terms.
 A large value meets a small one, so that what comes out is finite and every row or column has a scale of its own to be
 compared on."""
 from types import SimpleNamespace as NS
@@ -106,6 +106,19 @@ def test_products_of_values_near_the_lower_end(scale):
         got, want = _mean_layer(4200, 32, 512, edit)
         errors = {k: np.linalg.norm(got[k] - want[k]) / np.linalg.norm(want[k]) for k in got}
         assert all(e < 1e-6 for e in errors.values()), errors
+
+
+@pytest.mark.parametrize("rows", [1, 2, 3, 4])
+def test_weight_gradients_over_very_few_rows(rows):
+    """One product is rounded once: at most 2^-24 of it.  Sums of a few terms: a rounding per term, measured on the sum of the
+    magnitudes."""
+    keep = {}
+
+    def edit(x, w, g):
+        keep.update(x=x.astype(np.float64), g=g.astype(np.float64))
+    got, want = _mean_layer(rows, 64, 64, edit)
+    magnitude = np.abs(keep["x"][:rows]).T @ np.abs(keep["g"])
+    assert (np.abs(got["dw_root"] - want["dw_root"]) <= 1.01 * rows * 2.0 ** -24 * magnitude).all()
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
