@@ -83,13 +83,6 @@ template <int TM> struct WideMover {
       reg[i] = x;
     }
   }
-  template <typename F> __device__ __forceinline__ void store_f32(float *a, F f) {
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      const int v = threadIdx.x + i * kThreads, r = v / VPR, c = (v % VPR) * 4;
-      *reinterpret_cast<f32x4 *>(a + r * kWidePF + c) = f(reg[i]);
-    }
-  }
   template <typename F> __device__ __forceinline__ void store(bf16 (*a)[TM * PA], F f) {
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
@@ -166,13 +159,16 @@ __device__ __forceinline__ void wide_run_f32(f32x16 (&acc)[MI][NI], WideLds<MI, 
 #pragma unroll 1
   for (int k0 = 0; k0 < K; k0 += kWideBK) {
     {
-      WideMover<TM> ma;
+#pragma unroll 1
+      for (int v = tid; v < TM * (kWideBK / 4); v += kThreads) {
+        const int r = v / (kWideBK / 4), c = (v % (kWideBK / 4)) * 4;
+        f32x4 x = *reinterpret_cast<const f32x4 *>(A + (int64_t)min(a0 + r, a_extent - 1) * lda + min(k0 + c, K - 4));
+        if (k0 + c >= K) x = f32x4{0.f, 0.f, 0.f, 0.f};
+        *reinterpret_cast<f32x4 *>(af + r * kWidePF + c) = f(x, k0 + c);
+      }
       TileMover<bf16, BKC ? TN : kWideBK, BKC ? kWideBK : TN, PB, BKC> mb;
       mb.setup(ldb, b_extent, b0);
-      ma.load(A, lda, a_extent, a0, k0, K);
       mb.load_fast(BKC ? B + k0 : B + (int64_t)k0 * ldb, K - k0);
-      const int kc = k0 + (threadIdx.x % WideMover<TM>::VPR) * 4;
-      ma.store_f32(af, [&](f32x4 v) { return f(v, kc); });
       mb.store(sm.b);
     }
     __syncthreads();
