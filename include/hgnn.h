@@ -293,7 +293,8 @@ typedef struct {
 
 /* Bytes of the two device work areas of one layer on this graph:
  *   saved   written by hgnn_layer_fwd, read by hgnn_layer_bwd (per-relation aggregated features)
- *   scratch temporary for either call (contents undefined afterwards)
+ *   scratch temporary for either call (contents undefined afterwards); layers of few output tiles (128 of 64x64 in
+ *           bf16, 64 in fp32 with an activation, 512 without) have 16.8 MB in it for the forward's partial tiles
  * Both must be 256-byte aligned. */
 hgnn_status hgnn_layer_workspace_bytes(hgnn_ctx *ctx, hgnn_graph *g, int32_t layer,
                                        const hgnn_layer_params *p, size_t *saved_bytes,
@@ -320,7 +321,8 @@ hgnn_status hgnn_layer_fwd(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_t l
  * also the aggregate's low-order plane) in a fixed device array of HGNN_STATIC_SCRATCH_BYTES that the library
  * holds on every GPU it runs on until the process ends.  The call allocates nothing, on the device or the host.
  * Mean-aggregation layers only (HGNN_EUNSUPPORTED otherwise).  A layer that needs more than the fixed array
- * holds is refused with HGNN_EINVAL and a message that states both sizes; nothing is enqueued then.  `saved` is
+ * holds is refused with HGNN_EINVAL and a message that states both sizes; nothing is enqueued then.  (Behind the array the
+ * library holds 16.8 MB more for the partial tiles of layers of few output tiles; they do not count.)  `saved` is
  * as for hgnn_layer_fwd (size from hgnn_layer_workspace_bytes) and feeds hgnn_layer_bwd unchanged.
  * Every call on a GPU uses that GPU's one array: calls whose device work may overlap (different streams, or
  * several host threads) race; order them on one stream.  The array keeps the last call's contents; each call

@@ -635,7 +635,9 @@ __device__ __forceinline__ float relation_coef(const RelRows &rr, const float *_
 }
 
 // dW_s += m^T du, dq += coef sum t, db_s += coef q sum (1 - t^2) over `rows` rows of one relation: the block multiplies
-// m^T (1 - t^2) and scales the result (fp32 MFMA, whose rate bounds this part).
+// m^T (1 - t^2) and scales the result.  Both operands are split into planes on the way (six bf16 MFMAs per product): the
+// splitting and the LDS traffic of two fp32 tiles per K-step bound this part (on the fp32 MFMA, whose rate bound it, the
+// launch with dm took 739 us on 560k rows, so 600).
 __device__ __forceinline__ void attn_dws_part(GemmLds<float, 2, 2> &sm, const float *m, const float *t, int64_t row0, int k_begin, int k_end,
                                               int H, int f0, float coef, const float *qs, float *__restrict__ dws,
                                               float *__restrict__ dq, float *__restrict__ dbs) {
@@ -706,8 +708,8 @@ __device__ __forceinline__ void attn_dm_part(MixLds<TS, MI> &sm, const float *t,
   });
 }
 
-// Both products of the semantic attention's backward in ONE launch, their blocks interleaved: dW_s is bound by the fp32
-// matrix rate, dm by memory, and neither depends on the other.
+// Both products of the semantic attention's backward in ONE launch, their blocks interleaved: dW_s is bound by splitting its
+// operands and by LDS, dm by memory, and neither depends on the other.
 template <typename TS, int MI>
 __global__ void __launch_bounds__(kThreads, 2) attn_sem_bwd_kernel(RelRows dwt, RelRows dmt, SemBwd p, int H, const float *__restrict__ mbuf,
                                                                  const float *__restrict__ tbuf, const TS *__restrict__ w_sem,

@@ -5,6 +5,7 @@ libhgnn.so; PyTorch provides device memory and the stream.
 """
 from __future__ import annotations
 
+import functools
 import threading
 from typing import List, Optional
 
@@ -24,13 +25,20 @@ def to_device(a: np.ndarray, dtype: str, dev) -> torch.Tensor:
     return torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).to(dev).to(_tdtype(dtype)).contiguous()
 
 
+@functools.lru_cache(maxsize=None)
+def _upload_stream(index):
+    """One stream for the uploads of all models on a GPU: the first use of a stream costs a queue and, for tensors made on it,
+    a first block of device memory (1 ms together)."""
+    return torch.cuda.Stream(torch.device("cuda", index))
+
+
 class _Uploads:
-    """Integer lists to the device in one copy per mini-batch, through a pinned buffer and on a stream of its own, so that the
+    """Integer lists to the device in one copy per mini-batch, through a pinned buffer and on a stream of their own, so that the
     caller waits for the copy alone and not for what its own stream still has to do.  The lists are complete when put()
     returns, for every stream; several threads may call it."""
 
     def __init__(self, dev):
-        self.dev, self.stream, self.host, self.lock = dev, torch.cuda.Stream(dev), None, threading.Lock()
+        self.dev, self.stream, self.host, self.lock = dev, _upload_stream(dev.index), None, threading.Lock()
 
     def put(self, arrays):
         """Device int64 tensors with the values and shapes of the host arrays (views of one tensor)."""

@@ -218,10 +218,11 @@ def test_config7_widest_schema():
 
 @pytest.mark.parametrize("index", [0, 1])
 def test_fp32_products_of_values_beyond_bf16(index):
-    """fp32 GEMMs multiply on the bf16 matrix cores, three planes per operand.  A finite value that rounds to infinity in
-    bf16 (3.4e38) has no such planes: its tile is multiplied again on the fp32 units.  One such value each in the
-    features of a destination row (forward) and in the incoming gradient (backward); everything else small enough that no
-    product overflows.  Config 0: 64x64 tiles; config 1 at full size: forward tiles and both backward tile sizes."""
+    """A finite value that rounds to infinity in bf16 (3.4e38) has no planes for the products on the bf16 matrix cores.  One such
+    value each in the features of a destination row (forward: config 0 and both layers of config 1 form these sums on the fp32
+    MFMA) and, for config 0, in the incoming gradient (backward, 64x64 tiles: multiplied in planes and then again);
+    everything else small enough that no product overflows.  tests/test_gpu_fp32_products.py has such values in every other
+    place that multiplies planes."""
     big = np.float32(3.4e38)
 
     def features(cfg, g, mb, ws):
@@ -237,7 +238,8 @@ def test_fp32_products_of_values_beyond_bf16(index):
 
 
 def test_fp32_products_with_infinity():
-    """An infinite feature stays infinite (not NaN) in the outputs it reaches, and reaches no others."""
+    """An infinite feature stays infinite (not NaN) in the outputs it reaches, and reaches no others (forward of config 1, on
+    the fp32 MFMA; the products in planes have theirs in tests/test_gpu_fp32_products.py)."""
     import torch
     from paper_2408_08490_amd.runner import Model
     from tests.parity import prepare_inputs

@@ -96,3 +96,30 @@ def test_one_graph_from_two_streams():
         assert all(torch.equal(a, b) for a, b in zip(ref, got)) and all(torch.equal(a, b) for a, b in zip(ref, again))
         bt.graph.release()
     model.close()
+
+
+def test_the_first_call_on_a_graph_may_be_captured():
+    """Nothing is known yet of the upload when the layer is captured (it is asked for inside the capture); the captured layer gives
+    the eager bits on every replay."""
+    import torch
+    model, g, mb = _model(2, scale=0.05, batch=64)
+    first = model.prepare(mb, g.edge_type, use_edge_id=True)
+    out = model.run(first, backward=False)
+    want, x0 = out["h"][0].clone(), out["x0"].clone()
+    first.graph.release()
+    bt = model.prepare(mb, g.edge_type, use_edge_id=True)
+    sb, cb = model.ctx.hgnn_layer_workspace_bytes(bt.graph, 0, model.layers[0])
+    bt.graph.host_view(0)                      # the build is over; the upload is not asked for
+    torch.cuda.synchronize()
+    sv, sc = (torch.empty(max(n, 256), device=model.dev, dtype=torch.uint8) for n in (sb, cb))
+    h = torch.empty_like(want)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        model.ctx.hgnn_layer_fwd(bt.graph, 0, model.layers[0], x0, h, sv, sc)
+    for _ in range(3):
+        h.fill_(7.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(h, want)
+    bt.graph.release()
+    model.close()
