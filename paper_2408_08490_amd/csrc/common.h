@@ -146,8 +146,12 @@ struct Slab {  // pinned host block + device block of equal capacity
 // contexts keep more of them looking for work than the machine has cores, and every one's are asleep when its turn comes).
 // The crew has as many threads as the live context that asked for most; the last context to go takes them with it.
 // A thread builds a whole graph or takes chunks of the parallel phases of others' builds.  A phase lasts some 20 us, and
-// waking a thread costs more than that: while a graph is being built the threads look for work in a loop.  Between builds
-// they sleep (a loop of one build and one step of 0.6 ms: 10 cores busy instead of 16, 0.60 against 0.58 ms per pass).
+// waking a thread costs more than that: while a graph is being built the threads look for work in a loop, and behind it for
+// as long as the next one took to come last time, if that was less than kTailUs; otherwise they sleep between builds.
+// A loop of one build from lists and its step (1024 targets, 16 cores; us per pass and cores busy), with threads that always
+// look for work for 500 us before they sleep -> with this rule:
+//   back to back 510 to 570, 16 -> 530 to 550, 16      step waited for 660 to 750, 16 -> 690 to 710, 8
+//   and a pause of 0.5 ms 690 to 720, 10 -> 690 to 720, 5      of 2 ms 710 to 720, 4.7 -> 690 to 720, 2.2
 class Crew {
  public:
   static Crew &get();        // the process's; a forked child has its own, without threads until a context joins it
@@ -169,7 +173,7 @@ class Crew {
   // core to one of them
   bool look() const { return eager_.load(std::memory_order_relaxed) > 0 && at_work_.load(std::memory_order_relaxed) < target_.load(std::memory_order_relaxed); }
   static constexpr int kSpinUs = 500;   // how long a thread looks for work before it sleeps while a graph is being built
-  static constexpr int kTailUs = 50;    // and when none is
+  static constexpr int kTailUs = 300;   // and when none is, if the last one followed the one before it as soon as that
 
  private:
   static constexpr int kSlots = 32;
@@ -192,6 +196,8 @@ class Crew {
   Slot slots_[kSlots];
   std::atomic<int> active_{0}, target_{0}, sleepers_{0}, waiting_tasks_{0}, at_work_{0}, eager_{0};   // at_work_: threads in a task
   std::mutex m_, size_m_;
+  std::atomic<int64_t> idle_since_{0};        // when the last task under way ended (steady clock, ns)
+  std::atomic<bool> in_a_row_{false};         // whether the last task came within kTailUs of that
   std::atomic<uint32_t> calls_{0};            // what sleeping threads wait to see changed
   std::deque<std::function<void()>> tasks_;   // m_
   std::vector<int> sizes_;                    // threads asked for by each live context (size_m_)

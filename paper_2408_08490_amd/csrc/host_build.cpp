@@ -124,6 +124,7 @@ void Crew::run(int index) {
       if (task) {
         at_work_.fetch_add(1);
         task();
+        idle_since_.store(std::chrono::steady_clock::now().time_since_epoch().count(), std::memory_order_relaxed);
         at_work_.fetch_sub(1);
         did = true;
       }
@@ -137,7 +138,8 @@ void Crew::run(int index) {
       cpu_relax();
       if (++spins % 64) continue;
       const auto idle_for = std::chrono::steady_clock::now() - idle;
-      if (idle_for < std::chrono::microseconds(at_work_.load(std::memory_order_relaxed) > 0 ? kSpinUs : kTailUs)) continue;
+      const int look_us = at_work_.load(std::memory_order_relaxed) > 0 ? kSpinUs : in_a_row_.load(std::memory_order_relaxed) ? kTailUs : 0;
+      if (idle_for < std::chrono::microseconds(look_us)) continue;
     }
     // A sleeper looks once more after it has said so; work posted from there on changes the call it sleeps on.  No lock is
     // taken on the way out of the sleep: fifteen threads woken at once would pass it on one by one.
@@ -154,6 +156,8 @@ void Crew::wake_all() {
   calls_.notify_all();
 }
 void Crew::submit(std::function<void()> task) {
+  const int64_t idle_for = std::chrono::steady_clock::now().time_since_epoch().count() - idle_since_.load(std::memory_order_relaxed);
+  in_a_row_.store(at_work_.load(std::memory_order_relaxed) > 0 || idle_for < (int64_t)kTailUs * 1000, std::memory_order_relaxed);
   {
     std::lock_guard<std::mutex> lk(m_);
     tasks_.push_back(std::move(task));
