@@ -47,8 +47,9 @@ __global__ void __launch_bounds__(kThreads, MI == 1 ? 3 : 2) gemm_fwd_kernel(Typ
   // it, the aggregate's low-order remainder against the same weights), then the root term.  The first wavefront
   // looks at a window of relations at once, one per lane, and packs the ones that take part with a ballot.
   // fp32 with a ReLU: a unit within a rounding of zero takes the other decision when its sum is formed another way, and moves
-  // a whole term of the gradients; three of ten million units do (1024 targets, 256 wide: gradients 2e-3 apart).  So these sums
-  // are formed as they are without the three planes, one fp32 MFMA after the other: 39 -> 50 us there, of a step of 310.
+  // a whole term of the gradients; three of ten million units do (1024 targets, 256 wide: gradients 2e-3 apart).  Neither
+  // decision is the wrong one -- the planes' sums are the nearer ones to 64 bits -- but these sums stay on the fp32 MFMA, so
+  // that every form of the layer decides alike: 39 -> 50 us there, of a step of 310.
   gemm_finite<T, FAST>(acc, [&](auto split) {
   for (int cursor = 0; cursor < R; cursor += kRelWindow) {
     if (threadIdx.x < 64) {

@@ -235,7 +235,8 @@ __global__ void __launch_bounds__(256) gemm_fwd_direct_sum_kernel(DirectArgs arg
 //   fp32  16: 43 -> 16, 27 -> 16 (104 relations)   96: 41 -> 23   312: 54 -> 48      700: 47 -> 52 (not taken)
 //   bf16  72: 43 -> 22 (108 relations)   16: 24 -> 16   24: 15 -> 14   96: 24 -> 21   230: 15 -> 27 (not taken)
 // In fp32 with a ReLU the line is at 64 tiles: a sum formed in another order gives units within a rounding of zero the other
-// decision (three of ten million), which moves a whole term of the gradients; up to 64 tiles there is next to never one.
+// decision (three of ten million), which moves a whole term of the gradients away from what the staged kernel's forms of the
+// layer give; up to 64 tiles there is next to never one.
 static int launch_gemm_fwd_direct(hipStream_t s, int dtype, const TypeTab &tt, const RelTab &rt, const PtrTab &pt, const WtTab &wt,
                                    const uint32_t *live_mask, int H, int relu, const void *x, const void *z, const void *zlo,
                                    const void *wt_buf, void *h, float *part, bool count_only) {
