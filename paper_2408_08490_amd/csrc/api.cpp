@@ -88,7 +88,7 @@ struct Plan {
   int64_t total_dst = 0;
   size_t z_elems = 0, zroot_elems = 0, wt_elems = 0;
   size_t saved_bytes = 0, scratch_bytes = 0;
-  size_t off_wt = 0, off_gp = 0, off_dz = 0, off_partial = 0, off_acc32 = 0, off_bpart = 0, bpart_rows = 0, off_zlo = 0, off_gaddr = 0, off_part = 0;
+  size_t off_wt = 0, off_gp = 0, off_dz = 0, off_partial = 0, off_count = 0, off_acc32 = 0, off_bpart = 0, bpart_rows = 0, off_zlo = 0, off_gaddr = 0, off_part = 0;
 };
 
 // The buffer the root term reads holds the destination rows only (n_dst[t] rows per type, back to back).
@@ -170,6 +170,7 @@ static hgnn_status make_plan(hgnn_ctx *ctx, hgnn_graph *g, int32_t layer, const 
   pl.off_gp = o;      o += align_up(std::max<size_t>((size_t)pl.total_dst * Hpad, 1) * pl.es, 256);
   pl.off_dz = o;      o += align_up(std::max<size_t>(zr, 1) * pl.es, 256);
   pl.off_partial = o; o += align_up(std::max<size_t>((size_t)L.max_chunks * std::max(pl.max_dim, 1), 1) * 4, 256);
+  pl.off_count = o;   o += align_up((size_t)L.max_chunks * 4, 256);
   pl.off_acc32 = o;   o += align_up(std::max<size_t>((size_t)pl.total_dst * pl.H, 1) * 4, 256);
   // partial bias-gradient sums: one row of H floats per block of destination rows of a type (64 rows per block
   // when the row pass runs in its 16-bytes-per-lane form, which the width decides; 8 otherwise)
@@ -201,9 +202,9 @@ hgnn_status layer_dev(hgnn_ctx *ctx, hgnn_graph *g, int32_t layer, LayerDev &D) 
     D.rowptr = b + L.o_rowptr; D.colidx = b + L.o_colidx; D.cptr = b + L.o_cptr; D.crow = b + L.o_crow;
     D.cperm = b + L.o_cperm;
     D.chunk_row = b + L.o_chunk_row; D.chunk_beg = b + L.o_chunk_beg;
-    D.long_row = b + L.o_long_row; D.long_chunk0 = b + L.o_long_chunk0;
     D.rows = (int32_t)L.rows; D.edges = (int32_t)L.edges; D.src_rows = (int32_t)L.src_rows;
-    D.n_long = L.n_long; D.n_chunks = L.n_chunks;
+    D.chunk_count = nullptr;
+    D.n_chunks = L.n_chunks;
   }
   return HGNN_OK;
 }
@@ -526,8 +527,7 @@ hgnn_status plan_graph(hgnn_ctx *ctx, hgnn_graph *g, std::string &msg) {
     if (src_rows > INT32_MAX - 1 || rows > INT32_MAX - 1) return fail(HGNN_EOVERFLOW, "layer %d: more than 2^31-2 rows", l);
     L.rows = rows;
     L.src_rows = src_rows;
-    L.max_long = (int32_t)(L.edges / kLongRow + 1);
-    L.max_chunks = (int32_t)(L.edges / kChunk + L.max_long + 1);
+    L.max_chunks = (int32_t)(L.edges / kChunk + L.edges / (kLongRow + 1) + 1);   // whole ones, and a last one per long row
     L.o_rel_row_off = take(R + 1);
     L.o_rel_edge_off = take(R + 1);
     L.o_rowptr = take(rows + 1);
@@ -536,8 +536,6 @@ hgnn_status plan_graph(hgnn_ctx *ctx, hgnn_graph *g, std::string &msg) {
     L.o_crow = take(L.edges);
     L.o_chunk_row = take(L.max_chunks);
     L.o_chunk_beg = take(L.max_chunks);
-    L.o_long_row = take(L.max_long);
-    L.o_long_chunk0 = take(L.max_long + 1);
   }
   const bool cperm_on_device = ctx->agg == HGNN_AGG_ATTN;   // the attention backward walks edges by CSR position
   if (cperm_on_device)
@@ -1086,6 +1084,8 @@ static hgnn_status bwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
   char *sc = (char *)scratch;
   const LayerHost &L = g->L[layer];
   const int32_t *reo = g->slab.host + L.o_rel_edge_off;
+  pl.dev.chunk_count = gt.counters = (uint32_t *)(sc + pl.off_count);
+  gt.n_counters = grad_x_merged ? pl.dev.n_chunks : 0;
   if ((any_dw || any_db) && pl.total_dst == 0) {  // nothing flows back: the gradients are zero
     Probe pb(ctx, HGNN_K_ZERO_GRADS, layer);
     return launch_zero_grads(s, pl.tt, pl.rt, gt, pl.H);
@@ -1153,6 +1153,10 @@ static hgnn_status bwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
       for (int t = 0; t < T; ++t)
         if ((!p->input_grad || p->input_grad[t]) && !((L.tmask >> t) & 1u) && L.n_src[t] > 0)
           HGNN_FAIL(HGNN_EINVAL, "input gradient of type %d asked for, but the graph was built without its transpose entries", t);
+    if (want_dxn && gt.n_counters > 0) {
+      if ((st = launch_fill_zero(s, gt.counters, (size_t)gt.n_counters * 4)) != HGNN_OK) return st;
+      ++n;
+    }
     void *dzn = sc + pl.off_dz;
     const int tiles_hn = (pl.H + 127) / 128;
     for (int sgi = 0; sgi < R + T && pl.total_dst > 0; ++sgi) {
@@ -1189,7 +1193,7 @@ static hgnn_status bwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
       for (int t = 0; t < T; ++t) {
         if ((p->input_grad && !p->input_grad[t]) || L.n_src[t] == 0) continue;
         if ((st = launch_spmm_bwd(s, ctx->dtype, pl.dev, pl.tt, pl.rt, pl.pt, pl.max_dim, 1u << t, dzn, grad_x_merged, (float *)(sc + pl.off_partial))) != HGNN_OK) return st;
-        n += 1 + (pl.dev.n_long > 0);
+        ++n;
       }
     }
     if (launches) *launches = n;
@@ -1325,8 +1329,8 @@ hgnn_status hgnn_layer_launch_count(hgnn_ctx *ctx, hgnn_graph *g, int32_t layer,
   }
   if (bwd_launches) {
     // zero grads + ReLU mask + bias partial sums (one launch), dW and dA GEMMs + bias sums (one launch), transposed
-    // aggregation (+ long-row pass); without destination rows only the zeroing
-    *bwd_launches = pl.total_dst > 0 ? 2 + (pl.dev.src_rows > 0 ? 1 + (pl.dev.n_long > 0) : 0) : 1;
+    // aggregation; without destination rows only the zeroing
+    *bwd_launches = pl.total_dst > 0 ? 2 + (pl.dev.src_rows > 0) : 1;
   }
   return HGNN_OK;
 }

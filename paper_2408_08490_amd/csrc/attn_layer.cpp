@@ -24,7 +24,7 @@ struct AttnPlan {
   // saved (forward -> backward)
   size_t s_z = 0, s_m = 0, s_t = 0, s_mx = 0, s_ls = 0, s_beta = 0, s_wsum = 0, saved_bytes = 0;
   // scratch (backward)
-  size_t c_gp = 0, c_dbeta = 0, c_dm = 0, c_edge = 0, c_xsum = 0, c_dsum = 0, c_dz = 0, c_partial = 0, scratch_bytes = 0;
+  size_t c_gp = 0, c_dbeta = 0, c_dm = 0, c_edge = 0, c_xsum = 0, c_dsum = 0, c_dz = 0, c_partial = 0, c_count = 0, scratch_bytes = 0;
 };
 
 hgnn_status make_attn_plan(hgnn_ctx *ctx, hgnn_graph *g, int32_t layer, const hgnn_layer_params *p, AttnPlan &pl, bool need_built) {
@@ -109,6 +109,7 @@ hgnn_status make_attn_plan(hgnn_ctx *ctx, hgnn_graph *g, int32_t layer, const hg
   pl.c_dsum = take(o, (size_t)pl.rows * hd * 4);
   pl.c_dz = take(o, (size_t)pl.src_rows * H * es);
   pl.c_partial = take(o, (size_t)L.max_chunks * H * 4);
+  pl.c_count = take(o, (size_t)L.max_chunks * 4);
   pl.scratch_bytes = o;
   if (need_built) return layer_dev(ctx, g, layer, pl.dev);
   return HGNN_OK;
@@ -180,7 +181,7 @@ hgnn_status attn_bwd(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_t layer, 
   std::memset(&gt, 0, sizeof(gt));
   std::memset(&dap, 0, sizeof(dap));
   {
-    float *zp[2 * kMaxR + 2 * kMaxT + 8];
+    float *zp[2 * kMaxR + 2 * kMaxT + 8];   // the launcher's table holds as many
     int64_t zn[2 * kMaxR + 2 * kMaxT + 8];
     int n = 0;
     auto zero = [&](float *q, int64_t len) { zp[n] = q; zn[n++] = len; };
@@ -202,6 +203,8 @@ hgnn_status attn_bwd(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_t layer, 
     zero(go->db_sem, kSemDimHost);
     zero(go->dq_sem, kSemDimHost);
     zero(dbeta, kMaxR);
+    pl.dev.chunk_count = (uint32_t *)(sc + pl.c_count);
+    zero((float *)pl.dev.chunk_count, pl.dev.n_chunks);
     Probe pb(ctx, HGNN_K_ZERO_GRADS, layer);
     if ((st = launch_attn_zero(s, zp, zn, n)) != HGNN_OK) return st;
   }
@@ -273,8 +276,8 @@ hgnn_status attn_launch_count(hgnn_ctx *ctx, hgnn_graph *g, int32_t layer, const
   if (st != HGNN_OK) return st;
   // projection, aggregation, semantic scores, fusion
   if (fwd) *fwd = (pl.src_rows > 0) + 2 * (pl.rows > 0) + (pl.total_dst > 0);
-  // zero, mask + relation dots, semantic products, row pass, transpose pass (+ its long rows), projection
-  if (bwd) *bwd = 1 + (pl.total_dst > 0) + 2 * (pl.rows > 0) + (pl.src_rows > 0 ? 2 + (pl.dev.n_long > 0) : 0);
+  // zero, mask + relation dots, semantic products, row pass, transpose pass, projection
+  if (bwd) *bwd = 1 + (pl.total_dst > 0) + 2 * (pl.rows > 0) + (pl.src_rows > 0 ? 2 : 0);
   return HGNN_OK;
 }
 

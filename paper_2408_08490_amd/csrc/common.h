@@ -79,6 +79,8 @@ struct GradPtrTab {
   float *dw_rel[kMaxR];
   float *dw_root[kMaxT];
   float *dbias[kMaxT];
+  uint32_t *counters;   // cleared beside the gradients (LayerDev::chunk_count)
+  int32_t n_counters;
 };
 // Work list over GEMM segments (relation r -> segment r, root of type t -> segment R + t).
 struct SegTab {
@@ -116,22 +118,21 @@ struct TransposeJobs {
 struct LayerDev {
   const int32_t *rel_row_off, *rel_edge_off, *rowptr, *colidx, *cptr, *crow;
   const int32_t *cperm;                  // CSR position of each transpose entry (uploaded for the attention variant only)
-  const int32_t *chunk_row, *chunk_beg;  // transpose rows longer than kLongRow, split in chunks of kChunk edges
-  const int32_t *long_row, *long_chunk0; // the long rows and the first chunk of each (n_long + 1 entries)
-  int32_t rows, edges, src_rows, n_long, n_chunks;
+  const int32_t *chunk_row, *chunk_beg;  // transpose rows longer than kLongRow, split in chunks of kChunk entries
+  uint32_t *chunk_count;                 // in the work area of a backward pass: finished chunks of a row, at its first one's place
+  int32_t rows, edges, src_rows, n_chunks;
 };
 
-constexpr int kLongRow = 16;  // transpose rows above this length are reduced chunk-wise
-constexpr int kChunk = 16;
+constexpr int kLongRow = 16;  // transpose rows above this length are reduced chunk-wise, by whole blocks (long_rows.h)
+constexpr int kChunk = 128;
 
 struct LayerHost {
   int64_t rows = 0, edges = 0, src_rows = 0, tedges = 0;
   int64_t n_src[kMaxT], n_dst[kMaxT];
   // offsets in int32 units into the slab
   size_t o_rel_row_off = 0, o_rel_edge_off = 0, o_rowptr = 0, o_colidx = 0, o_perm = 0, o_cptr = 0,
-         o_crow = 0, o_cperm = 0, o_chunk_row = 0, o_chunk_beg = 0, o_long_row = 0, o_long_chunk0 = 0;
-  int32_t n_long = 0, n_chunks = 0;
-  int32_t max_chunks = 0, max_long = 0;
+         o_crow = 0, o_cperm = 0, o_chunk_row = 0, o_chunk_beg = 0;
+  int32_t n_chunks = 0, max_chunks = 0;
   uint32_t tmask = ~0u;  // vertex types whose source rows get transpose entries
   hgnn_coo_layer in;  // caller's arrays (valid until the build finishes)
 };

@@ -6,7 +6,7 @@
 //   keys      key[e] = rel_row_off[type(e)] + dst(e)  (the merged CSR row), value e; source row of x_merged per edge
 //   sort 1    stable radix sort by key  -> perm, rowptr (lower bound of every row in the sorted keys), colidx
 //   sort 2    stable radix sort of the CSR positions by source row -> cperm, cptr, crow (the transpose)
-//   chunks    transpose rows longer than kLongRow cut into chunks of kChunk entries (two prefix sums)
+//   chunks    transpose rows longer than kLongRow cut into chunks of kChunk entries (a prefix sum)
 // The call is synchronous: it returns after the arrays have been copied back into the graph's host block (the views
 // and the host-side tables of the layer calls read them there) and the counts that size later launches are known.
 #include <hipcub/hipcub.hpp>
@@ -109,41 +109,26 @@ __global__ void __launch_bounds__(256) dev_crow_kernel(int E, const int32_t *__r
   if (j < E) crow[j] = row_of[cperm[j]];
 }
 
-// per transpose row: 1 when it is long, and its number of chunks (entry src_rows of both arrays = 0, so that the
-// exclusive sums end with the totals)
-__global__ void __launch_bounds__(256) dev_long_flags_kernel(const int32_t *__restrict__ cptr, int src_rows, int32_t *__restrict__ is_long,
-                                                              int32_t *__restrict__ nchunk) {
+// per transpose row its number of chunks (entry src_rows = 0, so that the exclusive sum ends with the total)
+__global__ void __launch_bounds__(256) dev_long_flags_kernel(const int32_t *__restrict__ cptr, int src_rows, int32_t *__restrict__ nchunk) {
   const int c = blockIdx.x * 256 + threadIdx.x;
   if (c > src_rows) return;
-  int l = 0, n = 0;
-  if (c < src_rows) {
-    const int len = cptr[c + 1] - cptr[c];
-    if (len > kLongRow) {
-      l = 1;
-      n = (len + kChunk - 1) / kChunk;
-    }
-  }
-  is_long[c] = l;
-  nchunk[c] = n;
+  const int len = c < src_rows ? cptr[c + 1] - cptr[c] : 0;
+  nchunk[c] = len > kLongRow ? (len + kChunk - 1) / kChunk : 0;
 }
 
-__global__ void __launch_bounds__(256) dev_chunk_lists_kernel(const int32_t *__restrict__ cptr, int src_rows, const int32_t *__restrict__ long_at,
-                                                               const int32_t *__restrict__ chunk_at, int32_t *__restrict__ long_row,
-                                                               int32_t *__restrict__ long_chunk0, int32_t *__restrict__ chunk_row,
+__global__ void __launch_bounds__(256) dev_chunk_lists_kernel(const int32_t *__restrict__ cptr, int src_rows,
+                                                               const int32_t *__restrict__ chunk_at, int32_t *__restrict__ chunk_row,
                                                                int32_t *__restrict__ chunk_beg, int32_t *__restrict__ counts) {
   const int c = blockIdx.x * 256 + threadIdx.x;
   if (c > src_rows) return;
-  if (c == src_rows) {  // the totals, and the end of the last long row's chunks
-    counts[0] = long_at[c];
-    counts[1] = chunk_at[c];
-    long_chunk0[long_at[c]] = chunk_at[c];
+  if (c == src_rows) {  // the total
+    counts[0] = chunk_at[c];
     return;
   }
   const int beg = cptr[c], len = cptr[c + 1] - beg;
   if (len <= kLongRow) return;
-  const int i = long_at[c], j0 = chunk_at[c];
-  long_row[i] = c;
-  long_chunk0[i] = j0;
+  const int j0 = chunk_at[c];
   for (int m = 0, q = beg; q < beg + len; q += kChunk, ++m) {
     chunk_row[j0 + m] = c;
     chunk_beg[j0 + m] = q;
@@ -238,8 +223,8 @@ extern "C" hgnn_status hgnn_build_semantic_csr_device(hgnn_ctx *ctx, void *strea
   }
   auto up = [](size_t n) { return (n + 255) / 256 * 256; };
   const size_t e4 = up(max_e * 4), r4 = up(max_rows * 4);
-  // raw input (index pairs up to 16 bytes an edge, type or id up to 8), 7 int32 arrays of E, 4 of rows, library scratch, counters
-  const size_t total = up(max_e * 16) + up(max_e * 8) + 7 * e4 + 4 * r4 + up(std::max(sort_tmp, scan_tmp)) + 256 * (size_t)kMaxLayers;
+  // raw input (index pairs up to 16 bytes an edge, type or id up to 8), 7 int32 arrays of E, 2 of rows, library scratch, counters
+  const size_t total = up(max_e * 16) + up(max_e * 8) + 7 * e4 + 2 * r4 + up(std::max(sort_tmp, scan_tmp)) + 256 * (size_t)kMaxLayers;
   if ((st = need_tmp(ctx, total)) != HGNN_OK) {
     give_back(ctx, g);
     return st;
@@ -250,9 +235,9 @@ extern "C" hgnn_status hgnn_build_semantic_csr_device(hgnn_ctx *ctx, void *strea
   void *d_et = carve(up(max_e * 8));
   int32_t *key_a = (int32_t *)carve(e4), *key_b = (int32_t *)carve(e4), *val_a = (int32_t *)carve(e4), *val_b = (int32_t *)carve(e4);
   int32_t *colsrc = (int32_t *)carve(e4), *key2_b = (int32_t *)carve(e4), *val2_b = (int32_t *)carve(e4);
-  int32_t *is_long = (int32_t *)carve(r4), *nchunk = (int32_t *)carve(r4), *long_at = (int32_t *)carve(r4), *chunk_at = (int32_t *)carve(r4);
+  int32_t *nchunk = (int32_t *)carve(r4), *chunk_at = (int32_t *)carve(r4);
   void *lib_tmp = carve(up(std::max(sort_tmp, scan_tmp)));
-  int32_t *d_counts = (int32_t *)carve(256 * (size_t)kMaxLayers);   // per layer: n_long, n_chunks, error flags
+  int32_t *d_counts = (int32_t *)carve(256 * (size_t)kMaxLayers);   // per layer: n_chunks, -, error flags
   size_t lib_bytes = std::max(sort_tmp, scan_tmp);
   hipError_t he = hipMemsetAsync(d_counts, 0, 256 * (size_t)kMaxLayers, s);
   int32_t *base = g->slab.dev;
@@ -334,16 +319,14 @@ extern "C" hgnn_status hgnn_build_semantic_csr_device(hgnn_ctx *ctx, void *strea
     HGNN_LAUNCH(dev_rel_tables_kernel, dim3(1), dim3(256), 0, s, sc, rowptr, base + L.o_rel_row_off, base + L.o_rel_edge_off);
     // long transpose rows
     const int rb = (int)(L.src_rows + 256) / 256;
-    HGNN_LAUNCH(dev_long_flags_kernel, dim3(rb), dim3(256), 0, s, cptr, (int)L.src_rows, is_long, nchunk);
+    HGNN_LAUNCH(dev_long_flags_kernel, dim3(rb), dim3(256), 0, s, cptr, (int)L.src_rows, nchunk);
     {
       size_t nb = lib_bytes;
-      he = hipcub::DeviceScan::ExclusiveSum(lib_tmp, nb, is_long, long_at, (int)L.src_rows + 1, s);
-      nb = lib_bytes;
-      if (he == hipSuccess) he = hipcub::DeviceScan::ExclusiveSum(lib_tmp, nb, nchunk, chunk_at, (int)L.src_rows + 1, s);
+      he = hipcub::DeviceScan::ExclusiveSum(lib_tmp, nb, nchunk, chunk_at, (int)L.src_rows + 1, s);
       if (he != hipSuccess) break;
     }
-    HGNN_LAUNCH(dev_chunk_lists_kernel, dim3(rb), dim3(256), 0, s, cptr, (int)L.src_rows, long_at, chunk_at, base + L.o_long_row,
-                base + L.o_long_chunk0, base + L.o_chunk_row, base + L.o_chunk_beg, counts);
+    HGNN_LAUNCH(dev_chunk_lists_kernel, dim3(rb), dim3(256), 0, s, cptr, (int)L.src_rows, chunk_at, base + L.o_chunk_row,
+                base + L.o_chunk_beg, counts);
     // the permutations: on the device for the attention variant (cperm), host views otherwise
     if (E > 0) {
       const bool cperm_on_device = ctx->agg == HGNN_AGG_ATTN;
@@ -371,8 +354,7 @@ extern "C" hgnn_status hgnn_build_semantic_csr_device(hgnn_ctx *ctx, void *strea
                     (c[2] & kBadSrc) ? "source index outside its type's rows " : "", (c[2] & kBadDst) ? "destination index outside its type's rows" : "");
       return fail(HGNN_EINVAL, buf);
     }
-    g->L[l].n_long = c[0];
-    g->L[l].n_chunks = c[1];
+    g->L[l].n_chunks = c[0];
     g->L[l].tedges = g->slab.host[g->L[l].o_cptr + g->L[l].src_rows];
   }
   he = hipEventRecord(g->ready, s);

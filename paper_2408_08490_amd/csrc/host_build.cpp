@@ -625,23 +625,17 @@ static bool build_layer(hgnn_ctx *ctx, ThreadPool &pool, LayerScratch &bd, hgnn_
   L.tedges = base2[B2];
   tm.lap("csc level-2 buckets");
 
-  // long transpose rows are cut into chunks so that no single wave walks thousands of edges
+  // long transpose rows are cut into chunks so that no single block walks thousands of edges
   int32_t *chunk_row = base + L.o_chunk_row, *chunk_beg = base + L.o_chunk_beg;
-  int32_t *long_row = base + L.o_long_row, *long_chunk0 = base + L.o_long_chunk0;
-  int32_t nl = 0, nc = 0;
+  int32_t nc = 0;
   for (int b = 0; b < B2; ++b)
     for (int32_t c : longs[b]) {
-      long_row[nl] = c;
-      long_chunk0[nl] = nc;
-      ++nl;
       for (int32_t q = cptr[c]; q < cptr[c + 1]; q += kChunk) {
         chunk_row[nc] = c;
         chunk_beg[nc] = q;
         ++nc;
       }
     }
-  long_chunk0[nl] = nc;
-  L.n_long = nl;
   L.n_chunks = nc;
   tm.lap("long-row chunks");
   return true;

@@ -6,6 +6,7 @@
 #include "common.h"
 #include "bias_reduce.h"
 #include "device_types.h"
+#include "long_rows.h"
 #include "transpose_jobs.h"
 
 namespace hgnn {
@@ -185,12 +186,11 @@ hgnn_status launch_spmm_fwd(hipStream_t s, int dtype, const LayerDev &L, const T
 // ------------------------------------------------------------------------------------------
 // Backward of the aggregation for ragged widths: dx[c] = sum over the transpose row c of dz[crow] (dz rows arrive
 // already scaled by 1/|N_r(v)|) plus, for destination rows, the root-term gradient.
-// Rows longer than kLongRow are cut into chunks of kChunk edges: phase 0 handles the short rows
-// and writes fp32 partial sums for the chunks, phase 1 adds up the partials of each long row.
-// Blocks are cut per vertex type (lanes per row then fit the type's width).  The dz row of an entry starts at
-// base_r + rho F with one constant per relation; the relation of an entry is one of the few that read this type, which
-// a scan with the constants in scalar registers finds without a memory access (a binary search per entry cost five
-// dependent loads: 114 us -> 33 us on 10 types of 32 to 384 floats, 512 targets).
+// Rows longer than kLongRow are taken in pieces by the first blocks (long_rows.h).  The others are cut per vertex type
+// (lanes per row then fit the type's width).  The dz row of an entry starts at base_r + rho F with one constant per
+// relation; the relation of an entry is one of the few that read this type, which a scan with the constants in scalar
+// registers finds without a memory access (a binary search per entry cost five dependent loads: 114 us -> 33 us on 10 types
+// of 32 to 384 floats, 512 targets).
 // ------------------------------------------------------------------------------------------
 struct SrcTiles {
   int32_t tile_off[kMaxT + 1];   // blocks before vertex type t
@@ -199,38 +199,62 @@ struct SrcTiles {
   uint8_t rel[kMaxR];
 };
 
+// Start of the dz row of merged row rho, in 16-byte pieces, for one of the relations [j0, j1) that read a type of nvec
+// pieces: ascending relations, the last one that starts at or before the row is its own.
+template <typename T>
+__device__ __forceinline__ int64_t dz_row(const SrcTiles &sl, const RelTab &rt, int j0, int j1, int nvec, int rho) {
+  int64_t at = 0;
+  for (int j = j0; j < j1; ++j) {
+    const int r = sl.rel[j], off = sl.row_off[r];
+    const int64_t base = ((int64_t)rt.z_off4[r] * 4) / Vec16<T>::N - (int64_t)off * nvec;
+    if (rho >= off) at = base;
+  }
+  return at + (int64_t)rho * nvec;
+}
+
 template <typename T>
 __global__ void __launch_bounds__(256) spmm_bwd_kernel(LayerDev L, TypeTab tt, RelTab rt, SrcTiles sl, uint32_t root_mask, uint32_t want,
                                                         const T *__restrict__ dz, T *__restrict__ dx,
-                                                        float *__restrict__ partial, int max_dim, int row_blocks,
-                                                        int chunk_lanes_log2) {
+                                                        float *__restrict__ partial, int max_dim) {
   using V = Vec16<T>;
-  const bool chunk_part = (int)blockIdx.x >= row_blocks;
-  int c, beg, end, t = 0, l2, item = 0;
-  if (!chunk_part) {
-    while ((int)blockIdx.x >= sl.tile_off[t + 1]) ++t;
-    l2 = row_lanes_log2(tt.in_dim[t] / V::N);
-    c = tt.row_off[t] + ((int)blockIdx.x - sl.tile_off[t]) * (256 >> l2) + (threadIdx.x >> l2);
-    if (c >= tt.row_off[t + 1]) return;
-    beg = L.cptr[c];
-    end = L.cptr[c + 1];
-    if (end - beg > kLongRow) return;
-  } else {
-    l2 = chunk_lanes_log2;
-    item = ((int)blockIdx.x - row_blocks) * (256 >> l2) + (threadIdx.x >> l2);
-    if (item >= L.n_chunks) return;
-    c = L.chunk_row[item];
-    while (c >= tt.row_off[t + 1]) ++t;
+  const uint4 *zb = reinterpret_cast<const uint4 *>(dz);
+  int t = 0;
+  if ((int)blockIdx.x < L.n_chunks) {
+    __shared__ LongLds<V::N> sm;
+    __shared__ int64_t s_at[kChunk];
+    const LongPiece p = long_piece(L, blockIdx.x);
+    while (p.c >= tt.row_off[t + 1]) ++t;
     if (!((want >> t) & 1u)) return;  // the caller does not want input gradients of this vertex type
-    beg = L.chunk_beg[item];
-    end = min(beg + kChunk, L.cptr[c + 1]);
+    const int F = tt.in_dim[t], nvec = F / V::N, cl = p.c - tt.row_off[t];
+    for (int i = threadIdx.x; i < p.n; i += 256) s_at[i] = dz_row<T>(sl, rt, sl.first[t], sl.first[t + 1], nvec, L.crow[p.beg + i]);
+    __syncthreads();
+    long_row_piece<V::N>(p, blockIdx.x, row_lanes_log2(nvec), nvec, sm, partial, max_dim, L.chunk_count,
+      [&](int q, int g, int groups, float (&acc)[V::N]) {
+        for (int i = g; i < p.n; i += 4 * groups) {
+          uint4 v[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) v[u] = zb[s_at[min(i + u * groups, p.n - 1)] + q];
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            if (i + u * groups < p.n) V::add(acc, v[u]);
+        }
+      },
+      [&](int q, float (&acc)[V::N]) {
+        if (cl < tt.n_dst[t] && ((root_mask >> t) & 1u)) V::add(acc, reinterpret_cast<const uint4 *>(dz + (int64_t)rt.zroot_off4[t] * 4 + (int64_t)cl * F)[q]);
+        reinterpret_cast<uint4 *>(dx + tt.elem_off[t] + (int64_t)cl * F)[q] = V::pack(acc);
+      });
+    return;
   }
+  const int b = (int)blockIdx.x - L.n_chunks;
+  while (b >= sl.tile_off[t + 1]) ++t;
+  const int F = tt.in_dim[t], nvec = F / V::N, l2 = row_lanes_log2(nvec);
+  const int c = tt.row_off[t] + (b - sl.tile_off[t]) * (256 >> l2) + (threadIdx.x >> l2);
+  if (c >= tt.row_off[t + 1]) return;
+  const int beg = L.cptr[c], end = L.cptr[c + 1];
+  if (end - beg > kLongRow) return;
   const int lpr = 1 << l2, lane = threadIdx.x & (lpr - 1);
-  const int F = tt.in_dim[t];
-  const int nvec = F / V::N;
   const int cl = c - tt.row_off[t];
   const int j0 = sl.first[t], j1 = sl.first[t + 1];
-  const uint4 *zb = reinterpret_cast<const uint4 *>(dz);
   for (int q = lane; q < nvec; q += lpr) {
     float acc[V::N];
 #pragma unroll
@@ -244,7 +268,7 @@ __global__ void __launch_bounds__(256) spmm_bwd_kernel(LayerDev L, TypeTab tt, R
         rho[u] = L.crow[min(e + u, end - 1)];
         at[u] = 0;
       }
-      for (int j = j0; j < j1; ++j) {   // ascending relations: the last one that starts at or before the row is its own
+      for (int j = j0; j < j1; ++j) {   // dz_row for four entries at once
         const int r = sl.rel[j], off = sl.row_off[r];
         const int64_t base = ((int64_t)rt.z_off4[r] * 4) / V::N - (int64_t)off * nvec;
 #pragma unroll
@@ -257,73 +281,11 @@ __global__ void __launch_bounds__(256) spmm_bwd_kernel(LayerDev L, TypeTab tt, R
       for (int u = 0; u < 4; ++u)
         if (e + u < end) V::add(acc, v[u]);
     }
-    if (!chunk_part) {
-      if (cl < tt.n_dst[t] && ((root_mask >> t) & 1u)) {
-        const T *zr = dz + (int64_t)rt.zroot_off4[t] * 4 + (int64_t)cl * F;
-        V::add(acc, reinterpret_cast<const uint4 *>(zr)[q]);
-      }
-      reinterpret_cast<uint4 *>(dx + tt.elem_off[t] + (int64_t)cl * F)[q] = V::pack(acc);
-    } else {
-      float *pp = partial + (int64_t)item * max_dim + q * V::N;
-#pragma unroll
-      for (int i = 0; i < V::N; ++i) pp[i] = acc[i];
+    if (cl < tt.n_dst[t] && ((root_mask >> t) & 1u)) {
+      const T *zr = dz + (int64_t)rt.zroot_off4[t] * 4 + (int64_t)cl * F;
+      V::add(acc, reinterpret_cast<const uint4 *>(zr)[q]);
     }
-  }
-}
-
-// Long rows: sums the chunk partials of one source row (one block per row), adds the root part and writes
-// the row.  W = floats per load (4 when the row width allows).  The block's threads form `groups` groups of
-// `lanes` threads; group g sums chunks g, g + groups, ... four at a time, LDS adds the groups up.
-template <typename T, int W>
-__global__ void __launch_bounds__(256) spmm_bwd_long_kernel(LayerDev L, TypeTab tt, RelTab rt, uint32_t root_mask, uint32_t want,
-                                                             const T *__restrict__ dz, T *__restrict__ dx,
-                                                             const float *__restrict__ partial, int max_dim) {
-  typedef float fw __attribute__((ext_vector_type(W)));
-  __shared__ float red[256 * W];
-  const int i = blockIdx.x;  // one block per long row
-  const int c = L.long_row[i];
-  int t = 0;
-  while (c >= tt.row_off[t + 1]) ++t;
-  if (!((want >> t) & 1u)) return;
-  const int F = tt.in_dim[t];
-  const int cl = c - tt.row_off[t];
-  const int j0 = L.long_chunk0[i], j1 = L.long_chunk0[i + 1];
-  const bool root = cl < tt.n_dst[t] && ((root_mask >> t) & 1u);
-  const int nw = F / W;                       // loads per row (W divides F)
-  int lanes = 1;
-  while (lanes < nw && lanes < 256) lanes <<= 1;
-  const int groups = 256 / lanes, g = threadIdx.x / lanes, ln = threadIdx.x % lanes;
-  for (int q0 = 0; q0 < nw; q0 += lanes) {    // more than one pass only for rows wider than 256 loads
-    const int q = q0 + ln;
-    fw acc = {};
-    if (q < nw) {
-      int j = j0 + g;
-      for (; j + 3 * groups < j1; j += 4 * groups) {
-        const fw v0 = *reinterpret_cast<const fw *>(partial + (int64_t)j * max_dim + q * W);
-        const fw v1 = *reinterpret_cast<const fw *>(partial + (int64_t)(j + groups) * max_dim + q * W);
-        const fw v2 = *reinterpret_cast<const fw *>(partial + (int64_t)(j + 2 * groups) * max_dim + q * W);
-        const fw v3 = *reinterpret_cast<const fw *>(partial + (int64_t)(j + 3 * groups) * max_dim + q * W);
-        acc += (v0 + v1) + (v2 + v3);
-      }
-      for (; j < j1; j += groups) acc += *reinterpret_cast<const fw *>(partial + (int64_t)j * max_dim + q * W);
-    }
-    if (groups > 1) {
-      *reinterpret_cast<fw *>(red + threadIdx.x * W) = acc;
-      __syncthreads();
-      if (g == 0) {
-        for (int o = 1; o < groups; ++o) acc += *reinterpret_cast<const fw *>(red + (o * lanes + ln) * W);
-      }
-    }
-    if (g == 0 && q < nw) {
-#pragma unroll
-      for (int k = 0; k < W; ++k) {
-        const int f = q * W + k;
-        float v = acc[k];
-        if (root) v += to_float(dz[(int64_t)rt.zroot_off4[t] * 4 + (int64_t)cl * F + f]);
-        dx[tt.elem_off[t] + (int64_t)cl * F + f] = from_float<T>(v);
-      }
-    }
-    if (groups > 1) __syncthreads();
+    reinterpret_cast<uint4 *>(dx + tt.elem_off[t] + (int64_t)cl * F)[q] = V::pack(acc);
   }
 }
 
@@ -337,8 +299,8 @@ hgnn_status launch_spmm_bwd(hipStream_t s, int dtype, const LayerDev &L, const T
     if (pt.w_root[t]) root_mask |= 1u << t;
     if (tt.in_dim[t] != tt.in_dim[0]) uniform = false;
   }
-  // rows up to kLongRow edges: the uniform-width kernel when it applies, else the one for ragged widths
-  // (either launch also carries the chunks of the long rows; max_dim is the common width in the uniform one)
+  // the uniform-width kernel when it applies, else the one for ragged widths (the rows of `partial` are max_dim floats
+  // long, which is the common width in the uniform one)
   if (uniform && launch_spmm_bwd_uniform(s, dtype, L, tt, rt, pt, tt.in_dim[0], want, dz, dx, partial)) {
     HGNN_HIP(hipGetLastError());
   } else {
@@ -354,31 +316,14 @@ hgnn_status launch_spmm_bwd(hipStream_t s, int dtype, const LayerDev &L, const T
         if (rt.src[r] == t) sl.rel[n++] = (uint8_t)r;
     }
     sl.first[tt.num_types] = (uint16_t)n;
-    const int l2 = row_lanes_log2(max_dim * es / 16), row_blocks = sl.tile_off[tt.num_types];
-    const dim3 grid(row_blocks + (L.n_chunks + (256 >> l2) - 1) / (256 >> l2));
+    const dim3 grid(L.n_chunks + sl.tile_off[tt.num_types]);
     if (grid.x > 0) {
       if (dtype == HGNN_BF16)
-        HGNN_LAUNCH(spmm_bwd_kernel<bf16>, grid, dim3(256), 0, s, L, tt, rt, sl, root_mask, want, (const bf16 *)dz, (bf16 *)dx, partial,
-                    max_dim, row_blocks, l2);
+        HGNN_LAUNCH(spmm_bwd_kernel<bf16>, grid, dim3(256), 0, s, L, tt, rt, sl, root_mask, want, (const bf16 *)dz, (bf16 *)dx, partial, max_dim);
       else
-        HGNN_LAUNCH(spmm_bwd_kernel<float>, grid, dim3(256), 0, s, L, tt, rt, sl, root_mask, want, (const float *)dz, (float *)dx, partial,
-                    max_dim, row_blocks, l2);
+        HGNN_LAUNCH(spmm_bwd_kernel<float>, grid, dim3(256), 0, s, L, tt, rt, sl, root_mask, want, (const float *)dz, (float *)dx, partial, max_dim);
       HGNN_HIP(hipGetLastError());
     }
-  }
-  if (L.n_long > 0) {
-    bool w4 = (max_dim % 4) == 0;   // every row of the partial buffer starts 16-byte aligned
-    for (int t = 0; t < tt.num_types; ++t)
-      if (tt.in_dim[t] % 4) w4 = false;
-    const dim3 g(L.n_long), b(256);
-    if (dtype == HGNN_BF16) {
-      if (w4) HGNN_LAUNCH((spmm_bwd_long_kernel<bf16, 4>), g, b, 0, s, L, tt, rt, root_mask, want, (const bf16 *)dz, (bf16 *)dx, partial, max_dim);
-      else HGNN_LAUNCH((spmm_bwd_long_kernel<bf16, 1>), g, b, 0, s, L, tt, rt, root_mask, want, (const bf16 *)dz, (bf16 *)dx, partial, max_dim);
-    } else {
-      if (w4) HGNN_LAUNCH((spmm_bwd_long_kernel<float, 4>), g, b, 0, s, L, tt, rt, root_mask, want, (const float *)dz, (float *)dx, partial, max_dim);
-      else HGNN_LAUNCH((spmm_bwd_long_kernel<float, 1>), g, b, 0, s, L, tt, rt, root_mask, want, (const float *)dz, (float *)dx, partial, max_dim);
-    }
-    HGNN_HIP(hipGetLastError());
   }
   return HGNN_OK;
 }
@@ -650,13 +595,13 @@ hgnn_status launch_zero_grads(hipStream_t s, const TypeTab &tt, const RelTab &rt
 }
 
 // The start of a layer's backward pass in ONE launch: the ReLU mask / bias column sums over G (the first
-// nb_relu blocks; column sums go to bpart), zeroing of the weight gradients (nb_zero blocks) and the zero-padded
-// weight copies (the rest).  The three touch different memory and none is big enough to fill the chip alone.
+// nb_relu blocks; column sums go to bpart), zeroing of the weight gradients (nb_zero blocks) and of the counters of long
+// transpose rows (nb_count), and the zero-padded weight copies (the rest).  They touch different memory and none is big enough to fill the chip alone.
 template <typename T, bool VEC>
 __global__ void __launch_bounds__(256) bwd_prep_kernel(TypeTab tt, RelTab rt, PtrTab pt, WtTab wo, GradPtrTab gt, int H, int ldo,
                                                         int relu, int write, const T *__restrict__ g, const T *__restrict__ h,
                                                         T *__restrict__ gp, float *__restrict__ bpart, int nb_relu, int nb_zero,
-                                                        T *__restrict__ wpad) {
+                                                        int nb_count, T *__restrict__ wpad) {
   int b = blockIdx.x;
   if (b < nb_relu) {
     if constexpr (VEC) relu_bias_rows_vec<T>(tt, b, H, relu, g, h, gp, gt, bpart);
@@ -669,6 +614,11 @@ __global__ void __launch_bounds__(256) bwd_prep_kernel(TypeTab tt, RelTab rt, Pt
     return;
   }
   b -= nb_zero;
+  if (b < nb_count) {
+    for (int i = b * 256 + threadIdx.x; i < gt.n_counters; i += nb_count * 256) gt.counters[i] = 0;
+    return;
+  }
+  b -= nb_count;
   pad_weights_part<T>(tt, rt, pt, wo, H, ldo, wpad, b / 64, b % 64, 64);
 }
 
@@ -689,11 +639,12 @@ hgnn_status launch_bwd_prep(hipStream_t s, int dtype, const TypeTab &tt, const R
   }
   const int segs = rt.num_rels + tt.num_types;
   const int nb_zero = do_zero ? 32 * segs : 0, nb_pad = wpad ? 64 * segs : 0;
-  const int blocks = nb_relu + nb_zero + nb_pad;
+  const int nb_count = std::min(32, (gt.n_counters + 255) / 256);
+  const int blocks = nb_relu + nb_zero + nb_count + nb_pad;
   if (blocks == 0) return HGNN_OK;
 #define HGNN_PREP(TY, VE)                                                                                              \
   HGNN_LAUNCH((bwd_prep_kernel<TY, VE>), dim3(blocks), dim3(256), 0, s, tt, rt, pt, wo, gt, H, ldo, relu, write,        \
-              (const TY *)grad_h, (const TY *)h, (TY *)gp, bpart, nb_relu, nb_zero, (TY *)wpad)
+              (const TY *)grad_h, (const TY *)h, (TY *)gp, bpart, nb_relu, nb_zero, nb_count, (TY *)wpad)
   if (dtype == HGNN_BF16) {
     if (fast) HGNN_PREP(bf16, true); else HGNN_PREP(bf16, false);
   } else {

@@ -14,6 +14,7 @@
 
 #include "common.h"
 #include "device_types.h"
+#include "long_rows.h"
 #include "transpose_jobs.h"
 
 namespace hgnn {
@@ -263,7 +264,7 @@ hgnn_status launch_aggregate_literal(hipStream_t s, int dtype, const LayerDev &L
 // ------------------------------------------------------------------------------------------
 // Transpose: dx[c] = sum over transpose row c of dz[crow] (+ root-term gradient for destination rows).
 // Only the source rows of the vertex types listed in `ranges` are produced; rows longer than kLongRow are
-// left to the chunked path.
+// taken in pieces by the first blocks (long_rows.h).
 struct RowRange {
   int32_t lo, hi;        // merged source rows of one vertex type
   int32_t n_dst;         // its destination rows (prefix)
@@ -276,55 +277,52 @@ struct RowRanges {
 };
 
 template <typename T, int LPRL, int C>
-__global__ void __launch_bounds__(256) spmm_bwd_uniform_kernel(const int32_t *__restrict__ cptr, const int32_t *__restrict__ crow,
-                                                                RowRanges rr, const T *__restrict__ dz, T *__restrict__ dx, int F,
-                                                                const int32_t *__restrict__ chunk_row,
-                                                                const int32_t *__restrict__ chunk_beg, int n_chunks,
+__global__ void __launch_bounds__(256) spmm_bwd_uniform_kernel(LayerDev L, RowRanges rr, const T *__restrict__ dz, T *__restrict__ dx, int F,
                                                                 float *__restrict__ partial) {
   using V = Vec16<T>;
   constexpr int LPR = 1 << LPRL, RPW = 64 / LPR;
   static_assert(RPW < 64, "a lane for each of the RPW + 1 row pointers");
-  const int lane = threadIdx.x & 63;
-  const int wave = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (wave >= rr.total_waves) {
-    // The waves behind the row waves take the chunks of the long rows (kChunk entries each): fp32 partial sums
-    // for the pass that adds them up.  They ride in this launch because on their own they are a launch of a few
-    // blocks that the stream would run after this one.
-    const int item = (wave - rr.total_waves) * RPW + (lane >> LPRL), sub = lane & (LPR - 1);
-    if (item >= n_chunks) return;
-    const int c = chunk_row[item];
-    bool wanted = false;
-    for (int i = 0; i < rr.n; ++i) wanted |= c >= rr.r[i].lo && c < rr.r[i].hi;
-    if (!wanted) return;
-    const int beg = chunk_beg[item], end = min(beg + kChunk, cptr[c + 1]);
-    const int nvec = F / V::N;
-    const uint4 *zb = reinterpret_cast<const uint4 *>(dz);
-    for (int q = sub; q < nvec; q += LPR) {
-      float acc[V::N];
+  const int lane = threadIdx.x & 63, nvec = F / V::N;
+  const uint4 *zb = reinterpret_cast<const uint4 *>(dz);
+  if ((int)blockIdx.x < L.n_chunks) {
+    __shared__ LongLds<V::N> sm;
+    __shared__ int s_row[kChunk];
+    const LongPiece p = long_piece(L, blockIdx.x);
+    int ri = 0;
+    while (ri < rr.n && (p.c < rr.r[ri].lo || p.c >= rr.r[ri].hi)) ++ri;
+    if (ri == rr.n) return;   // nobody wants this type's gradient
+    const RowRange R = rr.r[ri];
+    for (int i = threadIdx.x; i < p.n; i += 256) s_row[i] = L.crow[p.beg + i];
+    __syncthreads();
+    long_row_piece<V::N>(p, blockIdx.x, min(LPRL + (C == 1 ? 0 : C == 2 ? 1 : 2), 6), nvec, sm, partial, F, L.chunk_count,
+      [&](int q, int g, int groups, float (&acc)[V::N]) {
+        for (int i = g; i < p.n; i += 4 * groups) {
+          uint4 v[4];
 #pragma unroll
-      for (int i = 0; i < V::N; ++i) acc[i] = 0.f;
-      int e = beg;
-      for (; e + 4 <= end; e += 4) {
-        const uint4 v0 = zb[(int64_t)crow[e] * nvec + q], v1 = zb[(int64_t)crow[e + 1] * nvec + q];
-        const uint4 v2 = zb[(int64_t)crow[e + 2] * nvec + q], v3 = zb[(int64_t)crow[e + 3] * nvec + q];
-        V::add(acc, v0); V::add(acc, v1); V::add(acc, v2); V::add(acc, v3);
-      }
-      for (; e < end; ++e) V::add(acc, zb[(int64_t)crow[e] * nvec + q]);
-      float *pp = partial + (int64_t)item * F + q * V::N;
+          for (int u = 0; u < 4; ++u) v[u] = zb[(int64_t)s_row[min(i + u * groups, p.n - 1)] * nvec + q];
 #pragma unroll
-      for (int i = 0; i < V::N; ++i) pp[i] = acc[i];
-    }
+          for (int u = 0; u < 4; ++u)
+            if (i + u * groups < p.n) V::add(acc, v[u]);
+        }
+      },
+      [&](int q, float (&acc)[V::N]) {
+        const int cl = p.c - R.lo;
+        if (R.root_off >= 0 && cl < R.n_dst) V::add(acc, reinterpret_cast<const uint4 *>(dz + R.root_off + (int64_t)cl * F)[q]);
+        reinterpret_cast<uint4 *>(dx + (int64_t)p.c * F)[q] = V::pack(acc);
+      });
     return;
   }
+  const int wave = ((int)blockIdx.x - L.n_chunks) * 4 + (threadIdx.x >> 6);
+  if (wave >= rr.total_waves) return;
   int ri = 0;
   while (ri + 1 < rr.n && wave >= rr.r[ri + 1].wave0) ++ri;
   const RowRange R = rr.r[ri];
   const int row0 = R.lo + (wave - R.wave0) * RPW;
   const int nrows = min(RPW, R.hi - row0);
-  const int rp = cptr[row0 + min(lane, nrows)];
+  const int rp = L.cptr[row0 + min(lane, nrows)];
   const int e0 = __shfl(rp, 0), eN = __shfl(rp, nrows);
-  const int c0 = e0 + lane < eN ? crow[e0 + lane] : 0;
-  const int c1 = e0 + 64 + lane < eN ? crow[e0 + 64 + lane] : 0;
+  const int c0 = e0 + lane < eN ? L.crow[e0 + lane] : 0;
+  const int c1 = e0 + 64 + lane < eN ? L.crow[e0 + 64 + lane] : 0;
   const int g = lane >> LPRL, sub = lane & (LPR - 1);
   const int beg = __shfl(rp, min(g, nrows)), end = __shfl(rp, min(g + 1, nrows));
   const bool is_long = end - beg > kLongRow;
@@ -332,8 +330,6 @@ __global__ void __launch_bounds__(256) spmm_bwd_uniform_kernel(const int32_t *__
   int maxlen = len;
 #pragma unroll
   for (int o = 32; o >= LPR; o >>= 1) maxlen = max(maxlen, __shfl_xor(maxlen, o));
-  const int nvec = F / V::N;
-  const uint4 *zb = reinterpret_cast<const uint4 *>(dz);
   float acc[C][V::N];
 #pragma unroll
   for (int p = 0; p < C; ++p)
@@ -348,7 +344,7 @@ __global__ void __launch_bounds__(256) spmm_bwd_uniform_kernel(const int32_t *__
     for (int j = 0; j < 4; ++j) {
       const bool on = i + j < len;
       int cj = col[j];
-      if (on && beg - e0 + i + j >= 128) cj = crow[beg + i + j];
+      if (on && beg - e0 + i + j >= 128) cj = L.crow[beg + i + j];
 #pragma unroll
       for (int p = 0; p < C; ++p) {
         const int q = sub + p * LPR;
@@ -381,10 +377,8 @@ static void launch_bwd_uniform(hipStream_t s, const LayerDev &L, RowRanges &rr, 
     w += (rr.r[i].hi - rr.r[i].lo + RPW - 1) / RPW;
   }
   rr.total_waves = w;
-  w += (L.n_chunks + RPW - 1) / RPW;  // the chunk waves
   if (w == 0) return;
-  HGNN_LAUNCH((spmm_bwd_uniform_kernel<T, LPRL, C>), dim3((w + 3) / 4), dim3(256), 0, s, L.cptr, L.crow, rr, (const T *)dz,
-                     (T *)dx, F, L.chunk_row, L.chunk_beg, L.n_chunks, partial);
+  HGNN_LAUNCH((spmm_bwd_uniform_kernel<T, LPRL, C>), dim3(L.n_chunks + (w + 3) / 4), dim3(256), 0, s, L, rr, (const T *)dz, (T *)dx, F, partial);
 }
 
 bool launch_spmm_bwd_uniform(hipStream_t s, int dtype, const LayerDev &L, const TypeTab &tt, const RelTab &rt, const PtrTab &pt,
