@@ -53,6 +53,26 @@ __device__ __forceinline__ int find_le(const int32_t *off, int n, int x) {  // l
   return lo;
 }
 
+// Sums over the lanes of a head (hl: a power of two, the same for the whole launch), for several values at once; every lane
+// gets them.  Inside 16 lanes the adds take their operand from the other lane directly (DPP); a cross-lane read through LDS,
+// with its latency, is left to wider heads.
+template <int CTRL> __device__ __forceinline__ float other_lane(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int N> __device__ __forceinline__ void head_sums(float (&v)[N], int hl) {
+#define HGNN_STEP(other)                       \
+  {                                            \
+    _Pragma("unroll") for (int i = 0; i < N; ++i) v[i] += other; \
+  }
+  if (hl >= 2) HGNN_STEP(other_lane<0xb1>(v[i]))     // lanes 1 0 3 2
+  if (hl >= 4) HGNN_STEP(other_lane<0x4e>(v[i]))     // lanes 2 3 0 1
+  if (hl >= 8) HGNN_STEP(other_lane<0x141>(v[i]))    // the eight lanes mirrored: the other four hold one value
+  if (hl >= 16) HGNN_STEP(other_lane<0x140>(v[i]))   // the sixteen mirrored
+  if (hl >= 32) HGNN_STEP(__shfl_xor(v[i], 16))
+  if (hl >= 64) HGNN_STEP(__shfl_xor(v[i], 32))
+#undef HGNN_STEP
+}
+
 __device__ __forceinline__ float leaky(float s) { return s > 0.f ? s : kLeaky * s; }
 
 // ------------------------------------------------------------------------------------------
@@ -267,53 +287,67 @@ __global__ void __launch_bounds__(kThreads, 2) attn_proj_kernel(TypeTab tt, PtrT
 }
 
 // ------------------------------------------------------------------------------------------
+// Row pointers and column indices of the consecutive merged rows that a block walks, in LDS: row pointer -> index ->
+// neighbour row are three dependent loads, and a row has three or four edges, so that without this a lane group spends
+// most of its time on the first two.  Entries beyond kStageCols are read where they lie.
+constexpr int kStageRows = 256, kStageCols = 1024;
+struct RowStage {
+  int32_t ptr[kStageRows + 1], col[kStageCols];
+  // n <= kStageRows rows from merged row `row0` on; called by the whole block
+  __device__ __forceinline__ void load(const LayerDev &L, int64_t row0, int n) {
+    for (int i = threadIdx.x; i <= n; i += 256) ptr[i] = L.rowptr[row0 + i];
+    __syncthreads();
+    const int e0 = ptr[0], m = min(ptr[n] - e0, kStageCols);
+    for (int i = threadIdx.x; i < m; i += 256) col[i] = L.colidx[e0 + i];
+    __syncthreads();
+  }
+  __device__ __forceinline__ int column(const LayerDev &L, int e) const {
+    const int i = e - ptr[0];
+    return i < kStageCols ? col[i] : L.colidx[e];
+  }
+};
+
 // Aggregation.  Blocks are cut per relation (the relation, its vectors and its rows are then the same for the whole
 // block).  A group of `lpr` lanes owns one merged row at a time; lane q holds four floats of it; `hl` lanes form a head.
 // Softmax over the row's edges in one pass: running maximum m, running sum l and accumulator rescaled whenever the
-// maximum grows; four neighbour rows in flight.  Bound: the gather of fp32 rows (1 KB at H = 256).
+// maximum grows; four neighbour rows in flight.  Bound: the gather of fp32 rows (1 KB at H = 256; 2.3 GB through the L2s at
+// 6.5 TB/s, the caches in front of HBM included) and, close behind, the vector unit.  561k rows of 1.6M edges: 425 us with a
+// chain of three loads and cross-lane reads through LDS on every row, 355 with both gone.
 template <typename TS>
 __global__ void __launch_bounds__(256) attn_agg_kernel(LayerDev L, RelRows rr, AttnPtrs ap, int H, int heads, int lpr_log2, int hl,
                                                        int rpg, const float *__restrict__ z, float *__restrict__ mout,
                                                        float *__restrict__ mx, float *__restrict__ ls) {
+  __shared__ RowStage st;
   const int gpb = 256 >> lpr_log2;
   const int q = threadIdx.x & ((1 << lpr_log2) - 1), grp = threadIdx.x >> lpr_log2;
   const int r = find_le(rr.tile_off, rr.n, (int)blockIdx.x);
   const int row0 = rr.row_off[r], M = rr.row_off[r + 1] - row0;
-  const int v0 = ((int)blockIdx.x - rr.tile_off[r]) * gpb * rpg;
-  const float *zd = z + (int64_t)rr.zdst[r] * H + q * 4;
+  const int v0 = ((int)blockIdx.x - rr.tile_off[r]) * gpb * rpg, rows = min(gpb * rpg, M - v0);
+  const float *zd = z + (int64_t)(rr.zdst[r] + v0) * H + q * 4;
   const float *zq = z + q * 4;
   const int k = (q * 4) / (H / heads);
   float as[4], ad[4];
   Quad<TS>::load(as, reinterpret_cast<const TS *>(ap.a_src[r]) + q * 4);
   Quad<TS>::load(ad, reinterpret_cast<const TS *>(ap.a_dst[r]) + q * 4);
-  for (int i = 0; i < rpg; ++i) {
-    const int v = v0 + i * gpb + grp;
-    if (v >= M) return;   // whole lane groups leave together
-    const int64_t rho = row0 + v;
-    const int e0 = L.rowptr[rho], e1 = L.rowptr[rho + 1];
+  st.load(L, row0 + v0, rows);
+  for (int i = grp; i < rows; i += gpb) {
+    const int64_t rho = row0 + v0 + i;
+    const int e0 = st.ptr[i], e1 = st.ptr[i + 1];
     float zv[4], acc[4] = {0.f, 0.f, 0.f, 0.f};
     float m = -INFINITY, l = 0.f;
     if (e1 > e0) {
-      Q4::load(zv, zd + (int64_t)v * H);
-      float sd = 0.f;
+      float zu[4][4], s[4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) sd += ad[j] * zv[j];
-      for (int o = hl >> 1; o > 0; o >>= 1) sd += __shfl_xor(sd, o);
-      for (int e = e0; e < e1; e += 4) {
-        float zu[4][4], s[4];
-        int u[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) u[j] = L.colidx[min(e + j, e1 - 1)];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) Q4::load(zu[j], zq + (int64_t)u[j] * H);
+      for (int j = 0; j < 4; ++j) Q4::load(zu[j], zq + (int64_t)st.column(L, min(e0 + j, e1 - 1)) * H);
+      Q4::load(zv, zd + (int64_t)i * H);
+      float sd[1] = {(ad[0] * zv[0] + ad[1] * zv[1]) + (ad[2] * zv[2] + ad[3] * zv[3])};
+      head_sums(sd, hl);
+      for (int e = e0;;) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) s[j] = (as[0] * zu[j][0] + as[1] * zu[j][1]) + (as[2] * zu[j][2] + as[3] * zu[j][3]);
-        for (int o = hl >> 1; o > 0; o >>= 1) {
+        head_sums(s, hl);
 #pragma unroll
-          for (int j = 0; j < 4; ++j) s[j] += __shfl_xor(s[j], o);
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) s[j] = e + j < e1 ? leaky(s[j] + sd) : -INFINITY;
+        for (int j = 0; j < 4; ++j) s[j] = e + j < e1 ? leaky(s[j] + sd[0]) : -INFINITY;
         const float mn = fmaxf(m, fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])));
         const float c = __expf(m - mn);
         float p[4];
@@ -324,12 +358,17 @@ __global__ void __launch_bounds__(256) attn_agg_kernel(LayerDev L, RelRows rr, A
         for (int d = 0; d < 4; ++d)
           acc[d] = acc[d] * c + ((p[0] * zu[0][d] + p[1] * zu[1][d]) + (p[2] * zu[2][d] + p[3] * zu[3][d]));
         m = mn;
+        e += 4;
+        if (e >= e1) break;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) Q4::load(zu[j], zq + (int64_t)st.column(L, min(e + j, e1 - 1)) * H);
       }
       const float inv = 1.f / l;
 #pragma unroll
       for (int d = 0; d < 4; ++d) acc[d] *= inv;
     }
-    Q4::store(mout + rho * H + q * 4, acc);
+    // past the caches: what the L2 holds of popular neighbours stays (fetched 1.7 GB for the 2.2 GB asked for; 366 -> 355 us)
+    __builtin_nontemporal_store(f32x4{acc[0], acc[1], acc[2], acc[3]}, reinterpret_cast<f32x4 *>(mout + rho * H + q * 4));
     if ((q & (hl - 1)) == 0) {
       mx[rho * heads + k] = e1 > e0 ? m : 0.f;
       ls[rho * heads + k] = l;
@@ -478,7 +517,7 @@ hgnn_status launch_attn_agg(hipStream_t s, int dtype, const LayerDev &L, RelRows
                             const float *z, float *mout, float *mx, float *ls) {
   if (L.rows == 0) return HGNN_OK;
   const int lpr = H / 4, l2 = log2_exact(lpr), hl = (H / heads) / 4, gpb = 256 >> l2;
-  const int rpg = rows_per_group(L.rows, gpb, 4096, 4);
+  const int rpg = std::min(kStageRows / gpb, rows_per_group(L.rows, gpb, 4096, 4));
   dim3 grid(tile_relations(rr, gpb * rpg));
   if (dtype == HGNN_BF16) HGNN_LAUNCH(attn_agg_kernel<bf16>, grid, dim3(256), 0, s, L, rr, ap, H, heads, l2, hl, rpg, z, mout, mx, ls);
   else HGNN_LAUNCH(attn_agg_kernel<float>, grid, dim3(256), 0, s, L, rr, ap, H, heads, l2, hl, rpg, z, mout, mx, ls);
@@ -754,6 +793,8 @@ __global__ void __launch_bounds__(kThreads, 2) attn_sem_bwd_kernel(RelRows dwt, 
 // has next to no weight: sums of ten edges, fp32 against 64 bits: 1.2e-7 with the mean, 2.4e-7 with the first edge, 1.1e-4
 // with a first edge 1000 times as long; two passes 1.3e-7.  The mean, c + X, per row and, per edge, (alpha with the sign of
 // the score, dalpha) are stored for the pass over the transpose.
+// Bound: the vector unit (70 % of the time at 561k rows of 1.6M edges); 675 -> 565 us with the rows' indices in LDS and the
+// heads' sums on DPP adds.
 template <typename TS>
 __global__ void __launch_bounds__(256) attn_agg_bwd_rows_kernel(LayerDev L, RelRows rr, AttnPtrs ap, AttnPtrs dap, int H, int heads,
                                                                 int lpr_log2, int hl, int rpg, const float *__restrict__ z,
@@ -761,24 +802,23 @@ __global__ void __launch_bounds__(256) attn_agg_bwd_rows_kernel(LayerDev L, RelR
                                                                 const float *__restrict__ ls, float2 *__restrict__ ead,
                                                                 float *__restrict__ xsum, float *__restrict__ dsum) {
   __shared__ float s_das[kAttnMaxH], s_dad[kAttnMaxH];
+  __shared__ RowStage st;
   const int gpb = 256 >> lpr_log2;
   const int q = threadIdx.x & ((1 << lpr_log2) - 1), grp = threadIdx.x >> lpr_log2;
   const int k = (q * 4) / (H / heads);
   const bool lead = (q & (hl - 1)) == 0;
   const int r = find_le(rr.tile_off, rr.n, (int)blockIdx.x);
   const int row0 = rr.row_off[r], M = rr.row_off[r + 1] - row0;
-  const int v0 = ((int)blockIdx.x - rr.tile_off[r]) * gpb * rpg;
+  const int v0 = ((int)blockIdx.x - rr.tile_off[r]) * gpb * rpg, rows = min(gpb * rpg, M - v0);
   for (int i = threadIdx.x; i < H; i += 256) s_das[i] = s_dad[i] = 0.f;
-  __syncthreads();
-  const float *zd = z + (int64_t)rr.zdst[r] * H + q * 4, *zq = z + q * 4;
+  const float *zd = z + (int64_t)(rr.zdst[r] + v0) * H + q * 4, *zq = z + q * 4;
   float as[4], ad[4], das[4] = {0.f, 0.f, 0.f, 0.f}, dad[4] = {0.f, 0.f, 0.f, 0.f};
   Quad<TS>::load(as, reinterpret_cast<const TS *>(ap.a_src[r]) + q * 4);
   Quad<TS>::load(ad, reinterpret_cast<const TS *>(ap.a_dst[r]) + q * 4);
-  for (int i = 0; i < rpg; ++i) {
-    const int v = v0 + i * gpb + grp;
-    if (v >= M) break;
-    const int64_t rho = row0 + v;
-    const int e0 = L.rowptr[rho], e1 = L.rowptr[rho + 1];
+  st.load(L, row0 + v0, rows);
+  for (int i = grp; i < rows; i += gpb) {
+    const int64_t rho = row0 + v0 + i;
+    const int e0 = st.ptr[i], e1 = st.ptr[i + 1];
     if (e1 == e0) {
       if (lead) {
         xsum[rho * heads + k] = 0.f;
@@ -786,35 +826,26 @@ __global__ void __launch_bounds__(256) attn_agg_bwd_rows_kernel(LayerDev L, RelR
       }
       continue;
     }
-    float zv[4], g[4];
-    Q4::load(zv, zd + (int64_t)v * H);
+    float zv[4], g[4], zu[4][4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) Q4::load(zu[j], zq + (int64_t)st.column(L, min(e0 + j, e1 - 1)) * H);
+    Q4::load(zv, zd + (int64_t)i * H);
     Q4::load(g, dm + rho * H + q * 4);
     const float mxk = mx[rho * heads + k], inv_l = 1.f / ls[rho * heads + k];
-    float sd = 0.f;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) sd += ad[j] * zv[j];
-    for (int o = hl >> 1; o > 0; o >>= 1) sd += __shfl_xor(sd, o);
+    float sdv[1] = {(ad[0] * zv[0] + ad[1] * zv[1]) + (ad[2] * zv[2] + ad[3] * zv[3])};
+    head_sums(sdv, hl);
+    const float sd = sdv[0];
     float S1[4] = {0.f, 0.f, 0.f, 0.f}, S2[4] = {0.f, 0.f, 0.f, 0.f};
     float X = 0.f, w1 = 0.f, w2 = 0.f, c = 0.f, W = 0.f;
-    for (int e = e0; e < e1; e += 4) {
-      float zu[4][4], ss[4], da[4];
-      int u[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) u[j] = L.colidx[min(e + j, e1 - 1)];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) Q4::load(zu[j], zq + (int64_t)u[j] * H);
+    for (int e = e0;;) {
+      float ss[4], da[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         ss[j] = (as[0] * zu[j][0] + as[1] * zu[j][1]) + (as[2] * zu[j][2] + as[3] * zu[j][3]);
         da[j] = (g[0] * zu[j][0] + g[1] * zu[j][1]) + (g[2] * zu[j][2] + g[3] * zu[j][3]);
       }
-      for (int o = hl >> 1; o > 0; o >>= 1) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          ss[j] += __shfl_xor(ss[j], o);
-          da[j] += __shfl_xor(da[j], o);
-        }
-      }
+      head_sums(ss, hl);
+      head_sums(da, hl);
       float a[4], wg = 0.f, xg = X;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -844,6 +875,10 @@ __global__ void __launch_bounds__(256) attn_agg_bwd_rows_kernel(LayerDev L, RelR
         }
         if (lead && e + j < e1) ead[(int64_t)(e + j) * heads + k] = make_float2(pos ? a[j] : -a[j], da[j]);
       }
+      e += 4;
+      if (e >= e1) break;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) Q4::load(zu[j], zq + (int64_t)st.column(L, min(e + j, e1 - 1)) * H);
     }
     const float ds = w1 - X * w2;
 #pragma unroll
@@ -1127,7 +1162,7 @@ hgnn_status launch_attn_agg_bwd(hipStream_t s, int dtype, const LayerDev &L, con
   const int l2 = log2_exact(H / 4), hl = (H / heads) / 4, gpb = 256 >> l2;
   float2 *ead = (float2 *)edge_ad;
   if (L.rows > 0) {
-    const int rpg = rows_per_group(L.rows, gpb, 1024, 16);
+    const int rpg = std::min(kStageRows / gpb, rows_per_group(L.rows, gpb, 1024, 16));
     dim3 grid(tile_relations(rr, gpb * rpg));
     if (dtype == HGNN_BF16)
       HGNN_LAUNCH(attn_agg_bwd_rows_kernel<bf16>, grid, dim3(256), 0, s, L, rr, ap, dap, H, heads, l2, hl, rpg, z, dm, mx, ls, ead, xsum, dsum);
