@@ -30,6 +30,16 @@ template <> __device__ __forceinline__ bf16 from_float<bf16>(float v) {
   return r;
 }
 
+// Largest i in [0, n) with off[i] <= x, for a table of the kernel's arguments (ascending, off[0] <= x) and an x that is the
+// same for the whole wavefront: a lane looks at an entry each, so that the search costs one memory round trip.  Walking the
+// table with scalar loads is one of 0.1 to 0.25 us per step (104 relations: 3 us in front of a launch's first useful load).
+template <typename I> __device__ __forceinline__ int wave_find(const I *off, int n, int x) {
+  const int lane = threadIdx.x & 63;
+  int c = 0;
+  for (int b = 0; b < n; b += 64) c += __popcll(__ballot(b + lane < n && (int)off[b + lane < n ? b + lane : 0] <= x));
+  return c - 1;
+}
+
 // A 16-byte piece of a feature row: N scalars of T.
 template <typename T> struct Vec16;
 template <> struct Vec16<float> {

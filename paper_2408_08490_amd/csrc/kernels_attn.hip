@@ -320,7 +320,7 @@ __global__ void __launch_bounds__(256) attn_agg_kernel(LayerDev L, RelRows rr, A
   __shared__ RowStage st;
   const int gpb = 256 >> lpr_log2;
   const int q = threadIdx.x & ((1 << lpr_log2) - 1), grp = threadIdx.x >> lpr_log2;
-  const int r = find_le(rr.tile_off, rr.n, (int)blockIdx.x);
+  const int r = wave_find(rr.tile_off, rr.n, (int)blockIdx.x);
   const int row0 = rr.row_off[r], M = rr.row_off[r + 1] - row0;
   const int v0 = ((int)blockIdx.x - rr.tile_off[r]) * gpb * rpg, rows = min(gpb * rpg, M - v0);
   const float *zd = z + (int64_t)(rr.zdst[r] + v0) * H + q * 4;
@@ -385,7 +385,7 @@ __global__ void __launch_bounds__(kThreads, 2) attn_sem_kernel(RelRows rr, int H
   constexpr int TM = 64 * MI;
   __shared__ MixLds<TS, MI> sm;
   __shared__ float red[4];
-  const int r = find_le(rr.tile_off, rr.n, (int)blockIdx.x);
+  const int r = wave_find(rr.tile_off, rr.n, (int)blockIdx.x);
   const int m0 = ((int)blockIdx.x - rr.tile_off[r]) * TM;
   const int64_t row0 = rr.row_off[r];
   const int M = rr.row_off[r + 1] - (int)row0;
@@ -436,7 +436,7 @@ __global__ void __launch_bounds__(256) attn_fuse_kernel(RelRows rr, TypeTiles ty
   if (blockIdx.x == 0 && threadIdx.x < rr.n) beta[threadIdx.x] = sb[threadIdx.x];
   const int gpb = 256 >> lpr_log2;
   const int q = threadIdx.x & ((1 << lpr_log2) - 1), grp = threadIdx.x >> lpr_log2;
-  const int d = find_le(ty.tile_off, ty.n, (int)blockIdx.x);
+  const int d = wave_find(ty.tile_off, ty.n, (int)blockIdx.x);
   const int M = ty.row_off[d + 1] - ty.row_off[d];
   const int v0 = ((int)blockIdx.x - ty.tile_off[d]) * gpb * rpg;
   float bv[4] = {0.f, 0.f, 0.f, 0.f};
@@ -614,7 +614,7 @@ __global__ void __launch_bounds__(256) attn_mask_dbeta_kernel(RelRows rr, TypeTi
   __shared__ float s_b[kAttnMaxH];
   const int lpr = 1 << lpr_log2, gpb = 256 >> lpr_log2;
   const int q = threadIdx.x & (lpr - 1), grp = threadIdx.x >> lpr_log2;
-  const int d = find_le(ty.tile_off, ty.n, (int)blockIdx.x);
+  const int d = wave_find(ty.tile_off, ty.n, (int)blockIdx.x);
   const int M = ty.row_off[d + 1] - ty.row_off[d];
   const int v0 = ((int)blockIdx.x - ty.tile_off[d]) * gpb * 4 * trips;
   const int j0 = ro.first[d], j1 = ro.first[d + 1];
@@ -769,13 +769,13 @@ __global__ void __launch_bounds__(kThreads, 2) attn_sem_bwd_kernel(RelRows dwt, 
   const int before = (int)(b * p.n_dw / total);
   if ((int)((b + 1) * p.n_dw / total) > before) {
     const int tiles_f = (H + 127) / 128, tf = before % tiles_f, sl = before / tiles_f;
-    const int r = find_le(dwt.tile_off, dwt.n, sl);
+    const int r = wave_find(dwt.tile_off, dwt.n, sl);
     const int64_t row0 = dwt.row_off[r];
     const int M = dwt.row_off[r + 1] - (int)row0, k0 = (sl - dwt.tile_off[r]) * p.dw_rows;
     attn_dws_part(sm.dw, mbuf, tbuf, row0, k0, min(k0 + p.dw_rows, M), H, tf * 128, relation_coef(dwt, beta, dbeta, r), qs, dws, dq, dbs);
   } else {
     const int tl = (int)b - before, tiles_n = (H + 127) / 128, tm = tl / tiles_n;
-    const int r = find_le(dmt.tile_off, dmt.n, tm);
+    const int r = wave_find(dmt.tile_off, dmt.n, tm);
     const int64_t row0 = dmt.row_off[r];
     const int M = dmt.row_off[r + 1] - (int)row0;
     attn_dm_part<TS, MI>(sm.dm, tbuf, w_sem, gp + (int64_t)dmt.gdst[r] * H, dm, row0, M, (tm - dmt.tile_off[r]) * 64 * MI,
@@ -807,7 +807,7 @@ __global__ void __launch_bounds__(256) attn_agg_bwd_rows_kernel(LayerDev L, RelR
   const int q = threadIdx.x & ((1 << lpr_log2) - 1), grp = threadIdx.x >> lpr_log2;
   const int k = (q * 4) / (H / heads);
   const bool lead = (q & (hl - 1)) == 0;
-  const int r = find_le(rr.tile_off, rr.n, (int)blockIdx.x);
+  const int r = wave_find(rr.tile_off, rr.n, (int)blockIdx.x);
   const int row0 = rr.row_off[r], M = rr.row_off[r + 1] - row0;
   const int v0 = ((int)blockIdx.x - rr.tile_off[r]) * gpb * rpg, rows = min(gpb * rpg, M - v0);
   for (int i = threadIdx.x; i < H; i += 256) s_das[i] = s_dad[i] = 0.f;

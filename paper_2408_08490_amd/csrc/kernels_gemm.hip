@@ -211,8 +211,7 @@ __device__ __forceinline__ void da_tile_grouped(GemmLds<T, MI, MI> &sm, int bid,
   while (tile >= tiles.tile_off[d + 1]) ++d;
   const int local = tile - tiles.tile_off[d];
   const int u = local % tiles.u_total[d], mt = local / tiles.u_total[d];
-  int e = tiles.first[d];
-  while (e + 1 < tiles.first[d + 1] && u >= tiles.u_off[e + 1]) ++e;
+  const int e = tiles.first[d] + wave_find(tiles.u_off + tiles.first[d], tiles.first[d + 1] - tiles.first[d], u);
   da_tile_at<T, FAST, MI>(sm, tiles.seg[e], mt * BM, (u - tiles.u_off[e]) * BN, L, tt, rt, pt, ldg, gp, dz);
 }
 
@@ -262,8 +261,7 @@ __device__ __forceinline__ void dw_tile(GemmLds<T, MI, MI> &sm, int bid, const T
   local /= tiles_h;
   const int u = local % tiles.u_total[d];
   const int sp = local / tiles.u_total[d];
-  int e = tiles.first[d];
-  while (e + 1 < tiles.first[d + 1] && u >= tiles.u_off[e + 1]) ++e;
+  const int e = tiles.first[d] + wave_find(tiles.u_off + tiles.first[d], tiles.first[d + 1] - tiles.first[d], u);
   const int seg = tiles.seg[e];
   const int tf = u - tiles.u_off[e];
   const bool is_rel = seg < R;

@@ -152,8 +152,13 @@ __global__ void __launch_bounds__(64 * kDirW, 2) gemm_fwd_direct_kernel(DirectAr
   for (int i = 0; i < MT; ++i) arow[i] = min(m0 + 16 * i + fr, M - 1);
 #pragma unroll
   for (int j = 0; j < NT; ++j) brow[j] = min(n0 + 16 * j + fr, H - 1);
-  int si = pa->seg0[d];
   const int si_last = pa->seg0[d + 1] - 1;
+  int si = pa->seg0[d];
+  {   // the segment of the wavefront's first K-step (wave_find on the steps in front of each)
+    int c = 0;
+    for (int b = si; b <= si_last; b += 64) c += __popcll(__ballot(b + lane <= si_last && pa->seg[min(b + lane, si_last)].first <= begin + wave));
+    si += max(c - 1, 0);
+  }
 #define HGNN_LOAD(stage, step_)                                                                      \
   {                                                                                                  \
     const int step = min(step_, end - 1);                                                            \

@@ -20,7 +20,7 @@ struct MergeTab {
   const int32_t *pos[kMaxT];   // index-first baseline: row of the interleaved buffer that holds row i of type t
   const char *inter;           // mode 2: the interleaved buffer rows are read from
   int64_t elem_off[kMaxT + 1];
-  int32_t row_off[kMaxT + 1];
+  int32_t row_off[kMaxT + 4];
   int32_t dim[kMaxT];
   int32_t num_types;
   int32_t mode;                // 0: stores -> type-first buffer; 1: stores -> interleaved buffer; 2: interleaved -> type-first
@@ -31,8 +31,11 @@ __global__ void __launch_bounds__(256) merge_kernel(MergeTab mt, char *out, int 
   const int row = blockIdx.x * (256 >> lpr_log2) + (threadIdx.x >> lpr_log2);
   const int lane = threadIdx.x & (lpr - 1);
   if (row >= mt.row_off[mt.num_types]) return;
-  int t = 0;
-  while (row >= mt.row_off[t + 1]) ++t;
+  int t = 0;   // scalar loads that do not depend on each other; the entries behind the last type's are never reached
+  for (int t0 = 1; t0 < mt.num_types; t0 += 4) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) t += row >= mt.row_off[t0 + u] && t0 + u < mt.num_types ? 1 : 0;
+  }
   const int i = row - mt.row_off[t];
   const int nvec = (mt.dim[t] * esize) >> 4;
   // interleaved position, clamped into the buffer (a caller's bad position cannot leave it)
@@ -109,11 +112,7 @@ __global__ void __launch_bounds__(256) spmm_fwd_kernel(LayerDev L, TypeTab tt, R
     return;
   }
   const int b = (int)blockIdx.x - tj.blocks;
-  int r = 0, r_end = rt.num_rels;
-  while (r_end - r > 1) {
-    const int mid = (r + r_end) >> 1;
-    if (rtl.tile_off[mid] <= b) r = mid; else r_end = mid;
-  }
+  const int r = wave_find(rtl.tile_off, rt.num_rels, b);
   const int st = rt.src[r];
   const int F = tt.in_dim[st];
   const int nvec = F / V::N, l2 = row_lanes_log2(nvec), lpr = 1 << l2;

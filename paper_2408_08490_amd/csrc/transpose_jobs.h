@@ -11,9 +11,8 @@ __device__ __forceinline__ void transpose_jobs_block(const TransposeJobs &tj, in
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
   const int total = tj.tile_off[tj.n];
   const int H = tj.H, tiles_h = (H + 31) / 32;
-  int job = 0;
   for (int tl = b; tl < total; tl += nb) {
-    while (tl >= tj.tile_off[job + 1]) ++job;
+    const int job = wave_find(tj.tile_off, tj.n, tl);
     const int local = tl - tj.tile_off[job];
     const int F = tj.F[job];
     const T *w = reinterpret_cast<const T *>(tj.w[job]);
