@@ -1226,7 +1226,7 @@ static hgnn_status bwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
   if (any_dw && pl.total_dst > 0) {
     // Work list: per destination type its live segments (relations with edges, then the root) and the row blocks of
     // their weight gradients, with the input-gradient tiles of the same launch beside it.  Tiles have 128 rows and
-    // columns, or 64 where the launch would not have a block of 128 for every compute unit.
+    // columns, or 64 (bwd_small_tiles).
     DwTab tl, da_grouped;
     const bool both = want_dx && da_tl.tile_off[da_tl.num_segs] > 0;
     const int bk = pl.es == 2 ? 64 : 32;
@@ -1260,7 +1260,7 @@ static hgnn_status bwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
       split_rows = dw_slice_rows(ctx->dtype, edge, dw_steps, da_steps);
       for (int d = 0; d < T; ++d)
         tl.tile_off[d + 1] = tl.tile_off[d] + tl.u_total[d] * tiles_h * ((pl.tt.n_dst[d] + split_rows - 1) / split_rows);
-      if (edge == 64 || tl.tile_off[T] + (both ? da_grouped.tile_off[T] : 0) >= 256) break;
+      if (edge == 64 || !bwd_small_tiles(ctx->dtype, tl.tile_off[T] + (both ? da_grouped.tile_off[T] : 0), ldg)) break;
     }
     Probe pb(ctx, HGNN_K_GEMM_DW, layer);
     if (both && tl.tile_off[T] > 0) {

@@ -235,7 +235,7 @@ hgnn_status attn_bwd(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_t layer, 
     tt2.out_row_off[i + 1] = pl.tt.row_off[i + 1];
     rt2.zroot_off4[i] = (uint32_t)(pl.tt.elem_off[i] / 4);
   }
-  // tiles of 128 rows and columns, or of 64 where the launch would not have a block of 128 for every compute unit
+  // tiles of 128 rows and columns, or of 64 (bwd_small_tiles)
   int split_rows = 0;
   for (int edge = 128;; edge = 64) {
     std::memset(&dt, 0, sizeof(dt));
@@ -261,7 +261,7 @@ hgnn_status attn_bwd(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_t layer, 
     split_rows = dw_slice_rows(dtype, edge, dw_steps, (int64_t)da.tile_off[T] * ((H + bk - 1) / bk));
     for (int i = 0; i < T; ++i)
       dt.tile_off[i + 1] = dt.tile_off[i] + dt.u_total[i] * tiles_h * (int)((L.n_src[i] + split_rows - 1) / split_rows);
-    if (edge == 64 || dt.tile_off[T] + da.tile_off[T] >= 256) break;
+    if (edge == 64 || !bwd_small_tiles(dtype, dt.tile_off[T] + da.tile_off[T], H)) break;
   }
   Probe pb(ctx, HGNN_K_GEMM_DW, layer);
   const void *dzp = sc + pl.c_dz;

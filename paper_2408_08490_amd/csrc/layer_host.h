@@ -49,6 +49,21 @@ struct AttnVariant {
 };
 AttnVariant &attn_variant();
 
+// Whether a backward launch of `tiles` tiles of 128x128, whose products run over rows of G' of `width` scalars, uses 64x64
+// ones instead.  The chip holds 512 of the large ones at a time and 768 of the small, which are a quarter of the work.
+// Below 256 large ones compute units stay empty.
+// fp32 tiles are split into planes on the way to LDS, and three small blocks of a compute unit cover each other's splitting,
+// loads and barriers better than two large ones; what speaks for the large ones is that an operand is split half as often.
+// They win where their rounds are nearly full (us, large -> small): 352 tiles 30 -> 29, 364 47 -> 37, 624 38 -> 34,
+// 664 68 -> 57, but 496 34 -> 38, 936 98 -> 108, 1044 116 -> 135, 1192 222 -> 276.
+// bf16: small ones where a launch of one round has short products (484 tiles of width 128 23 -> 17, 424 of 256 32 -> 29,
+// 360 of 256 31 -> 29, but 400 of 512 33 -> 37, 756 of 264 39 -> 51).
+static inline bool bwd_small_tiles(int dtype, int tiles, int width) {
+  if (tiles < 256) return true;
+  if (dtype == HGNN_BF16) return tiles < 512 && width <= 256;
+  return tiles < 384 || (tiles > 512 && tiles < 768);
+}
+
 // Rows per slice of the weight-gradient reduction in a launch of `dw_steps` K-steps (over all its tiles) beside
 // `other_steps` K-steps of other tiles.  A block's share is 1/640 of the launch's K-steps (1/1280 with 64x64 tiles, of
 // which twice as many are resident): a bit over the chip's block slots, so that the launch is one long round whose end
