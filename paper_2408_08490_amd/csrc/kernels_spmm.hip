@@ -45,15 +45,16 @@ __global__ void __launch_bounds__(256, (C <= 2 && !ADDR) ? 8 : 1) spmm_fwd_unifo
   using Idx = std::conditional_t<ADDR, unsigned long long, int>;
   constexpr int LPR = 1 << LPRL, RPW = 64 / LPR;
   static_assert(RPW < 64, "a lane for each of the RPW + 1 row pointers");
-  // The first tj.blocks blocks transpose the layer's weights for the GEMM that follows this launch: a few
+  // tj.blocks of the blocks transpose the layer's weights for the GEMM that follows this launch: a few
   // microseconds of work that would otherwise be a launch of its own in front of this one.
   __shared__ T tile[32][33];
-  if ((int)blockIdx.x < tj.blocks) {
-    transpose_jobs_block<T>(tj, blockIdx.x, tj.blocks, tile);
+  const JobSplit js(tj);
+  if (js.transposes(tj)) {
+    transpose_jobs_block<T>(tj, js.tb, tj.blocks, tile);
     return;
   }
   const int lane = threadIdx.x & 63;
-  const int row0 = row_begin + (((int)blockIdx.x - tj.blocks) * 4 + (threadIdx.x >> 6)) * RPW;
+  const int row0 = row_begin + (js.b * 4 + (int)(threadIdx.x >> 6)) * RPW;
   if (row0 >= row_end) return;  // whole wave
   const int nrows = min(RPW, row_end - row0);
   const int rp = rowptr[row0 + min(lane, nrows)];
