@@ -378,6 +378,10 @@ __global__ void __launch_bounds__(256) attn_agg_kernel(LayerDev L, RelRows rr, A
 
 // ------------------------------------------------------------------------------------------
 // Semantic scores: t = tanh(m W_s + b_s) stored for the backward pass; wsum[r] += sum over the segment's rows of q . t
+// The blocks take the rows from the end: what the kernel in front wrote last is still in the memory-side cache (256 MB)
+// when it is read first, and the kernel behind, from the start again, finds what this one touched last.  The same order in
+// the backward's launch between mask and aggregation (561k rows, m and dm of 573 MB each, us: scores 238 -> 230, fusion
+// 168 -> 161, backward 630 -> 617 and the aggregation's rows behind it 569 -> 558).
 template <typename TS, int MI>
 __global__ void __launch_bounds__(kThreads, 2) attn_sem_kernel(RelRows rr, int H, const float *__restrict__ mbuf, const TS *__restrict__ w_sem,
                                                              const TS *__restrict__ b_sem, const TS *__restrict__ q_sem,
@@ -385,8 +389,9 @@ __global__ void __launch_bounds__(kThreads, 2) attn_sem_kernel(RelRows rr, int H
   constexpr int TM = 64 * MI;
   __shared__ MixLds<TS, MI> sm;
   __shared__ float red[4];
-  const int r = wave_find(rr.tile_off, rr.n, (int)blockIdx.x);
-  const int m0 = ((int)blockIdx.x - rr.tile_off[r]) * TM;
+  const int b = (int)(gridDim.x - 1 - blockIdx.x);
+  const int r = wave_find(rr.tile_off, rr.n, b);
+  const int m0 = (b - rr.tile_off[r]) * TM;
   const int64_t row0 = rr.row_off[r];
   const int M = rr.row_off[r + 1] - (int)row0;
   f32x16 acc[MI][2];
@@ -426,9 +431,11 @@ __device__ __forceinline__ void relation_softmax(const RelRows &rr, const float 
 
 // h[v] = act( sum_{r -> type(v)} beta_r m[rel_row_off[r] + v] + b ).  Every block takes the softmax over the relations
 // itself (a few hundred flops; as a launch of one block it cost 5 us); the first one writes it out for the backward.
-template <typename TS>
+// A lane group takes U rows, their loads of one relation in flight together: bound by the read of m (169k rows of 1 KB, 561k
+// of m: one row after the other 161 us, four at once 132, 5 TB/s).
+template <typename TS, int U>
 __global__ void __launch_bounds__(256) attn_fuse_kernel(RelRows rr, TypeTiles ty, RelsOfType ro, PtrTab pt, int H, int relu, int lpr_log2,
-                                                        int rpg, const float *__restrict__ mbuf, const float *__restrict__ wsum,
+                                                        const float *__restrict__ mbuf, const float *__restrict__ wsum,
                                                         float *__restrict__ beta, TS *__restrict__ h) {
   __shared__ float sb[kMaxR];
   relation_softmax(rr, wsum, sb);
@@ -438,26 +445,36 @@ __global__ void __launch_bounds__(256) attn_fuse_kernel(RelRows rr, TypeTiles ty
   const int q = threadIdx.x & ((1 << lpr_log2) - 1), grp = threadIdx.x >> lpr_log2;
   const int d = wave_find(ty.tile_off, ty.n, (int)blockIdx.x);
   const int M = ty.row_off[d + 1] - ty.row_off[d];
-  const int v0 = ((int)blockIdx.x - ty.tile_off[d]) * gpb * rpg;
-  float bv[4] = {0.f, 0.f, 0.f, 0.f};
-  if (pt.bias[d]) Quad<TS>::load(bv, reinterpret_cast<const TS *>(pt.bias[d]) + q * 4);
-  for (int i = 0; i < rpg; ++i) {
-    const int v = v0 + i * gpb + grp;
-    if (v >= M) return;
-    float acc[4] = {bv[0], bv[1], bv[2], bv[3]};
-    for (int j = ro.first[d]; j < ro.first[d + 1]; ++j) {
-      const int r = ro.rel[j];
-      const float b = sb[r];
-      float mv[4];
-      Q4::load(mv, mbuf + ((int64_t)rr.row_off[r] + v) * H + q * 4);
+  const int v0 = ((int)blockIdx.x - ty.tile_off[d]) * gpb * U + grp;
+  if (v0 >= M) return;
+  float acc[U][4];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) acc[c] += b * mv[c];
-    }
+  for (int c = 0; c < 4; ++c) acc[0][c] = 0.f;
+  if (pt.bias[d]) Quad<TS>::load(acc[0], reinterpret_cast<const TS *>(pt.bias[d]) + q * 4);
+#pragma unroll
+  for (int u = 1; u < U; ++u)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[u][c] = acc[0][c];
+  for (int j = ro.first[d]; j < ro.first[d + 1]; ++j) {
+    const int r = ro.rel[j];
+    const float b = sb[r];
+    const float *mr = mbuf + (int64_t)rr.row_off[r] * H + q * 4;
+    float mv[U][4];
+#pragma unroll
+    for (int u = 0; u < U; ++u) Q4::load(mv[u], mr + (int64_t)min(v0 + u * gpb, M - 1) * H);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[u][c] += b * mv[u][c];
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    if (v0 + u * gpb >= M) break;
     if (relu) {
 #pragma unroll
-      for (int c = 0; c < 4; ++c) acc[c] = fmaxf(acc[c], 0.f);
+      for (int c = 0; c < 4; ++c) acc[u][c] = fmaxf(acc[u][c], 0.f);
     }
-    Quad<TS>::store(h + ((int64_t)ty.row_off[d] + v) * H + q * 4, acc);
+    Quad<TS>::store(h + ((int64_t)ty.row_off[d] + v0 + u * gpb) * H + q * 4, acc[u]);
   }
 }
 
@@ -571,10 +588,16 @@ hgnn_status launch_attn_fuse(hipStream_t s, int dtype, const TypeTab &tt, const 
   if (rows == 0) return HGNN_OK;
   RelsOfType ro;
   rels_of_type(rr, tt.num_types, ro);
-  const int l2 = log2_exact(H / 4), gpb = 256 >> l2, rpg = rows_per_group(rows, gpb, 2048, 4);
-  dim3 grid(tile_types(ty, gpb * rpg));
-  if (dtype == HGNN_BF16) HGNN_LAUNCH(attn_fuse_kernel<bf16>, grid, dim3(256), 0, s, rr, ty, ro, pt, H, relu, l2, rpg, mbuf, wsum, beta, (bf16 *)h);
-  else HGNN_LAUNCH(attn_fuse_kernel<float>, grid, dim3(256), 0, s, rr, ty, ro, pt, H, relu, l2, rpg, mbuf, wsum, beta, (float *)h);
+  const int l2 = log2_exact(H / 4), gpb = 256 >> l2;
+  const bool four = rows >= (int64_t)gpb * 4 * 1024;   // while that leaves four blocks per compute unit
+  dim3 grid(tile_types(ty, gpb * (four ? 4 : 1)));
+#define HGNN_FUSE(TY, U_) HGNN_LAUNCH((attn_fuse_kernel<TY, U_>), grid, dim3(256), 0, s, rr, ty, ro, pt, H, relu, l2, mbuf, wsum, beta, (TY *)h)
+  if (dtype == HGNN_BF16) {
+    if (four) HGNN_FUSE(bf16, 4); else HGNN_FUSE(bf16, 1);
+  } else {
+    if (four) HGNN_FUSE(float, 4); else HGNN_FUSE(float, 1);
+  }
+#undef HGNN_FUSE
   HGNN_HIP(hipGetLastError());
   return HGNN_OK;
 }
@@ -765,7 +788,7 @@ __global__ void __launch_bounds__(kThreads, 2) attn_sem_bwd_kernel(RelRows dwt, 
   __shared__ __attribute__((aligned(16))) float qs[kSemDim];
   if (threadIdx.x < kSemDim) qs[threadIdx.x] = to_float(q_sem[threadIdx.x]);
   __syncthreads();
-  const int64_t b = blockIdx.x, total = gridDim.x;
+  const int64_t total = gridDim.x, b = total - 1 - blockIdx.x;   // from the end: see attn_sem_kernel
   const int before = (int)(b * p.n_dw / total);
   if ((int)((b + 1) * p.n_dw / total) > before) {
     const int tiles_f = (H + 127) / 128, tf = before % tiles_f, sl = before / tiles_f;
