@@ -210,9 +210,12 @@ class Model:
         return t
 
     def _typed(self, name, numel):
-        es = 2 if self.dtype == "bf16" else 4
-        raw = self._get(name, numel * es)
-        return raw[: numel * es].view(_tdtype(self.dtype))
+        # kept in the compute type and handed out whole where the size fits: a slice and a view are 2 us of a small pass each
+        t = self._buf.get(name)
+        if t is None or t.numel() < numel:
+            t = torch.empty(max(numel, 128), device=self.dev, dtype=_tdtype(self.dtype))
+            self._buf[name] = t
+        return t if t.numel() == numel else t[:numel]
 
     # ---- host side of a step: upload ids / labels, start the semantic graph build ----
     def prepare(self, mb, global_edge_type=None, use_edge_id=False, device_build=False) -> Batch:
@@ -273,7 +276,7 @@ class Model:
             n0 = sum(n * f for n, f in zip(b.n_rows, self.feat_dim))
             x = self._typed("x0", n0)
             row_off, elem_off = ctx.hgnn_merge_features(self.stores, b.ids_dev, x, self.feat_dim)
-        xs, hs, saved = [x], [], []
+        xs, hs, saved, scratch = [x], [], [], []
         launches = []
         for l, lp in enumerate(self.layers):
             blk = b.blocks[l]
@@ -292,7 +295,7 @@ class Model:
                 ctx.hgnn_layer_fwd_gather(b.graph, l, lp, self.stores, b.ids_dev, xs[-1], h, sv, sc)
             else:
                 ctx.hgnn_layer_fwd(b.graph, l, lp, xs[-1], h, sv, sc)
-            hs.append(h); saved.append(sv); xs.append(h)
+            hs.append(h); saved.append(sv); scratch.append(cb); xs.append(h)
         out = dict(x0=x, h=hs, row_off=row_off, elem_off=elem_off, launches=launches)
         blk = b.blocks[-1]
         H = self.layers[-1].out_dim
@@ -316,8 +319,7 @@ class Model:
         for l in reversed(range(L)):
             lp = self.layers[l]
             blk = b.blocks[l]
-            sb, cb = ctx.hgnn_layer_workspace_bytes(b.graph, l, lp)
-            sc = self._get("scratch", cb)
+            sc = self._get("scratch", scratch[l])
             want_dx = need_input_grad or l > 0
             if layer_grads is not None and layer_grads[l] is not None:
                 g = layer_grads[l]
