@@ -1,0 +1,76 @@
+"""Kernels that walk blocks of rows: the attention aggregation, whose block keeps the indices of its rows in LDS (1024 of them)
+and sums a head over 1 to 64 lanes, and the backward products around the lines between tiles of 64 and of 128 rows."""
+from types import SimpleNamespace as NS
+
+import numpy as np
+import pytest
+
+from oracle import hgnn_oracle as O
+from tests.parity import rel_errors
+from workloads.synth import bf16_round
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"f32": 1e-5, "bf16": 1e-2}   # fp32 sums; terms and results rounded to 2^-9
+
+
+def _run(dtype, n_src, n_dst, src, dst, width, H, heads=0):
+    """Forward and backward of a layer of one relation (attention with heads > 0): pairs (this library, 64 bits)."""
+    import torch
+    from paper_2408_08490_amd.runner import Model
+    rng = np.random.default_rng(len(src) + H)
+    rnd = (lambda a: bf16_round(np.float32(a))) if dtype == "bf16" else np.float32
+    x = [rnd(rng.standard_normal((n, width))) for n in (n_src, n_dst)]
+    lw = NS(in_dim=[width, width], out_dim=H, relu=False, w_type=[], w_rel=[], w_root=[], bias=[rnd(rng.standard_normal(H)) for _ in range(2)])
+    weight = lambda: rnd(rng.standard_normal((width, H)) / width ** 0.5)
+    if heads:
+        lw.w_type = [weight(), weight()]
+        lw.a_src, lw.a_dst = ([rnd(rng.standard_normal((heads, H // heads)) * 0.3)] for _ in range(2))
+        lw.w_sem, lw.b_sem, lw.q_sem = (rnd(rng.standard_normal(s) * 0.1) for s in ((H, 128), 128, 128))
+    else:
+        lw.w_rel, lw.w_root = [weight()], [None, weight()]
+    block = NS(n_src=[n_src, n_dst], n_dst=[0, n_dst], edge_index=np.stack([src, dst]), edge_type=np.zeros(len(src), np.int32))
+    grad = [np.zeros((0, H), np.float32), rnd(rng.standard_normal((n_dst, H)))]
+    mb = NS(ids=[np.arange(n_src), np.arange(n_dst)], blocks=[block], labels=None, grad_out=grad)
+    model = Model(NS(num_types=2, num_rels=1, rel_src=[0], rel_dst=[1]), [width, width], x, [lw], dtype=dtype, loss="dot", target_type=1)
+    bt = model.prepare(mb)
+    out = model.run(bt)
+    torch.cuda.synchronize()
+    if heads:
+        want, cache = O.rgat_layer_forward(x, [(src, dst)], [0], [1], block.n_dst, lw.w_type, lw.a_src, lw.a_dst, lw.w_sem, lw.b_sem,
+                                           lw.q_sem, lw.bias, False, heads)
+        g = O.rgat_layer_backward(cache, grad)
+        dx, pairs = g["dx"], list(zip(model.weights[0]["dattn"]["dw_type"], g["dw_type"]))
+    else:
+        want, cache = O.rgcn_layer_forward(x, [(src, dst)], [0], [1], block.n_dst, lw.w_rel, lw.w_root, lw.bias, False)
+        dx, dw_rel, dw_root, _ = O.rgcn_layer_backward(cache, grad)
+        pairs = [(model.weights[0]["dw_rel"][0], dw_rel[0]), (model.weights[0]["dw_root"][1], dw_root[1])]
+    pairs += [(out["h"][0], want[1]), (out["dx"][0], np.concatenate([np.ravel(d) for d in dx]))]
+    errors = [rel_errors(got.float().cpu().numpy().ravel(), np.ravel(ref))[1] for got, ref in pairs]
+    bt.graph.release()
+    model.close()
+    return errors
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("H,heads", [(8, 2), (16, 2), (16, 1), (64, 2), (64, 1), (128, 1), (256, 1)])
+def test_attention_rows_beyond_the_staged_indices(H, heads, dtype):
+    rng = np.random.default_rng(H)
+    degrees = [0, 1, 4, 5, 1019, 3, 2, 8, 0, 1100] + [int(k) for k in rng.integers(0, 9, 290)]
+    n_src, n_dst = 1200, len(degrees)
+    src = np.concatenate([rng.permutation(n_src)[:k] for k in degrees])
+    dst = np.repeat(np.arange(n_dst), degrees)
+    order = rng.permutation(len(src))
+    errors = _run(dtype, n_src, n_dst, src[order], dst[order], 64, H, heads)
+    assert max(errors) < TOL[dtype], errors
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n_dst", [6000, 12289, 16100, 20500])
+def test_backward_tiles(n_dst, dtype):
+    """Two products of 256 columns per destination row: about 200, 400, 530 and 670 tiles of 128."""
+    n_src = 60
+    src = np.concatenate([np.arange(n_dst) % n_src, (np.arange(0, n_dst, 3) * 7 + 1) % n_src])
+    dst = np.concatenate([np.arange(n_dst), np.arange(0, n_dst, 3)])
+    errors = _run(dtype, n_src, n_dst, src, dst, 256, 96)
+    assert max(errors) < TOL[dtype], errors
