@@ -54,8 +54,18 @@ __device__ __forceinline__ int find_le(const int32_t *off, int n, int x) {  // l
 }
 
 // Sums over the lanes of a head (hl: a power of two, the same for the whole launch), for several values at once; every lane
-// gets them.  Inside 16 lanes the adds take their operand from the other lane directly (DPP); a cross-lane read through LDS,
-// with its latency, is left to wider heads.
+// gets them.  Inside 16 lanes the adds take their operand from the other lane directly (DPP), which has no move to the lane 8
+// or 4 away and so adds neighbours first; a cross-lane read through LDS, with its latency, is left to wider heads.
+// The scores stand in front of a softmax, a LeakyReLU and the next layers' ReLUs, so the order of their sums is fixed: pieces
+// of four floats hl / 2 apart first, then hl / 4, down to neighbours.  The lanes therefore hold the pieces of 16 of them in
+// bit-reversed places (head_piece), which costs nothing: a row's loads cover the same 256 bytes.  (With the pieces in the
+// lanes' order a score moves by an fp32 rounding, and of three ReLU layers over 600k rows single units decided otherwise:
+// input gradients off by up to their own size.)
+__device__ __forceinline__ int head_piece(int lane, int hl) {   // the piece of its row that lane `lane` of a lane group holds
+  const int w = min(hl, 16);
+  if (w == 1) return lane;
+  return (lane & ~(w - 1)) | (int)(__brev((unsigned)(lane & (w - 1))) >> (__clz(w) + 1));
+}
 template <int CTRL> __device__ __forceinline__ float other_lane(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
 }
@@ -64,13 +74,20 @@ template <int N> __device__ __forceinline__ void head_sums(float (&v)[N], int hl
   {                                            \
     _Pragma("unroll") for (int i = 0; i < N; ++i) v[i] += other; \
   }
-  if (hl >= 2) HGNN_STEP(other_lane<0xb1>(v[i]))     // lanes 1 0 3 2
+  if (hl >= 64) HGNN_STEP(__shfl_xor(v[i], 32))
+  if (hl >= 32) HGNN_STEP(__shfl_xor(v[i], 16))
+  if (hl >= 2) HGNN_STEP(other_lane<0xb1>(v[i]))     // lanes 1 0 3 2: pieces min(hl, 16) / 2 apart
   if (hl >= 4) HGNN_STEP(other_lane<0x4e>(v[i]))     // lanes 2 3 0 1
   if (hl >= 8) HGNN_STEP(other_lane<0x141>(v[i]))    // the eight lanes mirrored: the other four hold one value
   if (hl >= 16) HGNN_STEP(other_lane<0x140>(v[i]))   // the sixteen mirrored
-  if (hl >= 32) HGNN_STEP(__shfl_xor(v[i], 16))
-  if (hl >= 64) HGNN_STEP(__shfl_xor(v[i], 32))
 #undef HGNN_STEP
+}
+// A lane's four products of the destination's score, one after the other.
+__device__ __forceinline__ float dot_in_order(const float (&a)[4], const float (&b)[4]) {
+  float s = 0.f;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) s += a[j] * b[j];
+  return s;
 }
 
 __device__ __forceinline__ float leaky(float s) { return s > 0.f ? s : kLeaky * s; }
@@ -308,7 +325,8 @@ struct RowStage {
 };
 
 // Aggregation.  Blocks are cut per relation (the relation, its vectors and its rows are then the same for the whole
-// block).  A group of `lpr` lanes owns one merged row at a time; lane q holds four floats of it; `hl` lanes form a head.
+// block).  A group of `lpr` lanes owns one merged row at a time; a lane holds its q-th four floats (head_piece); `hl` lanes form
+// a head.
 // Softmax over the row's edges in one pass: running maximum m, running sum l and accumulator rescaled whenever the
 // maximum grows; four neighbour rows in flight.  Bound: the gather of fp32 rows (1 KB at H = 256; 2.3 GB through the L2s at
 // 6.5 TB/s, the caches in front of HBM included) and, close behind, the vector unit.  561k rows of 1.6M edges: 425 us with a
@@ -319,7 +337,7 @@ __global__ void __launch_bounds__(256) attn_agg_kernel(LayerDev L, RelRows rr, A
                                                        float *__restrict__ mx, float *__restrict__ ls) {
   __shared__ RowStage st;
   const int gpb = 256 >> lpr_log2;
-  const int q = threadIdx.x & ((1 << lpr_log2) - 1), grp = threadIdx.x >> lpr_log2;
+  const int q = head_piece(threadIdx.x & ((1 << lpr_log2) - 1), hl), grp = threadIdx.x >> lpr_log2;
   const int r = wave_find(rr.tile_off, rr.n, (int)blockIdx.x);
   const int row0 = rr.row_off[r], M = rr.row_off[r + 1] - row0;
   const int v0 = ((int)blockIdx.x - rr.tile_off[r]) * gpb * rpg, rows = min(gpb * rpg, M - v0);
@@ -340,7 +358,7 @@ __global__ void __launch_bounds__(256) attn_agg_kernel(LayerDev L, RelRows rr, A
 #pragma unroll
       for (int j = 0; j < 4; ++j) Q4::load(zu[j], zq + (int64_t)st.column(L, min(e0 + j, e1 - 1)) * H);
       Q4::load(zv, zd + (int64_t)i * H);
-      float sd[1] = {(ad[0] * zv[0] + ad[1] * zv[1]) + (ad[2] * zv[2] + ad[3] * zv[3])};
+      float sd[1] = {dot_in_order(ad, zv)};
       head_sums(sd, hl);
       for (int e = e0;;) {
 #pragma unroll
@@ -827,7 +845,7 @@ __global__ void __launch_bounds__(256) attn_agg_bwd_rows_kernel(LayerDev L, RelR
   __shared__ float s_das[kAttnMaxH], s_dad[kAttnMaxH];
   __shared__ RowStage st;
   const int gpb = 256 >> lpr_log2;
-  const int q = threadIdx.x & ((1 << lpr_log2) - 1), grp = threadIdx.x >> lpr_log2;
+  const int q = head_piece(threadIdx.x & ((1 << lpr_log2) - 1), hl), grp = threadIdx.x >> lpr_log2;
   const int k = (q * 4) / (H / heads);
   const bool lead = (q & (hl - 1)) == 0;
   const int r = wave_find(rr.tile_off, rr.n, (int)blockIdx.x);
@@ -855,7 +873,7 @@ __global__ void __launch_bounds__(256) attn_agg_bwd_rows_kernel(LayerDev L, RelR
     Q4::load(zv, zd + (int64_t)i * H);
     Q4::load(g, dm + rho * H + q * 4);
     const float mxk = mx[rho * heads + k], inv_l = 1.f / ls[rho * heads + k];
-    float sdv[1] = {(ad[0] * zv[0] + ad[1] * zv[1]) + (ad[2] * zv[2] + ad[3] * zv[3])};
+    float sdv[1] = {dot_in_order(ad, zv)};
     head_sums(sdv, hl);
     const float sd = sdv[0];
     float S1[4] = {0.f, 0.f, 0.f, 0.f}, S2[4] = {0.f, 0.f, 0.f, 0.f};

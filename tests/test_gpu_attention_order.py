@@ -1,0 +1,60 @@
+"""The order in which the attention layer adds up a score: it stands in front of a softmax, a LeakyReLU and the later layers'
+ReLUs, where a unit within a rounding of zero decides by it, so it is part of what the layer computes."""
+from types import SimpleNamespace as NS
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _head_sum(piece):
+    """Sum over the last axis (a power of two pieces): those half of it apart first, down to neighbours."""
+    while piece.shape[-1] > 1:
+        half = piece.shape[-1] // 2
+        piece = piece[..., :half] + piece[..., half:]
+    return piece[..., 0]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("H,heads", [(8, 2), (8, 1), (16, 1), (32, 1), (64, 1), (128, 1), (256, 1), (256, 8), (256, 4), (128, 32)])
+def test_scores_are_summed_in_the_stated_order(H, heads, dtype):
+    """Rows of one edge: the saved maximum is the score itself.  With weights of the identity the projected rows are the
+    inputs, and with attention vectors of ones and zeros every product is exact, so that all that rounds is the order of the
+    fp32 sums, which numpy forms in the same way.  The backward forms the score again: alpha is 1 to the bit, and the
+    source's gradient the incoming one, only if it gets the same bits."""
+    import torch
+    from paper_2408_08490_amd.runner import Model
+    n = 700
+    rng = np.random.default_rng(H + heads)
+    store = (lambda a: torch.from_numpy(np.float32(a)).bfloat16().float().numpy()) if dtype == "bf16" else np.float32
+    x = [store(rng.standard_normal((n, H)) * 10.0 ** rng.uniform(-2, 2, (n, H))) for _ in range(2)]
+    src = rng.permutation(n)
+    a_src = np.zeros((1, H // 4, 4), np.float32)
+    a_src[..., 0] = 1
+    lw = NS(in_dim=[H, H], out_dim=H, relu=False, w_rel=[], w_root=[], w_type=[np.eye(H, dtype=np.float32)] * 2, a_src=[a_src.reshape(heads, -1)],
+            a_dst=[np.ones((heads, H // heads), np.float32)], w_sem=np.zeros((H, 128), np.float32), b_sem=np.zeros(128, np.float32),
+            q_sem=np.zeros(128, np.float32), bias=[np.zeros(H, np.float32)] * 2)
+    grad = [np.zeros((0, H), np.float32), store(rng.standard_normal((n, H)))]
+    block = NS(n_src=[n, n], n_dst=[0, n], edge_index=np.stack([src, np.arange(n)]), edge_type=np.zeros(n, np.int32))
+    mb = NS(ids=[np.arange(n), np.arange(n)], blocks=[block], labels=None, grad_out=grad)
+    model = Model(NS(num_types=2, num_rels=1, rel_src=[0], rel_dst=[1]), [H, H], x, [lw], dtype=dtype, loss="dot", target_type=1)
+    bt = model.prepare(mb)
+    dx = model.run(bt)["dx"][0].float().cpu().numpy().reshape(2, n, H)
+    saved = model._buf["saved0"].cpu().numpy()
+    torch.cuda.synchronize()
+    # projected rows, aggregates, tanh of the semantic products (128 a row), maxima: fp32, each part on a multiple of 256 bytes
+    at, parts = 0, []
+    for count in (2 * n * H, n * H, n * 128, n * heads):
+        parts.append(saved[at: at + 4 * count].view(np.float32))
+        at += (4 * count + 255) // 256 * 256
+    z, _, _, mx = parts
+    assert np.array_equal(z.reshape(2, n, H), np.stack(x))
+    quads = [v.reshape(n, heads, -1, 4) for v in x]
+    s_src = _head_sum(quads[0][..., 0])
+    s_dst = _head_sum(((quads[1][..., 0] + quads[1][..., 1]) + quads[1][..., 2]) + quads[1][..., 3])
+    s = s_src[src] + s_dst
+    assert np.array_equal(mx.reshape(n, heads), np.where(s > 0, s, np.float32(0.2) * s))
+    assert np.array_equal(dx[0][src], grad[1])
+    bt.graph.release()
+    model.close()
