@@ -98,7 +98,7 @@ hgnn_status make_attn_plan(hgnn_ctx *ctx, hgnn_graph *g, int32_t layer, const hg
   pl.s_mx = take(o, (size_t)pl.rows * hd * 4);
   pl.s_ls = take(o, (size_t)pl.rows * hd * 4);
   pl.s_beta = take(o, (size_t)kMaxR * 4);
-  pl.s_wsum = take(o, (size_t)kMaxR * 4);
+  pl.s_wsum = take(o, (size_t)kMaxR * 8);
   pl.saved_bytes = o;
   o = 0;
   pl.c_gp = take(o, (size_t)pl.total_dst * H * es);            // incoming gradient masked by the activation
@@ -140,7 +140,8 @@ hgnn_status attn_fwd(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_t layer, 
   HGNN_HIP(wait_upload(g, s));
   char *sv = (char *)saved;
   float *z = (float *)(sv + pl.s_z), *m = (float *)(sv + pl.s_m), *t = (float *)(sv + pl.s_t);
-  float *wsum = (float *)(sv + pl.s_wsum), *beta = (float *)(sv + pl.s_beta);
+  double *wsum = (double *)(sv + pl.s_wsum);
+  float *beta = (float *)(sv + pl.s_beta);
   {
     Probe pb(ctx, HGNN_K_GEMM_FWD, layer);
     if ((st = launch_attn_proj(s, ctx->dtype, pl.tt, pl.pt, pl.H, x, z, wsum)) != HGNN_OK) return st;

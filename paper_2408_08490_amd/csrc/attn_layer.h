@@ -32,13 +32,13 @@ struct SemBwd {
 };
 
 hgnn_status launch_attn_proj(hipStream_t s, int dtype, const TypeTab &tt, const PtrTab &w_type_as_root, int H, const void *x, float *z,
-                             float *wsum);
+                             double *wsum);
 hgnn_status launch_attn_agg(hipStream_t s, int dtype, const LayerDev &L, RelRows rr, const AttnPtrs &ap, int H, int heads,
                             const float *z, float *mout, float *mx, float *ls);
 hgnn_status launch_attn_sem(hipStream_t s, int dtype, RelRows rr, int H, const float *mbuf, const void *w_sem, const void *b_sem,
-                            const void *q_sem, float *tbuf, float *wsum);
+                            const void *q_sem, float *tbuf, double *wsum);
 hgnn_status launch_attn_fuse(hipStream_t s, int dtype, const TypeTab &tt, const RelRows &rr, const PtrTab &pt, int H, int relu,
-                             const float *mbuf, const float *wsum, float *beta, void *h);
+                             const float *mbuf, const double *wsum, float *beta, void *h);
 hgnn_status launch_attn_zero(hipStream_t s, float *const *ptrs, const int64_t *counts, int n);
 hgnn_status launch_attn_mask_dbeta(hipStream_t s, int dtype, const TypeTab &tt, const RelRows &rr, const GradPtrTab &gt, int H, int relu,
                                    const void *g, const void *h, void *gp, const float *mbuf, float *dbeta);

@@ -59,7 +59,7 @@ __device__ __forceinline__ int find_le(const int32_t *off, int n, int x) {  // l
 // The scores stand in front of a softmax, a LeakyReLU and the next layers' ReLUs, so the order of their sums is fixed: pieces
 // of four floats hl / 2 apart first, then hl / 4, down to neighbours.  The lanes therefore hold the pieces of 16 of them in
 // bit-reversed places (head_piece), which costs nothing: a row's loads cover the same 256 bytes.  (With the pieces in the
-// lanes' order a score moves by an fp32 rounding, and of three ReLU layers over 600k rows single units decided otherwise:
+// lanes' order a score moves by an fp32 rounding, and behind two hidden layers over 600k rows single units decided otherwise:
 // input gradients off by up to their own size.)
 __device__ __forceinline__ int head_piece(int lane, int hl) {   // the piece of its row that lane `lane` of a lane group holds
   const int w = min(hl, 16);
@@ -283,10 +283,10 @@ __device__ __forceinline__ void mix_run(f32x16 (&acc)[MI][2], MixLds<TS, MI> &sm
 // bf16 numbers are exact in fp32).  Its first block also clears the score sums of the kernel after next.
 template <typename TS, int MI>
 __global__ void __launch_bounds__(kThreads, 2) attn_proj_kernel(TypeTab tt, PtrTab pt, SegTab tiles, int H, const TS *__restrict__ x,
-                                                              float *__restrict__ z, float *__restrict__ wsum) {
+                                                              float *__restrict__ z, double *__restrict__ wsum) {
   constexpr int BM = 64 * MI, BN = 64 * MI;
   __shared__ GemmLds<TS, MI, MI> sm;
-  if (blockIdx.x == 0 && threadIdx.x < kMaxR) wsum[threadIdx.x] = 0.f;
+  if (blockIdx.x == 0 && threadIdx.x < kMaxR) wsum[threadIdx.x] = 0.0;
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
   const int T_ = tt.num_types;
   if (tile >= tiles.tile_off[T_]) return;
@@ -396,6 +396,8 @@ __global__ void __launch_bounds__(256) attn_agg_kernel(LayerDev L, RelRows rr, A
 
 // ------------------------------------------------------------------------------------------
 // Semantic scores: t = tanh(m W_s + b_s) stored for the backward pass; wsum[r] += sum over the segment's rows of q . t
+// The blocks' sums are added in 64 bits: in 32 their order, which is not fixed, moved a relation's weight by a rounding and
+// with it every row of the output, and single units of the layers behind decided otherwise from one run to the next.
 // The blocks take the rows from the end: what the kernel in front wrote last is still in the memory-side cache (256 MB)
 // when it is read first, and the kernel behind, from the start again, finds what this one touched last.  The same order in
 // the backward's launch between mask and aggregation (561k rows, m and dm of 573 MB each, us: scores 238 -> 230, fusion
@@ -403,7 +405,7 @@ __global__ void __launch_bounds__(256) attn_agg_kernel(LayerDev L, RelRows rr, A
 template <typename TS, int MI>
 __global__ void __launch_bounds__(kThreads, 2) attn_sem_kernel(RelRows rr, int H, const float *__restrict__ mbuf, const TS *__restrict__ w_sem,
                                                              const TS *__restrict__ b_sem, const TS *__restrict__ q_sem,
-                                                             float *__restrict__ tbuf, float *__restrict__ wsum) {
+                                                             float *__restrict__ tbuf, double *__restrict__ wsum) {
   constexpr int TM = 64 * MI;
   __shared__ MixLds<TS, MI> sm;
   __shared__ float red[4];
@@ -426,12 +428,12 @@ __global__ void __launch_bounds__(kThreads, 2) attn_sem_kernel(RelRows rr, int H
   for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = part;
   __syncthreads();
-  if (threadIdx.x == 0) atomicAdd(wsum + r, red[0] + red[1] + red[2] + red[3]);
+  if (threadIdx.x == 0) unsafeAtomicAdd(wsum + r, (double)(red[0] + red[1] + red[2] + red[3]));   // device memory: the hardware's add
 }
 
 // beta[r] = softmax over the relations with the same destination type of wsum[r] / M_d, for all relations by the first
 // threads of a block.  `out` may be LDS or global memory.
-__device__ __forceinline__ void relation_softmax(const RelRows &rr, const float *__restrict__ wsum, float *out) {
+__device__ __forceinline__ void relation_softmax(const RelRows &rr, const double *__restrict__ wsum, float *out) {
   const int r = threadIdx.x;
   if (r >= rr.n) return;
   const int d = rr.dst[r], M = rr.row_off[r + 1] - rr.row_off[r];
@@ -441,10 +443,10 @@ __device__ __forceinline__ void relation_softmax(const RelRows &rr, const float 
   }
   float mxv = -INFINITY, s = 0.f;
   for (int o = 0; o < rr.n; ++o)
-    if (rr.dst[o] == d) mxv = fmaxf(mxv, wsum[o] / (float)M);
+    if (rr.dst[o] == d) mxv = fmaxf(mxv, (float)wsum[o] / (float)M);
   for (int o = 0; o < rr.n; ++o)
-    if (rr.dst[o] == d) s += __expf(wsum[o] / (float)M - mxv);
-  out[r] = __expf(wsum[r] / (float)M - mxv) / s;
+    if (rr.dst[o] == d) s += __expf((float)wsum[o] / (float)M - mxv);
+  out[r] = __expf((float)wsum[r] / (float)M - mxv) / s;
 }
 
 // h[v] = act( sum_{r -> type(v)} beta_r m[rel_row_off[r] + v] + b ).  Every block takes the softmax over the relations
@@ -453,7 +455,7 @@ __device__ __forceinline__ void relation_softmax(const RelRows &rr, const float 
 // of m: one row after the other 161 us, four at once 132, 5 TB/s).
 template <typename TS, int U>
 __global__ void __launch_bounds__(256) attn_fuse_kernel(RelRows rr, TypeTiles ty, RelsOfType ro, PtrTab pt, int H, int relu, int lpr_log2,
-                                                        const float *__restrict__ mbuf, const float *__restrict__ wsum,
+                                                        const float *__restrict__ mbuf, const double *__restrict__ wsum,
                                                         float *__restrict__ beta, TS *__restrict__ h) {
   __shared__ float sb[kMaxR];
   relation_softmax(rr, wsum, sb);
@@ -523,7 +525,7 @@ static int rows_per_group(int64_t rows, int gpb, int blocks, int most) {
 }
 
 hgnn_status launch_attn_proj(hipStream_t s, int dtype, const TypeTab &tt, const PtrTab &w_type_as_root, int H, const void *x, float *z,
-                             float *wsum) {
+                             double *wsum) {
   SegTab tiles;
   std::memset(&tiles, 0, sizeof(tiles));
   tiles.num_segs = tt.num_types;
@@ -564,7 +566,7 @@ hgnn_status launch_attn_agg(hipStream_t s, int dtype, const LayerDev &L, RelRows
 static int sem_tile_rows(RelRows &rr) { return tile_relations(rr, 128) >= 512 ? 128 : 64; }
 
 hgnn_status launch_attn_sem(hipStream_t s, int dtype, RelRows rr, int H, const float *mbuf, const void *w_sem, const void *b_sem,
-                            const void *q_sem, float *tbuf, float *wsum) {
+                            const void *q_sem, float *tbuf, double *wsum) {
   const int tm = sem_tile_rows(rr);
   const int n = tile_relations(rr, tm);
   if (n == 0) return HGNN_OK;
@@ -599,7 +601,7 @@ static void dst_types(const TypeTab &tt, TypeTiles &ty) {
 }
 
 hgnn_status launch_attn_fuse(hipStream_t s, int dtype, const TypeTab &tt, const RelRows &rr, const PtrTab &pt, int H, int relu,
-                             const float *mbuf, const float *wsum, float *beta, void *h) {
+                             const float *mbuf, const double *wsum, float *beta, void *h) {
   TypeTiles ty;
   dst_types(tt, ty);
   const int64_t rows = ty.row_off[ty.n];

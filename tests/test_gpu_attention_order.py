@@ -58,3 +58,31 @@ def test_scores_are_summed_in_the_stated_order(H, heads, dtype):
     assert np.array_equal(dx[0][src], grad[1])
     bt.graph.release()
     model.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_relation_weights_do_not_depend_on_the_order_of_the_blocks(dtype):
+    """The sums behind the relations' softmax run over 60k rows each, a block's after the other's in no fixed order: outputs
+    of every run have the same bits."""
+    import torch
+    from paper_2408_08490_amd.runner import Model
+    n, H = 60_000, 64
+    rng = np.random.default_rng(3)
+    store = (lambda a: torch.from_numpy(np.float32(a)).bfloat16().float().numpy()) if dtype == "bf16" else np.float32
+    x = [store(rng.standard_normal((n, H))) for _ in range(2)]
+    w = lambda *shape: store(rng.standard_normal(shape) * 0.2)
+    lw = NS(in_dim=[H, H], out_dim=H, relu=False, w_rel=[], w_root=[], w_type=[w(H, H) for _ in range(2)], a_src=[w(4, H // 4) for _ in range(3)],
+            a_dst=[w(4, H // 4) for _ in range(3)], w_sem=w(H, 128), b_sem=w(128), q_sem=w(128), bias=[w(H)] * 2)
+    edges = [np.stack([rng.integers(0, n, n), rng.permutation(n)]) for _ in range(3)]
+    block = NS(n_src=[n, n], n_dst=[0, n], edge_index=np.concatenate(edges, 1), edge_type=np.repeat(np.arange(3, dtype=np.int32), n))
+    mb = NS(ids=[np.arange(n), np.arange(n)], blocks=[block], labels=None, grad_out=None)
+    model = Model(NS(num_types=2, num_rels=3, rel_src=[0, 0, 1], rel_dst=[1, 1, 1]), [H, H], x, [lw], dtype=dtype, loss="dot", target_type=1)
+    bt = model.prepare(mb)
+    runs = []
+    for _ in range(12):
+        runs.append(model.run(bt, backward=False)["h"][0].clone())
+        runs[-1].float().square().sum()   # other work between the runs
+    torch.cuda.synchronize()
+    assert all(torch.equal(r, runs[0]) for r in runs)
+    bt.graph.release()
+    model.close()
