@@ -54,17 +54,17 @@ __device__ __forceinline__ int find_le(const int32_t *off, int n, int x) {  // l
 }
 
 // Sums over the lanes of a head (hl: a power of two, the same for the whole launch), for several values at once; every lane
-// gets them.  Inside 16 lanes the adds take their operand from the other lane directly (DPP), which has no move to the lane 8
-// or 4 away and so adds neighbours first; a cross-lane read through LDS, with its latency, is left to wider heads.
+// gets them.  Inside 16 lanes the adds take their operand from the other lane directly (DPP), which has no single move to the
+// lane 4 away and inside 8 lanes adds neighbours first; a cross-lane read through LDS, with its latency, is left to wider heads.
 // The scores stand in front of a softmax, a LeakyReLU and the next layers' ReLUs, so the order of their sums is fixed: pieces
-// of four floats hl / 2 apart first, then hl / 4, down to neighbours.  The lanes therefore hold the pieces of 16 of them in
-// bit-reversed places (head_piece), which costs nothing: a row's loads cover the same 256 bytes.  (With the pieces in the
-// lanes' order a score moves by an fp32 rounding, and behind two hidden layers over 600k rows single units decided otherwise:
-// input gradients off by up to their own size.)
+// of four floats hl / 2 apart first, then hl / 4, down to neighbours.  The lanes therefore hold the pieces of 8 of them in
+// bit-reversed places (head_piece), which costs nothing: they are one line of 128 bytes.  (Over 16 lanes, two lines, the
+// aggregation with heads of 64 floats took 2 % longer.  With the pieces in the lanes' order a score moves by an fp32 rounding,
+// and behind two hidden layers over 600k rows single units decided otherwise: input gradients off by up to their own size.)
 __device__ __forceinline__ int head_piece(int lane, int hl) {   // the piece of its row that lane `lane` of a lane group holds
-  const int w = min(hl, 16);
-  if (w == 1) return lane;
-  return (lane & ~(w - 1)) | (int)(__brev((unsigned)(lane & (w - 1))) >> (__clz(w) + 1));
+  if (hl >= 8) return (lane & ~5) | (lane & 1) << 2 | (lane & 4) >> 2;
+  if (hl == 4) return (lane & ~3) | (lane & 1) << 1 | (lane & 2) >> 1;
+  return lane;
 }
 template <int CTRL> __device__ __forceinline__ float other_lane(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
@@ -76,10 +76,10 @@ template <int N> __device__ __forceinline__ void head_sums(float (&v)[N], int hl
   }
   if (hl >= 64) HGNN_STEP(__shfl_xor(v[i], 32))
   if (hl >= 32) HGNN_STEP(__shfl_xor(v[i], 16))
-  if (hl >= 2) HGNN_STEP(other_lane<0xb1>(v[i]))     // lanes 1 0 3 2: pieces min(hl, 16) / 2 apart
+  if (hl >= 16) HGNN_STEP(other_lane<0x128>(v[i]))   // the sixteen turned by eight
+  if (hl >= 2) HGNN_STEP(other_lane<0xb1>(v[i]))     // lanes 1 0 3 2: pieces min(hl, 8) / 2 apart
   if (hl >= 4) HGNN_STEP(other_lane<0x4e>(v[i]))     // lanes 2 3 0 1
   if (hl >= 8) HGNN_STEP(other_lane<0x141>(v[i]))    // the eight lanes mirrored: the other four hold one value
-  if (hl >= 16) HGNN_STEP(other_lane<0x140>(v[i]))   // the sixteen mirrored
 #undef HGNN_STEP
 }
 // A lane's four products of the destination's score, one after the other.
