@@ -958,6 +958,7 @@ __global__ void __launch_bounds__(256) attn_agg_bwd_rows_kernel(LayerDev L, RelR
 // per lane group, fewer where the launch would have less than eight blocks per compute unit.
 // The result leaves in the storage type (the projection's backward reads it there).
 constexpr int kColRows = 64, kColEntries = kColRows * kLongRow;   // of a block, at most
+static_assert(kColEntries >= 4 * kChunk, "the entries of four pieces");
 
 // What a lane group does with its entries and its rows; lane q holds four floats of a row.
 template <typename TS> struct ColSum {
@@ -1025,7 +1026,7 @@ template <typename TS> struct ColSum {
   }
 };
 
-template <typename TS>
+template <typename TS, bool WAVE>
 __global__ void __launch_bounds__(256) attn_agg_bwd_cols_kernel(LayerDev L, TypeTab tt, RelRows rr, RelsOfType ro, AttnPtrs ap, int H, int heads,
                                                                 int lpr_log2, int rpb, const float *__restrict__ dm, const float2 *__restrict__ ead,
                                                                 const float *__restrict__ xsum, const float *__restrict__ dsum,
@@ -1037,44 +1038,48 @@ __global__ void __launch_bounds__(256) attn_agg_bwd_cols_kernel(LayerDev L, Type
   const int q = threadIdx.x & ((1 << lpr_log2) - 1);
   ColSum<TS> cs{rr, ro, ap, dm, xsum, dsum, ead, s_off, H, heads, q, (q * 4) / (H / heads)};
   int t = 0;
-  if ((int)blockIdx.x < L.n_chunks) {
+  const int nb_long = long_blocks(L.n_chunks, WAVE);
+  if ((int)blockIdx.x < nb_long) {
     __shared__ LongLds<4> sm;
-    const LongPiece p = long_piece(L, blockIdx.x);
+    const LongSlot<WAVE> slot(L.n_chunks);
+    const LongPiece p = long_piece(L, slot.item);
     while (p.c >= tt.row_off[t + 1]) ++t;
     __syncthreads();
-    for (int i = threadIdx.x; i < p.n; i += 256) {
-      s_rho[i] = L.crow[p.beg + i];
-      s_e[i] = L.cperm[p.beg + i];
-      s_rel[i] = (uint8_t)find_le(s_off, rr.n, s_rho[i]);
+    for (int i = slot.first; i < p.n; i += slot.step) {
+      const int rho = L.crow[p.beg + i];
+      s_rho[slot.lds + i] = rho;
+      s_e[slot.lds + i] = L.cperm[p.beg + i];
+      s_rel[slot.lds + i] = (uint8_t)find_le(s_off, rr.n, rho);
     }
     __syncthreads();
-    long_row_piece<4>(p, blockIdx.x, lpr_log2, H / 4, sm, partial, H, L.chunk_count,
-      [&](int, int g, int groups, float (&acc)[4]) {
-        for (int i = g; i < p.n; i += 4 * groups) {
-          int rho[4], e[4], rel[4];
+    if (!slot.on) return;   // whole wavefront
+    auto sum = [&](int, int g, int groups, float (&acc)[4]) {
+      for (int i = g; i < p.n; i += 4 * groups) {
+        int rho[4], e[4], rel[4];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const int at = min(i + u * groups, p.n - 1);
-            rho[u] = s_rho[at];
-            e[u] = s_e[at];
-            rel[u] = s_rel[at];
-          }
-          cs.add4(rho, e, rel, [&](int u) { return i + u * groups < p.n; });
+        for (int u = 0; u < 4; ++u) {
+          const int at = slot.lds + min(i + u * groups, p.n - 1);
+          rho[u] = s_rho[at];
+          e[u] = s_e[at];
+          rel[u] = s_rel[at];
         }
-        cs.flush();
+        cs.add4(rho, e, rel, [&](int u) { return i + u * groups < p.n; });
+      }
+      cs.flush();
 #pragma unroll
-        for (int i = 0; i < 4; ++i) acc[i] = cs.acc[i];
-      },
-      [&](int, float (&acc)[4]) {
+      for (int i = 0; i < 4; ++i) acc[i] = cs.acc[i];
+    };
+    auto done = [&](int, float (&acc)[4]) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) cs.acc[i] = acc[i];
-        const int v = p.c - tt.row_off[t];
-        if (v < tt.n_dst[t]) cs.add_destination(t, v);
-        Quad<TS>::store(dz + (int64_t)p.c * H + q * 4, cs.acc);
-      });
+      for (int i = 0; i < 4; ++i) cs.acc[i] = acc[i];
+      const int v = p.c - tt.row_off[t];
+      if (v < tt.n_dst[t]) cs.add_destination(t, v);
+      Quad<TS>::store(dz + (int64_t)p.c * H + q * 4, cs.acc);
+    };
+    long_row<WAVE, 4>(p, slot.item, lpr_log2, H / 4, sm, partial, H, L.chunk_count, sum, done);
     return;
   }
-  const int c0 = ((int)blockIdx.x - L.n_chunks) * rpb, nr = min(rpb, L.src_rows - c0);
+  const int c0 = ((int)blockIdx.x - nb_long) * rpb, nr = min(rpb, L.src_rows - c0);
   for (int i = threadIdx.x; i <= nr; i += 256) s_ptr[i] = L.cptr[c0 + i];
   __syncthreads();
   if (threadIdx.x < kColRows) {   // one wavefront
@@ -1217,11 +1222,17 @@ hgnn_status launch_attn_agg_bwd(hipStream_t s, int dtype, const LayerDev &L, con
     RelsOfType ro;
     rels_of_type(rr, tt.num_types, ro);
     const int cpb = std::min(kColRows, gpb * rows_per_group(L.src_rows, gpb, 2048, 8));
-    dim3 grid(L.n_chunks + (L.src_rows + cpb - 1) / cpb);
-    if (dtype == HGNN_BF16)
-      HGNN_LAUNCH(attn_agg_bwd_cols_kernel<bf16>, grid, dim3(256), 0, s, L, tt, rr, ro, ap, H, heads, l2, cpb, dm, ead, xsum, dsum, (bf16 *)dz, partial);
-    else
-      HGNN_LAUNCH(attn_agg_bwd_cols_kernel<float>, grid, dim3(256), 0, s, L, tt, rr, ro, ap, H, heads, l2, cpb, dm, ead, xsum, dsum, (float *)dz, partial);
+    const bool by_wave = long_rows_by_wave(L.n_chunks, l2);
+    dim3 grid(long_blocks(L.n_chunks, by_wave) + (L.src_rows + cpb - 1) / cpb);
+#define HGNN_COLS(TY, WAVE_)                                                                                                             \
+  HGNN_LAUNCH((attn_agg_bwd_cols_kernel<TY, WAVE_>), grid, dim3(256), 0, s, L, tt, rr, ro, ap, H, heads, l2, cpb, dm, ead, xsum, dsum,   \
+              (TY *)dz, partial)
+    if (dtype == HGNN_BF16) {
+      if (by_wave) HGNN_COLS(bf16, true); else HGNN_COLS(bf16, false);
+    } else {
+      if (by_wave) HGNN_COLS(float, true); else HGNN_COLS(float, false);
+    }
+#undef HGNN_COLS
     HGNN_HIP(hipGetLastError());
   }
   return HGNN_OK;

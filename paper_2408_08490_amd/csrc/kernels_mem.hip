@@ -212,40 +212,45 @@ __device__ __forceinline__ int64_t dz_row(const SrcTiles &sl, const RelTab &rt, 
   return at + (int64_t)rho * nvec;
 }
 
-template <typename T>
+template <typename T, bool WAVE>
 __global__ void __launch_bounds__(256) spmm_bwd_kernel(LayerDev L, TypeTab tt, RelTab rt, SrcTiles sl, uint32_t root_mask, uint32_t want,
                                                         const T *__restrict__ dz, T *__restrict__ dx,
                                                         float *__restrict__ partial, int max_dim) {
   using V = Vec16<T>;
   const uint4 *zb = reinterpret_cast<const uint4 *>(dz);
   int t = 0;
-  if ((int)blockIdx.x < L.n_chunks) {
+  const int nb_long = long_blocks(L.n_chunks, WAVE);
+  if ((int)blockIdx.x < nb_long) {
     __shared__ LongLds<V::N> sm;
-    __shared__ int64_t s_at[kChunk];
-    const LongPiece p = long_piece(L, blockIdx.x);
+    __shared__ int64_t s_ats[(WAVE ? 4 : 1) * kChunk];
+    const LongSlot<WAVE> slot(L.n_chunks);
+    const LongPiece p = long_piece(L, slot.item);
     while (p.c >= tt.row_off[t + 1]) ++t;
-    if (!((want >> t) & 1u)) return;  // the caller does not want input gradients of this vertex type
+    const bool wanted = slot.on && ((want >> t) & 1u);   // else the caller does not want input gradients of this vertex type
+    if (!WAVE && !wanted) return;
     const int F = tt.in_dim[t], nvec = F / V::N, cl = p.c - tt.row_off[t];
-    for (int i = threadIdx.x; i < p.n; i += 256) s_at[i] = dz_row<T>(sl, rt, sl.first[t], sl.first[t + 1], nvec, L.crow[p.beg + i]);
+    int64_t *s_at = s_ats + slot.lds;
+    for (int i = slot.first; i < p.n; i += slot.step) s_at[i] = dz_row<T>(sl, rt, sl.first[t], sl.first[t + 1], nvec, L.crow[p.beg + i]);
     __syncthreads();
-    long_row_piece<V::N>(p, blockIdx.x, row_lanes_log2(nvec), nvec, sm, partial, max_dim, L.chunk_count,
-      [&](int q, int g, int groups, float (&acc)[V::N]) {
-        for (int i = g; i < p.n; i += 4 * groups) {
-          uint4 v[4];
+    if (!wanted) return;   // whole wavefront
+    auto sum = [&](int q, int g, int groups, float (&acc)[V::N]) {
+      for (int i = g; i < p.n; i += 4 * groups) {
+        uint4 v[4];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) v[u] = zb[s_at[min(i + u * groups, p.n - 1)] + q];
+        for (int u = 0; u < 4; ++u) v[u] = zb[s_at[min(i + u * groups, p.n - 1)] + q];
 #pragma unroll
-          for (int u = 0; u < 4; ++u)
-            if (i + u * groups < p.n) V::add(acc, v[u]);
-        }
-      },
-      [&](int q, float (&acc)[V::N]) {
-        if (cl < tt.n_dst[t] && ((root_mask >> t) & 1u)) V::add(acc, reinterpret_cast<const uint4 *>(dz + (int64_t)rt.zroot_off4[t] * 4 + (int64_t)cl * F)[q]);
-        reinterpret_cast<uint4 *>(dx + tt.elem_off[t] + (int64_t)cl * F)[q] = V::pack(acc);
-      });
+        for (int u = 0; u < 4; ++u)
+          if (i + u * groups < p.n) V::add(acc, v[u]);
+      }
+    };
+    auto done = [&](int q, float (&acc)[V::N]) {
+      if (cl < tt.n_dst[t] && ((root_mask >> t) & 1u)) V::add(acc, reinterpret_cast<const uint4 *>(dz + (int64_t)rt.zroot_off4[t] * 4 + (int64_t)cl * F)[q]);
+      reinterpret_cast<uint4 *>(dx + tt.elem_off[t] + (int64_t)cl * F)[q] = V::pack(acc);
+    };
+    long_row<WAVE, V::N>(p, slot.item, row_lanes_log2(nvec), nvec, sm, partial, max_dim, L.chunk_count, sum, done);
     return;
   }
-  const int b = (int)blockIdx.x - L.n_chunks;
+  const int b = (int)blockIdx.x - nb_long;
   while (b >= sl.tile_off[t + 1]) ++t;
   const int F = tt.in_dim[t], nvec = F / V::N, l2 = row_lanes_log2(nvec);
   const int c = tt.row_off[t] + (b - sl.tile_off[t]) * (256 >> l2) + (threadIdx.x >> l2);
@@ -316,12 +321,18 @@ hgnn_status launch_spmm_bwd(hipStream_t s, int dtype, const LayerDev &L, const T
         if (rt.src[r] == t) sl.rel[n++] = (uint8_t)r;
     }
     sl.first[tt.num_types] = (uint16_t)n;
-    const dim3 grid(L.n_chunks + sl.tile_off[tt.num_types]);
+    const bool by_wave = long_rows_by_wave(L.n_chunks, row_lanes_log2(max_dim * es / 16));
+    const dim3 grid(long_blocks(L.n_chunks, by_wave) + sl.tile_off[tt.num_types]);
     if (grid.x > 0) {
-      if (dtype == HGNN_BF16)
-        HGNN_LAUNCH(spmm_bwd_kernel<bf16>, grid, dim3(256), 0, s, L, tt, rt, sl, root_mask, want, (const bf16 *)dz, (bf16 *)dx, partial, max_dim);
-      else
-        HGNN_LAUNCH(spmm_bwd_kernel<float>, grid, dim3(256), 0, s, L, tt, rt, sl, root_mask, want, (const float *)dz, (float *)dx, partial, max_dim);
+#define HGNN_BWD(TY, WAVE_)                                                                                                       \
+  HGNN_LAUNCH((spmm_bwd_kernel<TY, WAVE_>), grid, dim3(256), 0, s, L, tt, rt, sl, root_mask, want, (const TY *)dz, (TY *)dx, partial, \
+              max_dim)
+      if (dtype == HGNN_BF16) {
+        if (by_wave) HGNN_BWD(bf16, true); else HGNN_BWD(bf16, false);
+      } else {
+        if (by_wave) HGNN_BWD(float, true); else HGNN_BWD(float, false);
+      }
+#undef HGNN_BWD
       HGNN_HIP(hipGetLastError());
     }
   }

@@ -277,7 +277,7 @@ struct RowRanges {
   int32_t n, total_waves;
 };
 
-template <typename T, int LPRL, int C>
+template <typename T, int LPRL, int C, bool WAVE>
 __global__ void __launch_bounds__(256) spmm_bwd_uniform_kernel(LayerDev L, RowRanges rr, const T *__restrict__ dz, T *__restrict__ dx, int F,
                                                                 float *__restrict__ partial) {
   using V = Vec16<T>;
@@ -285,35 +285,40 @@ __global__ void __launch_bounds__(256) spmm_bwd_uniform_kernel(LayerDev L, RowRa
   static_assert(RPW < 64, "a lane for each of the RPW + 1 row pointers");
   const int lane = threadIdx.x & 63, nvec = F / V::N;
   const uint4 *zb = reinterpret_cast<const uint4 *>(dz);
-  if ((int)blockIdx.x < L.n_chunks) {
+  const int nb_long = long_blocks(L.n_chunks, WAVE);
+  if ((int)blockIdx.x < nb_long) {
     __shared__ LongLds<V::N> sm;
-    __shared__ int s_row[kChunk];
-    const LongPiece p = long_piece(L, blockIdx.x);
+    __shared__ int s_rows[(WAVE ? 4 : 1) * kChunk];
+    const LongSlot<WAVE> slot(L.n_chunks);
+    const LongPiece p = long_piece(L, slot.item);
     int ri = 0;
     while (ri < rr.n && (p.c < rr.r[ri].lo || p.c >= rr.r[ri].hi)) ++ri;
-    if (ri == rr.n) return;   // nobody wants this type's gradient
-    const RowRange R = rr.r[ri];
-    for (int i = threadIdx.x; i < p.n; i += 256) s_row[i] = L.crow[p.beg + i];
+    const bool wanted = slot.on && ri < rr.n;   // else nobody wants this type's gradient
+    if (!WAVE && !wanted) return;
+    const RowRange R = rr.r[min(ri, rr.n - 1)];
+    int *s_row = s_rows + slot.lds;
+    for (int i = slot.first; i < p.n; i += slot.step) s_row[i] = L.crow[p.beg + i];
     __syncthreads();
-    long_row_piece<V::N>(p, blockIdx.x, min(LPRL + (C == 1 ? 0 : C == 2 ? 1 : 2), 6), nvec, sm, partial, F, L.chunk_count,
-      [&](int q, int g, int groups, float (&acc)[V::N]) {
-        for (int i = g; i < p.n; i += 4 * groups) {
-          uint4 v[4];
+    if (!wanted) return;   // whole wavefront
+    auto sum = [&](int q, int g, int groups, float (&acc)[V::N]) {
+      for (int i = g; i < p.n; i += 4 * groups) {
+        uint4 v[4];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) v[u] = zb[(int64_t)s_row[min(i + u * groups, p.n - 1)] * nvec + q];
+        for (int u = 0; u < 4; ++u) v[u] = zb[(int64_t)s_row[min(i + u * groups, p.n - 1)] * nvec + q];
 #pragma unroll
-          for (int u = 0; u < 4; ++u)
-            if (i + u * groups < p.n) V::add(acc, v[u]);
-        }
-      },
-      [&](int q, float (&acc)[V::N]) {
-        const int cl = p.c - R.lo;
-        if (R.root_off >= 0 && cl < R.n_dst) V::add(acc, reinterpret_cast<const uint4 *>(dz + R.root_off + (int64_t)cl * F)[q]);
-        reinterpret_cast<uint4 *>(dx + (int64_t)p.c * F)[q] = V::pack(acc);
-      });
+        for (int u = 0; u < 4; ++u)
+          if (i + u * groups < p.n) V::add(acc, v[u]);
+      }
+    };
+    auto done = [&](int q, float (&acc)[V::N]) {
+      const int cl = p.c - R.lo;
+      if (R.root_off >= 0 && cl < R.n_dst) V::add(acc, reinterpret_cast<const uint4 *>(dz + R.root_off + (int64_t)cl * F)[q]);
+      reinterpret_cast<uint4 *>(dx + (int64_t)p.c * F)[q] = V::pack(acc);
+    };
+    long_row<WAVE, V::N>(p, slot.item, min(LPRL + (C == 1 ? 0 : C == 2 ? 1 : 2), 6), nvec, sm, partial, F, L.chunk_count, sum, done);
     return;
   }
-  const int wave = ((int)blockIdx.x - L.n_chunks) * 4 + (threadIdx.x >> 6);
+  const int wave = ((int)blockIdx.x - nb_long) * 4 + (threadIdx.x >> 6);
   if (wave >= rr.total_waves) return;
   int ri = 0;
   while (ri + 1 < rr.n && wave >= rr.r[ri + 1].wave0) ++ri;
@@ -379,7 +384,16 @@ static void launch_bwd_uniform(hipStream_t s, const LayerDev &L, RowRanges &rr, 
   }
   rr.total_waves = w;
   if (w == 0) return;
-  HGNN_LAUNCH((spmm_bwd_uniform_kernel<T, LPRL, C>), dim3(L.n_chunks + (w + 3) / 4), dim3(256), 0, s, L, rr, (const T *)dz, (T *)dx, F, partial);
+  const int row_blocks = (w + 3) / 4;
+  if constexpr (C == 1 && LPRL <= kWaveLanesLog2) {
+    if (long_rows_by_wave(L.n_chunks, LPRL)) {
+      HGNN_LAUNCH((spmm_bwd_uniform_kernel<T, LPRL, C, true>), dim3(long_blocks(L.n_chunks, true) + row_blocks), dim3(256), 0, s, L, rr,
+                  (const T *)dz, (T *)dx, F, partial);
+      return;
+    }
+  }
+  HGNN_LAUNCH((spmm_bwd_uniform_kernel<T, LPRL, C, false>), dim3(long_blocks(L.n_chunks, false) + row_blocks), dim3(256), 0, s, L, rr,
+              (const T *)dz, (T *)dx, F, partial);
 }
 
 bool launch_spmm_bwd_uniform(hipStream_t s, int dtype, const LayerDev &L, const TypeTab &tt, const RelTab &rt, const PtrTab &pt,
