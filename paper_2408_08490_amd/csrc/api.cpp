@@ -259,9 +259,9 @@ bool probe_take_events(hipEvent_t *start, hipEvent_t *stop) {
 }
 
 // A forward launch of fewer 128x128 tiles than this leaves compute units without a block (two fit on each of
-// the 256): it uses 64x64 tiles instead -- four times as many, four resident per compute unit.  (Measured on
-// the headline's second layer, 96 tiles of 40 K-steps: 42 -> 33 us.  The backward GEMMs have short reductions
-// and gain nothing from smaller tiles.)
+// the 256): it uses 64x64 tiles instead -- four times as many, three resident per compute unit.  (Measured on
+// the headline's second layer, 96 tiles of 40 K-steps: 42 -> 33 us.  The backward GEMMs have a rule of their own,
+// bwd_small_tiles.)
 constexpr int kSmallTileLimit = 512;
 
 // Tile table of the forward GEMM; returns the tile edge (128 or 64).
@@ -1231,6 +1231,7 @@ static hgnn_status bwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
     const bool both = want_dx && da_tl.tile_off[da_tl.num_segs] > 0;
     const int bk = pl.es == 2 ? 64 : 32;
     int split_rows = 0;
+    BwdCols cols;
     for (int edge = 128;; edge = 64) {
       std::memset(&tl, 0, sizeof(tl));
       tl.edge = edge;
@@ -1246,10 +1247,13 @@ static hgnn_status bwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
             if (is_rel ? (ctx->rel_dst[sgi] != d || reo[sgi + 1] == reo[sgi] || !gt.dw_rel[sgi]) : (sgi - R != d || !gt.dw_root[d])) continue;
             tl.seg[ne] = (uint8_t)sgi;
             tl.u_off[ne] = (uint16_t)u;
-            u += (pl.tt.in_dim[is_rel ? ctx->rel_src[sgi] : d] + edge - 1) / edge;
+            const int F = pl.tt.in_dim[is_rel ? ctx->rel_src[sgi] : d];
+            u += (F + edge - 1) / edge;
+            if (edge == 128) cols.segment(F);
             ++ne;
           }
         tl.u_total[d] = (uint16_t)u;
+        if (edge == 128 && u > 0) ++cols.types;
         dw_steps += (int64_t)u * tiles_h * ((pl.tt.n_dst[d] + bk - 1) / bk);
       }
       tl.first[T] = (uint16_t)ne;
@@ -1260,7 +1264,7 @@ static hgnn_status bwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
       split_rows = dw_slice_rows(ctx->dtype, edge, dw_steps, da_steps);
       for (int d = 0; d < T; ++d)
         tl.tile_off[d + 1] = tl.tile_off[d] + tl.u_total[d] * tiles_h * ((pl.tt.n_dst[d] + split_rows - 1) / split_rows);
-      if (edge == 64 || !bwd_small_tiles(ctx->dtype, tl.tile_off[T] + (both ? da_grouped.tile_off[T] : 0), ldg)) break;
+      if (edge == 64 || !bwd_small_tiles(ctx->dtype, tl.tile_off[T] + (both ? da_grouped.tile_off[T] : 0), ldg, cols)) break;
     }
     Probe pb(ctx, HGNN_K_GEMM_DW, layer);
     if (both && tl.tile_off[T] > 0) {

@@ -238,6 +238,12 @@ hgnn_status attn_bwd(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_t layer, 
   }
   // tiles of 128 rows and columns, or of 64 (bwd_small_tiles)
   int split_rows = 0;
+  BwdCols cols;
+  for (int i = 0; i < T; ++i)
+    if (L.n_src[i] > 0) {
+      cols.segment(p->in_dim[i]);
+      ++cols.types;
+    }
   for (int edge = 128;; edge = 64) {
     std::memset(&dt, 0, sizeof(dt));
     std::memset(&da, 0, sizeof(da));
@@ -262,7 +268,7 @@ hgnn_status attn_bwd(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_t layer, 
     split_rows = dw_slice_rows(dtype, edge, dw_steps, (int64_t)da.tile_off[T] * ((H + bk - 1) / bk));
     for (int i = 0; i < T; ++i)
       dt.tile_off[i + 1] = dt.tile_off[i] + dt.u_total[i] * tiles_h * (int)((L.n_src[i] + split_rows - 1) / split_rows);
-    if (edge == 64 || !bwd_small_tiles(dtype, dt.tile_off[T] + da.tile_off[T], H)) break;
+    if (edge == 64 || !bwd_small_tiles(dtype, dt.tile_off[T] + da.tile_off[T], H, cols)) break;
   }
   Probe pb(ctx, HGNN_K_GEMM_DW, layer);
   const void *dzp = sc + pl.c_dz;

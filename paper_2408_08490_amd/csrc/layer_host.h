@@ -49,25 +49,41 @@ struct AttnVariant {
 };
 AttnVariant &attn_variant();
 
+// Column blocks of a backward launch's segments, with tiles of 128 and of 64, and its destination types.
+struct BwdCols {
+  int c128 = 0, c64 = 0, types = 0;
+  void segment(int F) { c128 += (F + 127) / 128; c64 += (F + 63) / 64; }
+};
 // Whether a backward launch of `tiles` tiles of 128x128, whose products run over rows of G' of `width` scalars, uses 64x64
-// ones instead.  The chip holds 512 of the large ones at a time and 768 of the small, which are a quarter of the work.
-// Below 256 large ones compute units stay empty.
-// fp32 tiles are split into planes on the way to LDS, and three small blocks of a compute unit cover each other's splitting,
-// loads and barriers better than two large ones; what speaks for the large ones is that an operand is split half as often.
-// They win where their rounds are nearly full (us, large -> small): 352 tiles 30 -> 29, 364 47 -> 37, 624 38 -> 34,
-// 664 68 -> 57, but 496 34 -> 38, 936 98 -> 108, 1044 116 -> 135, 1192 222 -> 276.
-// bf16: small ones where a launch of one round has short products (484 tiles of width 128 23 -> 17, 424 of 256 32 -> 29,
-// 360 of 256 31 -> 29, but 400 of 512 33 -> 37, 756 of 264 39 -> 51).
-static inline bool bwd_small_tiles(int dtype, int tiles, int width) {
+// ones instead, which are a quarter of the work.  The chip holds 512 of the large ones at a time and 768 of the small.  Below 256
+// large tiles compute units stay empty.  (Figures: us, large / small, of a layer's whole backward in a loop.)
+// fp32 tiles are split into planes on the way to LDS.  Three small blocks of a compute unit cover each other's splitting, loads
+// and barriers better than two large ones; what speaks for the large ones is that an operand is split half as often.
+//   Up to 384 large tiles, one or two to a compute unit, small ones win with long products (width 176, 312 tiles 44.0 / 41.3;
+//   width 256, 324 47.8 / 43.0) and where more than a quarter of the large tiles' columns is padding (64 columns, width 128, 320
+//   32.5 / 27.4; width 64, 320 34.0 / 32.3), not otherwise (width 128: 384 columns 300 35.3 / 37.3, 6 x 128 columns 324 38.1 /
+//   40.5, 96 columns 304 35.6 / 38.8, 192 columns 352 34.5 / 36.0; width 160 348 37.6 / 40.3) except with one column block per
+//   row block, whose tiles share no operand (128 columns of each type, width 128: 308 66.9 / 66.6, 378 72.8 / 71.3).
+//   From there to a full round of 512 mostly large ones do (width 160 504 42.8 / 44.7; 384 columns, width 128 480 42.2 / 45.8).
+//   In a second round that is not full small ones win up to 768 (width 128, 600 58.5 / 48.9, 750 65.0 / 57.8; width 320, 760 99.3 /
+//   95.4), with longer products up to 700 (width 352, 636 100.0 / 91.9, 702 105.2 / 104.0, 750 107.4 / 111.2; width 512, 640
+//   125.5 / 116.6, 748 140 / 151) unless a quarter is padding (192 columns, width 512, 744 126.7 / 115.6).
+// bf16: small ones where a launch of one round of large tiles has products of at most 256 (width 128: 300 44.5 / 30.6, 476
+// 46.2 / 39.4; width 256: 400 46.7 / 43.3, 504 47.9 / 47.7; width 352: 480 50.7 / 52.7).
+static inline bool bwd_small_tiles(int dtype, int tiles, int width, const BwdCols &c) {
   if (tiles < 256) return true;
   if (dtype == HGNN_BF16) return tiles < 512 && width <= 256;
-  return tiles < 384 || (tiles > 512 && tiles < 768);
+  const int padding = 2 * c.c128 - c.c64;   // in blocks of 64 columns, of 2 c128
+  if (tiles < 384) return width > 160 || width <= 64 || 2 * padding > c.c128 || c.c128 <= c.types;
+  return tiles > 512 && tiles < (width <= 320 || 2 * padding >= c.c128 ? 768 : 700);
 }
 
 // Rows per slice of the weight-gradient reduction in a launch of `dw_steps` K-steps (over all its tiles) beside
-// `other_steps` K-steps of other tiles.  A block's share is 1/640 of the launch's K-steps (1/1280 with 64x64 tiles, of
-// which twice as many are resident): a bit over the chip's block slots, so that the launch is one long round whose end
-// the shorter blocks fill.  Every slice ends with a tile's worth of atomic adds (the chip does about 0.4e12 a second, 40 ns
+// `other_steps` K-steps of other tiles.  A block's share is 1/640 of the launch's K-steps: a bit over the chip's 512 block
+// slots, so that the launch is one long round whose end the shorter blocks fill.  With 64x64 tiles it is 1/1280, which is more
+// than the 768 of them that are resident: shares of 1/832 and 1/768 were up to a quarter faster in launches of some 500 small
+// tiles and up to 5 % slower in larger ones with long products (fp32, 128 columns, us at 1/1280, 1/832, 1/768: width 512, 320
+// large tiles 39.5, 29.8, 29.4, but 640 91.7, 96.3, 91.4; width 128, 304 27.4, -, 24.8).  Every slice ends with a tile's worth of atomic adds (the chip does about 0.4e12 a second, 40 ns
 // of all of it per 128x128 tile), hence the least number of K-steps: 32 of bf16 (8 measured 9 us worse on 4096 rows of
 // 512 x 349); an fp32 K-step is several times as long (1.7 us of a compute unit's matrix cores per 128x128 tile), which
 // both keeps the adds cheap beside it and makes long slices a serial chain (64 K-steps in one block were 183 us of a

@@ -68,9 +68,37 @@ def test_attention_rows_beyond_the_staged_indices(H, heads, dtype):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("n_dst", [6000, 12289, 16100, 20500])
 def test_backward_tiles(n_dst, dtype):
-    """Two products of 256 columns per destination row: about 200, 400, 530 and 670 tiles of 128."""
+    """Two products of 256 columns per destination row: about 200, 420, 540 and 690 tiles of 128 in bf16, 380, 700, 840 and 970
+    in fp32, whose weight gradients are cut finer."""
     n_src = 60
     src = np.concatenate([np.arange(n_dst) % n_src, (np.arange(0, n_dst, 3) * 7 + 1) % n_src])
     dst = np.concatenate([np.arange(n_dst), np.arange(0, n_dst, 3)])
     errors = _run(dtype, n_src, n_dst, src, dst, 256, 96)
+    assert max(errors) < TOL[dtype], errors
+
+
+def _tiles(dtype, n, F, H):
+    """Tiles of 128 of the two backward products of a layer of one relation and a root term over n rows: blocks of rows for the
+    input gradients, slices of the reduction for the weight gradients (a 1/640 of all K-steps each)."""
+    bk, least = (64, 32) if dtype == "bf16" else (32, 4)
+    up = lambda a, b: -(-a // b)
+    cols, cols_h = 2 * up(F, 128), up(H, 128)
+    da = cols * up(n, 128)
+    steps = up(cols * cols_h * up(n, bk) + da * up(H, bk), 640)
+    return da + cols * cols_h * up(n, bk * min(64, max(least, steps)))
+
+
+# both sides of the lines between the two sizes: 256 everywhere; fp32 at 384 (long products, or padded columns), 512 and 700 or
+# 768; bf16 at 512 and at products of 256
+@pytest.mark.parametrize("dtype,F,H,tiles", [("f32", 256, 96, 244), ("f32", 256, 96, 256), ("f32", 256, 96, 372), ("f32", 256, 96, 388), ("f32", 256, 96, 508),
+                                             ("f32", 256, 96, 520), ("f32", 256, 96, 760), ("f32", 256, 96, 772), ("f32", 64, 96, 300), ("f32", 64, 96, 400),
+                                             ("f32", 192, 96, 300), ("f32", 128, 352, 300), ("f32", 128, 352, 400), ("f32", 128, 352, 690), ("f32", 128, 352, 704),
+                                             ("f32", 192, 352, 710), ("bf16", 256, 96, 244), ("bf16", 256, 96, 300), ("bf16", 256, 96, 504), ("bf16", 256, 96, 516),
+                                             ("bf16", 128, 264, 240), ("bf16", 128, 264, 300)])
+def test_backward_tiles_on_both_sides_of_the_lines(dtype, F, H, tiles):
+    n_src, n_dst = 60, next(n for n in range(64, 40000, 8) if _tiles(dtype, n, F, H) >= tiles) + 3   # a ragged last tile
+    assert tiles <= _tiles(dtype, n_dst, F, H) <= tiles + 12
+    src = np.concatenate([np.arange(n_dst) % n_src, (np.arange(0, n_dst, 3) * 7 + 1) % n_src])
+    dst = np.concatenate([np.arange(n_dst), np.arange(0, n_dst, 3)])
+    errors = _run(dtype, n_src, n_dst, src, dst, F, H)
     assert max(errors) < TOL[dtype], errors
