@@ -801,7 +801,7 @@ hgnn_status hgnn_layer_workspace_bytes(hgnn_ctx *ctx, hgnn_graph *g, int32_t lay
   return HGNN_OK;
 }
 
-// Whether there is an aggregation launch (which carries the weight transposes as its first blocks).
+// Whether there is an aggregation launch (which carries the weight transposes as its first or last blocks).
 static bool transposes_ride(const Plan &pl) { return pl.dev.rows > 0; }
 
 // Bit r: relation r has an edge in the layer.
@@ -867,8 +867,8 @@ static hgnn_status fwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
   const int R = ctx->R, T = ctx->T;
   uint32_t live[kMaxR / 32];
   live_relations(ctx, g, layer, live);
-  // The weight transposes ride in the aggregation launch (as its first blocks) where there is one; otherwise they are a
-  // launch of their own.
+  // The weight transposes ride in the aggregation launch (JobSplit) where there is one; otherwise they are a launch of
+  // their own.
   TransposeJobs tj;
   make_transpose_jobs(pl.tt, pl.rt, pl.pt, pl.wt, pl.H, wtb, tj);
   const bool rides = !naive && !feature_cat && transposes_ride(pl);

@@ -104,7 +104,7 @@ struct WtTab {                      // where each transposed weight lives in the
 };
 
 // Weight transposes as a job list (Wt[h][f] = W[f][h] per K-segment, in 32x32 tiles), so that the blocks doing them can
-// be the first blocks of another launch.
+// ride in another launch (JobSplit).
 struct TransposeJobs {
   const void *w[kMaxSeg];
   uint32_t off4[kMaxSeg];           // scalars/4 of the transposed copy inside `out`
@@ -403,8 +403,7 @@ hgnn_status launch_merge(hipStream_t s, int dtype, int T, const void *const *sto
                          const int32_t *const *pos = nullptr, const void *interleaved = nullptr);
 // rows [row_begin,row_end) of the merged CSR: z[row] = mean of the x rows in colidx (rounded to the storage type);
 // zlo (optional, same layout): what that rounding dropped, rounded in turn
-// tj (optional): weight transposes that ride in the same launch as its first blocks (in a launch of their own when
-// the aggregation runs on the kernels for ragged widths)
+// tj (optional): weight transposes that ride in the same launch (JobSplit)
 hgnn_status launch_spmm_fwd(hipStream_t s, int dtype, const LayerDev &L, const TypeTab &tt, const RelTab &rt,
                             int max_dim, const void *x, void *z, void *zlo, int row_begin, int row_end,
                             const TransposeJobs *tj = nullptr);

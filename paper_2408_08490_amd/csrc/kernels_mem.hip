@@ -107,12 +107,11 @@ __global__ void __launch_bounds__(256) spmm_fwd_kernel(LayerDev L, TypeTab tt, R
                                                         T *__restrict__ z, T *__restrict__ zlo, TransposeJobs tj) {
   using V = Vec16<T>;
   __shared__ T tile[32][33];
-  const JobSplit js(tj);
-  if (js.transposes(tj)) {
-    transpose_jobs_block<T>(tj, js.tb, tj.blocks, tile);
+  if ((int)blockIdx.x < tj.blocks) {   // in front: see JobSplit
+    transpose_jobs_block<T>(tj, blockIdx.x, tj.blocks, tile);
     return;
   }
-  const int b = js.b;
+  const int b = (int)blockIdx.x - tj.blocks;
   const int r = wave_find(rtl.tile_off, rt.num_rels, b);
   const int st = rt.src[r];
   const int F = tt.in_dim[st];
