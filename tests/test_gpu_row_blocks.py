@@ -102,3 +102,18 @@ def test_backward_tiles_on_both_sides_of_the_lines(dtype, F, H, tiles):
     dst = np.concatenate([np.arange(n_dst), np.arange(0, n_dst, 3)])
     errors = _run(dtype, n_src, n_dst, src, dst, F, H)
     assert max(errors) < TOL[dtype], errors
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_attention_with_several_rows_per_lane_group(dtype):
+    """33000 merged rows of 256 floats: lane groups walk two rows each in the forward, four in the backward by rows and four in
+    the one over the transpose (69000 source rows), beside 40 source rows of 17 to 300 entries."""
+    rng = np.random.default_rng(41)
+    n_src, n_dst = 36_000, 33_000
+    src, dst = rng.integers(40, n_src, n_dst), rng.permutation(n_dst)
+    lengths = np.linspace(17, 300, 40).astype(int)
+    src = np.concatenate([src, np.repeat(np.arange(40), lengths)])
+    dst = np.concatenate([dst, *(rng.permutation(n_dst - 5)[:k] for k in lengths)])   # five rows keep one edge; some have several
+    order = rng.permutation(len(src))
+    errors = _run(dtype, n_src, n_dst, src[order], dst[order], 32, 256, 8)
+    assert max(errors) < TOL[dtype], errors
