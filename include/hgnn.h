@@ -442,8 +442,8 @@ hgnn_status hgnn_adam_update_rows(hgnn_ctx *ctx, void *stream, void *store, floa
 /* ---- Measurement aid --------------------------------------------------------------------
  * Attaches a pair of HIP events to every later dispatch of the selected kernels (the events carry the
  * dispatch's own begin and end timestamps) so that a benchmark can report a kernel's average duration
- * without a profiler attached.  A call that launches several kernels (transposed aggregation with
- * long rows) adds their durations up.
+ * without a profiler attached.  A call that launches several kernels (a forward GEMM
+ * whose reduction is split over blocks, the attention aggregation's backward) adds their durations up.
  *   hgnn_probe_select(kernel, layer): adds (kernel, layer) to the selection (at most 4 entries);
  *     kernel = hgnn_kernel_id, layer = layer index or < 0 for every layer; kernel < 0 clears the
  *     selection and discards what was collected.

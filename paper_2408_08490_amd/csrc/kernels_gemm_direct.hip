@@ -234,14 +234,16 @@ __global__ void __launch_bounds__(256) gemm_fwd_direct_sum_kernel(DirectArgs arg
 }
 
 // For launches of fewer than kDirectTiles tiles of 64x64 (a quarter of that in bf16); `part` holds kDirectPartBytes.
-// Returns the kernels that it launches (with count_only: that it would launch), 0: not for this launch.  Beyond the line a tile per block keeps the compute units busy and the staged kernel, whose
-// four wavefronts share a tile's operands, needs half the operand traffic; the fp32 products are 16 times as long, so that
-// the line lies further out.  Both kernels of this file together against the staged one, in us (tiles: before -> now):
+// Returns the kernels that it launches (with count_only: that it would launch), 0: not for this launch.  Beyond the line a tile
+// per block keeps the compute units busy and the staged kernel, whose four wavefronts share a tile's operands, needs half the
+// operand traffic; the fp32 products are 16 times as long, so that the line lies further out.  Both kernels of this file
+// together against the staged one, in us (tiles: before -> now):
 //   fp32  16: 43 -> 16, 27 -> 16 (104 relations)   96: 41 -> 23   312: 54 -> 48      700: 47 -> 52 (not taken)
 //   bf16  72: 43 -> 22 (108 relations)   16: 24 -> 16   24: 15 -> 14   96: 24 -> 21   230: 15 -> 27 (not taken)
 // In fp32 with a ReLU the line is at 64 tiles: a sum formed in another order gives units within a rounding of zero the other
 // decision (three of ten million), which moves a whole term of the gradients away from what the staged kernel's forms of the
-// layer give; up to 64 tiles there is next to never one.
+// layer give; up to 64 tiles there is next to never one.  How the K-steps are dealt out (`target` below) is part of that order:
+// each number of splits rounds its sums its own way, below the line too.
 static int launch_gemm_fwd_direct(hipStream_t s, int dtype, const TypeTab &tt, const RelTab &rt, const PtrTab &pt, const WtTab &wt,
                                    const uint32_t *live_mask, int H, int relu, const void *x, const void *z, const void *zlo,
                                    const void *wt_buf, void *h, float *part, bool count_only) {
@@ -279,10 +281,14 @@ static int launch_gemm_fwd_direct(hipStream_t s, int dtype, const TypeTab &tt, c
   }
   da.seg0[T] = (uint16_t)n;
   da.seg[n] = DirectSeg{0, 0, 0, INT32_MAX};
-  // K-steps per block: those of two blocks per compute unit, but in bf16 two for every wavefront, which cost about what the
-  // block's own start and end do, and one in fp32, whose MFMAs take 1.7 us a step (30 blocks 11.4 us -> 54 blocks 9.8, 6 blocks
-  // 11.7 -> 12 blocks 9.3; the kernel that adds up the partial tiles stays at 4)
-  const int64_t target = std::max<int64_t>(dtype == HGNN_BF16 ? 2 * kDirW : kDirW, (work + 511) / 512);
+  // K-steps per block: those of two blocks per compute unit, but two for every wavefront, which cost about what the block's own
+  // start and end do, and in fp32, whose MFMAs take 1.7 us a step, one where tiles are split in any case (30 blocks 11.4 us -> 54
+  // blocks 9.8, 6 blocks 11.7 -> 12 blocks 9.3; the kernel that adds up the partial tiles stays at 4).  Where two a wavefront are
+  // the whole tile, splitting it would only add that kernel (28 tiles of 8 steps 13.4 -> 15.5).
+  int most = 0;
+  for (int d = 0; d < T; ++d)
+    if (da.tile_off[d + 1] > da.tile_off[d]) most = std::max(most, da.steps[d]);
+  const int64_t target = std::max<int64_t>(dtype == HGNN_BF16 || most <= 2 * kDirW ? 2 * kDirW : kDirW, (work + 511) / 512);
   int units = 0, max_splits = 1;
   for (int i = 0; i < kMaxT + 8; ++i) da.unit_off[i] = INT32_MAX;
   for (int d = 0; d < T; ++d) {
