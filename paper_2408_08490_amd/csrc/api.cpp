@@ -169,7 +169,7 @@ static hgnn_status make_plan(hgnn_ctx *ctx, hgnn_graph *g, int32_t layer, const 
   pl.off_wt = o;      o += align_up(std::max<size_t>(w / pl.H * Hpad, 1) * pl.es, 256);
   pl.off_gp = o;      o += align_up(std::max<size_t>((size_t)pl.total_dst * Hpad, 1) * pl.es, 256);
   pl.off_dz = o;      o += align_up(std::max<size_t>(zr, 1) * pl.es, 256);
-  pl.off_partial = o; o += align_up(std::max<size_t>((size_t)L.max_chunks * std::max(pl.max_dim, 1), 1) * 4, 256);
+  pl.off_partial = o; o += align_up(std::max<size_t>((size_t)long_partials(L.max_chunks) * std::max(pl.max_dim, 1), 1) * 4, 256);
   pl.off_count = o;   o += align_up((size_t)L.max_chunks * 4, 256);
   pl.off_acc32 = o;   o += align_up(std::max<size_t>((size_t)pl.total_dst * pl.H, 1) * 4, 256);
   // partial bias-gradient sums: one row of H floats per block of destination rows of a type (64 rows per block

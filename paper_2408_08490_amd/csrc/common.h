@@ -125,6 +125,9 @@ struct LayerDev {
 
 constexpr int kLongRow = 16;  // transpose rows above this length are reduced chunk-wise, by whole blocks (long_rows.h)
 constexpr int kChunk = 128;
+constexpr int kHalvedChunks = 128;   // up to as many a chunk of wide rows is two pieces
+// rows of partial sums that the pieces of at most `chunks` chunks take
+inline int64_t long_partials(int64_t chunks) { return chunks <= kHalvedChunks ? 2 * chunks : chunks < 2 * kHalvedChunks ? 2 * kHalvedChunks : chunks; }
 
 struct LayerHost {
   int64_t rows = 0, edges = 0, src_rows = 0, tedges = 0;

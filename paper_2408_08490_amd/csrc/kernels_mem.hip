@@ -214,19 +214,19 @@ __device__ __forceinline__ int64_t dz_row(const SrcTiles &sl, const RelTab &rt, 
 template <typename T, bool WAVE>
 __global__ void __launch_bounds__(256) spmm_bwd_kernel(LayerDev L, TypeTab tt, RelTab rt, SrcTiles sl, uint32_t root_mask, uint32_t want,
                                                         const T *__restrict__ dz, T *__restrict__ dx,
-                                                        float *__restrict__ partial, int max_dim) {
+                                                        float *__restrict__ partial, int max_dim, int halves) {
   using V = Vec16<T>;
   const uint4 *zb = reinterpret_cast<const uint4 *>(dz);
   int t = 0;
-  const int nb_long = long_blocks(L.n_chunks, WAVE);
+  const int pieces = WAVE ? L.n_chunks : L.n_chunks << halves, nb_long = long_blocks(pieces, WAVE);
   if ((int)blockIdx.x < nb_long) {
     __shared__ LongLds<V::N> sm;
     __shared__ int64_t s_ats[(WAVE ? 4 : 1) * kChunk];
-    const LongSlot<WAVE> slot(L.n_chunks);
-    const LongPiece p = long_piece(L, slot.item);
+    const LongSlot<WAVE> slot(pieces);
+    const LongPiece p = long_piece(L, slot.item, WAVE ? 0 : halves);
     while (p.c >= tt.row_off[t + 1]) ++t;
     const bool wanted = slot.on && ((want >> t) & 1u);   // else the caller does not want input gradients of this vertex type
-    if (!WAVE && !wanted) return;
+    if (!WAVE && (!wanted || p.n <= 0)) return;
     const int F = tt.in_dim[t], nvec = F / V::N, cl = p.c - tt.row_off[t];
     int64_t *s_at = s_ats + slot.lds;
     for (int i = slot.first; i < p.n; i += slot.step) s_at[i] = dz_row<T>(sl, rt, sl.first[t], sl.first[t + 1], nvec, L.crow[p.beg + i]);
@@ -320,12 +320,13 @@ hgnn_status launch_spmm_bwd(hipStream_t s, int dtype, const LayerDev &L, const T
         if (rt.src[r] == t) sl.rel[n++] = (uint8_t)r;
     }
     sl.first[tt.num_types] = (uint16_t)n;
-    const bool by_wave = long_rows_by_wave(L.n_chunks, row_lanes_log2(max_dim * es / 16));
-    const dim3 grid(long_blocks(L.n_chunks, by_wave) + sl.tile_off[tt.num_types]);
+    const int l2 = row_lanes_log2(max_dim * es / 16), halves = long_halves(L.n_chunks, l2);
+    const bool by_wave = long_rows_by_wave(L.n_chunks, l2);
+    const dim3 grid(long_blocks(L.n_chunks << halves, by_wave) + sl.tile_off[tt.num_types]);
     if (grid.x > 0) {
-#define HGNN_BWD(TY, WAVE_)                                                                                                       \
-  HGNN_LAUNCH((spmm_bwd_kernel<TY, WAVE_>), grid, dim3(256), 0, s, L, tt, rt, sl, root_mask, want, (const TY *)dz, (TY *)dx, partial, \
-              max_dim)
+#define HGNN_BWD(TY, WAVE)                                                                                                        \
+  HGNN_LAUNCH((spmm_bwd_kernel<TY, WAVE>), grid, dim3(256), 0, s, L, tt, rt, sl, root_mask, want, (const TY *)dz, (TY *)dx, partial, \
+              max_dim, halves)
       if (dtype == HGNN_BF16) {
         if (by_wave) HGNN_BWD(bf16, true); else HGNN_BWD(bf16, false);
       } else {

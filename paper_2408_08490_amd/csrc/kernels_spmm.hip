@@ -279,34 +279,36 @@ struct RowRanges {
 
 template <typename T, int LPRL, int C, bool WAVE>
 __global__ void __launch_bounds__(256) spmm_bwd_uniform_kernel(LayerDev L, RowRanges rr, const T *__restrict__ dz, T *__restrict__ dx, int F,
-                                                                float *__restrict__ partial) {
+                                                                int halves, float *__restrict__ partial) {
   using V = Vec16<T>;
   constexpr int LPR = 1 << LPRL, RPW = 64 / LPR;
   static_assert(RPW < 64, "a lane for each of the RPW + 1 row pointers");
   const int lane = threadIdx.x & 63, nvec = F / V::N;
   const uint4 *zb = reinterpret_cast<const uint4 *>(dz);
-  const int nb_long = long_blocks(L.n_chunks, WAVE);
+  const int pieces = WAVE ? L.n_chunks : L.n_chunks << halves, nb_long = long_blocks(pieces, WAVE);
   if ((int)blockIdx.x < nb_long) {
     __shared__ LongLds<V::N> sm;
     __shared__ int s_rows[(WAVE ? 4 : 1) * kChunk];
-    const LongSlot<WAVE> slot(L.n_chunks);
-    const LongPiece p = long_piece(L, slot.item);
+    const LongSlot<WAVE> slot(pieces);
+    const LongPiece p = long_piece(L, slot.item, WAVE ? 0 : halves);
     int ri = 0;
     while (ri < rr.n && (p.c < rr.r[ri].lo || p.c >= rr.r[ri].hi)) ++ri;
     const bool wanted = slot.on && ri < rr.n;   // else nobody wants this type's gradient
-    if (!WAVE && !wanted) return;
+    if (!WAVE && (!wanted || p.n <= 0)) return;
     const RowRange R = rr.r[min(ri, rr.n - 1)];
     int *s_row = s_rows + slot.lds;
     for (int i = slot.first; i < p.n; i += slot.step) s_row[i] = L.crow[p.beg + i];
     __syncthreads();
     if (!wanted) return;   // whole wavefront
     auto sum = [&](int q, int g, int groups, float (&acc)[V::N]) {
-      for (int i = g; i < p.n; i += 4 * groups) {
-        uint4 v[4];
+      // four entries in flight; eight where the row takes several passes, whose loads come one pass after the other
+      constexpr int U = LPRL == 6 && C > 1 ? 8 : 4;
+      for (int i = g; i < p.n; i += U * groups) {
+        uint4 v[U];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = zb[(int64_t)s_row[min(i + u * groups, p.n - 1)] * nvec + q];
+        for (int u = 0; u < U; ++u) v[u] = zb[(int64_t)s_row[min(i + u * groups, p.n - 1)] * nvec + q];
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < U; ++u)
           if (i + u * groups < p.n) V::add(acc, v[u]);
       }
     };
@@ -385,15 +387,16 @@ static void launch_bwd_uniform(hipStream_t s, const LayerDev &L, RowRanges &rr, 
   rr.total_waves = w;
   if (w == 0) return;
   const int row_blocks = (w + 3) / 4;
+  const int lanes = C == 1 ? LPRL : 6, halves = long_halves(L.n_chunks, lanes);
+  const bool by_wave = long_rows_by_wave(L.n_chunks, lanes);
+  const dim3 grid(long_blocks(L.n_chunks << halves, by_wave) + row_blocks);
+#define HGNN_BWD(WAVE) HGNN_LAUNCH((spmm_bwd_uniform_kernel<T, LPRL, C, WAVE>), grid, dim3(256), 0, s, L, rr, (const T *)dz, (T *)dx, F, halves, partial)
   if constexpr (C == 1 && LPRL <= kWaveLanesLog2) {
-    if (long_rows_by_wave(L.n_chunks, LPRL)) {
-      HGNN_LAUNCH((spmm_bwd_uniform_kernel<T, LPRL, C, true>), dim3(long_blocks(L.n_chunks, true) + row_blocks), dim3(256), 0, s, L, rr,
-                  (const T *)dz, (T *)dx, F, partial);
-      return;
-    }
+    if (by_wave) HGNN_BWD(true); else HGNN_BWD(false);
+  } else {
+    HGNN_BWD(false);
   }
-  HGNN_LAUNCH((spmm_bwd_uniform_kernel<T, LPRL, C, false>), dim3(long_blocks(L.n_chunks, false) + row_blocks), dim3(256), 0, s, L, rr,
-              (const T *)dz, (T *)dx, F, partial);
+#undef HGNN_BWD
 }
 
 bool launch_spmm_bwd_uniform(hipStream_t s, int dtype, const LayerDev &L, const TypeTab &tt, const RelTab &rt, const PtrTab &pt,

@@ -13,32 +13,41 @@
 namespace hgnn {
 
 struct LongPiece {
-  int c, beg, n;       // source row, first entry, entries of the piece
-  int first, pieces;   // first piece of the row, its pieces
+  int c, beg, n;            // source row, first entry, entries of the piece
+  int first, pieces, row;   // place of the row's first piece among the partial sums, its pieces, its first chunk
 };
-__device__ __forceinline__ LongPiece long_piece(const LayerDev &L, int item) {
+// `halves`: 1 where a chunk of kChunk entries is two pieces, else 0
+__device__ __forceinline__ LongPiece long_piece(const LayerDev &L, int item, int halves = 0) {
+  const int chunk = item >> halves, size = kChunk >> halves;
   LongPiece p;
-  p.c = L.chunk_row[item];
-  p.beg = L.chunk_beg[item];
-  const int j0 = L.cptr[p.c], j1 = L.cptr[p.c + 1];
-  p.n = min(kChunk, j1 - p.beg);
-  p.first = item - (p.beg - j0) / kChunk;
-  p.pieces = (j1 - j0 + kChunk - 1) / kChunk;
+  p.c = L.chunk_row[chunk];
+  const int j0 = L.cptr[p.c], j1 = L.cptr[p.c + 1], beg = L.chunk_beg[chunk];
+  p.beg = beg + (item - (chunk << halves)) * size;
+  p.n = min(size, j1 - p.beg);   // none behind a row's last entry
+  p.row = chunk - (beg - j0) / kChunk;
+  p.first = p.row << halves;
+  p.pieces = (j1 - j0 + size - 1) >> (31 - __clz(kChunk) - halves);
   return p;
 }
 
-// Whether a wavefront takes a piece instead of a block, four to a block.  While the chip holds a block for every piece (2048)
+// Whether a wavefront takes a piece instead of a block, four to a block.  While the chip holds a block for every piece (kLongBlocks)
 // four wavefronts are done sooner than one.  With more, in a batch of dense neighbourhoods, what counts is how many pieces are in
 // flight, and a piece of narrow rows has too little work for a block (of 17 entries of 2 lanes it uses an eighth); up to 8 lanes
 // that shows from half as many on.  Rows of more than 16 lanes stay with the block: they give it enough to do, and a wavefront
 // would add up 64 entries and more one after the other.  us, a block / a wavefront per piece, rows x entries: 2 lanes, 20000 x
 // 17 43 / 15, 4000 x 200 37 / 13, 1500 x 17 7.1 / 5.0, 200 x 128 5.1 / 6.2; 8 lanes, 20000 x 17 35 / 15, 1500 x 128 8.7 / 8.9, 500 x
 // 128 7.1 / 8.1; 16 lanes, 20000 x 17 37 / 18, 4000 x 200 35 / 21, 1500 x 128 10.8 / 12.8.
-constexpr int kWaveLanesLog2 = 4;
+constexpr int kWaveLanesLog2 = 4, kLongBlocks = 2048;
 inline bool long_rows_by_wave(int pieces, int lanes_log2) {
-  return lanes_log2 <= kWaveLanesLog2 && pieces > (lanes_log2 < kWaveLanesLog2 ? 1024 : 2048);
+  return lanes_log2 <= kWaveLanesLog2 && pieces > (lanes_log2 < kWaveLanesLog2 ? kLongBlocks / 2 : kLongBlocks);
 }
 __host__ __device__ inline int long_blocks(int pieces, bool by_wave) { return by_wave ? (pieces + 3) / 4 : pieces; }
+
+// 1 where a block's piece is half a chunk: where rows are wide, a block's groups are few and its share of 128 entries is the
+// longest chain of a launch that leaves the chip idle.  A layer's backward with 1500 destinations, us, with pieces of 16 entries
+// and a launch of its own for their sums / whole chunks / halves: one row of 180 entries, 512 features in fp32 25.0 / 30.5 / 24.2,
+// 1024 in bf16 25.4 / 32.4 / 25.0; 300 rows of 128 entries, 1024 in bf16 30.8 / 29.6 / 32.7.
+inline int long_halves(int chunks, int lanes_log2) { return lanes_log2 > kWaveLanesLog2 && chunks <= kHalvedChunks ? 1 : 0; }
 
 // The piece of the calling thread: the block's, or its wavefront's.  `on`: whether there is one (the wavefronts behind the last
 // piece stand in for it up to the barrier).  Threads first, first + step, ... bring its entries to its part of an LDS array.
@@ -134,7 +143,7 @@ __device__ __forceinline__ void long_row_piece(const LongPiece &p, int item, int
   }
   if (p.pieces == 1) return;
   if (wave == 0) {   // the one that stored
-    const uint32_t before = count_piece(count + p.first);
+    const uint32_t before = count_piece(count + p.row);
     if (lane == 0) sm.before = before;
   }
   __syncthreads();
@@ -175,7 +184,7 @@ __device__ __forceinline__ void long_row_wave(const LongPiece &p, int item, int 
     return;
   }
   if (mine) put_partial<N>(partial + (int64_t)item * pitch + q * N, acc);
-  if (count_piece(count + p.first) != (uint32_t)(p.pieces - 1)) return;
+  if (count_piece(count + p.row) != (uint32_t)(p.pieces - 1)) return;
   clear();
   if (q < nvec)
     for (int j = g; j < p.pieces; j += groups) add_partial<N>(acc, partial + (int64_t)(p.first + j) * pitch + q * N);
