@@ -10,9 +10,12 @@ namespace hgnn {
 // is none of them), and b, its place among the others.  In front the transposes' weights, which come from HBM, the longest chain
 // of loads in the launch, are under way from the start; behind, the transposes fill the places that become free instead of
 // holding those of blocks with more to do.
-// Behind is the better of the two from a chip's worth of blocks on (2048 of 256 threads) in the aggregation of one width.  Forward of a layer, us, in front / behind: 108 relations, two layers 57.0 / 54.6; 8 relations, 128 features in bf16, 888
-// blocks 31.3 / 31.3, 1688 34.5 / 34.8, 3288 49.1 / 48.4; read from the stores 2688 48.9 / 48.3; rows of 3 KB, of whose blocks the
-// chip holds 1024, 1752 53.0 / 51.5 and 2552 77.2 / 76.6 in bf16, but 1280 of them in fp32, 1476 76.7 / 77.2.
+// Behind is mostly the better of the two from a chip's worth of blocks on (2048 of 256 threads) in the aggregation of one width.
+// Forward of a layer, us, in front / behind: 108 relations, two layers 57.0 / 54.6; 8 relations, 128 features in bf16, 888 blocks
+// 31.3 / 31.3, 1688 34.5 / 34.8, 3288 49.1 / 48.4, with 512 outputs 8576 130.9 / 129.3; read from the stores 2688 48.9 / 48.3; rows of
+// 3 KB, of whose blocks the chip holds 1024, 1752 53.0 / 51.5 and 2552 77.2 / 76.6 in bf16, but 1280 of them in fp32, 1476 76.7 /
+// 77.2.  Not always: 10 types, 256 features in bf16, rows of 7 edges, 3500 blocks 64.0 / 66.6; 30 relations, 64 features, rows of 2
+// edges, 8248 blocks 60.9 / 61.6.
 // Ragged widths keep them in front: 96 and 128 features in bf16, 2280 blocks 34.3 / 35.3, 3280 38.6 / 39.1; in fp32, 2140 45.0 / 45.6;
 // 32 and 384, 3484 44.1 / 45.1; 10 types of 32 to 384, two layers of 72 and 242 outputs 111.9 / 112.3, of 424 and 75 160.0 / 159.1.
 struct JobSplit {
