@@ -333,7 +333,7 @@ struct RowStage {
 // chain of three loads and cross-lane reads through LDS on every row, 355 with both gone.
 template <typename TS>
 __global__ void __launch_bounds__(256) attn_agg_kernel(LayerDev L, RelRows rr, AttnPtrs ap, int H, int heads, int lpr_log2, int hl,
-                                                       int rpg, const float *__restrict__ z, float *__restrict__ mout,
+                                                       int rpg, int past, const float *__restrict__ z, float *__restrict__ mout,
                                                        float *__restrict__ mx, float *__restrict__ ls) {
   __shared__ RowStage st;
   const int gpb = 256 >> lpr_log2;
@@ -385,8 +385,11 @@ __global__ void __launch_bounds__(256) attn_agg_kernel(LayerDev L, RelRows rr, A
 #pragma unroll
       for (int d = 0; d < 4; ++d) acc[d] *= inv;
     }
-    // past the caches: what the L2 holds of popular neighbours stays (fetched 1.7 GB for the 2.2 GB asked for; 366 -> 355 us)
-    __builtin_nontemporal_store(f32x4{acc[0], acc[1], acc[2], acc[3]}, reinterpret_cast<f32x4 *>(mout + rho * H + q * 4));
+    // Aggregates that the caches cannot hold until they are read go past them: what the L2 holds of popular neighbours stays
+    // (573 MB: fetched 1.7 GB for the 2.2 GB asked for; 366 -> 355 us).
+    const f32x4 out = {acc[0], acc[1], acc[2], acc[3]};
+    if (past) __builtin_nontemporal_store(out, reinterpret_cast<f32x4 *>(mout + rho * H + q * 4));
+    else *reinterpret_cast<f32x4 *>(mout + rho * H + q * 4) = out;
     if ((q & (hl - 1)) == 0) {
       mx[rho * heads + k] = e1 > e0 ? m : 0.f;
       ls[rho * heads + k] = l;
@@ -553,14 +556,18 @@ hgnn_status launch_attn_proj(hipStream_t s, int dtype, const TypeTab &tt, const 
   return HGNN_OK;
 }
 
+// bytes of aggregates from which on their stores go past the caches: what the memory-side cache holds
+constexpr int64_t kAggPast = (int64_t)256 << 20;
+
 hgnn_status launch_attn_agg(hipStream_t s, int dtype, const LayerDev &L, RelRows rr, const AttnPtrs &ap, int H, int heads,
                             const float *z, float *mout, float *mx, float *ls) {
   if (L.rows == 0) return HGNN_OK;
   const int lpr = H / 4, l2 = log2_exact(lpr), hl = (H / heads) / 4, gpb = 256 >> l2;
   const int rpg = std::min(kStageRows / gpb, rows_per_group(L.rows, gpb, 4096, 4));
+  const int past = (int64_t)L.rows * H * 4 > kAggPast;
   dim3 grid(tile_relations(rr, gpb * rpg));
-  if (dtype == HGNN_BF16) HGNN_LAUNCH(attn_agg_kernel<bf16>, grid, dim3(256), 0, s, L, rr, ap, H, heads, l2, hl, rpg, z, mout, mx, ls);
-  else HGNN_LAUNCH(attn_agg_kernel<float>, grid, dim3(256), 0, s, L, rr, ap, H, heads, l2, hl, rpg, z, mout, mx, ls);
+  if (dtype == HGNN_BF16) HGNN_LAUNCH(attn_agg_kernel<bf16>, grid, dim3(256), 0, s, L, rr, ap, H, heads, l2, hl, rpg, past, z, mout, mx, ls);
+  else HGNN_LAUNCH(attn_agg_kernel<float>, grid, dim3(256), 0, s, L, rr, ap, H, heads, l2, hl, rpg, past, z, mout, mx, ls);
   HGNN_HIP(hipGetLastError());
   return HGNN_OK;
 }
