@@ -1090,10 +1090,10 @@ __global__ void __launch_bounds__(256) attn_agg_bwd_cols_kernel(LayerDev L, Type
     return;
   }
   const int c0 = ((int)blockIdx.x - nb_long) * rpb, nr = min(rpb, L.src_rows - c0);
-  for (int i = threadIdx.x; i <= nr; i += 256) s_ptr[i] = L.cptr[c0 + i];
-  __syncthreads();
   if (threadIdx.x < kColRows) {   // one wavefront
-    const int i = threadIdx.x, len = i < nr ? s_ptr[i + 1] - s_ptr[i] : 0;
+    const int i = threadIdx.x, p0 = L.cptr[c0 + min(i, nr)], p1 = L.cptr[c0 + min(i + 1, nr)], len = p1 - p0;
+    s_ptr[i] = p0;
+    if (i == kColRows - 1) s_ptr[kColRows] = p1;
     int n = len > kLongRow ? 0 : len;
     const int own = n;
     for (int o = 1; o < 64; o <<= 1) {
