@@ -7,6 +7,8 @@
 // (As a launch of its own behind the sums, with pieces of 16 entries, the last step was 4 to 8 us of every layer and 27 us of
 // the attention variant's largest.)
 #pragma once
+#include <type_traits>
+
 #include "common.h"
 #include "device_types.h"
 
@@ -30,16 +32,17 @@ __device__ __forceinline__ LongPiece long_piece(const LayerDev &L, int item, int
   return p;
 }
 
-// Whether a wavefront takes a piece instead of a block, four to a block.  While the chip holds a block for every piece (kLongBlocks)
-// four wavefronts are done sooner than one.  With more, in a batch of dense neighbourhoods, what counts is how many pieces are in
-// flight, and a piece of narrow rows has too little work for a block (of 17 entries of 2 lanes it uses an eighth); up to 8 lanes
-// that shows from half as many on.  Rows of more than 16 lanes stay with the block: they give it enough to do, and a wavefront
-// would add up 64 entries and more one after the other.  us, a block / a wavefront per piece, rows x entries: 2 lanes, 20000 x
-// 17 43 / 15, 4000 x 200 37 / 13, 1500 x 17 7.1 / 5.0, 200 x 128 5.1 / 6.2; 8 lanes, 20000 x 17 35 / 15, 1500 x 128 8.7 / 8.9, 500 x
-// 128 7.1 / 8.1; 16 lanes, 20000 x 17 37 / 18, 4000 x 200 35 / 21, 1500 x 128 10.8 / 12.8.
-constexpr int kWaveLanesLog2 = 4, kLongBlocks = 2048;
+// Whether a wavefront takes a piece instead of a block, four to a block.  As long as the chip gets through the blocks in a round
+// or two (it holds 2048) four wavefronts are done sooner than one, with a popular row's many pieces above all.  With more, in a
+// batch of dense neighbourhoods, what counts is how many pieces are in flight, and a piece of narrow rows has too little work for
+// a block (of 17 entries of 2 lanes it uses an eighth).  Rows of more than 16 lanes stay with the block: they give it enough to
+// do, and a wavefront would add up 64 entries and more one after the other.  us, a block / a wavefront per piece, rows x entries: 2
+// lanes, 20000 x 17 43 / 15, 4000 x 200 37 / 13, 1500 x 17 7.1 / 5.0, 200 x 128 5.1 / 6.2; 8 lanes, 20000 x 17 35 / 15, 1500 x 128
+// 8.7 / 8.9, 500 x 128 7.1 / 8.1; 16 lanes, 20000 x 17 37 / 18, 4000 x 200 35 / 21, 1500 x 128 10.8 / 12.8, 3000 x 30 and 5 x 10000
+// 11.5 / 16.1.
+constexpr int kWaveLanesLog2 = 4;
 inline bool long_rows_by_wave(int pieces, int lanes_log2) {
-  return lanes_log2 <= kWaveLanesLog2 && pieces > (lanes_log2 < kWaveLanesLog2 ? kLongBlocks / 2 : kLongBlocks);
+  return lanes_log2 <= kWaveLanesLog2 && pieces > (lanes_log2 <= 2 ? 1024 : 256 << lanes_log2);
 }
 __host__ __device__ inline int long_blocks(int pieces, bool by_wave) { return by_wave ? (pieces + 3) / 4 : pieces; }
 
@@ -78,16 +81,30 @@ template <int N> __device__ __forceinline__ void put_partial(float *at, const fl
     __hip_atomic_store(o + k / 2, (unsigned long long)__float_as_uint(acc[k]) | ((unsigned long long)__float_as_uint(acc[k + 1]) << 32),
                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-template <int N> __device__ __forceinline__ void add_partial(float (&acc)[N], const float *at) {
-  const unsigned long long *o = reinterpret_cast<const unsigned long long *>(at);
-  unsigned long long v[N / 2];
+// Adds the same vector of the partial sums g, g + groups, ... of n, `pitch` floats apart.  A source of 50k destinations has 400 of
+// them, so U are in flight as long as there are U: 16 floats a lane where a block takes a piece, which leaves the launch's short
+// rows their eight wavefronts per SIMD, 32 where a wavefront does.
+template <int N, int U> __device__ __forceinline__ void add_partials(float (&acc)[N], const float *at, int pitch, int g, int groups, int n) {
+  auto take = [&](auto count, int j) {
+    constexpr int C = decltype(count)::value;
+    unsigned long long v[C][N / 2];
 #pragma unroll
-  for (int k = 0; k < N / 2; ++k) v[k] = __hip_atomic_load(o + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int u = 0; u < C; ++u) {
+      const unsigned long long *o = reinterpret_cast<const unsigned long long *>(at + (int64_t)(j + u * groups) * pitch);
 #pragma unroll
-  for (int k = 0; k < N; k += 2) {
-    acc[k] += __uint_as_float((uint32_t)v[k / 2]);
-    acc[k + 1] += __uint_as_float((uint32_t)(v[k / 2] >> 32));
-  }
+      for (int k = 0; k < N / 2; ++k) v[u][k] = __hip_atomic_load(o + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+#pragma unroll
+    for (int u = 0; u < C; ++u)
+#pragma unroll
+      for (int k = 0; k < N; k += 2) {
+        acc[k] += __uint_as_float((uint32_t)v[u][k / 2]);
+        acc[k + 1] += __uint_as_float((uint32_t)(v[u][k / 2] >> 32));
+      }
+  };
+  int j = g;
+  for (; j + (U - 1) * groups < n; j += U * groups) take(std::integral_constant<int, U>{}, j);
+  for (; j < n; j += groups) take(std::integral_constant<int, 1>{}, j);
 }
 // Called by the wavefront that stored a piece's partial sum: its stores are at the coherence point before the count goes up.
 // Returns how many pieces of the row were there before.
@@ -153,8 +170,7 @@ __device__ __forceinline__ void long_row_piece(const LongPiece &p, int item, int
     float acc[N];
 #pragma unroll
     for (int k = 0; k < N; ++k) acc[k] = 0.f;
-    if (q < nvec)
-      for (int j = g; j < p.pieces; j += groups) add_partial<N>(acc, partial + (int64_t)(p.first + j) * pitch + q * N);
+    if (q < nvec) add_partials<N, 16 / N>(acc, partial + (int64_t)p.first * pitch + q * N, pitch, g, groups, p.pieces);
     if (meet(acc) && q < nvec) done(q, acc);
   }
 }
@@ -186,8 +202,7 @@ __device__ __forceinline__ void long_row_wave(const LongPiece &p, int item, int 
   if (mine) put_partial<N>(partial + (int64_t)item * pitch + q * N, acc);
   if (count_piece(count + p.row) != (uint32_t)(p.pieces - 1)) return;
   clear();
-  if (q < nvec)
-    for (int j = g; j < p.pieces; j += groups) add_partial<N>(acc, partial + (int64_t)(p.first + j) * pitch + q * N);
+  if (q < nvec) add_partials<N, 32 / N>(acc, partial + (int64_t)p.first * pitch + q * N, pitch, g, groups, p.pieces);
   meet();
   if (mine) done(q, acc);
 }

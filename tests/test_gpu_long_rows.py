@@ -75,7 +75,7 @@ def test_long_transpose_rows(kind, widths, H, heads, dtype):
     model.close()
 
 
-MIXES = {"few": LENGTHS + [1] * 60, "many": [17, 18, 31, 64, 65, 127, 128, 129, 300, 2] * 200}   # the second: 2400 pieces
+MIXES = {"few": LENGTHS + [1] * 60, "many": [17, 18, 31, 64, 65, 127, 128, 129, 300, 2] * 360}   # the second: 4320 pieces
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
