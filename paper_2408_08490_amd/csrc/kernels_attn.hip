@@ -331,9 +331,9 @@ struct RowStage {
 // maximum grows; four neighbour rows in flight.  Bound: the gather of fp32 rows (1 KB at H = 256; 2.3 GB through the L2s at
 // 6.5 TB/s, the caches in front of HBM included) and, close behind, the vector unit.  561k rows of 1.6M edges: 425 us with a
 // chain of three loads and cross-lane reads through LDS on every row, 355 with both gone.
-template <typename TS>
+template <typename TS, bool PAST>
 __global__ void __launch_bounds__(256) attn_agg_kernel(LayerDev L, RelRows rr, AttnPtrs ap, int H, int heads, int lpr_log2, int hl,
-                                                       int rpg, int past, const float *__restrict__ z, float *__restrict__ mout,
+                                                       int rpg, const float *__restrict__ z, float *__restrict__ mout,
                                                        float *__restrict__ mx, float *__restrict__ ls) {
   __shared__ RowStage st;
   const int gpb = 256 >> lpr_log2;
@@ -385,10 +385,10 @@ __global__ void __launch_bounds__(256) attn_agg_kernel(LayerDev L, RelRows rr, A
 #pragma unroll
       for (int d = 0; d < 4; ++d) acc[d] *= inv;
     }
-    // Aggregates that the caches cannot hold until they are read go past them: what the L2 holds of popular neighbours stays
-    // (573 MB: fetched 1.7 GB for the 2.2 GB asked for; 366 -> 355 us).
+    // PAST: the caches keep what the L2 holds of popular neighbours (573 MB of aggregates: fetched 1.7 GB for the 2.2 GB asked for;
+    // 366 -> 355 us).
     const f32x4 out = {acc[0], acc[1], acc[2], acc[3]};
-    if (past) __builtin_nontemporal_store(out, reinterpret_cast<f32x4 *>(mout + rho * H + q * 4));
+    if constexpr (PAST) __builtin_nontemporal_store(out, reinterpret_cast<f32x4 *>(mout + rho * H + q * 4));
     else *reinterpret_cast<f32x4 *>(mout + rho * H + q * 4) = out;
     if ((q & (hl - 1)) == 0) {
       mx[rho * heads + k] = e1 > e0 ? m : 0.f;
@@ -556,18 +556,25 @@ hgnn_status launch_attn_proj(hipStream_t s, int dtype, const TypeTab &tt, const 
   return HGNN_OK;
 }
 
-// bytes of aggregates from which on their stores go past the caches: what the memory-side cache holds
-constexpr int64_t kAggPast = (int64_t)256 << 20;
+// Aggregates go past the caches where the memory-side one (256 MB) cannot hold them beside the projected rows until the scores'
+// kernel reads them (forward of a layer, us, through the caches / past them: 160k rows from 35k of 256 floats, 200 MB, 191 / 207;
+// 110k from 179k, 290 MB, 168.9 / 165.8; 561k from 607k, 1.2 GB, 871 / 858).
+constexpr int64_t kMemorySideCache = (int64_t)256 << 20;
 
 hgnn_status launch_attn_agg(hipStream_t s, int dtype, const LayerDev &L, RelRows rr, const AttnPtrs &ap, int H, int heads,
                             const float *z, float *mout, float *mx, float *ls) {
   if (L.rows == 0) return HGNN_OK;
   const int lpr = H / 4, l2 = log2_exact(lpr), hl = (H / heads) / 4, gpb = 256 >> l2;
   const int rpg = std::min(kStageRows / gpb, rows_per_group(L.rows, gpb, 4096, 4));
-  const int past = (int64_t)L.rows * H * 4 > kAggPast;
+  const bool past = ((int64_t)L.rows + L.src_rows) * H * 4 > kMemorySideCache;
   dim3 grid(tile_relations(rr, gpb * rpg));
-  if (dtype == HGNN_BF16) HGNN_LAUNCH(attn_agg_kernel<bf16>, grid, dim3(256), 0, s, L, rr, ap, H, heads, l2, hl, rpg, past, z, mout, mx, ls);
-  else HGNN_LAUNCH(attn_agg_kernel<float>, grid, dim3(256), 0, s, L, rr, ap, H, heads, l2, hl, rpg, past, z, mout, mx, ls);
+#define HGNN_AGG(TY, PAST) HGNN_LAUNCH((attn_agg_kernel<TY, PAST>), grid, dim3(256), 0, s, L, rr, ap, H, heads, l2, hl, rpg, z, mout, mx, ls)
+  if (dtype == HGNN_BF16) {
+    if (past) HGNN_AGG(bf16, true); else HGNN_AGG(bf16, false);
+  } else {
+    if (past) HGNN_AGG(float, true); else HGNN_AGG(float, false);
+  }
+#undef HGNN_AGG
   HGNN_HIP(hipGetLastError());
   return HGNN_OK;
 }
