@@ -18,6 +18,7 @@ namespace hgnn {
 // edges, 8248 blocks 60.9 / 61.6.
 // Ragged widths keep them in front: 96 and 128 features in bf16, 2280 blocks 34.3 / 35.3, 3280 38.6 / 39.1; in fp32, 2140 45.0 / 45.6;
 // 32 and 384, 3484 44.1 / 45.1; 10 types of 32 to 384, two layers of 72 and 242 outputs 111.9 / 112.3, of 424 and 75 160.0 / 159.1.
+// (With many relations behind would be the better: 104 of ragged widths, 1173 destinations, 34.1 / 32.6.)
 struct JobSplit {
   int tb, b;
   __device__ __forceinline__ explicit JobSplit(const TransposeJobs &tj) {
