@@ -283,18 +283,18 @@ static int launch_gemm_fwd_direct(hipStream_t s, int dtype, const TypeTab &tt, c
   da.seg[n] = DirectSeg{0, 0, 0, INT32_MAX};
   // K-steps per block: those of two blocks per compute unit, but two for every wavefront, which cost about what the block's own
   // start and end do.  In fp32, whose MFMAs take 1.7 us a step, one for every wavefront where the tiles are split in any case
-  // into few blocks and few pieces.  Forward of a layer, us, with two / one: 4 splits, 32 blocks 18.0 / 17.5; 2 splits, 60 blocks
-  // 18.6 / 17.4; 4 splits, 64 blocks 18.4 / 18.5; 5 splits, 150 blocks 21.6 / 24.1; 4 splits, 240 blocks 23.3 / 29.4; 18 splits,
-  // 144 blocks 24.6 / 31.3: twice the pieces are written and added up again.  9 splits, 9 blocks 18.3 / 17.6; 16 and 18 splits,
-  // as many blocks, 19.1 and 19.3 / 19.3 and 19.5: the second kernel's chain.  Where two a wavefront are the whole tile,
-  // splitting it would only add that kernel (28 tiles of 8 steps 13.4 / 15.5).
+  // into few blocks and few pieces: twice the pieces are written and added up again.  Forward of a layer, us, with two / one: 2
+  // splits, 60 blocks 18.6 / 17.4; 3 splits, 90 blocks 18.9 / 18.0, 96 19.5 / 19.3; 5 splits, 95 blocks 20.8 / 20.5, 150 21.6 / 24.1;
+  // 4 splits, 240 blocks 23.3 / 29.4; 8 splits, 8 blocks 18.2 / 17.5, 64 19.3 / 20.0; 9 splits, 9 blocks 18.3 / 17.6, 72 20.7 / 21.1.
+  // 16 and 18 splits, as many blocks, 19.1 and 19.3 / 19.3 and 19.5: the second kernel's chain.  Where two a wavefront are the
+  // whole tile, splitting it would only add that kernel (28 tiles of 8 steps 13.4 / 15.5).
   int64_t most = 0, blocks = 0;
   for (int d = 0; d < T; ++d) {
     const int td = da.tile_off[d + 1] - da.tile_off[d];
     if (td > 0) most = std::max<int64_t>(most, da.steps[d]);
     blocks += (int64_t)td * ((da.steps[d] + 2 * kDirW - 1) / (2 * kDirW));
   }
-  const bool single = dtype != HGNN_BF16 && most > 2 * kDirW && most <= 10 * 2 * kDirW && blocks < 64;
+  const bool single = dtype != HGNN_BF16 && most > 2 * kDirW && most <= 10 * 2 * kDirW && blocks < (most <= 5 * 2 * kDirW ? 112 : 64);
   const int64_t target = std::max<int64_t>(single ? kDirW : 2 * kDirW, (work + 511) / 512);
   int units = 0, max_splits = 1;
   for (int i = 0; i < kMaxT + 8; ++i) da.unit_off[i] = INT32_MAX;
