@@ -8,18 +8,18 @@
 namespace hgnn {
 
 // Block bx (256 threads) of bias_reduce_blocks(): 32 columns of one type; eight groups of 32 lanes sum every
-// eighth row each, four independent loads per trip.
-__device__ __forceinline__ void bias_reduce_part(const TypeTab &tt, const GradPtrTab &gt, int H, int rpb,
-                                                 const float *__restrict__ bpart, int bx) {
+// eighth row each, four independent loads per trip.  n_dst / dbias: per type.
+template <typename N, typename D>
+__device__ __forceinline__ void bias_reduce_part(N n_dst, D dbias, int H, int rpb, const float *__restrict__ bpart, int bx) {
   __shared__ float red[256];
   const int cb = (H + 31) / 32;
   const int t = bx / cb, lane32 = threadIdx.x & 31, part = threadIdx.x >> 5;
   const int c = (bx % cb) * 32 + lane32;
-  float *db = gt.dbias[t];
+  float *db = dbias[t];
   if (!db) return;  // whole block
   int b0 = 0;
-  for (int u = 0; u < t; ++u) b0 += (tt.n_dst[u] + rpb - 1) / rpb;
-  const int nb = (tt.n_dst[t] + rpb - 1) / rpb;
+  for (int u = 0; u < t; ++u) b0 += (n_dst[u] + rpb - 1) / rpb;
+  const int nb = (n_dst[t] + rpb - 1) / rpb;
   float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
   if (c < H) {
     const float *p = bpart + (int64_t)b0 * H + c;

@@ -18,8 +18,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // (64 MI) x (64 NI).  BM x BN is the default tile (MI = NI = 2); launches that would not fill the chip with
 // those use 64x64 tiles (MI = NI = 1).
 constexpr int BM = 128, BN = 128, kThreads = 256;
-constexpr int kSegCap = 96;  // K-segments staged in LDS at a time
-constexpr int kRelWindow = (kSegCap - 1) / 2;  // relations examined per pass of the forward kernel (up to two segments each, and the root)
 
 template <typename T> struct Mma;
 template <> struct Mma<bf16> {
@@ -37,9 +35,9 @@ template <> struct Mma<float> {
 template <typename T> constexpr bool ks_swizzled(int extent) { return sizeof(T) == 2 && extent == 128; }
 template <typename T> constexpr int ks_pitch(int extent) { return ks_swizzled<T>(extent) ? extent : extent + Mma<T>::KSPAD; }
 __device__ __forceinline__ int ks_swizzle_col(int col, int row) { return (((col >> 5) ^ (row & 3)) << 5) | (col & 31); }
-// elements of one LDS stage of an operand tile with `extent` output indices, in either orientation
-template <typename T> constexpr int lds_elems(int extent) {
-  return (extent * Mma<T>::PKC > Mma<T>::BK * ks_pitch<T>(extent)) ? extent * Mma<T>::PKC : Mma<T>::BK * ks_pitch<T>(extent);
+// elements of one LDS stage of an operand tile with `extent` output indices, in either orientation or with K contiguous
+template <typename T> constexpr int lds_elems(int extent, bool kc) {
+  return kc || extent * Mma<T>::PKC > Mma<T>::BK * ks_pitch<T>(extent) ? extent * Mma<T>::PKC : Mma<T>::BK * ks_pitch<T>(extent);
 }
 
 // One K-segment of a tile's reduction: sum over k in [kb, ke) of Aop[.][k] * Bop[.][k].
@@ -64,30 +62,32 @@ struct TileMover {
   typedef const unsigned int __attribute__((address_space(1))) *g32_t;
   typedef const char __attribute__((address_space(1))) *gbyte_t;
   u32x4 reg[NV];
-  unsigned voff[NV];    // byte offset of this thread's pieces from the K-step's base (FAST)
   unsigned okmask = ~0u;  // pieces to keep; the others are stored as zero
 
-  // `o0` = first output index of the tile, `extent` = number of valid output indices, ld in elements.
-  __device__ __forceinline__ void setup(int ld, int extent, int o0) {
+  struct Offsets {   // byte offsets of this thread's pieces from a K-step's base (FAST), the same for all steps of a segment
+    unsigned voff[NV];
+    // `o0` = first output index of the tile, `extent` = number of valid output indices, ld in elements.
+    __device__ __forceinline__ void setup(int ld, int extent, int o0) {
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      const int v = threadIdx.x + i * kThreads;
-      const int r = v / VPR, c = (v % VPR) * VEC;
-      if constexpr (KC) {  // rows = output index, cols = k
-        const int o = o0 + r < extent ? o0 + r : 0;
-        voff[i] = (unsigned)((o * ld + c) * (int)sizeof(T));
-      } else {             // rows = k, cols = output index
-        const int o = o0 + c < extent ? o0 + c : 0;
-        voff[i] = (unsigned)((r * ld + o) * (int)sizeof(T));
+      for (int i = 0; i < NV; ++i) {
+        const int v = threadIdx.x + i * kThreads;
+        const int r = v / VPR, c = (v % VPR) * VEC;
+        if constexpr (KC) {  // rows = output index, cols = k
+          const int o = o0 + r < extent ? o0 + r : 0;
+          voff[i] = (unsigned)((o * ld + c) * (int)sizeof(T));
+        } else {             // rows = k, cols = output index
+          const int o = o0 + c < extent ? o0 + c : 0;
+          voff[i] = (unsigned)((r * ld + o) * (int)sizeof(T));
+        }
       }
     }
-  }
+  };
   // base = operand base advanced to the K-step (KC: + k0 elements, KS: + k0 rows); krem = ke - k0 > 0
-  __device__ __forceinline__ void load_fast(const T *base, int krem) {
+  __device__ __forceinline__ void load_fast(const Offsets &at, const T *base, int krem) {
     gbyte_t b = (gbyte_t)base;
     if (krem >= (KC ? COLS : ROWS)) {
 #pragma unroll
-      for (int i = 0; i < NV; ++i) reg[i] = *(gvec_t)(b + voff[i]);
+      for (int i = 0; i < NV; ++i) reg[i] = *(gvec_t)(b + at.voff[i]);
       okmask = ~0u;
     } else {
       unsigned m = 0;
@@ -96,7 +96,7 @@ struct TileMover {
         const int v = threadIdx.x + i * kThreads;
         const int kk = KC ? (v % VPR) * VEC : v / VPR;   // first k index of the piece within the step
         const bool ok = kk < krem;                        // K extents are multiples of VEC here
-        reg[i] = *(gvec_t)(b + (ok ? voff[i] : 0u));
+        reg[i] = *(gvec_t)(b + (ok ? at.voff[i] : 0u));
         m |= ok ? (1u << i) : 0u;
       }
       okmask = m;
@@ -300,12 +300,11 @@ __device__ __forceinline__ void mma_tile_split(f32x16 (&acc)[MI][NI], const bf16
   }
 }
 
-// LDS of one block: two stages of (A tile, B tile) -- reused as the output staging tile by the epilogues --
-// and the K-segment table.
-template <typename T, int MI = 2, int NI = 2> struct GemmLds {
-  __attribute__((aligned(16))) T a[2][lds_elems<T>(64 * MI)];
-  __attribute__((aligned(16))) T b[2][lds_elems<T>(64 * NI)];
-  Seg<T> seg[kSegCap];
+// LDS of one block: two stages of (A tile, B tile), reused as the output staging tile by the epilogues.
+// KC: both operands with K contiguous.
+template <typename T, int MI = 2, int NI = 2, bool KC = false> struct GemmLds {
+  __attribute__((aligned(16))) T a[2][lds_elems<T>(64 * MI, KC)];
+  __attribute__((aligned(16))) T b[2][lds_elems<T>(64 * NI, KC)];
   float rowscale[64 * MI];
 };
 constexpr int kOutPitchPad = 8;  // floats: staged rows stay 16-byte aligned, rows r and r + 4 lie 32 banks apart
@@ -321,15 +320,26 @@ struct NoXform {
   template <typename M> __device__ __forceinline__ void operator()(M &, int) const {}
 };
 
-// Runs the K-steps of sm.seg[0..nseg) (must be visible to the whole block) into `acc`.
+// A reduction over one segment.
+template <typename T> struct OneSeg {
+  static constexpr bool kRedo = true;   // on the fp32 MFMA it is only what gemm_finite falls back on
+  Seg<T> g;
+  __device__ __forceinline__ int steps() const { return (g.ke - g.kb + Mma<T>::BK - 1) / Mma<T>::BK; }
+  __device__ __forceinline__ void next(Seg<T> &o) { o = g; }
+};
+
+// Runs the K-steps of the segments that `segs` hands out one after the other (the same ones to every lane) into `acc`; steps():
+// how many there are.  Segments come from scalar registers and scalar loads: a table of them in LDS, made by the first wavefront
+// from the general tables, was 2.7 us in front of a tile's first load.
 // KC operand: matrix [extent x K] row-major (ld); KS operand: matrix [K x extent] row-major (ld).
 // xa(mover, step) / xb: what happens to a K-step's operand tile in the registers, on its way to LDS.
 // FAST fp32 tiles run on the bf16 matrix cores (see mma_tile_split) unless SPLIT is false; call them through
 // gemm_finite, which sees to infinities.
-template <typename T, bool FAST, bool AKC, bool BKC, bool SPLIT = FAST && sizeof(T) == 4, int MI, int NI, typename XA = NoXform, typename XB = NoXform>
-__device__ __forceinline__ void gemm_run(f32x16 (&acc)[MI][NI], GemmLds<T, MI, NI> &sm, int nseg, int a_extent, int a0,
+template <typename T, bool FAST, bool AKC, bool BKC, bool SPLIT = FAST && sizeof(T) == 4, int MI, int NI, bool LKC, typename Segs, typename XA = NoXform, typename XB = NoXform>
+__device__ __forceinline__ void gemm_run(f32x16 (&acc)[MI][NI], GemmLds<T, MI, NI, LKC> &sm, Segs segs, int a_extent, int a0,
                                          int b_extent, int b0, XA xa = XA(), XB xb = XB()) {
   using M = Mma<T>;
+  static_assert(!LKC || (AKC && BKC));
   constexpr int TM = 64 * MI, TN = 64 * NI;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = (wave >> 1) * 32 * MI, wn = (wave & 1) * 32 * NI;
@@ -337,34 +347,34 @@ __device__ __forceinline__ void gemm_run(f32x16 (&acc)[MI][NI], GemmLds<T, MI, N
   using MoverB = TileMover<T, BKC ? TN : M::BK, BKC ? M::BK : TN, BKC ? M::PKC : ks_pitch<T>(TN), BKC>;
   MoverA ta0, ta1;
   MoverB tb0, tb1;
-  int total = 0;
-  for (int s = 0; s < nseg; ++s) total += (sm.seg[s].ke - sm.seg[s].kb + M::BK - 1) / M::BK;
-  int s_ld = 0, k_ld = nseg > 0 ? sm.seg[0].kb : 0;  // cursor of the loader, two K-steps ahead of the multiplier
-  int s_set0 = -1, s_set1 = -1;                      // segment each register set's offsets were computed for
-  // The loader's segment is kept in scalar registers and read from LDS only when the loader moves on to the next
-  // one: read per K-step, the LDS round trip sits in the step's chain of dependent operations.
+  const int total = segs.steps();
+  // cursor of the loader, two K-steps ahead of the multiplier, and its segment
   Seg<T> g;
-  int s_cached = -1;
-  auto issue = [&](MoverA &ta, MoverB &tb, int &s_set) {
-    if (s_ld >= nseg) return;
-    if (s_cached != s_ld) {
-      const Seg<T> v = sm.seg[s_ld];
+  g.ke = 0;
+  int k_ld = 0, to_load = total;
+  typename MoverA::Offsets oa;
+  typename MoverB::Offsets ob;
+  auto issue = [&](MoverA &ta, MoverB &tb) {
+    if (to_load <= 0) return;
+    --to_load;
+    if (k_ld >= g.ke) {
+      Seg<T> v;
+      segs.next(v);
       g.A = uniform_ptr(v.A);
       g.B = uniform_ptr(v.B);
       g.lda = __builtin_amdgcn_readfirstlane(v.lda);
       g.ldb = __builtin_amdgcn_readfirstlane(v.ldb);
       g.kb = __builtin_amdgcn_readfirstlane(v.kb);
       g.ke = __builtin_amdgcn_readfirstlane(v.ke);
-      s_cached = s_ld;
+      k_ld = g.kb;
+      if constexpr (FAST) {
+        oa.setup(g.lda, a_extent, a0);
+        ob.setup(g.ldb, b_extent, b0);
+      }
     }
     if constexpr (FAST) {
-      if (s_set != s_ld) {
-        ta.setup(g.lda, a_extent, a0);
-        tb.setup(g.ldb, b_extent, b0);
-        s_set = s_ld;
-      }
-      ta.load_fast(AKC ? g.A + k_ld : g.A + (int64_t)k_ld * g.lda, g.ke - k_ld);
-      tb.load_fast(BKC ? g.B + k_ld : g.B + (int64_t)k_ld * g.ldb, g.ke - k_ld);
+      ta.load_fast(oa, AKC ? g.A + k_ld : g.A + (int64_t)k_ld * g.lda, g.ke - k_ld);
+      tb.load_fast(ob, BKC ? g.B + k_ld : g.B + (int64_t)k_ld * g.ldb, g.ke - k_ld);
     } else {
       if constexpr (AKC) ta.load_slow(g.A, g.lda, a_extent, g.ke, a0, k_ld);
       else ta.load_slow(g.A, g.lda, g.ke, a_extent, k_ld, a0);
@@ -372,31 +382,40 @@ __device__ __forceinline__ void gemm_run(f32x16 (&acc)[MI][NI], GemmLds<T, MI, N
       else tb.load_slow(g.B, g.ldb, g.ke, b_extent, k_ld, b0);
     }
     k_ld += M::BK;
-    if (k_ld >= g.ke) {
-      ++s_ld;
-      if (s_ld < nseg) k_ld = sm.seg[s_ld].kb;
-    }
   };
-  issue(ta0, tb0, s_set0);
-  issue(ta1, tb1, s_set1);
+  if constexpr (FAST && sizeof(T) == 4 && !SPLIT && Segs::kRedo) {   // nothing in flight: it needs no registers beside the planes' form
+#pragma unroll 1
+    for (int step = 0; step < total; ++step) {
+      issue(ta0, tb0);
+      xa(ta0, step);
+      xb(tb0, step);
+      ta0.store(sm.a[0]);
+      tb0.store(sm.b[0]);
+      __syncthreads();
+      mma_tile<T, AKC, BKC>(acc, sm.a[0], sm.b[0], wm, wn, lane);
+      __syncthreads();
+    }
+    return;
+  }
+  issue(ta0, tb0);
+  issue(ta1, tb1);
   if constexpr (SPLIT) {
     static_assert(3 * split_plane<AKC>(TM) * sizeof(bf16) <= sizeof(sm.a) && 3 * split_plane<BKC>(TN) * sizeof(bf16) <= sizeof(sm.b), "planes must fit the stages");
     bf16 *pa = reinterpret_cast<bf16 *>(&sm.a[0][0]), *pb = reinterpret_cast<bf16 *>(&sm.b[0][0]);
-    auto one = [&](MoverA &ta, MoverB &tb, int &s_set, int step) {
+    auto one = [&](MoverA &ta, MoverB &tb, int step) {
       xa(ta, step);
       xb(tb, step);
       split_store<AKC, TM>(ta, pa);
       split_store<BKC, TN>(tb, pb);
       __syncthreads();
-      issue(ta, tb, s_set);
+      issue(ta, tb);
       mma_tile_split<AKC, BKC>(acc, pa, pb, wm, wn, lane);
       __syncthreads();
     };
     for (int step = 0; step < total; step += 2) {
-      one(ta0, tb0, s_set0, step);
-      if (step + 1 < total) one(ta1, tb1, s_set1, step + 1);
+      one(ta0, tb0, step);
+      if (step + 1 < total) one(ta1, tb1, step + 1);
     }
-    __syncthreads();   // a caller without K-steps may rewrite the segment table too
     return;
   }
   for (int step = 0; step < total; step += 2) {
@@ -405,7 +424,7 @@ __device__ __forceinline__ void gemm_run(f32x16 (&acc)[MI][NI], GemmLds<T, MI, N
     ta0.store(sm.a[0]);
     tb0.store(sm.b[0]);
     __syncthreads();
-    issue(ta0, tb0, s_set0);
+    issue(ta0, tb0);
     mma_tile<T, AKC, BKC>(acc, sm.a[0], sm.b[0], wm, wn, lane);
     if (step + 1 < total) {
       xa(ta1, step + 1);
@@ -413,11 +432,11 @@ __device__ __forceinline__ void gemm_run(f32x16 (&acc)[MI][NI], GemmLds<T, MI, N
       ta1.store(sm.a[1]);
       tb1.store(sm.b[1]);
       __syncthreads();
-      issue(ta1, tb1, s_set1);
+      issue(ta1, tb1);
       mma_tile<T, AKC, BKC>(acc, sm.a[1], sm.b[1], wm, wn, lane);
     }
   }
-  __syncthreads();  // the segment table and the stages may be rewritten by the caller
+  __syncthreads();  // the stages may be rewritten by the caller
 }
 
 template <int MI, int NI> __device__ __forceinline__ void zero_acc(f32x16 (&acc)[MI][NI]) {
@@ -482,8 +501,8 @@ __device__ __forceinline__ void gemm_finite(f32x16 (&acc)[MI][NI], F run, bool f
 // The output type TO may differ from the operands' T (bf16 operands, fp32 result).  The staged tile is fp32 whatever T is: 32-bit LDS writes with a pitch that puts the two half-waves
 // (rows r and r + 4 of one store) on disjoint banks; two lanes writing the halves of one dword would be
 // serialised.  Conversion to T happens on the way out.
-template <typename T, typename TO, typename F, int MI, int NI>
-__device__ __forceinline__ void write_tile(f32x16 (&acc)[MI][NI], GemmLds<T, MI, NI> &sm, TO *out, int64_t ld, int rows, int cols, F f) {
+template <typename T, typename TO, typename F, int MI, int NI, bool LKC>
+__device__ __forceinline__ void write_tile(f32x16 (&acc)[MI][NI], GemmLds<T, MI, NI, LKC> &sm, TO *out, int64_t ld, int rows, int cols, F f) {
   constexpr int TM = 64 * MI, TN = 64 * NI;
   constexpr int V = 16 / sizeof(TO), P = TN + kOutPitchPad;
   static_assert(sizeof(sm.a) + sizeof(sm.b) >= sizeof(float) * P * TM, "fp32 output tile must fit the stages");
@@ -575,9 +594,5 @@ static inline int balance_xcd(const int32_t *tile_off, const int64_t *cost, int 
   return longest * 8;
 }
 
-template <typename T>
-__device__ __forceinline__ void put_seg(Seg<T> &g, const T *A, int lda, const T *B, int ldb, int kb, int ke) {
-  g.A = A; g.B = B; g.lda = lda; g.ldb = ldb; g.kb = kb; g.ke = ke;
-}
 
 }  // namespace hgnn

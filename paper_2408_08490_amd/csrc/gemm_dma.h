@@ -13,6 +13,9 @@
 #include "gemm_core.h"
 
 namespace hgnn {
+__device__ __forceinline__ void put_seg(Seg<bf16> &g, const bf16 *A, int lda, const bf16 *B, int ldb, int kb, int ke) {
+  g.A = A; g.B = B; g.lda = lda; g.ldb = ldb; g.kb = kb; g.ke = ke;
+}
 namespace dma {
 
 constexpr int kThreads = 512, kWaves = 8;

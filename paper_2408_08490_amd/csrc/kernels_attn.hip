@@ -143,9 +143,10 @@ __device__ __forceinline__ void wide_run(f32x16 (&acc)[MI][NI], WideLds<MI, NI> 
   const int wm = (wave >> 1) * 32 * MI, wn = (wave & 1) * 32 * NI;
   WideMover<TM> ma;
   TileMover<bf16, BKC ? TN : kWideBK, BKC ? kWideBK : TN, PB, BKC> mb;
-  mb.setup(ldb, b_extent, b0);
+  typename decltype(mb)::Offsets ob;
+  ob.setup(ldb, b_extent, b0);
   ma.load(A, lda, a_extent, a0, 0, K);
-  mb.load_fast(B, K);
+  mb.load_fast(ob, B, K);
   for (int k0 = 0; k0 < K; k0 += kWideBK) {
     const int kc = k0 + (threadIdx.x % WideMover<TM>::VPR) * 4;
     ma.store(sm.a, [&](f32x4 v) { return f(v, kc); });
@@ -153,7 +154,7 @@ __device__ __forceinline__ void wide_run(f32x16 (&acc)[MI][NI], WideLds<MI, NI> 
     __syncthreads();
     if (k0 + kWideBK < K) {
       ma.load(A, lda, a_extent, a0, k0 + kWideBK, K);
-      mb.load_fast(BKC ? B + k0 + kWideBK : B + (int64_t)(k0 + kWideBK) * ldb, K - k0 - kWideBK);
+      mb.load_fast(ob, BKC ? B + k0 + kWideBK : B + (int64_t)(k0 + kWideBK) * ldb, K - k0 - kWideBK);
     }
     constexpr int NK = kWideBK / 16;
     bf16x8_t b[NK][NI];
@@ -205,8 +206,9 @@ __device__ __forceinline__ void wide_run_f32(f32x16 (&acc)[MI][NI], WideLds<MI, 
         *reinterpret_cast<f32x4 *>(af + r * kWidePF + c) = f(x, k0 + c);
       }
       TileMover<bf16, BKC ? TN : kWideBK, BKC ? kWideBK : TN, PB, BKC> mb;
-      mb.setup(ldb, b_extent, b0);
-      mb.load_fast(BKC ? B + k0 : B + (int64_t)k0 * ldb, K - k0);
+      typename decltype(mb)::Offsets ob;
+      ob.setup(ldb, b_extent, b0);
+      mb.load_fast(ob, BKC ? B + k0 : B + (int64_t)k0 * ldb, K - k0);
       mb.store(sm.b);
     }
     __syncthreads();
@@ -267,10 +269,9 @@ __device__ __forceinline__ void mix_run(f32x16 (&acc)[MI][2], MixLds<TS, MI> &sm
       else wide_run_f32<BKC>(acc, sm.w, A, lda, a_extent, a0, B, ldb, b_extent, b0, K, f);
     });
   } else {
-    if (threadIdx.x == 0) put_seg(sm.g.seg[0], A, lda, B, ldb, 0, K);
-    __syncthreads();
+    const OneSeg<float> one{Seg<float>{A, B, lda, ldb, 0, K}};
     gemm_finite<float, true>(acc, [&](auto split) {
-      gemm_run<float, true, true, BKC, split.value>(acc, sm.g, 1, a_extent, a0, b_extent, b0, [&](auto &mv, int step) {
+      gemm_run<float, true, true, BKC, split.value>(acc, sm.g, one, a_extent, a0, b_extent, b0, [&](auto &mv, int step) {
         const int kc = step * Mma<float>::BK + (threadIdx.x % (Mma<float>::BK / 4)) * 4;
         for (auto &r : mv.reg) r = __builtin_bit_cast(u32x4, f(__builtin_bit_cast(f32x4, r), kc));
       });
@@ -297,9 +298,8 @@ __global__ void __launch_bounds__(kThreads, 2) attn_proj_kernel(TypeTab tt, PtrT
   const int m0 = (local / tiles_n) * BM, n0 = (local % tiles_n) * BN;
   const int M = tt.row_off[t + 1] - tt.row_off[t], F = tt.in_dim[t];
   f32x16 acc[MI][MI];
-  if (threadIdx.x == 0) put_seg(sm.seg[0], x + tt.elem_off[t], F, reinterpret_cast<const TS *>(pt.w_root[t]), H, 0, F);
-  __syncthreads();
-  gemm_finite<TS, true>(acc, [&](auto split) { gemm_run<TS, true, true, false, split.value>(acc, sm, 1, M, m0, H, n0); });
+  const OneSeg<TS> one{Seg<TS>{x + tt.elem_off[t], reinterpret_cast<const TS *>(pt.w_root[t]), F, H, 0, F}};
+  gemm_finite<TS, true>(acc, [&](auto split) { gemm_run<TS, true, true, false, split.value>(acc, sm, one, M, m0, H, n0); });
   write_tile(acc, sm, z + ((int64_t)tt.row_off[t] + m0) * H + n0, H, M - m0, H - n0, [](float v, int, int) { return v; });
 }
 
@@ -742,13 +742,12 @@ __device__ __forceinline__ void attn_dws_part(GemmLds<float, 2, 2> &sm, const fl
                                               int H, int f0, float coef, const float *qs, float *__restrict__ dws,
                                               float *__restrict__ dq, float *__restrict__ dbs) {
   f32x16 acc[2][2];
-  if (threadIdx.x == 0) put_seg(sm.seg[0], m + row0 * H, H, t + row0 * kSemDim, kSemDim, k_begin, k_end);
-  __syncthreads();
+  const OneSeg<float> one{Seg<float>{m + row0 * H, t + row0 * kSemDim, H, kSemDim, k_begin, k_end}};
   float st[4], s1[4];
   gemm_finite<float, true>(acc, [&](auto split) {
 #pragma unroll
     for (int c = 0; c < 4; ++c) st[c] = s1[c] = 0.f;
-    gemm_run<float, true, false, false, split.value>(acc, sm, 1, H, f0, kSemDim, 0, NoXform(), [&](auto &mv, int) {
+    gemm_run<float, true, false, false, split.value>(acc, sm, one, H, f0, kSemDim, 0, NoXform(), [&](auto &mv, int) {
       int i = 0;
       for (auto &rg : mv.reg) {
         const f32x4 v = __builtin_bit_cast(f32x4, rg);
