@@ -34,7 +34,7 @@ template <> __device__ __forceinline__ bf16 from_float<bf16>(float v) {
 // same for the whole wavefront: a lane looks at an entry each, so that the search costs one memory round trip.  Walking the
 // table with scalar loads is one of 0.1 to 0.25 us per step (104 relations: 3 us in front of a launch's first useful load), which
 // is the shorter way through a few entries (one relation: 0.3 us of each of the attention layer's launches).
-template <typename I> __device__ __forceinline__ int wave_find(const I *off, int n, int x) {
+template <typename P> __device__ __forceinline__ int wave_find(P off, int n, int x) {
   if (n <= 3) return n > 1 && (int)off[1] <= x ? (n > 2 && (int)off[2] <= x ? 2 : 1) : 0;
   const int lane = threadIdx.x & 63;
   int c = 0;

@@ -725,13 +725,18 @@ __global__ void __launch_bounds__(256) attn_mask_dbeta_kernel(RelRows rr, TypeTi
   for (int i = threadIdx.x; i < j1 - j0; i += 256) atomicAdd(dbeta + ro.rel[j0 + i], part[i]);
 }
 
-// coef_r = beta_r (dbeta_r - sum_r' beta_r' dbeta_r') / M_d, the factor of q (1 - t^2) in du.
-__device__ __forceinline__ float relation_coef(const RelRows &rr, const float *__restrict__ beta, const float *__restrict__ dbeta, int r) {
-  const int d = rr.dst[r];
+// coef_r = beta_r (dbeta_r - sum_r' beta_r' dbeta_r') / M_d, the factor of q (1 - t^2) in du.  A lane takes a relation each, so
+// that the sum costs one memory round trip; r is the same for the wavefront.  (561k rows, 8 relations, one after the other 620 us, so 601.)
+typedef const RelRows __attribute__((address_space(4))) *rel_rows_t;   // an argument, read where it lies
+__device__ __forceinline__ float relation_coef(rel_rows_t rr, const float *__restrict__ beta, const float *__restrict__ dbeta, int r) {
+  const int d = rr->dst[r], lane = threadIdx.x & 63;
+  const float br = beta[r], dbr = dbeta[r];
   float dot = 0.f;
-  for (int o = 0; o < rr.n; ++o)
-    if (rr.dst[o] == d) dot += beta[o] * dbeta[o];
-  return beta[r] * (dbeta[r] - dot) / (float)(rr.row_off[r + 1] - rr.row_off[r]);
+  for (int o = lane; o < rr->n; o += 64)
+    if (rr->dst[o] == d) dot += beta[o] * dbeta[o];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) dot += __shfl_xor(dot, o);
+  return br * (dbr - dot) / (float)(rr->row_off[r + 1] - rr->row_off[r]);
 }
 
 // dW_s += m^T du, dq += coef sum t, db_s += coef q sum (1 - t^2) over `rows` rows of one relation: the block multiplies
@@ -810,7 +815,7 @@ __device__ __forceinline__ void attn_dm_part(MixLds<TS, MI> &sm, const float *t,
 // Both products of the semantic attention's backward in ONE launch, their blocks interleaved: dW_s is bound by splitting its
 // operands and by LDS, dm by memory, and neither depends on the other.
 template <typename TS, int MI>
-__global__ void __launch_bounds__(kThreads, 2) attn_sem_bwd_kernel(RelRows dwt, RelRows dmt, SemBwd p, int H, const float *__restrict__ mbuf,
+__global__ void __launch_bounds__(kThreads, 2) attn_sem_bwd_kernel(RelRows, RelRows, SemBwd p, int H, const float *__restrict__ mbuf,
                                                                  const float *__restrict__ tbuf, const TS *__restrict__ w_sem,
                                                                  const TS *__restrict__ q_sem, const TS *__restrict__ gp,
                                                                  const float *__restrict__ beta, const float *__restrict__ dbeta,
@@ -822,24 +827,22 @@ __global__ void __launch_bounds__(kThreads, 2) attn_sem_bwd_kernel(RelRows dwt, 
   };
   __shared__ Lds sm;
   __shared__ __attribute__((aligned(16))) float qs[kSemDim];
-  if (threadIdx.x < kSemDim) qs[threadIdx.x] = to_float(q_sem[threadIdx.x]);
-  __syncthreads();
+  const float qv = threadIdx.x < kSemDim ? to_float(q_sem[threadIdx.x]) : 0.f;
   const int64_t total = gridDim.x, b = total - 1 - blockIdx.x;   // from the end: see attn_sem_kernel
-  const int before = (int)(b * p.n_dw / total);
-  if ((int)((b + 1) * p.n_dw / total) > before) {
-    const int tiles_f = (H + 127) / 128, tf = before % tiles_f, sl = before / tiles_f;
-    const int r = wave_find(dwt.tile_off, dwt.n, sl);
-    const int64_t row0 = dwt.row_off[r];
-    const int M = dwt.row_off[r + 1] - (int)row0, k0 = (sl - dwt.tile_off[r]) * p.dw_rows;
-    attn_dws_part(sm.dw, mbuf, tbuf, row0, k0, min(k0 + p.dw_rows, M), H, tf * 128, relation_coef(dwt, beta, dbeta, r), qs, dws, dq, dbs);
-  } else {
-    const int tl = (int)b - before, tiles_n = (H + 127) / 128, tm = tl / tiles_n;
-    const int r = wave_find(dmt.tile_off, dmt.n, tm);
-    const int64_t row0 = dmt.row_off[r];
-    const int M = dmt.row_off[r + 1] - (int)row0;
-    attn_dm_part<TS, MI>(sm.dm, tbuf, w_sem, gp + (int64_t)dmt.gdst[r] * H, dm, row0, M, (tm - dmt.tile_off[r]) * 64 * MI,
-                         (tl % tiles_n) * 128, H, relation_coef(dmt, beta, dbeta, r), beta[r], qs);
-  }
+  const int before = (int)(b * p.n_dw / total), tiles_n = (H + 127) / 128;
+  const bool dw = (int)((b + 1) * p.n_dw / total) > before;
+  const int item = dw ? before : (int)b - before, col = item % tiles_n, tl = item / tiles_n;
+  const rel_rows_t rr = (rel_rows_t)__builtin_amdgcn_kernarg_segment_ptr() + (dw ? 0 : 1);   // dwt or dmt
+  const int r = __builtin_amdgcn_readfirstlane(wave_find(rr->tile_off, rr->n, tl)), k0 = tl - rr->tile_off[r];
+  const int64_t row0 = rr->row_off[r];
+  const int M = rr->row_off[r + 1] - (int)row0;
+  const float coef = relation_coef(rr, beta, dbeta, r);
+  if (threadIdx.x < kSemDim) qs[threadIdx.x] = qv;
+  __syncthreads();
+  if (dw)
+    attn_dws_part(sm.dw, mbuf, tbuf, row0, k0 * p.dw_rows, min((k0 + 1) * p.dw_rows, M), H, col * 128, coef, qs, dws, dq, dbs);
+  else
+    attn_dm_part<TS, MI>(sm.dm, tbuf, w_sem, gp + (int64_t)rr->gdst[r] * H, dm, row0, M, k0 * 64 * MI, col * 128, H, coef, beta[r], qs);
 }
 
 // Aggregation backward, by merged row; blocks are cut per relation.  A lane group walks `rpg` rows and keeps the sums
