@@ -869,8 +869,12 @@ static hgnn_status fwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
   live_relations(ctx, g, layer, live);
   // The weight transposes ride in the aggregation launch (JobSplit) where there is one; otherwise they are a launch of
   // their own.
+  // A relation without edges takes no part in the products: no tile reads its weight.
   TransposeJobs tj;
-  make_transpose_jobs(pl.tt, pl.rt, pl.pt, pl.wt, pl.H, wtb, tj);
+  PtrTab used = pl.pt;
+  for (int r = 0; r < R; ++r)
+    if (!((live[r >> 5] >> (r & 31)) & 1u)) used.w_rel[r] = nullptr;
+  make_transpose_jobs(pl.tt, pl.rt, used, pl.wt, pl.H, wtb, tj);
   const bool rides = !naive && !feature_cat && transposes_ride(pl);
   if (!rides) {
     Probe pb(ctx, HGNN_K_TRANSPOSE_W, layer, !static_area);
@@ -1208,8 +1212,11 @@ static hgnn_status bwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
   int rpb = 0;  // rows of G per row of bpart: set by the launcher
   if (pl.total_dst > 0) {
     void *gpw = sc + pl.off_gp;
+    PtrTab used = pl.pt;   // a relation without edges has no input gradient, so that nobody reads a padded copy of its weight
+    for (int r = 0; r < R; ++r)
+      if (reo[r + 1] == reo[r]) used.w_rel[r] = nullptr;
     Probe pb(ctx, HGNN_K_RELU_BIAS_BWD, layer);
-    if ((st = launch_bwd_prep(s, ctx->dtype, pl.tt, pl.rt, pl.pt, wo, gt, pl.H, ldg, p->relu, row_pass, any_dw, grad_h, h_out, gpw,
+    if ((st = launch_bwd_prep(s, ctx->dtype, pl.tt, pl.rt, used, wo, gt, pl.H, ldg, p->relu, row_pass, any_dw, grad_h, h_out, gpw,
                               bpart, pl.bpart_rows, wpad, &rpb)) != HGNN_OK) return st;
     if (p->relu || ldg != pl.H) gp = gpw;
   }

@@ -112,7 +112,10 @@ __device__ __forceinline__ void put_quad(T *q, int H, int ncols, f32x4 s, const 
   }
 }
 
-constexpr int kDirW = 4, kDirMT = 4, kDirNT = 4;   // wavefronts; 16x16 tiles per wavefront: a 64x64 tile
+// Wavefronts; 16x16 tiles per wavefront: 64 rows, and 64 columns where there are more than 32 (NT = 4).  A tile of 16 or 32
+// columns is a quarter or half of the MFMAs, 1.7 us of a K-step of 64 columns in fp32 (one tile of 16 columns 8.5 -> 6.7 us; eight of
+// 32, in pieces, with their sum 13.2 -> 10.8 in fp32).
+constexpr int kDirW = 4, kDirMT = 4;
 
 __device__ __forceinline__ int unit_type(direct_args_t pa, int unit) {
   int d = 0;
@@ -123,11 +126,11 @@ __device__ __forceinline__ int unit_type(direct_args_t pa, int unit) {
   return d;
 }
 
-template <typename T>
+template <typename T, int NT>
 __global__ void __launch_bounds__(64 * kDirW, 2) gemm_fwd_direct_kernel(DirectArgs args, const T *__restrict__ x, const T *__restrict__ z,
                                                                         const T *__restrict__ zlo, const T *__restrict__ wtb, T *__restrict__ h,
                                                                         float *__restrict__ part) {
-  constexpr int MT = kDirMT, NT = kDirNT, W = kDirW, BM = 16 * MT, BN = 16 * NT, KS = 2 * Direct<T>::KG, VEC = 16 / sizeof(T), P = BN + 4;
+  constexpr int MT = kDirMT, W = kDirW, BM = 16 * MT, BN = 16 * NT, KS = 2 * Direct<T>::KG, VEC = 16 / sizeof(T), P = BN + 4;
   __shared__ __attribute__((aligned(16))) float red[W][BM * P];
   // The first argument, read where it lies (constant memory, scalar loads): indexed as an ordinary object it can end up
   // copied to every lane's scratch memory first.
@@ -140,6 +143,12 @@ __global__ void __launch_bounds__(64 * kDirW, 2) gemm_fwd_direct_kernel(DirectAr
   const int unit = (int)blockIdx.x - pa->unit_off[d], split = unit / tiles_d, tile = unit % tiles_d;
   const int m0 = (tile / tiles_n) * BM, n0 = (tile % tiles_n) * BN;
   const int begin = (int)((int64_t)steps * split / splits), end = (int)((int64_t)steps * (split + 1) / splits);
+  constexpr int PPR = BN / 4;
+  const int rows = min(BM, M - m0), cols = H - n0, c = (threadIdx.x % PPR) * 4;
+  float bv[4];
+  const T *bias = reinterpret_cast<const T *>(pa->bias[d]);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) bv[k] = splits == 1 && bias && c + k < cols ? to_float(bias[n0 + c + k]) : 0.f;
   f32x4 acc[MT][NT];
 #pragma unroll
   for (int i = 0; i < MT; ++i)
@@ -187,20 +196,14 @@ __global__ void __launch_bounds__(64 * kDirW, 2) gemm_fwd_direct_kernel(DirectAr
 #pragma unroll
       for (int v = 0; v < 4; ++v) red[wave][(16 * i + 4 * (lane >> 4) + v) * P + 16 * j + fr] = acc[i][j][v];
   __syncthreads();
-  constexpr int PPR = BN / 4;
-  const int rows = min(BM, M - m0), cols = H - n0, c = (threadIdx.x % PPR) * 4;
   if (c >= cols) return;
-  float bv[4];
-  const T *bias = reinterpret_cast<const T *>(pa->bias[d]);
-#pragma unroll
-  for (int k = 0; k < 4; ++k) bv[k] = splits == 1 && bias && c + k < cols ? to_float(bias[n0 + c + k]) : 0.f;
-  float *pt = part + (int64_t)(pa->unit_off[d] + tile * splits + split) * (BM * BN);
+  float *pt = part + (int64_t)(pa->unit_off[d] + tile * splits + split) * (64 * 64);
   T *out = h + ((int64_t)pa->out_row[d] + m0) * H + n0 + c;
   for (int r = threadIdx.x / PPR; r < rows; r += 64 * W / PPR) {
     f32x4 s = *reinterpret_cast<const f32x4 *>(&red[0][r * P + c]);
 #pragma unroll
     for (int w = 1; w < W; ++w) s += *reinterpret_cast<const f32x4 *>(&red[w][r * P + c]);
-    if (splits > 1) *reinterpret_cast<f32x4 *>(pt + r * BN + c) = s;
+    if (splits > 1) *reinterpret_cast<f32x4 *>(pt + r * 64 + c) = s;
     else put_quad(out + (int64_t)r * H, H, cols - c, s, bv, pa->relu);
   }
 }
@@ -271,7 +274,7 @@ static int launch_gemm_fwd_direct(hipStream_t s, int dtype, const TypeTab &tt, c
     if (tt.n_dst[d] > 0) {
       for (int r = 0; r < R; ++r)
         if (rt.dst[r] == d && ((live_mask[r >> 5] >> (r & 31)) & 1u) && !put(rt.z_off4[r], wt.rel4[r], tt.in_dim[rt.src[r]], false)) return 0;
-      if (pt.w_root[d] && !put((uint32_t)(tt.xroot_off[d] / 4), wt.root4[d], tt.in_dim[d], true)) return 0;
+      if (pt.w_root[d] && (tt.xroot_off[d] / 4 > UINT32_MAX || !put((uint32_t)(tt.xroot_off[d] / 4), wt.root4[d], tt.in_dim[d], true))) return 0;
     }
     da.n_dst[d] = tt.n_dst[d];
     da.out_row[d] = tt.out_row_off[d];
@@ -309,13 +312,18 @@ static int launch_gemm_fwd_direct(hipStream_t s, int dtype, const TypeTab &tt, c
   if (units > kDirectUnits) return 0;
   const int launches = max_splits > 1 ? 2 : 1;
   if (count_only) return launches;
-#define HGNN_DIRECT(TY)                                                                                                           \
-  {                                                                                                                               \
-    HGNN_LAUNCH(gemm_fwd_direct_kernel<TY>, dim3(units), dim3(64 * kDirW), 0, s, da, (const TY *)x, (const TY *)z, (const TY *)zlo, \
-                (const TY *)wt_buf, (TY *)h, part);                                                                                \
-    if (launches > 1) HGNN_LAUNCH(gemm_fwd_direct_sum_kernel<TY>, dim3(tiles * 4), dim3(256), 0, s, da, part, (TY *)h);             \
+#define HGNN_DIRECT(TY, NT)                                                                                                           \
+  HGNN_LAUNCH((gemm_fwd_direct_kernel<TY, NT>), dim3(units), dim3(64 * kDirW), 0, s, da, (const TY *)x, (const TY *)z, (const TY *)zlo, \
+              (const TY *)wt_buf, (TY *)h, part)
+#define HGNN_DIRECT_N(TY)                                                                                             \
+  {                                                                                                                   \
+    if (H <= 16) HGNN_DIRECT(TY, 1);                                                                                  \
+    else if (H <= 32) HGNN_DIRECT(TY, 2);                                                                             \
+    else HGNN_DIRECT(TY, 4);                                                                                          \
+    if (launches > 1) HGNN_LAUNCH(gemm_fwd_direct_sum_kernel<TY>, dim3(tiles * 4), dim3(256), 0, s, da, part, (TY *)h); \
   }
-  if (dtype == HGNN_BF16) HGNN_DIRECT(bf16) else HGNN_DIRECT(float)
+  if (dtype == HGNN_BF16) HGNN_DIRECT_N(bf16) else HGNN_DIRECT_N(float)
+#undef HGNN_DIRECT_N
 #undef HGNN_DIRECT
   return launches;
 }
