@@ -259,8 +259,8 @@ bool probe_take_events(hipEvent_t *start, hipEvent_t *stop) {
 }
 
 // A forward launch of fewer 128x128 tiles than this leaves compute units without a block (two fit on each of
-// the 256): it uses 64x64 tiles instead -- four times as many, three resident per compute unit.  (Measured on
-// the headline's second layer, 96 tiles of 40 K-steps: 42 -> 33 us.  The backward GEMMs have a rule of their own,
+// the 256): it uses 64x64 tiles instead -- four times as many, four resident per compute unit.  (Measured on
+// the headline's second layer, 96 tiles of 40 K-steps: 42 -> 25 us.  The backward GEMMs have a rule of their own,
 // bwd_small_tiles.)
 constexpr int kSmallTileLimit = 512;
 

@@ -8,10 +8,9 @@
 namespace hgnn {
 
 // Block bx (256 threads) of bias_reduce_blocks(): 32 columns of one type; eight groups of 32 lanes sum every
-// eighth row each, four independent loads per trip.  n_dst / dbias: per type.
+// eighth row each, four independent loads per trip.  n_dst / dbias: per type; red: 256 floats of LDS.
 template <typename N, typename D>
-__device__ __forceinline__ void bias_reduce_part(N n_dst, D dbias, int H, int rpb, const float *__restrict__ bpart, int bx) {
-  __shared__ float red[256];
+__device__ __forceinline__ void bias_reduce_part(N n_dst, D dbias, int H, int rpb, const float *__restrict__ bpart, int bx, float *red) {
   const int cb = (H + 31) / 32;
   const int t = bx / cb, lane32 = threadIdx.x & 31, part = threadIdx.x >> 5;
   const int c = (bx % cb) * 32 + lane32;

@@ -305,7 +305,11 @@ __device__ __forceinline__ void mma_tile_split(f32x16 (&acc)[MI][NI], const bf16
 template <typename T, int MI = 2, int NI = 2, bool KC = false> struct GemmLds {
   __attribute__((aligned(16))) T a[2][lds_elems<T>(64 * MI, KC)];
   __attribute__((aligned(16))) T b[2][lds_elems<T>(64 * NI, KC)];
-  float rowscale[64 * MI];
+  // a factor per row of the output tile, behind the staged tile (once the K loop is done)
+  __device__ __forceinline__ float *rowscale() {
+    static_assert(sizeof(b) >= sizeof(float) * 64 * MI && sizeof(a) + sizeof(b) - sizeof(float) * 64 * MI >= sizeof(float) * (64 * NI + 8) * 64 * MI);
+    return reinterpret_cast<float *>(&b[2]) - 64 * MI;
+  }
 };
 constexpr int kOutPitchPad = 8;  // floats: staged rows stay 16-byte aligned, rows r and r + 4 lie 32 banks apart
 

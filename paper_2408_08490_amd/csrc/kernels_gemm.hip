@@ -234,10 +234,11 @@ __device__ __forceinline__ void da_tile_at(GemmLds<T, MI, MI> &sm, bwd_args_t ar
   const OneSeg<T> one{Seg<T>{gp + (int64_t)args->type[d].g0 * ldg, reinterpret_cast<const T *>(seg->W), ldg, ldg, 0, ldg}};
   f32x16 acc[MI][MI];
   gemm_finite<T, FAST>(acc, [&](auto split) { gemm_run<T, FAST, true, true, split.value>(acc, sm, one, M, m0, F, n0); });
-  if (threadIdx.x < BM) sm.rowscale[threadIdx.x] = end > beg ? 1.f / (float)(end - beg) : 0.f;
+  float *rowscale = sm.rowscale();
+  if (threadIdx.x < BM) rowscale[threadIdx.x] = end > beg ? 1.f / (float)(end - beg) : 0.f;
   __syncthreads();
   write_tile(acc, sm, dz + (int64_t)seg->dz4 * 4 + (int64_t)m0 * F + n0, F, M - m0, F - n0,
-             [&](float v, int row, int) { return v * sm.rowscale[row]; });
+             [&](float v, int row, int) { return v * rowscale[row]; });
 }
 
 // Tiles grouped by destination type and row block (the DwTab's `u` then runs over the column blocks of all the
@@ -369,7 +370,7 @@ __global__ void __launch_bounds__(kThreads, MI == 1 ? 3 : 2) gemm_dw_kernel(BwdA
 // The last n_bias blocks (when bpart is given) add up the partial bias-gradient sums that the row pass over G'
 // left: a few microseconds of work that would otherwise be a launch of its own.
 template <typename T, bool FAST, int MI>
-__global__ void __launch_bounds__(kThreads, MI == 1 ? (sizeof(T) == 4 ? 4 : 3) : 2) gemm_bwd_kernel(BwdArgs args_, const int32_t *__restrict__ rowptr,
+__global__ void __launch_bounds__(kThreads, MI == 1 ? 4 : 2) gemm_bwd_kernel(BwdArgs args_, const int32_t *__restrict__ rowptr,
                                                             const T *__restrict__ x, const T *__restrict__ z, const T *__restrict__ gp,
                                                             T *__restrict__ dz, const float *__restrict__ bpart) {
   __shared__ GemmLds<T, MI, MI> sm;
@@ -381,7 +382,7 @@ __global__ void __launch_bounds__(kThreads, MI == 1 ? (sizeof(T) == 4 ? 4 : 3) :
       bwd_args_t args;
       __device__ __forceinline__ int operator[](int t) const { return args->type[t].n_dst; }
     };
-    bias_reduce_part(TypeRows{args}, args->dbias, args->H, args->rpb, bpart, (int)blockIdx.x - n_gemm);
+    bias_reduce_part(TypeRows{args}, args->dbias, args->H, args->rpb, bpart, (int)blockIdx.x - n_gemm, reinterpret_cast<float *>(&sm));
     return;
   }
   if ((int)blockIdx.x < n_dw) dw_tile<T, FAST, MI>(sm, args, blockIdx.x, x, z, gp);

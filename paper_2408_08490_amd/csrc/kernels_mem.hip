@@ -667,7 +667,8 @@ hgnn_status launch_bwd_prep(hipStream_t s, int dtype, const TypeTab &tt, const R
 }
 
 __global__ void __launch_bounds__(256) bias_reduce_kernel(TypeTab tt, GradPtrTab gt, int H, int rpb, const float *__restrict__ bpart) {
-  bias_reduce_part(tt.n_dst, gt.dbias, H, rpb, bpart, blockIdx.x);
+  __shared__ float red[256];
+  bias_reduce_part(tt.n_dst, gt.dbias, H, rpb, bpart, blockIdx.x, red);
 }
 
 hgnn_status launch_bias_reduce(hipStream_t s, const TypeTab &tt, const GradPtrTab &gt, int H, int rpb, const float *bpart) {

@@ -55,35 +55,34 @@ struct BwdCols {
   void segment(int F) { c128 += (F + 127) / 128; c64 += (F + 63) / 64; }
 };
 // Whether a backward launch of `tiles` tiles of 128x128, whose products run over rows of G' of `width` scalars, uses 64x64
-// ones instead, which are a quarter of the work.  The chip holds 512 of the large ones at a time and 768 of the small.  Below 256
-// large tiles compute units stay empty.  (Figures: us, large / small, of a layer's whole backward in a loop.)
-// fp32 tiles are split into planes on the way to LDS.  Three small blocks of a compute unit cover each other's splitting, loads
-// and barriers better than two large ones; what speaks for the large ones is that an operand is split half as often.
-//   Up to 384 large tiles, one or two to a compute unit, small ones win with long products (width 176, 312 tiles 44.0 / 41.3;
-//   width 256, 324 47.8 / 43.0) and where more than a quarter of the large tiles' columns is padding (64 columns, width 128, 320
-//   32.5 / 27.4; width 64, 320 34.0 / 32.3), not otherwise (width 128: 384 columns 300 35.3 / 37.3, 6 x 128 columns 324 38.1 /
-//   40.5, 96 columns 304 35.6 / 38.8, 192 columns 352 34.5 / 36.0; width 160 348 37.6 / 40.3) except with one column block per
-//   row block, whose tiles share no operand (128 columns of each type, width 128: 308 66.9 / 66.6, 378 72.8 / 71.3).
-//   From there to a full round of 512 mostly large ones do (width 160 504 42.8 / 44.7; 384 columns, width 128 480 42.2 / 45.8).
-//   In a second round that is not full small ones win up to 768 (width 128, 600 58.5 / 48.9, 750 65.0 / 57.8; width 320, 760 99.3 /
-//   95.4), with longer products up to 700 (width 352, 636 100.0 / 91.9, 702 105.2 / 104.0, 750 107.4 / 111.2; width 512, 640
-//   125.5 / 116.6, 748 140 / 151) unless a quarter is padding (192 columns, width 512, 744 126.7 / 115.6).
-// bf16: small ones where a launch of one round of large tiles has products of at most 256 (width 128: 300 44.5 / 30.6, 476
-// 46.2 / 39.4; width 256: 400 46.7 / 43.3, 504 47.9 / 47.7; width 352: 480 50.7 / 52.7).
+// ones instead, which are a quarter of the work.  The chip holds 512 of the large ones at a time and 1024 of the small: four small
+// blocks of a compute unit cover each other's loads, splitting into planes (fp32) and barriers better than two large ones; what
+// speaks for the large ones is that they bring in (and split) an operand half as often, the more the longer the products are.
+// Hence the line falls with the width.  (us, large / small, of a layer's whole backward in a loop; columns: of each of the launch's
+// segments.)
+//   fp32, width 64: 470 tiles 38.8 / 36.9, 1110 70.3 / 62.9, 2928 188 / 174; 128: 640 67.0 / 52.9, 1335 112 / 106 (96 columns 101.2 /
+//   100.9), 1880 155 / 157; 160: 1410 128.1 / 127.5, 1965 188 / 192; 192: 985 98.7 / 93.1, 384 columns 1485 146 / 149; 224: 965 105.2 /
+//   106.5; 256: 675 84.6 / 74.4, 830 99.5 / 96.2 (96 columns 91.5 / 92.7), 1025 121 / 123; 320: 685 97.0 / 87.7, 855 113.4 / 111.7; 512: 675
+//   126 / 120, 696 127.2 / 123.5, 830 148 / 156.
+//   Where a quarter and more of the large tiles' columns is padding, farther out: 192 columns, width 128 1570 113 / 99, 256 1570 165 / 155,
+//   512 1570 279 / 272.  And one full round of large tiles is as good as the small ones at widths of 65 to 160 that they pad little: 128
+//   columns, width 128 320 40.1 / 40.1; 96 columns 300 36 / 36, 400 39.5 / 41.4; width 160 420 41.4 / 42.2.
+//   bf16, width 64: 835 tiles 47.6 / 40.7, 1336 52.5 / 54.7; 128: 545 45.7 / 38.2, 872 49.3 / 47.5, 1336 56 / 61; 256: 648 49.3 / 47.4, 885
+//   55.0 / 59.8; 352: 448 49.9 / 47.9, 615 53.2 / 56.2; 512: 320 50.9 / 45.1, 455 52.4 / 51.0, 472 52.3 / 52.2, 650 57.4 / 63.1.
 static inline bool bwd_small_tiles(int dtype, int tiles, int width, const BwdCols &c) {
   if (tiles < 256) return true;
-  if (dtype == HGNN_BF16) return tiles < 512 && width <= 256;
+  if (dtype == HGNN_BF16) return tiles < (width <= 64 ? 1000 : width <= 128 ? 880 : width <= 256 ? 680 : width <= 352 ? 500 : 460);
   const int padding = 2 * c.c128 - c.c64;   // in blocks of 64 columns, of 2 c128
-  if (tiles < 384) return width > 160 || width <= 64 || 2 * padding > c.c128 || c.c128 <= c.types;
-  return tiles > 512 && tiles < (width <= 320 || 2 * padding >= c.c128 ? 768 : 700);
+  if (2 * padding >= c.c128) return tiles < 1600;
+  if (width <= 64) return tiles < 3000;
+  if (width <= 160 && tiles < 512) return c.c128 <= c.types;   // (one column block per row block: its tiles share no operand)
+  return tiles < (width <= 160 ? 1350 : width <= 192 ? 1000 : width <= 320 ? 800 : 700);
 }
 
 // Rows per slice of the weight-gradient reduction in a launch of `dw_steps` K-steps (over all its tiles) beside
 // `other_steps` K-steps of other tiles.  A block's share is 1/640 of the launch's K-steps: a bit over the chip's 512 block
-// slots, so that the launch is one long round whose end the shorter blocks fill.  With 64x64 tiles it is 1/1280, which is more
-// than the 768 of them that are resident: shares of 1/832 and 1/768 were up to a quarter faster in launches of some 500 small
-// tiles and up to 5 % slower in larger ones with long products (fp32, 128 columns, us at 1/1280, 1/832, 1/768: width 512, 320
-// large tiles 39.5, 29.8, 29.4, but 640 91.7, 96.3, 91.4; width 128, 304 27.4, -, 24.8).  Every slice ends with a tile's worth of atomic adds (the chip does about 0.4e12 a second, 40 ns
+// slots, so that the launch is one long round whose end the shorter blocks fill.  With 64x64 tiles, of which 1024 are resident, it
+// is 1/1280 (1/1024 is within 1 % nearly everywhere; fp32, width 512, 160 large tiles 64.7 / 58.8 us, 728 168.5 / 174.1).  Every slice ends with a tile's worth of atomic adds (the chip does about 0.4e12 a second, 40 ns
 // of all of it per 128x128 tile), hence the least number of K-steps: 32 of bf16 (8 measured 9 us worse on 4096 rows of
 // 512 x 349); an fp32 K-step is several times as long (1.7 us of a compute unit's matrix cores per 128x128 tile), which
 // both keeps the adds cheap beside it and makes long slices a serial chain (64 K-steps in one block were 183 us of a
