@@ -48,10 +48,11 @@ template <typename T> struct Seg {
 
 // One operand tile on its way global -> registers -> LDS.  The tile is ROWS x COLS in the operand's own
 // row-major orientation (COLS contiguous).
-//  * FAST: per-thread byte offsets are computed once per segment (`setup`); a full K-step is NV 16-byte
-//    loads from a wave-uniform base plus those offsets and nothing else.  Pieces whose OUTPUT index is out of
-//    range read a clamped address and are stored as they are: they only feed output rows / columns that the
-//    epilogue never writes.  Only the last, partial K-step of a segment masks (and zero-fills) pieces.
+//  * FAST: per-thread byte offsets are computed once per segment (`setup`); a K-step is NV 16-byte buffer loads from a
+//    wave-uniform base.  Pieces whose OUTPUT index is out of range read a clamped address: they only feed output rows / columns
+//    that the epilogue never writes.  Pieces beyond the segment's end, and whole steps beyond the last (krem <= 0), ask for an
+//    offset outside the buffer, which gives zeros and fetches nothing.  So a K loop issues its loads without a branch around
+//    them: where there is one, the compiler waits for the newest loads before it stores the oldest, and two steps in flight are one.
 //  * generic: element-wise, zero-filled loads.
 template <typename T, int ROWS, int COLS, int PITCH, bool KC>
 struct TileMover {
@@ -62,7 +63,7 @@ struct TileMover {
   typedef const unsigned int __attribute__((address_space(1))) *g32_t;
   typedef const char __attribute__((address_space(1))) *gbyte_t;
   u32x4 reg[NV];
-  unsigned okmask = ~0u;  // pieces to keep; the others are stored as zero
+  unsigned okmask;        // pieces inside the segment (FAST); the others are zero
 
   struct Offsets {   // byte offsets of this thread's pieces from a K-step's base (FAST), the same for all steps of a segment
     unsigned voff[NV];
@@ -73,33 +74,26 @@ struct TileMover {
         const int v = threadIdx.x + i * kThreads;
         const int r = v / VPR, c = (v % VPR) * VEC;
         if constexpr (KC) {  // rows = output index, cols = k
-          const int o = o0 + r < extent ? o0 + r : 0;
-          voff[i] = (unsigned)((o * ld + c) * (int)sizeof(T));
+          voff[i] = (unsigned)(min(r, extent - 1 - o0) * ld + c) * (unsigned)sizeof(T);
         } else {             // rows = k, cols = output index
-          const int o = o0 + c < extent ? o0 + c : 0;
-          voff[i] = (unsigned)((r * ld + o) * (int)sizeof(T));
+          voff[i] = (unsigned)(r * ld + (c < extent - o0 ? c : 0)) * (unsigned)sizeof(T);
         }
       }
     }
   };
-  // base = operand base advanced to the K-step (KC: + k0 elements, KS: + k0 rows); krem = ke - k0 > 0
+  // base = operand base advanced to the tile's first output index and to the K-step; krem = ke - k0
   __device__ __forceinline__ void load_fast(const Offsets &at, const T *base, int krem) {
-    gbyte_t b = (gbyte_t)base;
-    if (krem >= (KC ? COLS : ROWS)) {
+    constexpr int kInside = 0x7ffffff0;
+    constexpr unsigned kOutside = 0x80000000u;
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<T *>(base), 0, krem > 0 ? kInside : 0, 0x00027000);
+    okmask = 0;
 #pragma unroll
-      for (int i = 0; i < NV; ++i) reg[i] = *(gvec_t)(b + at.voff[i]);
-      okmask = ~0u;
-    } else {
-      unsigned m = 0;
-#pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        const int v = threadIdx.x + i * kThreads;
-        const int kk = KC ? (v % VPR) * VEC : v / VPR;   // first k index of the piece within the step
-        const bool ok = kk < krem;                        // K extents are multiples of VEC here
-        reg[i] = *(gvec_t)(b + (ok ? at.voff[i] : 0u));
-        m |= ok ? (1u << i) : 0u;
-      }
-      okmask = m;
+    for (int i = 0; i < NV; ++i) {
+      const int v = threadIdx.x + i * kThreads;
+      const int kk = KC ? (v % VPR) * VEC : v / VPR;   // first k index of the piece within the step
+      const bool ok = kk < krem;                        // K extents are multiples of VEC here
+      reg[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, ok ? at.voff[i] : kOutside, 0, 0);
+      okmask |= ok ? (1u << i) : 0u;
     }
   }
   __device__ __forceinline__ void load_slow(const T *base, int64_t ld, int nrows, int ncols, int r0, int c0) {
@@ -121,14 +115,8 @@ struct TileMover {
       else
         reg[i] = u32x4{e[0], e[1], e[2], e[3]};
     }
-    okmask = ~0u;
   }
   __device__ __forceinline__ void store(T *lds) {
-    if (okmask != ~0u) {
-#pragma unroll
-      for (int i = 0; i < NV; ++i)
-        if (!((okmask >> i) & 1u)) reg[i] = u32x4{0u, 0u, 0u, 0u};
-    }
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       const int v = threadIdx.x + i * kThreads;
@@ -177,6 +165,41 @@ template <typename T, bool AKC, bool BKC, int MI, int NI>
 __device__ __forceinline__ void mma_tile(f32x16 (&acc)[MI][NI], const T *As, const T *Bs, int wm, int wn, int lane) {
   using M = Mma<T>;
   constexpr int PA = AKC ? M::PKC : ks_pitch<T>(64 * MI), PB = BKC ? M::PKC : ks_pitch<T>(64 * NI);
+  if constexpr (sizeof(T) == 4 && AKC && BKC) {
+    // Eight K at a time: a lane reads four of its row, the lower half of the wavefront the first ones, and the halves swap two of
+    // them, which leaves the operands of four MFMAs in order.  Read one by one, in front of every second MFMA, the reads' latency
+    // was on the way of an accumulator's chain.
+    constexpr int G = M::BK / 8;
+    float a[G][MI][4], b[G][NI][4];
+    auto read = [&](float (&f)[4], const float *s, int o, int pitch, int g) {
+      const u32x4 q = *reinterpret_cast<const u32x4 *>(s + (o + (lane & 31)) * pitch + 8 * g + 4 * (lane >> 5));
+      const auto lo = __builtin_amdgcn_permlane32_swap(q.x, q.y, false, false), hi = __builtin_amdgcn_permlane32_swap(q.z, q.w, false, false);
+      f[0] = __uint_as_float(lo[0]);
+      f[1] = __uint_as_float(hi[0]);
+      f[2] = __uint_as_float(lo[1]);
+      f[3] = __uint_as_float(hi[1]);
+    };
+    constexpr int GG = MI * NI > 1 ? 2 : G;   // read ahead
+#pragma unroll
+    for (int g0 = 0; g0 < G; g0 += GG) {
+#pragma unroll
+      for (int g = g0; g < g0 + GG; ++g) {
+#pragma unroll
+        for (int i = 0; i < MI; ++i) read(a[g][i], reinterpret_cast<const float *>(As), wm + i * 32, PA, g);
+#pragma unroll
+        for (int j = 0; j < NI; ++j) read(b[g][j], reinterpret_cast<const float *>(Bs), wn + j * 32, PB, g);
+      }
+#pragma unroll
+      for (int g = g0; g < g0 + GG; ++g)
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+          for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[g][i][k], b[g][j][k], acc[i][j], 0, 0, 0);
+    }
+    return;
+  }
 #pragma unroll
   for (int ks = 0; ks < M::BK / M::KSTEP; ++ks) {
     if constexpr (sizeof(T) == 2) {
@@ -250,11 +273,6 @@ template <bool KC, int EXTENT, typename Mover>
 __device__ __forceinline__ void split_store(Mover &mv, bf16 *lds) {
   constexpr int COLS = KC ? Mma<float>::BK : EXTENT, VPR = COLS / 4, NV = sizeof(mv.reg) / sizeof(mv.reg[0]);
   constexpr int PITCH = split_pitch<KC>(EXTENT), PLANE = split_plane<KC>(EXTENT);
-  if (mv.okmask != ~0u) {
-#pragma unroll
-    for (int i = 0; i < NV; ++i)
-      if (!((mv.okmask >> i) & 1u)) mv.reg[i] = u32x4{0u, 0u, 0u, 0u};
-  }
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
     const int v = threadIdx.x + i * kThreads, row = v / VPR;
@@ -351,17 +369,14 @@ __device__ __forceinline__ void gemm_run(f32x16 (&acc)[MI][NI], GemmLds<T, MI, N
   using MoverB = TileMover<T, BKC ? TN : M::BK, BKC ? M::BK : TN, BKC ? M::PKC : ks_pitch<T>(TN), BKC>;
   MoverA ta0, ta1;
   MoverB tb0, tb1;
-  const int total = segs.steps();
-  // cursor of the loader, two K-steps ahead of the multiplier, and its segment
-  Seg<T> g;
-  g.ke = 0;
+  const int total = __builtin_amdgcn_readfirstlane(segs.steps());
+  // cursor of the loader, two K-steps ahead of the multiplier, and its segment; behind the last step it loads nothing
+  Seg<T> g{};
   int k_ld = 0, to_load = total;
   typename MoverA::Offsets oa;
   typename MoverB::Offsets ob;
   auto issue = [&](MoverA &ta, MoverB &tb) {
-    if (to_load <= 0) return;
-    --to_load;
-    if (k_ld >= g.ke) {
+    if (to_load > 0 && k_ld >= g.ke) {
       Seg<T> v;
       segs.next(v);
       g.A = uniform_ptr(v.A);
@@ -377,16 +392,19 @@ __device__ __forceinline__ void gemm_run(f32x16 (&acc)[MI][NI], GemmLds<T, MI, N
       }
     }
     if constexpr (FAST) {
-      ta.load_fast(oa, AKC ? g.A + k_ld : g.A + (int64_t)k_ld * g.lda, g.ke - k_ld);
-      tb.load_fast(ob, BKC ? g.B + k_ld : g.B + (int64_t)k_ld * g.ldb, g.ke - k_ld);
-    } else {
+      const int krem = to_load > 0 ? g.ke - k_ld : 0;
+      ta.load_fast(oa, AKC ? g.A + (int64_t)a0 * g.lda + k_ld : g.A + (int64_t)k_ld * g.lda + a0, krem);
+      tb.load_fast(ob, BKC ? g.B + (int64_t)b0 * g.ldb + k_ld : g.B + (int64_t)k_ld * g.ldb + b0, krem);
+    } else if (to_load > 0) {
       if constexpr (AKC) ta.load_slow(g.A, g.lda, a_extent, g.ke, a0, k_ld);
       else ta.load_slow(g.A, g.lda, g.ke, a_extent, k_ld, a0);
       if constexpr (BKC) tb.load_slow(g.B, g.ldb, b_extent, g.ke, b0, k_ld);
       else tb.load_slow(g.B, g.ldb, g.ke, b_extent, k_ld, b0);
     }
+    --to_load;
     k_ld += M::BK;
   };
+  if (total <= 0) return;
   if constexpr (FAST && sizeof(T) == 4 && !SPLIT && Segs::kRedo) {   // nothing in flight: it needs no registers beside the planes' form
 #pragma unroll 1
     for (int step = 0; step < total; ++step) {
@@ -416,30 +434,29 @@ __device__ __forceinline__ void gemm_run(f32x16 (&acc)[MI][NI], GemmLds<T, MI, N
       mma_tile_split<AKC, BKC>(acc, pa, pb, wm, wn, lane);
       __syncthreads();
     };
-    for (int step = 0; step < total; step += 2) {
+    for (int step = 0;; step += 2) {
       one(ta0, tb0, step);
-      if (step + 1 < total) one(ta1, tb1, step + 1);
+      if (step + 1 >= total) break;
+      one(ta1, tb1, step + 1);
+      if (step + 2 >= total) break;
     }
     return;
   }
-  for (int step = 0; step < total; step += 2) {
-    xa(ta0, step);
-    xb(tb0, step);
-    ta0.store(sm.a[0]);
-    tb0.store(sm.b[0]);
+  auto one = [&](MoverA &ta, MoverB &tb, int stage, int step, bool more = true) {
+    xa(ta, step);
+    xb(tb, step);
+    ta.store(sm.a[stage]);
+    tb.store(sm.b[stage]);
     __syncthreads();
-    issue(ta0, tb0);
-    mma_tile<T, AKC, BKC>(acc, sm.a[0], sm.b[0], wm, wn, lane);
-    if (step + 1 < total) {
-      xa(ta1, step + 1);
-      xb(tb1, step + 1);
-      ta1.store(sm.a[1]);
-      tb1.store(sm.b[1]);
-      __syncthreads();
-      issue(ta1, tb1);
-      mma_tile<T, AKC, BKC>(acc, sm.a[1], sm.b[1], wm, wn, lane);
-    }
+    if (more) issue(ta, tb);
+    mma_tile<T, AKC, BKC>(acc, sm.a[stage], sm.b[stage], wm, wn, lane);
+  };
+  int step = 0;
+  for (; step + 1 < total; step += 2) {   // one way back to the loop's head: see TileMover
+    one(ta0, tb0, 0, step);
+    one(ta1, tb1, 1, step + 1);
   }
+  if (step < total) one(ta0, tb0, 0, step, false);
   __syncthreads();  // the stages may be rewritten by the caller
 }
 

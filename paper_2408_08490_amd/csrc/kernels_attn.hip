@@ -146,7 +146,8 @@ __device__ __forceinline__ void wide_run(f32x16 (&acc)[MI][NI], WideLds<MI, NI> 
   typename decltype(mb)::Offsets ob;
   ob.setup(ldb, b_extent, b0);
   ma.load(A, lda, a_extent, a0, 0, K);
-  mb.load_fast(ob, B, K);
+  const bf16 *bt = BKC ? B + (int64_t)b0 * ldb : B + b0;
+  mb.load_fast(ob, bt, K);
   for (int k0 = 0; k0 < K; k0 += kWideBK) {
     const int kc = k0 + (threadIdx.x % WideMover<TM>::VPR) * 4;
     ma.store(sm.a, [&](f32x4 v) { return f(v, kc); });
@@ -154,7 +155,7 @@ __device__ __forceinline__ void wide_run(f32x16 (&acc)[MI][NI], WideLds<MI, NI> 
     __syncthreads();
     if (k0 + kWideBK < K) {
       ma.load(A, lda, a_extent, a0, k0 + kWideBK, K);
-      mb.load_fast(ob, BKC ? B + k0 + kWideBK : B + (int64_t)(k0 + kWideBK) * ldb, K - k0 - kWideBK);
+      mb.load_fast(ob, BKC ? bt + k0 + kWideBK : bt + (int64_t)(k0 + kWideBK) * ldb, K - k0 - kWideBK);
     }
     constexpr int NK = kWideBK / 16;
     bf16x8_t b[NK][NI];
@@ -208,7 +209,7 @@ __device__ __forceinline__ void wide_run_f32(f32x16 (&acc)[MI][NI], WideLds<MI, 
       TileMover<bf16, BKC ? TN : kWideBK, BKC ? kWideBK : TN, PB, BKC> mb;
       typename decltype(mb)::Offsets ob;
       ob.setup(ldb, b_extent, b0);
-      mb.load_fast(ob, BKC ? B + k0 : B + (int64_t)k0 * ldb, K - k0);
+      mb.load_fast(ob, BKC ? B + (int64_t)b0 * ldb + k0 : B + (int64_t)k0 * ldb + b0, K - k0);
       mb.store(sm.b);
     }
     __syncthreads();
