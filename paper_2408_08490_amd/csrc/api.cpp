@@ -258,21 +258,32 @@ bool probe_take_events(hipEvent_t *start, hipEvent_t *stop) {
   return true;
 }
 
-// A forward launch of fewer 128x128 tiles than this leaves compute units without a block (two fit on each of
-// the 256): it uses 64x64 tiles instead -- four times as many, four resident per compute unit.  (Measured on
-// the headline's second layer, 96 tiles of 40 K-steps: 42 -> 25 us.  The backward GEMMs have a rule of their own,
-// bwd_small_tiles.)
-constexpr int kSmallTileLimit = 512;
+// Whether a forward launch of `tiles` tiles of 128x128 uses 64x64 ones instead, of which a compute unit holds four (of the large
+// ones two).  Up to 320 or so large ones leave compute units with one block or none; from there to a full round they bring in an
+// operand half as often as small ones.  In fp32 in front of a ReLU the sums are the fp32 MFMA's, which is the bound, and the small
+// tiles' finer rounds count for more; outputs of 64 columns are half padding in a large tile.  us, large / small, of a layer's whole
+// forward (4 relations of 128 columns, and 3 of 256), outputs wide x tiles:
+//   bf16, ReLU: 64 x 547 80.5 / 73.2; 128 x 352 56.0 / 58.5; 256 x 314 41.8 / 40.8 and 55.1 / 56.4, x 470 51.1 / 56.5; 352 x 306 38.3 /
+//   36.5 and 48.6 / 50.0, x 471 44.3 / 51.7; 512 x 408 39.7 / 43.3, x 940 72.5 / 80.8.  Without it the same: 256 x 314 31.3 / 31.8, x 470
+//   37.7 / 43.0.
+//   fp32, ReLU: 128 x 352 132 / 119; 256 x 314 110 / 89, x 470 123 / 128, x 704 178 / 176, x 1094 285 / 270; 352 x 471 113 / 122, x 1056 262 /
+//   238; 512 x 408 106 / 104, x 628 156 / 144, x 1408 304 / 293, x 2188 456 / 463.  Without it: 256 x 314 80.5 / 75.9, x 470 95 / 107; 352 x
+//   306 74.0 / 68.8, x 705 132 / 135; 512 x 408 79.6 / 84.7.
+static bool fwd_small_tiles(const Plan &pl, bool relu, int tiles) {
+  if (pl.H <= 64) return tiles < 1000;
+  if (pl.es == 4 && relu) return tiles < 420 || (tiles > 512 && tiles < 2000);
+  return tiles < 320;
+}
 
 // Tile table of the forward GEMM; returns the tile edge (128 or 64).
-static int fwd_tiles(const Plan &pl, SegTab &tl, bool allow_small) {
+static int fwd_tiles(const Plan &pl, SegTab &tl, bool relu, bool allow_small) {
   const int T = pl.tt.num_types;
   for (int mn = 128;; mn = 64) {
     std::memset(&tl, 0, sizeof(tl));
     const int tn = (pl.H + mn - 1) / mn;
     for (int t = 0; t < T; ++t) tl.tile_off[t + 1] = tl.tile_off[t] + ((pl.tt.n_dst[t] + mn - 1) / mn) * tn;
     tl.num_segs = T;
-    if (mn == 64 || !allow_small || tl.tile_off[T] >= kSmallTileLimit) return mn;
+    if (mn == 64 || !allow_small || !fwd_small_tiles(pl, relu, tl.tile_off[T])) return mn;
   }
 }
 
@@ -863,7 +874,7 @@ static hgnn_status fwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
   void *zlo = (ctx->dtype == HGNN_BF16 && p->relu) ? sc + pl.off_zlo : nullptr;
   int n = 0;
   SegTab tl;
-  const int tile_mn = fwd_tiles(pl, tl, !naive);
+  const int tile_mn = fwd_tiles(pl, tl, p->relu != 0, !naive);
   const int R = ctx->R, T = ctx->T;
   uint32_t live[kMaxR / 32];
   live_relations(ctx, g, layer, live);
