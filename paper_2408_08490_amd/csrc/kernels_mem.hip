@@ -191,31 +191,46 @@ hgnn_status launch_spmm_fwd(hipStream_t s, int dtype, const LayerDev &L, const T
 // registers finds without a memory access (a binary search per entry cost five dependent loads: 114 us -> 33 us on 10 types
 // of 32 to 384 floats, 512 targets).
 // ------------------------------------------------------------------------------------------
+struct SrcRel {
+  int64_t base;   // 16-byte pieces before the dz row of merged row 0, as if the relation's rows went back to there
+  int32_t off;    // merged rows before the relation's
+  int32_t pad;
+};
 struct SrcTiles {
   int32_t tile_off[kMaxT + 1];   // blocks before vertex type t
-  int32_t row_off[kMaxR];        // merged rows before relation r
-  uint16_t first[kMaxT + 1];     // relations reading type t: rel[first[t] .. first[t + 1])
-  uint8_t rel[kMaxR];
+  int32_t first[kMaxT + 1];      // relations reading type t: rel[first[t] .. first[t + 1]), ascending
+  SrcRel rel[kMaxR + 4];
 };
+typedef const SrcTiles __attribute__((address_space(4))) *src_tiles_t;   // the kernel's first argument, read where it lies
 
-// Start of the dz row of merged row rho, in 16-byte pieces, for one of the relations [j0, j1) that read a type of nvec
-// pieces: ascending relations, the last one that starts at or before the row is its own.
-template <typename T>
-__device__ __forceinline__ int64_t dz_row(const SrcTiles &sl, const RelTab &rt, int j0, int j1, int nvec, int rho) {
-  int64_t at = 0;
-  for (int j = j0; j < j1; ++j) {
-    const int r = sl.rel[j], off = sl.row_off[r];
-    const int64_t base = ((int64_t)rt.z_off4[r] * 4) / Vec16<T>::N - (int64_t)off * nvec;
-    if (rho >= off) at = base;
+// Where the dz rows of U merged rows start, in 16-byte pieces, for one of the relations [j0, j1) that read a type of nvec
+// pieces: ascending relations, the last one that starts at or before the row is its own.  Their constants come four at a time: one
+// relation after the other, through a list and two tables, each was three dependent loads for every four entries (72k source rows of
+// 32 to 384 floats, 268k entries, with the root term's row loaded behind its entries' instead of before: 48.3 -> 41.6 us).
+template <int U> __device__ __forceinline__ void dz_rows(src_tiles_t sl, int j0, int j1, int nvec, const int (&rho)[U], int64_t (&at)[U]) {
+#pragma unroll
+  for (int u = 0; u < U; ++u) at[u] = 0;
+  for (int j = j0; j < j1; j += 4) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {   // four places behind the last one exist
+      const int off = j + k < j1 ? sl->rel[j + k].off : INT32_MAX;
+      const int64_t base = sl->rel[j + k].base;
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (rho[u] >= off) at[u] = base;
+    }
   }
-  return at + (int64_t)rho * nvec;
+#pragma unroll
+  for (int u = 0; u < U; ++u) at[u] += (int64_t)rho[u] * nvec;
 }
 
 template <typename T, bool WAVE>
-__global__ void __launch_bounds__(256) spmm_bwd_kernel(LayerDev L, TypeTab tt, RelTab rt, SrcTiles sl, uint32_t root_mask, uint32_t want,
+__global__ void __launch_bounds__(256) spmm_bwd_kernel(SrcTiles sl_, LayerDev L, TypeTab tt, RelTab rt, uint32_t root_mask, uint32_t want,
                                                         const T *__restrict__ dz, T *__restrict__ dx,
                                                         float *__restrict__ partial, int max_dim, int halves) {
   using V = Vec16<T>;
+  const src_tiles_t sl = (src_tiles_t)__builtin_amdgcn_kernarg_segment_ptr();
+  (void)sl_;
   const uint4 *zb = reinterpret_cast<const uint4 *>(dz);
   int t = 0;
   const int pieces = WAVE ? L.n_chunks : L.n_chunks << halves, nb_long = long_blocks(pieces, WAVE);
@@ -229,7 +244,12 @@ __global__ void __launch_bounds__(256) spmm_bwd_kernel(LayerDev L, TypeTab tt, R
     if (!WAVE && (!wanted || p.n <= 0)) return;
     const int F = tt.in_dim[t], nvec = F / V::N, cl = p.c - tt.row_off[t];
     int64_t *s_at = s_ats + slot.lds;
-    for (int i = slot.first; i < p.n; i += slot.step) s_at[i] = dz_row<T>(sl, rt, sl.first[t], sl.first[t + 1], nvec, L.crow[p.beg + i]);
+    for (int i = slot.first; i < p.n; i += slot.step) {
+      const int rho[1] = {L.crow[p.beg + i]};
+      int64_t at[1];
+      dz_rows(sl, sl->first[t], sl->first[t + 1], nvec, rho, at);
+      s_at[i] = at[0];
+    }
     __syncthreads();
     if (!wanted) return;   // whole wavefront
     auto sum = [&](int q, int g, int groups, float (&acc)[V::N]) {
@@ -250,16 +270,20 @@ __global__ void __launch_bounds__(256) spmm_bwd_kernel(LayerDev L, TypeTab tt, R
     return;
   }
   const int b = (int)blockIdx.x - nb_long;
-  while (b >= sl.tile_off[t + 1]) ++t;
+  while (b >= sl->tile_off[t + 1]) ++t;
   const int F = tt.in_dim[t], nvec = F / V::N, l2 = row_lanes_log2(nvec);
-  const int c = tt.row_off[t] + (b - sl.tile_off[t]) * (256 >> l2) + (threadIdx.x >> l2);
+  const int c = tt.row_off[t] + (b - sl->tile_off[t]) * (256 >> l2) + (threadIdx.x >> l2);
   if (c >= tt.row_off[t + 1]) return;
   const int beg = L.cptr[c], end = L.cptr[c + 1];
-  if (end - beg > kLongRow) return;
   const int lpr = 1 << l2, lane = threadIdx.x & (lpr - 1);
   const int cl = c - tt.row_off[t];
-  const int j0 = sl.first[t], j1 = sl.first[t + 1];
+  const int j0 = sl->first[t], j1 = sl->first[t + 1];
+  const bool root = cl < tt.n_dst[t] && ((root_mask >> t) & 1u);
+  const uint4 *zr = reinterpret_cast<const uint4 *>(dz + (int64_t)rt.zroot_off4[t] * 4 + (int64_t)cl * F);
+  if (end - beg > kLongRow) return;
   for (int q = lane; q < nvec; q += lpr) {
+    uint4 rv = make_uint4(0, 0, 0, 0);   // under way while the entries are looked up
+    if (root) rv = zr[q];
     float acc[V::N];
 #pragma unroll
     for (int i = 0; i < V::N; ++i) acc[i] = 0.f;
@@ -268,27 +292,15 @@ __global__ void __launch_bounds__(256) spmm_bwd_kernel(LayerDev L, TypeTab tt, R
       int64_t at[4];
       uint4 v[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        rho[u] = L.crow[min(e + u, end - 1)];
-        at[u] = 0;
-      }
-      for (int j = j0; j < j1; ++j) {   // dz_row for four entries at once
-        const int r = sl.rel[j], off = sl.row_off[r];
-        const int64_t base = ((int64_t)rt.z_off4[r] * 4) / V::N - (int64_t)off * nvec;
+      for (int u = 0; u < 4; ++u) rho[u] = L.crow[min(e + u, end - 1)];
+      dz_rows(sl, j0, j1, nvec, rho, at);
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (rho[u] >= off) at[u] = base;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = zb[at[u] + (int64_t)rho[u] * nvec + q];
+      for (int u = 0; u < 4; ++u) v[u] = zb[at[u] + q];
 #pragma unroll
       for (int u = 0; u < 4; ++u)
         if (e + u < end) V::add(acc, v[u]);
     }
-    if (cl < tt.n_dst[t] && ((root_mask >> t) & 1u)) {
-      const T *zr = dz + (int64_t)rt.zroot_off4[t] * 4 + (int64_t)cl * F;
-      V::add(acc, reinterpret_cast<const uint4 *>(zr)[q]);
-    }
+    if (root) V::add(acc, rv);
     reinterpret_cast<uint4 *>(dx + tt.elem_off[t] + (int64_t)cl * F)[q] = V::pack(acc);
   }
 }
@@ -309,23 +321,25 @@ hgnn_status launch_spmm_bwd(hipStream_t s, int dtype, const LayerDev &L, const T
     HGNN_HIP(hipGetLastError());
   } else {
     SrcTiles sl;
-    std::memset(&sl, 0, sizeof(sl));
-    for (int r = 1; r < rt.num_rels; ++r) sl.row_off[r] = sl.row_off[r - 1] + tt.n_dst[rt.dst[r - 1]];
-    int n = 0;
+    int n = 0, row_off[kMaxR];
+    row_off[0] = 0;
+    for (int r = 1; r < rt.num_rels; ++r) row_off[r] = row_off[r - 1] + tt.n_dst[rt.dst[r - 1]];
+    sl.tile_off[0] = 0;
     for (int t = 0; t < tt.num_types; ++t) {
-      const int rpb = 256 >> row_lanes_log2(tt.in_dim[t] * es / 16), rows = ((want >> t) & 1u) ? tt.row_off[t + 1] - tt.row_off[t] : 0;
+      const int nvec = tt.in_dim[t] * es / 16, rpb = 256 >> row_lanes_log2(nvec), rows = ((want >> t) & 1u) ? tt.row_off[t + 1] - tt.row_off[t] : 0;
       sl.tile_off[t + 1] = sl.tile_off[t] + (rows + rpb - 1) / rpb;
-      sl.first[t] = (uint16_t)n;
+      sl.first[t] = n;
       for (int r = 0; r < rt.num_rels; ++r)
-        if (rt.src[r] == t) sl.rel[n++] = (uint8_t)r;
+        if (rt.src[r] == t) sl.rel[n++] = SrcRel{(int64_t)rt.z_off4[r] * 4 * es / 16 - (int64_t)row_off[r] * nvec, row_off[r], 0};
     }
-    sl.first[tt.num_types] = (uint16_t)n;
+    sl.first[tt.num_types] = n;
+    for (int i = n; i < n + 4; ++i) sl.rel[i] = SrcRel{0, INT32_MAX, 0};
     const int l2 = row_lanes_log2(max_dim * es / 16), halves = long_halves(L.n_chunks, l2);
     const bool by_wave = long_rows_by_wave(L.n_chunks, l2);
     const dim3 grid(long_blocks(L.n_chunks << halves, by_wave) + sl.tile_off[tt.num_types]);
     if (grid.x > 0) {
 #define HGNN_BWD(TY, WAVE)                                                                                                        \
-  HGNN_LAUNCH((spmm_bwd_kernel<TY, WAVE>), grid, dim3(256), 0, s, L, tt, rt, sl, root_mask, want, (const TY *)dz, (TY *)dx, partial, \
+  HGNN_LAUNCH((spmm_bwd_kernel<TY, WAVE>), grid, dim3(256), 0, s, sl, L, tt, rt, root_mask, want, (const TY *)dz, (TY *)dx, partial, \
               max_dim, halves)
       if (dtype == HGNN_BF16) {
         if (by_wave) HGNN_BWD(bf16, true); else HGNN_BWD(bf16, false);
