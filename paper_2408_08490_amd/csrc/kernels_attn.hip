@@ -663,9 +663,46 @@ __global__ void attn_zero_kernel(ZeroList zl) {
   for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < zl.n[i]; j += gridDim.x * blockDim.x) p[j] = 0.f;
 }
 
+// The rows of a block against N relations of their type (FIRST: also gp and the bias sums): a lane group takes four rows at a time,
+// the loads of all N relations for them are under way together, and a lane keeps its share of the dots until its last row.
+template <typename TS, int N, bool FIRST>
+__device__ __forceinline__ void mask_dbeta_rows(const float *const *mr, float *dot, float *bsum, int64_t row0, int M, int vb, int gpb, int trips,
+                                                int H, int q, int relu, const TS *__restrict__ g, const TS *__restrict__ h, TS *__restrict__ gp) {
+  const TS *hp = relu ? h : g;
+  for (int it = 0; it < trips && vb < M; ++it, vb += gpb * 4) {   // whole groups
+    float gv[4][4], hv[4][4], mv[N ? N : 1][4][4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t at = (row0 + min(vb + u * gpb, M - 1)) * H + q * 4;
+      Quad<TS>::load(gv[u], g + at);
+      Quad<TS>::load(hv[u], hp + at);
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) Q4::load(mv[j][u], mr[j] + (int64_t)min(vb + u * gpb, M - 1) * H);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const bool on = vb + u * gpb < M;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        if (!on || (relu && !(hv[u][c] > 0.f))) gv[u][c] = 0.f;
+        if (FIRST) bsum[c] += gv[u][c];
+      }
+      if (FIRST && relu && on) Quad<TS>::store(gp + (row0 + vb + u * gpb) * H + q * 4, gv[u]);
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        dot[j] += (gv[u][0] * mv[j][u][0] + gv[u][1] * mv[j][u][1]) + (gv[u][2] * mv[j][u][2] + gv[u][3] * mv[j][u][3]);
+  }
+}
+
 // One pass over the incoming gradient: mask by the activation (gp), bias gradient, and dbeta[r] += sum of G'[v] . m[row]
-// for every relation that ends in the row's type.  A lane group takes four rows at a time: their G' stay in registers
-// while the aggregates of one relation after the other are read.  Bound: the read of m.
+// for every relation that ends in the row's type, up to four of them at a time.  Bound: the read of m where that is large (84k rows
+// of 256 columns with 561k aggregates: one relation after the other 184 us, so, with twice the blocks, 166 us or 4.2 TB/s; 23k rows
+// 38.4 -> 40.2), a chain of latencies where it is not (1.3k rows of 128 columns in fp32 10.1 -> 8.7 us).
 template <typename TS>
 __global__ void __launch_bounds__(256) attn_mask_dbeta_kernel(RelRows rr, TypeTiles ty, RelsOfType ro, GradPtrTab gt, int H, int relu,
                                                               int lpr_log2, int trips, const TS *__restrict__ g, const TS *__restrict__ h,
@@ -677,44 +714,40 @@ __global__ void __launch_bounds__(256) attn_mask_dbeta_kernel(RelRows rr, TypeTi
   const int q = threadIdx.x & (lpr - 1), grp = threadIdx.x >> lpr_log2;
   const int d = wave_find(ty.tile_off, ty.n, (int)blockIdx.x);
   const int M = ty.row_off[d + 1] - ty.row_off[d];
-  const int v0 = ((int)blockIdx.x - ty.tile_off[d]) * gpb * 4 * trips;
+  const int vb = ((int)blockIdx.x - ty.tile_off[d]) * gpb * 4 * trips + grp;
   const int j0 = ro.first[d], j1 = ro.first[d + 1];
   for (int i = threadIdx.x; i < kMaxR; i += 256) part[i] = 0.f;
   for (int i = threadIdx.x; i < kAttnMaxH; i += 256) s_b[i] = 0.f;
   __syncthreads();
   float bsum[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int it = 0; it < trips; ++it) {
-    const int vb = v0 + it * gpb * 4 + grp;
-    if (vb >= M) break;   // whole groups
-    float gv[4][4], hv[4][4];
+  int j = j0;
+  do {
+    const int n = min(4, j1 - j);
+    const float *mr[4];
+    float dot[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int64_t at = ((int64_t)ty.row_off[d] + min(vb + u * gpb, M - 1)) * H + q * 4;
-      Quad<TS>::load(gv[u], g + at);
-      if (relu) Quad<TS>::load(hv[u], h + at);
+    for (int k = 0; k < 4; ++k) mr[k] = k < n ? mbuf + (int64_t)rr.row_off[ro.rel[j + k]] * H + q * 4 : mbuf;
+#define HGNN_ROWS(N_, F_) mask_dbeta_rows<TS, N_, F_>(mr, dot, bsum, ty.row_off[d], M, vb, gpb, trips, H, q, relu, g, h, gp)
+    if (j == j0) {
+      if (n == 4) HGNN_ROWS(4, true);
+      else if (n == 3) HGNN_ROWS(3, true);
+      else if (n == 2) HGNN_ROWS(2, true);
+      else if (n == 1) HGNN_ROWS(1, true);
+      else HGNN_ROWS(0, true);
+    } else if (n > 2) {
+      if (n == 4) HGNN_ROWS(4, false); else HGNN_ROWS(3, false);
+    } else {
+      if (n == 2) HGNN_ROWS(2, false); else HGNN_ROWS(1, false);
     }
+#undef HGNN_ROWS
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const bool on = vb + u * gpb < M;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        if (!on || (relu && !(hv[u][c] > 0.f))) gv[u][c] = 0.f;
-        bsum[c] += gv[u][c];
-      }
-      if (relu && on) Quad<TS>::store(gp + ((int64_t)ty.row_off[d] + vb + u * gpb) * H + q * 4, gv[u]);
+    for (int k = 0; k < 4; ++k) {
+      if (k >= n) break;
+      for (int o = 32; o > 0; o >>= 1) dot[k] += __shfl_xor(dot[k], o);
+      if ((threadIdx.x & 63) == 0) atomicAdd(&part[j + k - j0], dot[k]);
     }
-    for (int j = j0; j < j1; ++j) {
-      const float *mr = mbuf + (int64_t)rr.row_off[ro.rel[j]] * H + q * 4;
-      float mv[4][4], dot = 0.f;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) Q4::load(mv[u], mr + (int64_t)min(vb + u * gpb, M - 1) * H);
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        dot += (gv[u][0] * mv[u][0] + gv[u][1] * mv[u][1]) + (gv[u][2] * mv[u][2] + gv[u][3] * mv[u][3]);
-      for (int o = lpr >> 1; o > 0; o >>= 1) dot += __shfl_xor(dot, o);
-      if (q == 0) atomicAdd(&part[j - j0], dot);
-    }
-  }
+    j += 4;
+  } while (j < j1);
   float *db = gt.dbias[d];
   if (db) {
 #pragma unroll
@@ -1186,7 +1219,7 @@ hgnn_status launch_attn_mask_dbeta(hipStream_t s, int dtype, const TypeTab &tt, 
   rels_of_type(rr, tt.num_types, ro);
   // a block ends with an atomic add to every dbeta and bias element of its type; adds to one address are serialised
   // (~11 ns each), so large batches take more rows per block
-  const int l2 = log2_exact(H / 4), gpb = 256 >> l2, trips = rows_per_group(rows, gpb * 4, 1024, 16);
+  const int l2 = log2_exact(H / 4), gpb = 256 >> l2, trips = rows_per_group(rows, gpb * 4, 2048, 16);
   dim3 grid(tile_types(ty, gpb * 4 * trips));
   if (dtype == HGNN_BF16)
     HGNN_LAUNCH(attn_mask_dbeta_kernel<bf16>, grid, dim3(256), 0, s, rr, ty, ro, gt, H, relu, l2, trips, (const bf16 *)g, (const bf16 *)h,
