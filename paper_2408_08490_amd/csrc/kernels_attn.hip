@@ -7,6 +7,7 @@
 //                in its epilogue), softmax over the relations of a destination type, weighted sum + bias + act
 // Everything between the boundary's tensors (z, m, t, dm and the small statistics) is fp32 in both storage types; the
 // kernels read parameters, the incoming gradient and the features in the storage type TS and widen them on load.
+#include <cmath>
 #include <cstring>
 
 #include "attn_layer.h"
@@ -1238,11 +1239,13 @@ hgnn_status launch_attn_sem_bwd(hipStream_t s, int dtype, const RelRows &rr, int
   RelRows dwt = rr, dmt = rr;
   const int tiles = (H + 127) / 128, tm = sem_tile_rows(dmt);
   const int n_dm = tile_relations(dmt, tm) * tiles;
-  // rows per block of the dW_s part: about three rounds of the chip's 512 block slots (a round that is nearly empty at
-  // the end then costs little), but at least four K-steps of 32 rows for one tile's worth of atomic adds
+  // Rows per block of the dW_s part, in K-steps of 32: a block's chain grows with them, the atomic adds of whole 128x128 tiles
+  // fall with them, so that the best number goes with the root of the work, and at least four steps.  Measured (steps: us with 1/1500
+  // of them a block, and with this rule): 512: 28, 28; 2.9k: 118, 101; 4.1k: 106, 84; 4.5k: 172, 167; 36k: 592, 591; half as many
+  // rows again or more is slower from 2.9k on (105, 88, 173, 606), two steps are below 512 (28 -> 36).
   SemBwd p;
   const int64_t steps = (int64_t)rr.row_off[rr.n] / 32 * tiles;
-  p.dw_rows = 32 * (int)std::max<int64_t>(4, (steps + 1499) / 1500);
+  p.dw_rows = 32 * std::max(4, (int)std::ceil(std::sqrt((double)steps) / 8));
   p.n_dw = tile_relations(dwt, p.dw_rows) * tiles;
 #define HGNN_SEMB(TY, MI_)                                                                                                         \
   HGNN_LAUNCH((attn_sem_bwd_kernel<TY, MI_>), dim3(p.n_dw + n_dm), dim3(kThreads), 0, s, dwt, dmt, p, H, mbuf, tbuf,                 \
