@@ -1,5 +1,5 @@
 // MFMA GEMM core shared by the layer GEMMs: tile movers (global -> registers -> LDS), MFMA fragment reads,
-// the software-pipelined K loop over a segment table, and the LDS-staged epilogue.
+// the software-pipelined K loop over a tile's segments, and the LDS-staged epilogue.
 #pragma once
 #include <type_traits>
 
