@@ -263,9 +263,9 @@ bool probe_take_events(hipEvent_t *start, hipEvent_t *stop) {
 // operand half as often as small ones.  In fp32 in front of a ReLU the sums are the fp32 MFMA's, which is the bound, and the small
 // tiles' finer rounds count for more; outputs of 64 columns are half padding in a large tile.  us, large / small, of a layer's whole
 // forward (4 relations of 128 columns, and 3 of 256), outputs wide x tiles:
-//   bf16, ReLU: 64 x 547 80.5 / 73.2; 128 x 352 56.0 / 58.5; 256 x 314 41.8 / 40.8 and 55.1 / 56.4, x 470 51.1 / 56.5; 352 x 306 38.3 /
-//   36.5 and 48.6 / 50.0, x 471 44.3 / 51.7; 512 x 408 39.7 / 43.3, x 940 72.5 / 80.8.  Without it the same: 256 x 314 31.3 / 31.8, x 470
-//   37.7 / 43.0.
+//   bf16, ReLU (3 relations of 128 columns): 64 x 547 80.5 / 73.2; 128 x 300 44.9 / 42.4, x 400 50.7 / 53.1; 264 x 318 37.9 / 37.5; 512 x 280
+//   36.8 / 36.3, x 360 38.7 / 40.2; of 256 columns: 256 x 314 58.9 / 56.5, x 400 62.9 / 70.6; 349 x 306 54.5 / 53.4, x 390 58.9 / 66.1.  (Between 200
+//   and 256 large ones, one to a compute unit, are 1.0 to 1.06 times as fast.)  Without it: 256 x 314 31.3 / 31.8, x 470 37.7 / 43.0.
 //   fp32, ReLU: 128 x 352 132 / 119; 256 x 314 110 / 89, x 470 123 / 128, x 704 178 / 176, x 1094 285 / 270; 352 x 471 113 / 122, x 1056 262 /
 //   238; 512 x 408 106 / 104, x 628 156 / 144, x 1408 304 / 293, x 2188 456 / 463.  Without it: 256 x 314 80.5 / 75.9, x 470 95 / 107; 352 x
 //   306 74.0 / 68.8, x 705 132 / 135; 512 x 408 79.6 / 84.7.

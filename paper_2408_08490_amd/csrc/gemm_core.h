@@ -460,95 +460,6 @@ __device__ __forceinline__ void gemm_run(f32x16 (&acc)[MI][NI], GemmLds<T, MI, N
   __syncthreads();  // the stages may be rewritten by the caller
 }
 
-// The same in bf16 for rows of A that are the sum of two planes (a value and its rounded remainder): segs.next(g, low) hands out a
-// segment and its low-order plane, or null.  A K-step brings both planes and one tile of B: what bounds these tiles is LDS (with a
-// K-step for each plane 192 bytes a clock of its 128 at the matrix cores' full rate), and a fragment of B that meets both planes is
-// stored and read once: 144.
-template <int MI, typename Segs>
-__device__ __forceinline__ void gemm_run_planes(f32x16 (&acc)[MI][MI], GemmLds<bf16, MI, MI, true> &sm, Segs segs, int a_extent, int a0,
-                                                int b_extent, int b0) {
-  using M = Mma<bf16>;
-  constexpr int TM = 64 * MI, P = M::PKC;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = (wave >> 1) * 32 * MI, wn = (wave & 1) * 32 * MI;
-  using Mover = TileMover<bf16, TM, M::BK, P, true>;
-  struct Step {
-    Mover a, lo, b;
-    bool two;
-  };
-  Step s0, s1;
-  const int total = __builtin_amdgcn_readfirstlane(segs.steps());
-  if (total <= 0) return;
-  typename Mover::Offsets oa, ob;
-  const bf16 *pa = nullptr, *pl = nullptr, *pb = nullptr;   // the loader's segment
-  int F = 0, k_ld = 0, to_load = total;
-  auto issue = [&](Step &s) {
-    if (to_load > 0 && k_ld >= F) {
-      Seg<bf16> g;
-      const bf16 *low;
-      segs.next(g, low);
-      F = __builtin_amdgcn_readfirstlane(g.ke);
-      pa = uniform_ptr(g.A) + (int64_t)a0 * F;
-      pb = uniform_ptr(g.B) + (int64_t)b0 * F;
-      pl = uniform_ptr(low);
-      if (pl) pl += (int64_t)a0 * F;
-      oa.setup(F, a_extent, a0);
-      ob.setup(F, b_extent, b0);
-      k_ld = 0;
-    }
-    const int krem = to_load > 0 ? F - k_ld : 0;
-    s.two = pl != nullptr;
-    s.a.load_fast(oa, pa + k_ld, krem);
-    s.lo.load_fast(oa, (pl ? pl : pa) + k_ld, pl ? krem : 0);
-    s.b.load_fast(ob, pb + k_ld, krem);
-    --to_load;
-    k_ld += M::BK;
-  };
-  auto multiply = [&](auto two) {
-#pragma unroll
-    for (int ks = 0; ks < M::BK / M::KSTEP; ++ks) {
-      bf16x8_t a[MI], l[MI], b[MI];
-#pragma unroll
-      for (int i = 0; i < MI; ++i) a[i] = frag_bf16<true, P>(sm.a[0], wm + i * 32, ks, lane);
-#pragma unroll
-      for (int j = 0; j < MI; ++j) b[j] = frag_bf16<true, P>(sm.b[0], wn + j * 32, ks, lane);
-      if constexpr (two.value) {
-#pragma unroll
-        for (int i = 0; i < MI; ++i) l[i] = frag_bf16<true, P>(sm.a[1], wm + i * 32, ks, lane);
-      }
-#pragma unroll
-      for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < MI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-      if constexpr (two.value) {
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-          for (int j = 0; j < MI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(l[i], b[j], acc[i][j], 0, 0, 0);
-      }
-    }
-  };
-  auto one = [&](Step &s) {
-    s.a.store(sm.a[0]);
-    s.lo.store(sm.a[1]);
-    s.b.store(sm.b[0]);
-    const bool two = s.two;
-    __syncthreads();
-    issue(s);
-    if (two) multiply(std::true_type());
-    else multiply(std::false_type());
-    __syncthreads();
-  };
-  issue(s0);
-  issue(s1);
-  int step = 0;
-  for (; step + 1 < total; step += 2) {   // one way back to the loop's head: see TileMover
-    one(s0);
-    one(s1);
-  }
-  if (step < total) one(s0);
-}
-
 template <int MI, int NI> __device__ __forceinline__ void zero_acc(f32x16 (&acc)[MI][NI]) {
 #pragma unroll
   for (int i = 0; i < MI; ++i)

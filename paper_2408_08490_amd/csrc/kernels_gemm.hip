@@ -79,29 +79,9 @@ template <typename T> struct FwdSegs {
   }
 };
 
-// A type's segments, both planes of the aggregate in one.
-struct FwdPlaneSegs {
-  fwd_args_t args;
-  const bf16 *x, *z, *zlo, *wtb;
-  int64_t xroot;
-  int si, n_steps;
-  __device__ __forceinline__ int steps() const { return n_steps; }
-  __device__ __forceinline__ void next(Seg<bf16> &g, const bf16 *&low) {
-    const uint32_t a4 = args->seg[si].a4, b4 = args->seg[si].b4;
-    const bool root = args->seg[si].root != 0;
-    const int64_t o = (int64_t)a4 * 4;
-    g.A = root ? x + xroot : z + o;
-    low = root ? nullptr : zlo + o;
-    g.B = wtb + (int64_t)b4 * 4;
-    g.lda = g.ldb = g.ke = args->seg[si].F;
-    g.kb = 0;
-    ++si;
-  }
-};
-
 // Four of the small tiles are resident on a compute unit (their LDS holds operands with K contiguous only): the 950 tiles of 12000
 // rows and 264 columns in bf16 are one round then and not two, 28.2 -> 20.7 us.
-template <typename T, bool FAST, int MI, bool PLANES>
+template <typename T, bool FAST, int MI>
 __global__ void __launch_bounds__(kThreads, MI == 1 ? 4 : 2) gemm_fwd_kernel(FwdArgs args_, const T *__restrict__ x, const T *__restrict__ z,
                                                             const T *__restrict__ zlo, const T *__restrict__ wtb,
                                                             T *__restrict__ h, float *__restrict__ acc32) {
@@ -125,17 +105,12 @@ __global__ void __launch_bounds__(kThreads, MI == 1 ? 4 : 2) gemm_fwd_kernel(Fwd
     bv[j] = (bias && c < H) ? to_float(bias[c]) : 0.f;
   }
   f32x16 acc[MI][MI];
-  if constexpr (PLANES) {
-    zero_acc(acc);
-    gemm_run_planes(acc, sm, FwdPlaneSegs{args, x, z, zlo, wtb, args->type[d].xroot, args->type[d].seg0, args->type[d].steps}, M, m0, H, n0);
-  } else {
-    const FwdSegs<T> segs{args, x, z, zlo, wtb, args->type[d].xroot, args->type[d].seg0, args->type[d].steps, false};
-    // fp32 with a ReLU: a unit within a rounding of zero takes the other decision when its sum is formed another way, and moves
-    // a whole term of the gradients; three of ten million units do (1024 targets, 256 wide: gradients 2e-3 apart).  Neither
-    // decision is the wrong one -- the planes' sums are the nearer ones to 64 bits -- but these sums stay on the fp32 MFMA, so
-    // that every form of the layer decides alike: 39 -> 50 us there, of a step of 310.
-    gemm_finite<T, FAST>(acc, [&](auto split) { gemm_run<T, FAST, true, true, split.value>(acc, sm, segs, M, m0, H, n0); }, relu != 0);
-  }
+  const FwdSegs<T> segs{args, x, z, zlo, wtb, args->type[d].xroot, args->type[d].seg0, args->type[d].steps, false};
+  // fp32 with a ReLU: a unit within a rounding of zero takes the other decision when its sum is formed another way, and moves
+  // a whole term of the gradients; three of ten million units do (1024 targets, 256 wide: gradients 2e-3 apart).  Neither
+  // decision is the wrong one -- the planes' sums are the nearer ones to 64 bits -- but these sums stay on the fp32 MFMA, so
+  // that every form of the layer decides alike: 39 -> 50 us there, of a step of 310.
+  gemm_finite<T, FAST>(acc, [&](auto split) { gemm_run<T, FAST, true, true, split.value>(acc, sm, segs, M, m0, H, n0); }, relu != 0);
   const int64_t orow = args->type[d].out_row;
   if (acc32) {
     HGNN_FOR_EACH_ACC({
@@ -162,9 +137,6 @@ hgnn_status launch_gemm_fwd(hipStream_t s, int dtype, const LayerDev &L, const T
   args.num_types = T;
   args.H = H;
   args.relu = relu;
-  // Small tiles take both planes of the aggregate in one K-step (12000 rows, 264 columns 20.3 -> 18.4 us); for large ones, which would
-  // have one step in flight instead of two, it is no gain (the headline's first layer 60.3 / 63.1).
-  const bool planes_in_one = zlo && tile_mn == 64;
   // A tile's cost: its K-steps (destination types differ in the number of relations that end in them) plus
   // the fixed part (pipeline fill, epilogue), which is worth about four K-steps.
   int64_t cost[kMaxT];
@@ -172,33 +144,28 @@ hgnn_status launch_gemm_fwd(hipStream_t s, int dtype, const LayerDev &L, const T
   for (int d = 0; d < T; ++d) {
     FwdType &ty = args.type[d];
     ty = FwdType{tt.n_dst[d], tt.out_row_off[d], 0, ns, pt.bias[d], tt.xroot_off[d]};
-    int planes = 0;
     for (int r = 0; r < R; ++r)
       if (rt.dst[r] == d && (only_seg < 0 || only_seg == r) && ((live_mask[r >> 5] >> (r & 31)) & 1u)) {   // no edge: all zero
         const int F = tt.in_dim[rt.src[r]];
         args.seg[ns++] = FwdSeg{rt.z_off4[r], wt.rel4[r], F, 0};
-        ty.steps += (zlo && !planes_in_one ? 2 : 1) * ((F + bk - 1) / bk);
-        planes += (zlo ? 2 : 1) * ((F + bk - 1) / bk);
+        ty.steps += (zlo ? 2 : 1) * ((F + bk - 1) / bk);
       }
     if (pt.w_root[d] && (only_seg < 0 || only_seg == R + d)) {
       args.seg[ns++] = FwdSeg{0, wt.root4[d], tt.in_dim[d], 1};
       ty.steps += (tt.in_dim[d] + bk - 1) / bk;
-      planes += (tt.in_dim[d] + bk - 1) / bk;
     }
-    cost[d] = planes + 4;
+    cost[d] = ty.steps + 4;
   }
   dim3 grid(balance_xcd(tiles.tile_off, cost, T, args.xmap));
   // operands of the forward are the library's own aligned buffers (aggregates, transposed weights) and
   // x_merged, whose row widths are multiples of 16 bytes: always the FAST form
-#define HGNN_FWD(TY, MI_, PL)                                                                                        \
-  HGNN_LAUNCH((gemm_fwd_kernel<TY, true, MI_, PL>), grid, dim3(kThreads), 0, s, args, (const TY *)x, (const TY *)z, (const TY *)zlo, \
+#define HGNN_FWD(TY, MI_)                                                                                                        \
+  HGNN_LAUNCH((gemm_fwd_kernel<TY, true, MI_>), grid, dim3(kThreads), 0, s, args, (const TY *)x, (const TY *)z, (const TY *)zlo, \
               (const TY *)wt_buf, (TY *)h, acc32)
-  if (planes_in_one) {
-    HGNN_FWD(bf16, 1, true);
-  } else if (dtype == HGNN_BF16) {
-    if (tile_mn == 64) HGNN_FWD(bf16, 1, false); else HGNN_FWD(bf16, 2, false);
+  if (dtype == HGNN_BF16) {
+    if (tile_mn == 64) HGNN_FWD(bf16, 1); else HGNN_FWD(bf16, 2);
   } else {
-    if (tile_mn == 64) HGNN_FWD(float, 1, false); else HGNN_FWD(float, 2, false);
+    if (tile_mn == 64) HGNN_FWD(float, 1); else HGNN_FWD(float, 2);
   }
 #undef HGNN_FWD
   HGNN_HIP(hipGetLastError());
