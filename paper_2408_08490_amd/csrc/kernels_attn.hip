@@ -701,9 +701,11 @@ __device__ __forceinline__ void mask_dbeta_rows(const float *const *mr, float *d
 }
 
 // One pass over the incoming gradient: mask by the activation (gp), bias gradient, and dbeta[r] += sum of G'[v] . m[row]
-// for every relation that ends in the row's type, up to four of them at a time.  Bound: the read of m where that is large (84k rows
-// of 256 columns with 561k aggregates: one relation after the other 184 us, so, with twice the blocks, 166 us or 4.2 TB/s; 23k rows
-// 38.4 -> 40.2), a chain of latencies where it is not (1.3k rows of 128 columns in fp32 10.1 -> 8.7 us).
+// for every relation that ends in the row's type, up to four of them at a time.  Bound: the read of m where that is large (169k rows
+// of 256 columns with 561k aggregates, bf16: one relation after the other 177 us, so 156 or 5.3 TB/s), a chain of latencies where it is not
+// (1.3k rows of 128 columns in fp32 10 -> 8.7 us).  One after the other, with seven wavefronts on a SIMD instead of three, also: 23k rows of
+// 128 columns in fp32, 1 relation 26.3 / 27, 4 30.5 / 30, 8 36.8 / 37; 84k of 256 in bf16, 1 67 / 57, 5 125 / 121; but 150k, 8 relations
+// without an activation, where the gradients are read twice, 230 / 250.
 template <typename TS>
 __global__ void __launch_bounds__(256) attn_mask_dbeta_kernel(RelRows rr, TypeTiles ty, RelsOfType ro, GradPtrTab gt, int H, int relu,
                                                               int lpr_log2, int trips, const TS *__restrict__ g, const TS *__restrict__ h,
@@ -1218,9 +1220,12 @@ hgnn_status launch_attn_mask_dbeta(hipStream_t s, int dtype, const TypeTab &tt, 
   if (rows == 0) return HGNN_OK;
   RelsOfType ro;
   rels_of_type(rr, tt.num_types, ro);
-  // a block ends with an atomic add to every dbeta and bias element of its type; adds to one address are serialised
-  // (~11 ns each), so large batches take more rows per block
-  const int l2 = log2_exact(H / 4), gpb = 256 >> l2, trips = rows_per_group(rows, gpb * 4, 2048, 16);
+  // A block ends with an atomic add to every dbeta and bias element of its type, some 30 ns of the launch, so that large batches take
+  // more rows per block: about 1024 of them, and 2048, whose ends are evener, where the aggregates take longer than that to read.  us with
+  // some 1300 / 2600: 84k rows, 1 relation of 256 columns, bf16, 57 / 80, 2 58 / 82, 5 121 / 122; 40k, 4 relations, 51 / 76; 84k, 4, fp32,
+  // 93 / 94; 150k, 3, fp32, 193 / 186; 169k rows of four types with 561k aggregates, bf16, 163 / 156.
+  const int blocks = (int64_t)rr.row_off[rr.n] * H * 4 > (int64_t)400 << 20 ? 2048 : 1024;
+  const int l2 = log2_exact(H / 4), gpb = 256 >> l2, trips = rows_per_group(rows, gpb * 4, blocks, 16);
   dim3 grid(tile_types(ty, gpb * 4 * trips));
   if (dtype == HGNN_BF16)
     HGNN_LAUNCH(attn_mask_dbeta_kernel<bf16>, grid, dim3(256), 0, s, rr, ty, ro, gt, H, relu, l2, trips, (const bf16 *)g, (const bf16 *)h,
