@@ -342,8 +342,10 @@ struct NoXform {
   template <typename M> __device__ __forceinline__ void operator()(M &, int) const {}
 };
 
-// A reduction over one segment.
-template <typename T> struct OneSeg {
+// A reduction over one segment.  AHEAD: K-steps whose loads are under way in front of the one that is multiplied, where fp32 operands
+// are split into planes.
+template <typename T, int AHEAD = 2> struct OneSeg {
+  static constexpr int kAhead = AHEAD;
   static constexpr bool kRedo = true;   // on the fp32 MFMA it is only what gemm_finite falls back on
   Seg<T> g;
   __device__ __forceinline__ int steps() const { return (g.ke - g.kb + Mma<T>::BK - 1) / Mma<T>::BK; }
@@ -420,7 +422,7 @@ __device__ __forceinline__ void gemm_run(f32x16 (&acc)[MI][NI], GemmLds<T, MI, N
     return;
   }
   issue(ta0, tb0);
-  issue(ta1, tb1);
+  if constexpr (!SPLIT || Segs::kAhead == 2) issue(ta1, tb1);
   if constexpr (SPLIT) {
     static_assert(3 * split_plane<AKC>(TM) * sizeof(bf16) <= sizeof(sm.a) && 3 * split_plane<BKC>(TN) * sizeof(bf16) <= sizeof(sm.b), "planes must fit the stages");
     bf16 *pa = reinterpret_cast<bf16 *>(&sm.a[0][0]), *pb = reinterpret_cast<bf16 *>(&sm.b[0][0]);
@@ -434,6 +436,11 @@ __device__ __forceinline__ void gemm_run(f32x16 (&acc)[MI][NI], GemmLds<T, MI, N
       mma_tile_split<AKC, BKC>(acc, pa, pb, wm, wn, lane);
       __syncthreads();
     };
+    if constexpr (Segs::kAhead == 1) {
+#pragma unroll 1
+      for (int step = 0; step < total; ++step) one(ta0, tb0, step);
+      return;
+    }
     for (int step = 0;; step += 2) {
       one(ta0, tb0, step);
       if (step + 1 >= total) break;

@@ -271,7 +271,10 @@ __device__ __forceinline__ void mix_run(f32x16 (&acc)[MI][2], MixLds<TS, MI> &sm
       else wide_run_f32<BKC>(acc, sm.w, A, lda, a_extent, a0, B, ldb, b_extent, b0, K, f);
     });
   } else {
-    const OneSeg<float> one{Seg<float>{A, B, lda, ldb, 0, K}};
+    // The backward's product has four K-steps; on tiles of 128 rows a second set of loads does not fit beside what `f` and the epilogue keep
+    // in registers (17 of a lane's were in scratch memory).  Its launch, us, two steps ahead / one: 23k rows of 4 relations of 128 columns 85 / 73,
+    // 84k of 4 of 256 465 / 423; on tiles of 64 rows, and in the forward's with up to eight steps, two are as good or better (H = 256 66.5 / 68.5).
+    const OneSeg<float, BKC && MI == 2 ? 1 : 2> one{Seg<float>{A, B, lda, ldb, 0, K}};
     gemm_finite<float, true>(acc, [&](auto split) {
       gemm_run<float, true, true, BKC, split.value>(acc, sm.g, one, a_extent, a0, b_extent, b0, [&](auto &mv, int step) {
         const int kc = step * Mma<float>::BK + (threadIdx.x % (Mma<float>::BK / 4)) * 4;

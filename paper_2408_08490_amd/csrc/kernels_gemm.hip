@@ -60,6 +60,7 @@ typedef const FwdArgs __attribute__((address_space(4))) *fwd_args_t;
 // low-order remainder against the same weights), then the root term.
 template <typename T> struct FwdSegs {
   static constexpr bool kRedo = false;
+  static constexpr int kAhead = 2;
   fwd_args_t args;
   const T *x, *z, *zlo, *wtb;
   int64_t xroot;

@@ -122,16 +122,17 @@ def test_weight_gradients_over_very_few_rows(rows):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("n", [200, 20000])
+@pytest.mark.parametrize("n", [200, 20000, 33000])
 def test_attention_products_beyond_the_planes(dtype, n):
     """Two relations into one type.  Column 3 of the projected features is 2^110 times as large and meets a row of W_s that much
-    smaller (projection in fp32, scores, dW_s with its column sums); column 5 is 2^-120 times as large and meets a row of
-    2^120 (dm).  64- and 128-row tiles."""
+    smaller (projection in fp32, scores, dW_s with its column sums); column 5 is 2^-120 or 2^-116 times as large and meets a row that
+    much larger (dm).  Tiles of 64 rows and, where there are 512 of 128 and more (33000 rows), of 128."""
     import torch
     from paper_2408_08490_amd.runner import Model
     from workloads import bf16_round
     F = H = 64
-    UP, DOWN = 2.0 ** 110, 2.0 ** -120
+    # dW's column 5 sums 2n terms of 1 / DOWN and either sign, some 4 sqrt(2n) / DOWN: with 2^120 that is 2^130 for 33000 rows, beyond fp32
+    UP, DOWN = 2.0 ** 110, 2.0 ** (-120 if n <= 20000 else -116)
     rng = np.random.default_rng(23)
     store = bf16_round if dtype == "bf16" else (lambda a: a)
     x, g = store(f32(rng.standard_normal((2 * n, F)))), f32(rng.standard_normal((n, H)))
