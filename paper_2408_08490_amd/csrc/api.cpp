@@ -258,23 +258,6 @@ bool probe_take_events(hipEvent_t *start, hipEvent_t *stop) {
   return true;
 }
 
-// Whether a forward launch of `tiles` tiles of 128x128 uses 64x64 ones instead, of which a compute unit holds four (of the large
-// ones two).  Up to 320 or so large ones leave compute units with one block or none; from there to a full round they bring in an
-// operand half as often as small ones.  In fp32 in front of a ReLU the sums are the fp32 MFMA's, which is the bound, and the small
-// tiles' finer rounds count for more; outputs of 64 columns are half padding in a large tile.  us, large / small, of a layer's whole
-// forward (4 relations of 128 columns, and 3 of 256), outputs wide x tiles:
-//   bf16, ReLU (3 relations of 128 columns): 64 x 547 80.5 / 73.2; 128 x 300 44.9 / 42.4, x 400 50.7 / 53.1; 264 x 318 37.9 / 37.5; 512 x 280
-//   36.8 / 36.3, x 360 38.7 / 40.2; of 256 columns: 256 x 314 58.9 / 56.5, x 400 62.9 / 70.6; 349 x 306 54.5 / 53.4, x 390 58.9 / 66.1.  (Between 200
-//   and 256 large ones, one to a compute unit, are 1.0 to 1.06 times as fast.)  Without it: 256 x 314 31.3 / 31.8, x 470 37.7 / 43.0.
-//   fp32, ReLU: 128 x 352 132 / 119; 256 x 314 110 / 89, x 470 123 / 128, x 704 178 / 176, x 1094 285 / 270; 352 x 471 113 / 122, x 1056 262 /
-//   238; 512 x 408 106 / 104, x 628 156 / 144, x 1408 304 / 293, x 2188 456 / 463.  Without it: 256 x 314 80.5 / 75.9, x 470 95 / 107; 352 x
-//   306 74.0 / 68.8, x 705 132 / 135; 512 x 408 79.6 / 84.7.
-static bool fwd_small_tiles(const Plan &pl, bool relu, int tiles) {
-  if (pl.H <= 64) return tiles < 1000;
-  if (pl.es == 4 && relu) return tiles < 420 || (tiles > 512 && tiles < 2000);
-  return tiles < 320;
-}
-
 // Tile table of the forward GEMM; returns the tile edge (128 or 64).
 static int fwd_tiles(const Plan &pl, SegTab &tl, bool relu, bool allow_small) {
   const int T = pl.tt.num_types;
@@ -283,7 +266,7 @@ static int fwd_tiles(const Plan &pl, SegTab &tl, bool relu, bool allow_small) {
     const int tn = (pl.H + mn - 1) / mn;
     for (int t = 0; t < T; ++t) tl.tile_off[t + 1] = tl.tile_off[t] + ((pl.tt.n_dst[t] + mn - 1) / mn) * tn;
     tl.num_segs = T;
-    if (mn == 64 || !allow_small || !fwd_small_tiles(pl, relu, tl.tile_off[T])) return mn;
+    if (mn == 64 || !allow_small || !fwd_small_tiles(pl.es == 2 ? HGNN_BF16 : HGNN_F32, pl.H, relu, tl.tile_off[T])) return mn;
   }
 }
 

@@ -49,6 +49,26 @@ struct AttnVariant {
 };
 AttnVariant &attn_variant();
 
+// Whether a forward launch of `tiles` tiles of 128x128 uses 64x64 ones instead, of which a compute unit holds four (of the large
+// ones two).  Up to 320 or so large ones leave compute units with one block or none; from there to a full round they bring in an
+// operand half as often as small ones.  In fp32 in front of a ReLU the sums are the fp32 MFMA's, which is the bound, and the small
+// tiles' finer rounds count for more.  Outputs of up to 64 columns leave half of a large tile to padding, which fp32 pays for at every
+// size, and bf16 until memory bounds both forms.  us, large / small, of a layer's whole forward, outputs wide x tiles:
+//   bf16, ReLU, 3 relations of 128 columns: 128 x 300 44.9 / 42.4, x 400 50.7 / 53.1; 264 x 318 37.9 / 37.5; 512 x 280 36.8 / 36.3, x 360 38.7 /
+//   40.2; of 256 columns: 256 x 314 58.9 / 56.5, x 400 62.9 / 70.6; 349 x 306 54.5 / 53.4, x 390 58.9 / 66.1.  (Between 200 and 256 large ones, one to
+//   a compute unit, are 1.0 to 1.06 times as fast.)  Without it: 256 x 314 31.3 / 31.8, x 470 37.7 / 43.0.
+//   fp32, ReLU: 128 x 352 132 / 119; 256 x 314 110 / 89, x 470 123 / 128, x 704 178 / 176, x 1094 285 / 270; 352 x 471 113 / 122, x 1056 262 /
+//   238; 512 x 408 106 / 104, x 628 156 / 144, x 1408 304 / 293, x 2188 456 / 463.  Without it: 256 x 314 80.5 / 75.9, x 470 95 / 107; 352 x
+//   306 74.0 / 68.8, x 705 132 / 135; 512 x 408 79.6 / 84.7.
+//   Up to 64 columns, 3 relations of 128: fp32, ReLU, 64 x 700 173 / 123, x 1500 354 / 255, x 2100 514 / 361; without it 64 x 330 87 / 65, x 1500 285 / 243,
+//   32 x 1500 277 / 236; of 256 64 x 960 389 / 347.  bf16, ReLU, 64 x 330 45.7 / 40.8, x 960 103 / 98, x 1500 176 / 178, of 256 64 x 960 230 / 233; without it
+//   64 x 960 73 / 68, x 1500 111 / 103.
+static inline bool fwd_small_tiles(int dtype, int H, bool relu, int tiles) {
+  if (H <= 64) return dtype == HGNN_F32 || tiles < 1000;
+  if (dtype == HGNN_F32 && relu) return tiles < 420 || (tiles > 512 && tiles < 2000);
+  return tiles < 320;
+}
+
 // Column blocks of a backward launch's segments, with tiles of 128 and of 64, and its destination types.
 struct BwdCols {
   int c128 = 0, c64 = 0, types = 0;
