@@ -1265,7 +1265,7 @@ static hgnn_status bwd_common(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_
       split_rows = dw_slice_rows(ctx->dtype, edge, dw_steps, da_steps);
       for (int d = 0; d < T; ++d)
         tl.tile_off[d + 1] = tl.tile_off[d] + tl.u_total[d] * tiles_h * ((pl.tt.n_dst[d] + split_rows - 1) / split_rows);
-      if (edge == 64 || !bwd_small_tiles(ctx->dtype, tl.tile_off[T] + (both ? da_grouped.tile_off[T] : 0), ldg, cols)) break;
+      if (edge == 64 || !bwd_small_tiles(ctx->dtype, tl.tile_off[T] + (both ? da_grouped.tile_off[T] : 0), ldg, cols, both)) break;
     }
     Probe pb(ctx, HGNN_K_GEMM_DW, layer);
     if (both && tl.tile_off[T] > 0) {

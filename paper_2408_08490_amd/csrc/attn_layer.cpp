@@ -268,7 +268,7 @@ hgnn_status attn_bwd(hgnn_ctx *ctx, void *stream, hgnn_graph *g, int32_t layer, 
     split_rows = dw_slice_rows(dtype, edge, dw_steps, (int64_t)da.tile_off[T] * ((H + bk - 1) / bk));
     for (int i = 0; i < T; ++i)
       dt.tile_off[i + 1] = dt.tile_off[i] + dt.u_total[i] * tiles_h * (int)((L.n_src[i] + split_rows - 1) / split_rows);
-    if (edge == 64 || !bwd_small_tiles(dtype, dt.tile_off[T] + da.tile_off[T], H, cols)) break;
+    if (edge == 64 || !bwd_small_tiles(dtype, dt.tile_off[T] + da.tile_off[T], H, cols, da.tile_off[T] > 0)) break;
   }
   Probe pb(ctx, HGNN_K_GEMM_DW, layer);
   const void *dzp = sc + pl.c_dz;

@@ -80,7 +80,8 @@ struct BwdCols {
 // speaks for the large ones is that they bring in (and split) an operand half as often, the more the longer the products are.
 // Hence the line falls with the width.  (us, large / small, of a layer's whole backward in a loop; columns: of each of the launch's
 // segments.)
-//   fp32, width 64: 470 tiles 38.8 / 36.9, 1110 70.3 / 62.9, 2928 188 / 174; 128: 640 67.0 / 52.9, 1335 112 / 106 (96 columns 101.2 /
+//   fp32, width 64: 470 tiles 38.8 / 36.9, 1110 70.3 / 62.9, 2928 188 / 174, 5200 265 / 240 (the launch; of 256 columns 243 / 217), half of whose
+//   large tiles is padding; 128: 640 67.0 / 52.9, 1335 112 / 106 (96 columns 101.2 /
 //   100.9), 1880 155 / 157; 160: 1410 128.1 / 127.5, 1965 188 / 192; 192: 985 98.7 / 93.1, 384 columns 1485 146 / 149; 224: 965 105.2 /
 //   106.5; 256: 675 84.6 / 74.4, 830 99.5 / 96.2 (96 columns 91.5 / 92.7), 1025 121 / 123; 320: 685 97.0 / 87.7, 855 113.4 / 111.7; 512: 675
 //   126 / 120, 696 127.2 / 123.5, 830 148 / 156.
@@ -89,12 +90,23 @@ struct BwdCols {
 //   columns, width 128 320 40.1 / 40.1; 96 columns 300 36 / 36, 400 39.5 / 41.4; width 160 420 41.4 / 42.2.
 //   bf16, width 64: 835 tiles 47.6 / 40.7, 1336 52.5 / 54.7; 128: 545 45.7 / 38.2, 872 49.3 / 47.5, 1336 56 / 61; 256: 648 49.3 / 47.4, 885
 //   55.0 / 59.8; 352: 448 49.9 / 47.9, 615 53.2 / 56.2; 512: 320 50.9 / 45.1, 455 52.4 / 51.0, 472 52.3 / 52.2, 650 57.4 / 63.1.
-static inline bool bwd_small_tiles(int dtype, int tiles, int width, const BwdCols &c) {
+//   Without input gradients (`both` false) a tile's reduction is long, and the slices are cut so that some 640 large tiles are left whatever
+//   the rows; beyond, a block has 64 K-steps.  There small ones win to the end of their own round and then lose more.  Large / small tiles, us
+//   of the launch, bf16: width 64: 336 47.5 / 37.5, 480 51.4 / 55.0, 544 70.8 / 64.0, 720 160 / 177; 128: 272 49.2 / 38.1, 336 56.7 / 55.5, 400 55.9 / 66.4,
+//   624 94.8 / 102; 256: 288 46.2 / 39.4, 352 44.7 / 45.0, 480 51.9 / 59.1, 640 74.2 / 85.1; 349: 288 47.6 / 44.8, 336 52.2 / 55.7, 480 58.4 / 67.5, 912 170 / 254;
+//   512: 320 43.9 / 37.2, 384 44.0 / 43.7, 448 48.4 / 52.0, 960 158 / 239.  Of 64 columns, half padding, 128: 400 42.5 / 35.2, 600 67.1 / 57.8;
+//   of 192, a quarter, 512 55.7 / 68.1.
+//   fp32: 640 and fewer always (512: 448 32.5 / 26.4, 640 48.6 / 30.5); 128: 800 361 / 385, 1008 384 / 477; 256: 800 349 / 376; 320: 912 352 / 357; but 64: 800
+//   339 / 231; 160: 1312 516 / 460; 176: 800 344 / 297, 1408 513 / 491; 192 columns, 128: 1200 480 / 444.
+static inline bool bwd_small_tiles(int dtype, int tiles, int width, const BwdCols &c, bool both) {
   if (tiles < 256) return true;
-  if (dtype == HGNN_BF16) return tiles < (width <= 64 ? 1000 : width <= 128 ? 880 : width <= 256 ? 680 : width <= 352 ? 500 : 460);
   const int padding = 2 * c.c128 - c.c64;   // in blocks of 64 columns, of 2 c128
-  if (2 * padding >= c.c128) return tiles < 1600;
-  if (width <= 64) return tiles < 3000;
+  const bool padded = 2 * padding >= c.c128;
+  if (!both && dtype == HGNN_BF16) return tiles < (padding >= c.c128 || width <= 64 ? 640 : 320);
+  if (dtype == HGNN_BF16) return tiles < (width <= 64 ? 1000 : width <= 128 ? 880 : width <= 256 ? 680 : width <= 352 ? 500 : 460);
+  if (width <= 64) return true;
+  if (padded) return tiles < 1600;
+  if (!both) return tiles < (width > 128 && width <= 192 ? 1600 : 700);
   if (width <= 160 && tiles < 512) return c.c128 <= c.types;   // (one column block per row block: its tiles share no operand)
   return tiles < (width <= 160 ? 1350 : width <= 192 ? 1000 : width <= 320 ? 800 : 700);
 }
