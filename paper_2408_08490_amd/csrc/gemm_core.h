@@ -58,10 +58,8 @@ template <typename T, int ROWS, int COLS, int PITCH, bool KC>
 struct TileMover {
   static constexpr int VEC = 16 / sizeof(T), VPR = COLS / VEC, NV = ROWS * VPR / kThreads;
   static_assert(ROWS * VPR % kThreads == 0, "tile must split evenly over the block");
-  typedef const u32x4 __attribute__((address_space(1))) *gvec_t;
   typedef const unsigned short __attribute__((address_space(1))) *g16_t;
   typedef const unsigned int __attribute__((address_space(1))) *g32_t;
-  typedef const char __attribute__((address_space(1))) *gbyte_t;
   u32x4 reg[NV];
   unsigned okmask;        // pieces inside the segment (FAST); the others are zero
 
@@ -592,10 +590,6 @@ static inline int round_up8(int n) { return (n + 7) & ~7; }
 struct XcdMap {
   int32_t first[9];
 };
-__device__ __forceinline__ int xcd_tile(const XcdMap &m, int bid) {
-  const int x = bid & 7, t = m.first[x] + (bid >> 3);
-  return t < m.first[x + 1] ? t : -1;
-}
 // Returns the number of blocks to launch.
 static inline int balance_xcd(const int32_t *tile_off, const int64_t *cost, int ngroups, XcdMap &m) {
   int64_t total = 0;
@@ -621,6 +615,5 @@ static inline int balance_xcd(const int32_t *tile_off, const int64_t *cost, int 
   }
   return longest * 8;
 }
-
 
 }  // namespace hgnn

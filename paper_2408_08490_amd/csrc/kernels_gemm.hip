@@ -4,15 +4,16 @@
 //             end in d, then the root term), bias and activation in the epilogue;
 //   dA      : dZ_s = (G' W_s^T) scaled per row by 1/|N_r(v)|                          per K-segment s
 //   dW      : dW_s = A_s^T G'  (reduction over the destination rows, split and added atomically)
-// One 256-thread block (2x2 wavefronts) computes a 128x128 tile; every wavefront owns 64x64 of it as
-// 2x2 MFMA 32x32 accumulators.  The reduction runs as ONE flat sequence of K-steps over all segments of
-// the tile, software-pipelined: operands go global -> registers -> LDS, the global loads of the next
-// two K-steps are in flight while the current one is multiplied, and LDS is double-buffered so that a
-// step costs one barrier.  An operand is kept in LDS the way it lies in memory: "KC" = the reduction
-// index is contiguous (rows = output index), "KS" = the output index is contiguous.
+// One 256-thread block (2x2 wavefronts) computes a 128x128 tile, every wavefront 64x64 of it as 2x2 MFMA 32x32
+// accumulators, or a 64x64 tile, 32x32 each.  The reduction runs as ONE flat sequence of K-steps over all segments of
+// the tile, software-pipelined: operands go global -> registers -> LDS, and the global loads of the next
+// two K-steps are in flight while the current one is multiplied.  LDS is double-buffered, so that a step costs one
+// barrier, but for fp32 operands split into three bf16 planes, which take both stages: two barriers.  An operand is kept
+// in LDS the way it lies in memory: "KC" = the reduction index is contiguous (rows = output index), "KS" = the output
+// index is contiguous.
 // Every kernel exists in a FAST form (all operands 16-byte aligned: per-thread offsets are computed once
-// per segment, a K-step is 8 vector loads from wave-uniform bases) and a generic form (element-wise,
-// zero-filled loads) for unaligned shapes.
+// per segment, a K-step is one to four vector loads per operand and lane from wave-uniform bases) and a generic form
+// (element-wise, zero-filled loads) for unaligned shapes.
 #include "bias_reduce.h"
 #include "gemm_core.h"
 
@@ -260,18 +261,17 @@ __device__ __forceinline__ void da_tile_grouped(GemmLds<T, MI, MI> &sm, bwd_args
 }
 
 // One segment's tiles after the other's: `tile_off` has the tiles before each.
-template <typename T, bool FAST, int MI>
-__global__ void __launch_bounds__(kThreads, MI == 1 ? 4 : 2) gemm_da_kernel(BwdArgs args_, RelTab rt, SegTab tiles, const int32_t *__restrict__ rowptr,
+template <typename T, bool FAST>
+__global__ void __launch_bounds__(kThreads, 2) gemm_da_kernel(BwdArgs args_, RelTab rt, SegTab tiles, const int32_t *__restrict__ rowptr,
                                                            const T *__restrict__ gp, T *__restrict__ dz) {
-  constexpr int BM = 64 * MI, BN = 64 * MI;
-  __shared__ GemmLds<T, MI, MI> sm;
+  __shared__ GemmLds<T, 2, 2> sm;
   const bwd_args_t args = (bwd_args_t)__builtin_amdgcn_kernarg_segment_ptr();
   (void)args_;
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
   if (tile >= tiles.tile_off[tiles.num_segs]) return;
   const int s = wave_find(tiles.tile_off, tiles.num_segs, tile), R = rt.num_rels;
   const int F = args->seg[s].F, tiles_n = (F + BN - 1) / BN, local = tile - tiles.tile_off[s];
-  da_tile_at<T, FAST, MI>(sm, args, &args->seg[s], s < R ? rt.dst[s] : s - R, (local / tiles_n) * BM, (local % tiles_n) * BN, rowptr, gp, dz);
+  da_tile_at<T, FAST, 2>(sm, args, &args->seg[s], s < R ? rt.dst[s] : s - R, (local / tiles_n) * BM, (local % tiles_n) * BN, rowptr, gp, dz);
 }
 
 static void put_bwd_tiles(BwdTiles &to, const DwTab &tl, int num_types) {
@@ -310,15 +310,13 @@ hgnn_status launch_gemm_da(hipStream_t s, int dtype, const LayerDev &L, const Ty
   dim3 grid(round_up8(n)), blk(kThreads);
   BwdArgs args;
   put_bwd_args(args, tt, rt, &pt, nullptr, 0, ldg);
-#define HGNN_DA(TY, FA, MI_) \
-  HGNN_LAUNCH((gemm_da_kernel<TY, FA, MI_>), grid, blk, 0, s, args, rt, tiles, L.rowptr, (const TY *)gp, (TY *)dz)
-#define HGNN_DA2(TY, FA) { HGNN_DA(TY, FA, 2); }
+#define HGNN_DA(TY, FA) \
+  HGNN_LAUNCH((gemm_da_kernel<TY, FA>), grid, blk, 0, s, args, rt, tiles, L.rowptr, (const TY *)gp, (TY *)dz)
   if (dtype == HGNN_BF16) {
-    if (fast) HGNN_DA2(bf16, true) else HGNN_DA2(bf16, false)
+    if (fast) HGNN_DA(bf16, true); else HGNN_DA(bf16, false);
   } else {
-    if (fast) HGNN_DA2(float, true) else HGNN_DA2(float, false)
+    if (fast) HGNN_DA(float, true); else HGNN_DA(float, false);
   }
-#undef HGNN_DA2
 #undef HGNN_DA
   HGNN_HIP(hipGetLastError());
   return HGNN_OK;
@@ -357,7 +355,7 @@ __device__ __forceinline__ void dw_tile(GemmLds<T, MI, MI> &sm, bwd_args_t args,
 }
 
 template <typename T, bool FAST, int MI>
-__global__ void __launch_bounds__(kThreads, MI == 1 ? 3 : 2) gemm_dw_kernel(BwdArgs args_, const T *__restrict__ x, const T *__restrict__ z,
+__global__ void __launch_bounds__(kThreads, MI == 1 ? 4 : 2) gemm_dw_kernel(BwdArgs args_, const T *__restrict__ x, const T *__restrict__ z,
                                                            const T *__restrict__ gp) {
   __shared__ GemmLds<T, MI, MI> sm;
   const bwd_args_t args = (bwd_args_t)__builtin_amdgcn_kernarg_segment_ptr();
