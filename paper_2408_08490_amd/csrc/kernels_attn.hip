@@ -262,7 +262,12 @@ template <int MI> struct MixLds<float, MI> {
   __device__ __forceinline__ float *stage() { return reinterpret_cast<float *>(&g.a[0][0]); }
 };
 
-template <bool BKC, typename TS, int MI, typename F>
+// AHEAD: K-steps of fp32 operands whose loads are under way.  One where a tile has up to four, on tiles of 128 rows: there the second set
+// costs more than it brings, and in the backward it does not fit beside what `f` and the epilogue keep in registers (17 of a lane's were
+// in scratch memory).  The launch, us, two steps / one: backward, 23k rows of 4 relations of 128 columns 85 / 73, 84k of 4 of 256 465 / 423;
+// scores of 128 columns, 23k rows of 4 47.5 / 44, of 8 84.5 / 79.5.  Of 256 columns, eight steps, two are better (66.5 / 68.5), on tiles of 64
+// rows too (a step on 200 targets 206.5 / 207.9).
+template <bool BKC, int AHEAD, typename TS, int MI, typename F>
 __device__ __forceinline__ void mix_run(f32x16 (&acc)[MI][2], MixLds<TS, MI> &sm, const float *A, int lda, int a_extent, int a0,
                                         const TS *B, int ldb, int b_extent, int b0, int K, F f) {
   if constexpr (sizeof(TS) == 2) {
@@ -271,10 +276,7 @@ __device__ __forceinline__ void mix_run(f32x16 (&acc)[MI][2], MixLds<TS, MI> &sm
       else wide_run_f32<BKC>(acc, sm.w, A, lda, a_extent, a0, B, ldb, b_extent, b0, K, f);
     });
   } else {
-    // The backward's product has four K-steps; on tiles of 128 rows a second set of loads does not fit beside what `f` and the epilogue keep
-    // in registers (17 of a lane's were in scratch memory).  Its launch, us, two steps ahead / one: 23k rows of 4 relations of 128 columns 85 / 73,
-    // 84k of 4 of 256 465 / 423; on tiles of 64 rows, and in the forward's with up to eight steps, two are as good or better (H = 256 66.5 / 68.5).
-    const OneSeg<float, BKC && MI == 2 ? 1 : 2> one{Seg<float>{A, B, lda, ldb, 0, K}};
+    const OneSeg<float, AHEAD> one{Seg<float>{A, B, lda, ldb, 0, K}};
     gemm_finite<float, true>(acc, [&](auto split) {
       gemm_run<float, true, true, BKC, split.value>(acc, sm.g, one, a_extent, a0, b_extent, b0, [&](auto &mv, int step) {
         const int kc = step * Mma<float>::BK + (threadIdx.x % (Mma<float>::BK / 4)) * 4;
@@ -410,7 +412,7 @@ __global__ void __launch_bounds__(256) attn_agg_kernel(LayerDev L, RelRows rr, A
 // when it is read first, and the kernel behind, from the start again, finds what this one touched last.  The same order in
 // the backward's launch between mask and aggregation (561k rows, m and dm of 573 MB each, us: scores 238 -> 230, fusion
 // 168 -> 161, backward 630 -> 617 and the aggregation's rows behind it 569 -> 558).
-template <typename TS, int MI>
+template <typename TS, int MI, int AHEAD>
 __global__ void __launch_bounds__(kThreads, 2) attn_sem_kernel(RelRows rr, int H, const float *__restrict__ mbuf, const TS *__restrict__ w_sem,
                                                              const TS *__restrict__ b_sem, const TS *__restrict__ q_sem,
                                                              float *__restrict__ tbuf, double *__restrict__ wsum) {
@@ -423,7 +425,7 @@ __global__ void __launch_bounds__(kThreads, 2) attn_sem_kernel(RelRows rr, int H
   const int64_t row0 = rr.row_off[r];
   const int M = rr.row_off[r + 1] - (int)row0;
   f32x16 acc[MI][2];
-  mix_run<false>(acc, sm, mbuf + row0 * H, H, M, m0, w_sem, kSemDim, kSemDim, 0, H, [](f32x4 v, int) { return v; });
+  mix_run<false, AHEAD>(acc, sm, mbuf + row0 * H, H, M, m0, w_sem, kSemDim, kSemDim, 0, H, [](f32x4 v, int) { return v; });
   float bs[4], qs[4], part = 0.f;
   const int cc = (threadIdx.x % (kSemDim / 4)) * 4;
   Quad<TS>::load(bs, b_sem + cc);
@@ -592,13 +594,15 @@ hgnn_status launch_attn_sem(hipStream_t s, int dtype, RelRows rr, int H, const f
   const int tm = sem_tile_rows(rr);
   const int n = tile_relations(rr, tm);
   if (n == 0) return HGNN_OK;
-#define HGNN_SEM(TY, MI_)                                                                                                       \
-  HGNN_LAUNCH((attn_sem_kernel<TY, MI_>), dim3(n), dim3(kThreads), 0, s, rr, H, mbuf, (const TY *)w_sem, (const TY *)b_sem,      \
+#define HGNN_SEM(TY, MI_, AHEAD_)                                                                                               \
+  HGNN_LAUNCH((attn_sem_kernel<TY, MI_, AHEAD_>), dim3(n), dim3(kThreads), 0, s, rr, H, mbuf, (const TY *)w_sem, (const TY *)b_sem, \
               (const TY *)q_sem, tbuf, wsum)
   if (dtype == HGNN_BF16) {
-    if (tm == 128) HGNN_SEM(bf16, 2); else HGNN_SEM(bf16, 1);
+    if (tm == 128) HGNN_SEM(bf16, 2, 2); else HGNN_SEM(bf16, 1, 2);
+  } else if (tm == 128) {
+    if (H <= 128) HGNN_SEM(float, 2, 1); else HGNN_SEM(float, 2, 2);
   } else {
-    if (tm == 128) HGNN_SEM(float, 2); else HGNN_SEM(float, 1);
+    HGNN_SEM(float, 1, 2);
   }
 #undef HGNN_SEM
   HGNN_HIP(hipGetLastError());
@@ -839,7 +843,7 @@ __device__ __forceinline__ void attn_dm_part(MixLds<TS, MI> &sm, const float *t,
                                              float *__restrict__ dm, int64_t row0, int M, int m0, int n0, int H, float coef, float beta,
                                              const float *qs) {
   f32x16 acc[MI][2];
-  mix_run<true>(acc, sm, t + row0 * kSemDim, kSemDim, M, m0, w_sem, kSemDim, H, n0, kSemDim, [&](f32x4 v, int k) {
+  mix_run<true, MI == 2 ? 1 : 2>(acc, sm, t + row0 * kSemDim, kSemDim, M, m0, w_sem, kSemDim, H, n0, kSemDim, [&](f32x4 v, int k) {
     const f32x4 q = *reinterpret_cast<const f32x4 *>(qs + k);
     return f32x4{coef * q.x * (1.f - v.x * v.x), coef * q.y * (1.f - v.y * v.y), coef * q.z * (1.f - v.z * v.z), coef * q.w * (1.f - v.w * v.w)};
   });
